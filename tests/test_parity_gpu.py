@@ -73,6 +73,28 @@ def test_pack_ternary_degenerate_matrices():
     assert alpha.item() == 3.0 and (packed.cpu().numpy().view(np.uint32) == 0).all()
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("shape", [(32, 128), (64, 384), (160, 2048)])
+def test_pack_ternary_at_the_rounding_threshold(shape, dtype):
+    """Weights within 64 units in the last place of alpha / 2 on both sides (fp32; the few nearest bf16
+    values else): every code must be what the rounded division gives, and every position of a tile is hit."""
+    M = _m()
+    rng = np.random.default_rng(shape[0] + shape[1])
+    n = shape[0] * shape[1]
+    a = np.float32(0.0173)
+    if dtype == "f32":
+        half = (np.float32(a / 2).view(np.int32) + rng.integers(-64, 65, n // 2).astype(np.int32)).view(np.float32)
+    else:
+        half = ((np.float32(a / 2).view(np.int32) >> 16) + rng.integers(-2, 3, n // 2).astype(np.int32) << 16).view(np.float32)
+    w = np.concatenate([half, (2 * a - half).astype(np.float32)]) * rng.choice(np.float32([-1, 1]), n)   # mean |w| = a
+    wt = torch.from_numpy(rng.permutation(w).reshape(shape)).to(torch.bfloat16 if dtype == "bf16" else torch.float32)
+    packed, alpha = M.mote_pack_ternary(wt.cuda())
+    t, al = O.ternarize(wt.float().numpy())
+    assert alpha.item() == al
+    assert (t[np.abs(wt.float().numpy()) < a] == 0).any() and (np.abs(t[np.abs(wt.float().numpy()) < a]) == 1).any()
+    assert np.array_equal(packed.cpu().numpy().view(np.uint32), O.pack_int2(t))
+
+
 # ----------------------------------------------------------------------------- router
 @pytest.mark.parametrize("T,d,E,k,bias", [(64, 256, 4, 2, False), (1, 256, 4, 1, False), (37, 384, 8, 2, True),
                                           (515, 896, 8, 2, False), (130, 2048, 16, 2, True),
