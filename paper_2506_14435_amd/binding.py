@@ -204,7 +204,7 @@ def mote_router_balance(x: torch.Tensor, w_router: torch.Tensor, k: int, router_
     dev = x.device
     idx = torch.empty(n_tok, k, dtype=torch.int32, device=dev)
     p = torch.empty(n_tok, k, dtype=torch.float32, device=dev)
-    counts = torch.zeros(n_exp, dtype=torch.int32, device=dev)
+    counts = torch.empty(n_exp, dtype=torch.int32, device=dev)   # written by the call for every batch it takes (T >= 1)
     gate_p = torch.empty(n_tok, n_exp, dtype=torch.float32, device=dev)
     gate_sum = torch.empty(n_exp, dtype=torch.float32, device=dev)
     loss = torch.empty(1, dtype=torch.float32, device=dev)

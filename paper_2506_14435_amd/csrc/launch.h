@@ -130,9 +130,9 @@ hipError_t launch_rtn_dequant(const void* packed, int64_t n_out, int64_t n_in, i
 // LN(.) of Eq.1-2: kind 1 RMSNorm, kind 2 layer normalisation (beta used by kind 2 only)
 hipError_t launch_norm_rows(const uint16_t* x, const uint16_t* gamma, const uint16_t* beta, int kind, double eps, int T,
                             int d, uint16_t* y, hipStream_t stream);
-// Eq.12 from the gate probabilities [T, E] and the routed counts [E]
-hipError_t launch_balance(const float* gate_p, const int32_t* counts, int T, int E, float* gate_p_sum, float* loss,
-                          hipStream_t stream);
+// Eq.12 from the gate probabilities [T, E] and the selected experts [T, k]; also writes the routed counts [E]
+hipError_t launch_balance(const float* gate_p, const int32_t* topk_idx, int T, int k, int E, int32_t* counts,
+                          float* gate_p_sum, float* loss, hipStream_t stream);
 
 // out = bf16( y_s + sum_j p[t,j] * (acc_down[row_of[t,j]] * (beta_h/127 * alpha_down)) ).
 // y_s and acc_down may come as several partial planes (decode K splits), added in plane order.

@@ -254,8 +254,7 @@ mote_status mote_router_balance(const void* x, const void* w_router, const float
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
   MOTE_HIP(launch_router_quant(static_cast<const uint16_t*>(x), static_cast<const uint16_t*>(w_router), router_bias,
                                T, d, E, k, topk_idx, topk_p, nullptr, nullptr, nullptr, gate_p, stream));
-  MOTE_HIP(launch_expert_counts(topk_idx, T * k, E, expert_counts, stream));
-  MOTE_HIP(launch_balance(gate_p, expert_counts, T, E, gate_p_sum, loss, stream));
+  MOTE_HIP(launch_balance(gate_p, topk_idx, T, k, E, expert_counts, gate_p_sum, loss, stream));
   return MOTE_OK;
 }
 

@@ -105,6 +105,26 @@ def test_router_balance_matches_oracle(T, d, E, k, bias):
     assert torch.equal(idx, idx2) and torch.equal(p, p2) and torch.equal(counts, counts2)
 
 
+# column groups of the balance kernel: 16-byte groups that do and do not divide the workgroup, single experts,
+# rows that end inside a pass of the workgroup, fewer rows than lanes
+@pytest.mark.parametrize("T,d,E,k", [(1030, 128, 12, 2), (2050, 128, 64, 8), (3, 128, 64, 1), (1025, 128, 1, 1),
+                                     (7, 128, 5, 2), (9000, 128, 4, 2)])
+def test_router_balance_column_groups(T, d, E, k):
+    M = _m()
+    g = torch.Generator().manual_seed(T + E)
+    x = torch.randn(T, d, generator=g).to(torch.bfloat16)
+    wr = (torch.randn(d, E, generator=g) * d ** -0.5).to(torch.bfloat16)
+    idx, p, counts, gate_p, gate_sum, loss = M.mote_router_balance(x.cuda(), wr.cuda(), k)
+    torch.cuda.synchronize()
+    _, p_o, idx_o, _ = O.router(W.bf16_bits(x), W.bf16_bits(wr), None, k)
+    t_o, s_o, loss_o = O.load_balance(p_o, idx_o)
+    assert np.array_equal(idx.cpu().numpy(), idx_o) and np.array_equal(counts.cpu().numpy(), t_o)
+    # the sums of the GPU's own fp32 probabilities differ from their fp64 sums by one fp32 rounding (2^-24)
+    own = gate_p.double().sum(0).cpu().numpy()
+    assert (np.abs(gate_sum.cpu().numpy() - own) <= 2.0 ** -23 * own).all()
+    assert np.allclose(gate_sum.cpu().numpy(), s_o, rtol=1e-6) and loss.item() == pytest.approx(loss_o, rel=1e-6)
+
+
 # ------------------------------------------------------------------------- block (Eq.1-2)
 def _norm_inputs(cfg, kind, seed):
     g = torch.Generator().manual_seed(seed)
