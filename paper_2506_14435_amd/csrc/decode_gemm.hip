@@ -9,6 +9,8 @@
 //                              than 16 K steps)
 //   shared_wave_kernel<0/1>:   bf16 shared expert (Eq.2) for T <= 64 tokens, one wavefront per
 //                              workgroup with a private LDS ring
+//   decode_head / decode_mid kernels: the shared expert's two kernels with the router and the row
+//                              quantiser as further workgroups of their grids
 //
 // Cross-workgroup K splits (down projections) are written as separate partial planes that the
 // combine kernel adds in a fixed order, so the result does not depend on scheduling.
@@ -28,13 +30,107 @@
 #include <algorithm>
 #include "common.h"
 #include "launch.h"
+#include "quant_body.h"
+#include "router_body.h"
 
 namespace mote {
 
 constexpr int kDecThreads = 256;
 
+// ------------------------------------------------------------------------- dispatch plan in place
+// The dispatch plan of a small decode step (at most 512 dispatch rows, 16 experts, 32-row tiles), made by every
+// workgroup of the gate-up kernel for itself: one load of the selected experts, then a histogram and a stable
+// compaction by ballots.  It takes the place of the two dependent loads of a finished plan, so the gate-up
+// kernel takes about as long as before (d = 2048: T = 1 12.0 -> 12.2 us, T = 64 36.6 -> 38.0) and the plan kernel
+// (5.2 us) with its launch is gone: forward 68.3 -> 64.3 us at T = 1.  Workgroup 0 writes the plan for the kernels that follow.
+struct LocalPlan {
+  int n_tiles;
+  int tok[kLocalPlanRows];
+  int expert[kLocalPlanRows / 32 + kRoleMaxExperts], row0[kLocalPlanRows / 32 + kRoleMaxExperts];
+  int rows[kLocalPlanRows / 32 + kRoleMaxExperts];
+  int cnt[kLocalPlanRows / 64][kRoleMaxExperts];   // selected experts per 64 indices
+};
+
+template <int NT>
+__device__ __forceinline__ void make_local_plan(const RoutedGemmArgs& a, LocalPlan& p) {
+  constexpr int NW = NT / 64, G = kLocalPlanRows / 64;   // groups of 64 indices, dealt to the wavefronts
+  static_assert(G % NW == 0 && kRoleMaxExperts == 16, "");
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int R = static_cast<int>(a.out_rows);
+  const bool writer = blockIdx.x == 0;
+  int v[G / NW], before[G / NW];
+#pragma unroll
+  for (int j = 0; j < G / NW; ++j) {
+    const int i = (j * NW + wave) * 64 + lane;
+    v[j] = i < R ? a.topk_idx[i] : -1;
+  }
+#pragma unroll
+  for (int j = 0; j < G / NW; ++j) {
+    int c = 0;
+    before[j] = 0;
+#pragma unroll
+    for (int e = 0; e < kRoleMaxExperts; ++e) {
+      const uint64_t mask = __ballot(v[j] == e);
+      if (v[j] == e) before[j] = __popcll(mask & ((1ull << lane) - 1ull));
+      if (lane == e) c = __popcll(mask);
+    }
+    if (lane < kRoleMaxExperts) p.cnt[j * NW + wave][lane] = c;
+  }
+  __syncthreads();
+  // lane e: rows of expert e, its first row and its first tile (every wavefront for itself)
+  int c = 0;
+  if (lane < kRoleMaxExperts) {
+#pragma unroll
+    for (int g = 0; g < G; ++g) c += p.cnt[g][lane];
+  }
+  const int t = (c + 31) >> 5;
+  int off = c, tile = t;
+#pragma unroll
+  for (int s = 1; s < kRoleMaxExperts; s <<= 1) {
+    const int o = __shfl_up(off, s, kWave), u = __shfl_up(tile, s, kWave);
+    if (lane >= s) { off += o; tile += u; }
+  }
+  const int n_tiles = __shfl(tile, kRoleMaxExperts - 1, kWave);
+  off -= c;
+  tile -= t;
+#pragma unroll
+  for (int j = 0; j < G / NW; ++j) {
+    const int e = v[j] < 0 ? 0 : v[j];
+    int slot = __shfl(off, e, kWave) + before[j];
+    for (int g = 0; g < j * NW + wave; ++g) slot += p.cnt[g][e];
+    if (v[j] >= 0) {
+      const int i = (j * NW + wave) * 64 + lane, tok = i / a.k;
+      p.tok[slot] = tok;
+      if (writer) {
+        a.plan.row_of[i] = slot;
+        a.plan.tok_of[slot] = tok;
+      }
+    }
+  }
+  if (wave == 0 && lane < kRoleMaxExperts) {
+    for (int m = 0; m < t; ++m) {
+      const int rows = min(32, c - m * 32);
+      p.expert[tile + m] = lane;
+      p.row0[tile + m] = off + m * 32;
+      p.rows[tile + m] = rows;
+      if (writer) {
+        a.plan.tile_expert[tile + m] = lane;
+        a.plan.tile_row0[tile + m] = off + m * 32;
+        a.plan.tile_rows[tile + m] = rows;
+      }
+    }
+    if (lane == 0) p.n_tiles = n_tiles;
+    if (writer && lane < a.E) {
+      a.plan.counts[lane] = c;
+      a.plan.offsets[lane] = off;
+      if (lane == 0) { a.plan.n_tiles[0] = n_tiles; a.plan.offsets[a.E] = R; }
+    }
+  }
+  __syncthreads();
+}
+
 // ------------------------------------------------------------------------- routed experts
-template <int MODE>
+template <int MODE, bool LOCAL>
 __global__ __launch_bounds__(kDecThreads) void routed_decode_kernel(RoutedGemmArgs a, int n_frags, int kc_count,
                                                                     int steps_per_wave) {
   constexpr int NMAT = MODE == 0 ? 2 : 1;
@@ -46,16 +142,18 @@ __global__ __launch_bounds__(kDecThreads) void routed_decode_kernel(RoutedGemmAr
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int r32 = lane & 31, g = lane >> 5;
   const int64_t expert_bytes = static_cast<int64_t>(N) * K / 4;
-  const int n_tiles = a.plan.n_tiles[0];
+  __shared__ LocalPlan s_plan[1];
+  if constexpr (LOCAL) make_local_plan<kDecThreads>(a, s_plan[0]);
+  const int n_tiles = LOCAL ? s_plan[0].n_tiles : a.plan.n_tiles[0];
   const int units = n_tiles * n_frags * kc_count;
 
   for (int u = blockIdx.x; u < units; u += gridDim.x) {
     const int kc = u % kc_count;
     const int nf = (u / kc_count) % n_frags;
     const int mt = u / (kc_count * n_frags);
-    const int expert = a.plan.tile_expert[mt];
-    const int row0 = a.plan.tile_row0[mt];
-    const int rows = a.plan.tile_rows[mt];
+    const int expert = LOCAL ? __builtin_amdgcn_readfirstlane(s_plan[0].expert[mt]) : a.plan.tile_expert[mt];
+    const int row0 = LOCAL ? __builtin_amdgcn_readfirstlane(s_plan[0].row0[mt]) : a.plan.tile_row0[mt];
+    const int rows = LOCAL ? __builtin_amdgcn_readfirstlane(s_plan[0].rows[mt]) : a.plan.tile_rows[mt];
     const int step0 = (kc * 4 + wave) * steps_per_wave;
     const int nsteps = max(0, min(steps_per_wave, KT - step0));
 
@@ -77,7 +175,7 @@ __global__ __launch_bounds__(kDecThreads) void routed_decode_kernel(RoutedGemmAr
     }
     // activation rows: lane (r32, g) reads 16 bytes per 32-channel sub-step
     const int slot = row0 + min(r32, rows - 1);
-    const int src = a.gather ? a.gather[slot] : slot;
+    const int src = LOCAL ? s_plan[0].tok[slot] : (a.gather ? a.gather[slot] : slot);
     const unsigned char* ap = reinterpret_cast<const unsigned char*>(a.q) + static_cast<int64_t>(src) * K +
                               static_cast<int64_t>(step0) * 128 + g * 16;
     // epilogue metadata of the row this thread finishes (row tid % 32)
@@ -177,7 +275,7 @@ __global__ __launch_bounds__(kDecThreads) void routed_decode_kernel(RoutedGemmAr
 // weight loads stay in flight across the per-fragment reduction and epilogue.  The LDS
 // reduction buffer is double buffered: one barrier per fragment.
 // Requires K <= 2048 per plane: gate-up with d_model <= 2048, and every down plane.
-template <int MODE>
+template <int MODE, bool LOCAL>
 __global__ __launch_bounds__(kDecThreads, 2) void routed_stream_kernel(RoutedGemmArgs a, int n_frags, int kc_count) {
   constexpr int NMAT = MODE == 0 ? 2 : 1;
   __shared__ __attribute__((aligned(16))) int s_part[2][4 * NMAT * 16 * 64];
@@ -188,7 +286,9 @@ __global__ __launch_bounds__(kDecThreads, 2) void routed_stream_kernel(RoutedGem
   const int r32 = lane & 31, g = lane >> 5, q = tid >> 6;
   const int64_t expert_bytes = static_cast<int64_t>(N) * K / 4;
   const int64_t frag_bytes = static_cast<int64_t>(KT) * 1024;
-  const int64_t total = static_cast<int64_t>(a.plan.n_tiles[0]) * kc_count * n_frags;
+  __shared__ LocalPlan s_plan[1];
+  if constexpr (LOCAL) make_local_plan<kDecThreads>(a, s_plan[0]);
+  const int64_t total = static_cast<int64_t>(LOCAL ? __builtin_amdgcn_readfirstlane(s_plan[0].n_tiles) : a.plan.n_tiles[0]) * kc_count * n_frags;
   int64_t u = blockIdx.x * total / gridDim.x;
   const int64_t hi = (blockIdx.x + 1) * total / gridDim.x;
   int buf = 0;
@@ -198,9 +298,9 @@ __global__ __launch_bounds__(kDecThreads, 2) void routed_stream_kernel(RoutedGem
     const int nf0 = static_cast<int>(u - static_cast<int64_t>(grp) * n_frags);
     const int nf_end = static_cast<int>(min(static_cast<int64_t>(n_frags), nf0 + (hi - u)));
     const int mt = grp / kc_count, kc = grp - mt * kc_count;
-    const int expert = a.plan.tile_expert[mt];
-    const int row0 = a.plan.tile_row0[mt];
-    const int rows = a.plan.tile_rows[mt];
+    const int expert = LOCAL ? __builtin_amdgcn_readfirstlane(s_plan[0].expert[mt]) : a.plan.tile_expert[mt];
+    const int row0 = LOCAL ? __builtin_amdgcn_readfirstlane(s_plan[0].row0[mt]) : a.plan.tile_row0[mt];
+    const int rows = LOCAL ? __builtin_amdgcn_readfirstlane(s_plan[0].rows[mt]) : a.plan.tile_rows[mt];
     const int step0 = (kc * 4 + wave) * 4;
     const int nsteps = max(0, min(4, KT - step0));
 
@@ -220,7 +320,7 @@ __global__ __launch_bounds__(kDecThreads, 2) void routed_stream_kernel(RoutedGem
 
     // resident activation fragments of this wavefront's K slice
     const int slot = row0 + min(r32, rows - 1);
-    const int src = a.gather ? a.gather[slot] : slot;
+    const int src = LOCAL ? s_plan[0].tok[slot] : (a.gather ? a.gather[slot] : slot);
     const unsigned char* ap = reinterpret_cast<const unsigned char*>(a.q) + static_cast<int64_t>(src) * K +
                               static_cast<int64_t>(step0) * 128 + g * 16;
     const float m_beta = a.beta[src];
@@ -329,7 +429,7 @@ extern "C" int mote_debug_dtrace(void* dst, size_t bytes) { return (int)hipMemcp
 // two workgroups of four: the second workgroup of a CU got its plane 4-5 us after the first (its
 // loads queue behind the first one's weight ring) and ended 6 us later; alone the kernel takes the
 // same time either way, beside the shared expert's kernels the forward is 3-7 % faster (T = 16..64).
-template <int MODE, int MF, int NW>
+template <int MODE, int MF, int NW, bool LOCAL>
 __global__ __launch_bounds__(64 * NW, 2) void routed_wave_kernel(RoutedGemmArgs a, int n_frags, int kc_count) {
   constexpr int NMAT = MODE == 0 ? 2 : 1;
   constexpr int NT = 64 * NW;                             // threads of the workgroup (NW wavefronts)
@@ -367,14 +467,24 @@ __global__ __launch_bounds__(64 * NW, 2) void routed_wave_kernel(RoutedGemmArgs 
   const v4i rsrc_q = make_rsrc(a.q, a.q_rows * K);
   // The tile list (at most 64 entries here) is fetched whole, lane l entry l, beside the tile
   // count it depends on: the weights can then be requested after one memory round trip.
-  const bool tile_table = a.max_tiles <= 64;
-  int t_expert = 0, t_row0 = 0, t_rows = 0;
-  if (tile_table && lane < a.max_tiles) {
+  __shared__ LocalPlan s_plan[1];
+  const bool tile_table = LOCAL || a.max_tiles <= 64;
+  int t_expert = 0, t_row0 = 0, t_rows = 0, n_tiles = 0;
+  if constexpr (LOCAL) {
+    make_local_plan<NT>(a, s_plan[0]);
+    n_tiles = __builtin_amdgcn_readfirstlane(s_plan[0].n_tiles);
+    if (lane < n_tiles) {
+      t_expert = s_plan[0].expert[lane];
+      t_row0 = s_plan[0].row0[lane];
+      t_rows = s_plan[0].rows[lane];
+    }
+  } else if (tile_table && lane < a.max_tiles) {
     t_expert = a.plan.tile_expert[lane];
     t_row0 = a.plan.tile_row0[lane];
     t_rows = a.plan.tile_rows[lane];
   }
-  const int groups = load_uniform(a.plan.n_tiles) * kc_count;
+  if constexpr (!LOCAL) n_tiles = load_uniform(a.plan.n_tiles);
+  const int groups = n_tiles * kc_count;
   // Each (row tile, K plane) group is shared evenly by floor(grid / groups) workgroups.  Where that
   // would leave more than a quarter of the grid idle (MF = 2: one workgroup per CU, groups often
   // between half the grid and the grid), the (group, fragment) units are cut into equal runs instead
@@ -421,12 +531,12 @@ __global__ __launch_bounds__(64 * NW, 2) void routed_wave_kernel(RoutedGemmArgs 
     const int lblock = wave % RB;
     const int lrow = lblock * 8 + (lane & 7);
     const int lslot = row0 + min(lrow, rows - 1);
-    const int lsrc = a.gather ? a.gather[lslot] : lslot;
+    const int lsrc = LOCAL ? s_plan[0].tok[lslot] : (a.gather ? a.gather[lslot] : lslot);
     int src_f[MF];   // rows of this lane in the MFMA layout: fragment f holds row 32 f + r32
 #pragma unroll
     for (int f = 0; f < MF; ++f) {
       const int slot = row0 + min(f * 32 + r32, rows - 1);
-      src_f[f] = a.gather ? a.gather[slot] : slot;
+      src_f[f] = LOCAL ? s_plan[0].tok[slot] : (a.gather ? a.gather[slot] : slot);
     }
     __builtin_amdgcn_sched_barrier(0);
 
@@ -604,17 +714,17 @@ static int device_cus() {
 
 int routed_decode_down_planes(int K) { return ((K >> 7) + 15) / 16; }
 
-template <int MODE, int MF, int NW>
+template <int MODE, int MF, int NW, bool LOCAL>
 static hipError_t launch_wave(const RoutedGemmArgs& a, int n_frags, int kc, hipStream_t stream) {
   constexpr int kLds = 16 * 8 * 32 * MF * 16;   // the activation plane
   static bool attr_set = false;
   if (!attr_set) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(routed_wave_kernel<MODE, MF, NW>),
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(routed_wave_kernel<MODE, MF, NW, LOCAL>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
     if (e != hipSuccess) return e;
     attr_set = true;
   }
-  routed_wave_kernel<MODE, MF, NW><<<device_cus() * (8 / NW), 64 * NW, kLds, stream>>>(a, n_frags, kc);
+  routed_wave_kernel<MODE, MF, NW, LOCAL><<<device_cus() * (8 / NW), 64 * NW, kLds, stream>>>(a, n_frags, kc);
   return hipGetLastError();
 }
 
@@ -647,14 +757,20 @@ hipError_t launch_routed_decode_gate_up(const RoutedGemmArgs& a, hipStream_t str
   const int64_t max_units = static_cast<int64_t>(a.max_tiles) * n_frags;
   int64_t blocks = static_cast<int64_t>(device_cus()) * 4;
   if (blocks > max_units) blocks = max_units;
-  if (a.tile_m == 64) return launch_wave<0, 2, 8>(a, n_frags, 1, stream);
+  if (a.tile_m == 64) return launch_wave<0, 2, 8, false>(a, n_frags, 1, stream);
+  const bool local = a.topk_idx != nullptr;
   if (KT <= 16) {
-    if (use_wave_kernel(a, n_frags, 1))
-      return knob(kKnobDecodeVariant) == 1 ? launch_wave<0, 1, 4>(a, n_frags, 1, stream) : launch_wave<0, 1, 8>(a, n_frags, 1, stream);
-    routed_stream_kernel<0><<<device_cus() * 2, kDecThreads, 0, stream>>>(a, n_frags, 1);
+    if (use_wave_kernel(a, n_frags, 1)) {
+      if (knob(kKnobDecodeVariant) == 1)
+        return local ? launch_wave<0, 1, 4, true>(a, n_frags, 1, stream) : launch_wave<0, 1, 4, false>(a, n_frags, 1, stream);
+      return local ? launch_wave<0, 1, 8, true>(a, n_frags, 1, stream) : launch_wave<0, 1, 8, false>(a, n_frags, 1, stream);
+    }
+    if (local) routed_stream_kernel<0, true><<<device_cus() * 2, kDecThreads, 0, stream>>>(a, n_frags, 1);
+    else routed_stream_kernel<0, false><<<device_cus() * 2, kDecThreads, 0, stream>>>(a, n_frags, 1);
     return hipGetLastError();
   }
-  routed_decode_kernel<0><<<static_cast<unsigned>(blocks), kDecThreads, 0, stream>>>(a, n_frags, 1, (KT + 3) / 4);
+  if (local) routed_decode_kernel<0, true><<<static_cast<unsigned>(blocks), kDecThreads, 0, stream>>>(a, n_frags, 1, (KT + 3) / 4);
+  else routed_decode_kernel<0, false><<<static_cast<unsigned>(blocks), kDecThreads, 0, stream>>>(a, n_frags, 1, (KT + 3) / 4);
   return hipGetLastError();
 }
 
@@ -662,10 +778,10 @@ hipError_t launch_routed_decode_down(const RoutedGemmArgs& a, hipStream_t stream
   if (a.max_tiles == 0) return hipSuccess;
   const int n_frags = a.N / 32;
   const int kc = routed_decode_down_planes(a.K);
-  if (a.tile_m == 64) return launch_wave<1, 2, 8>(a, n_frags, kc, stream);
+  if (a.tile_m == 64) return launch_wave<1, 2, 8, false>(a, n_frags, kc, stream);
   if (use_wave_kernel(a, n_frags, kc))
-    return knob(kKnobDecodeVariant) == 1 ? launch_wave<1, 1, 4>(a, n_frags, kc, stream) : launch_wave<1, 1, 8>(a, n_frags, kc, stream);
-  routed_stream_kernel<1><<<device_cus() * 3, kDecThreads, 0, stream>>>(a, n_frags, kc);
+    return knob(kKnobDecodeVariant) == 1 ? launch_wave<1, 1, 4, false>(a, n_frags, kc, stream) : launch_wave<1, 1, 8, false>(a, n_frags, kc, stream);
+  routed_stream_kernel<1, false><<<device_cus() * 3, kDecThreads, 0, stream>>>(a, n_frags, kc);
   return hipGetLastError();
 }
 
@@ -705,7 +821,7 @@ __device__ __forceinline__ void wait_steps_ahead(int ahead) {
 // AL = 1-KiB loads of token rows per K step (8 rows each): 1, 2, 4 or 8 for T <= 8, 16, 32, 64.
 // Token rows beyond the batch are never loaded: the MFMA reads whatever the ring holds there
 // and the output rows it produces from it are not stored.
-template <int MODE, int AL>
+template <int MODE, int AL, int LDS_KIB = 64>
 struct SharedWaveCfg {
   static constexpr int NMAT = MODE == 0 ? 2 : 1;
   static constexpr int MFR = AL > 4 ? 2 : 1;                // 32-row fragments of tokens
@@ -713,29 +829,31 @@ struct SharedWaveCfg {
   static constexpr int A_OFF = W_LOADS * 1024;              // token rows follow the weight rows in a slot
   static constexpr int SLOT = L * 1024;                     // only the loaded rows: reads of the other token rows run into the next slot
   static constexpr int TAIL = (MFR * 4 - AL) * 1024;        // ... or, in the last slot, into this much padding
-  static constexpr int S_LDS = (65536 - TAIL) / SLOT, S_CNT = 2 + 63 / L;
+  static constexpr int S_LDS = (LDS_KIB * 1024 - TAIL) / SLOT, S_CNT = 2 + 63 / L;
   static constexpr int S = S_LDS < S_CNT ? S_LDS : S_CNT;   // ring slots: LDS and the 6-bit load counter bound it
   static constexpr int LDS = S * SLOT + TAIL;
+  static_assert(S >= 2, "at least one K step in flight");
 };
 
-template <int MODE, int AL>
-__global__ __launch_bounds__(64) void shared_wave_kernel(SharedDecodeArgs a, int kc_count, int steps_per_plane) {
-  using Cfg = SharedWaveCfg<MODE, AL>;
+// unit `blk` of `n_blk`: a run of channels (gate-up) or a (fragment, K plane) pair (down)
+template <int MODE, int AL, int LDS_KIB>
+__device__ __forceinline__ void shared_wave_unit(const SharedDecodeArgs& a, int blk, int n_blk, int kc_count, int steps_per_plane) {
+  using Cfg = SharedWaveCfg<MODE, AL, LDS_KIB>;
   constexpr int NMAT = Cfg::NMAT, MFR = Cfg::MFR, L = Cfg::L, SLOT = Cfg::SLOT, S = Cfg::S, A_LOADS = AL;
   constexpr int kBufferFlags = 0x00020000;
   extern __shared__ __attribute__((aligned(16))) unsigned char s_ring[];
   const int M = a.M, N = a.N, K = a.K, KT = K >> 6;
   const int lane = threadIdx.x, r32 = lane & 31, g = lane >> 5;
   // Down projection: workgroup = (32-channel fragment, K plane).  Gate-up (no K planes: the
-  // epilogue needs the whole sums): the channels are cut into gridDim.x nearly equal runs of
+  // epilogue needs the whole sums): the channels are cut into n_blk nearly equal runs of
   // whole quads, at most 32 channels each, so that every CU streams the same number of weight
   // rows (with whole 32-channel fragments 344 workgroups on 256 CUs left a third of the CUs
   // with twice the bytes of the others; a CU serves its requests in order at its share of the
   // HBM bandwidth).  Rows of the fragment past the run are not fetched and not stored.
-  const int kc = MODE == 1 ? blockIdx.x % kc_count : 0;
+  const int kc = MODE == 1 ? blk % kc_count : 0;
   const int quads = N >> 2;
-  const int c0 = MODE == 1 ? (blockIdx.x / kc_count) * 32 : static_cast<int>(static_cast<int64_t>(blockIdx.x) * quads / gridDim.x) * 4;
-  const int c1 = MODE == 1 ? c0 + 32 : static_cast<int>(static_cast<int64_t>(blockIdx.x + 1) * quads / gridDim.x) * 4;
+  const int c0 = MODE == 1 ? (blk / kc_count) * 32 : static_cast<int>(static_cast<int64_t>(blk) * quads / n_blk) * 4;
+  const int c1 = MODE == 1 ? c0 + 32 : static_cast<int>(static_cast<int64_t>(blk + 1) * quads / n_blk) * 4;
   const int step0 = kc * steps_per_plane;
   const int nsteps = min(steps_per_plane, KT - step0);
   const uint32_t lds0 = (uint32_t)(uintptr_t)((__attribute__((address_space(3))) unsigned char*)s_ring);
@@ -841,6 +959,11 @@ __global__ __launch_bounds__(64) void shared_wave_kernel(SharedDecodeArgs a, int
   }
 }
 
+template <int MODE, int AL>
+__global__ __launch_bounds__(64) void shared_wave_kernel(SharedDecodeArgs a, int kc_count, int steps_per_plane) {
+  shared_wave_unit<MODE, AL, 64>(a, blockIdx.x, gridDim.x, kc_count, steps_per_plane);
+}
+
 // ---------------------------------------------------------- quantised shared expert (decode)
 // The shared expert with RTN INT8 / INT4 weights (Section 4.3): same wave-streaming scheme as
 // shared_wave_kernel, K steps of 64 channels, bf16 token rows, but a weight row of a step is 64
@@ -905,8 +1028,7 @@ __device__ __forceinline__ bf16x8 codes_to_bf16(uint32_t lo, uint32_t hi) {
 }
 
 template <int MODE, int BITS, int AL>
-__global__ __launch_bounds__((64 * SharedQWaveCfg<MODE, BITS, AL>::NW)) void shared_qwave_kernel(SharedQDecodeArgs a, int kc_count,
-                                                                                              int steps_per_plane) {
+__device__ __forceinline__ void shared_qwave_unit(const SharedQDecodeArgs& a, int blk, int n_blk, int kc_count, int steps_per_plane) {
   using Cfg = SharedQWaveCfg<MODE, BITS, AL>;
   constexpr int NMAT = Cfg::NMAT, MFR = Cfg::MFR, L = Cfg::L, SLOT = Cfg::SLOT, S = Cfg::S, A_LOADS = AL, WL = Cfg::WL;
   constexpr int NW = Cfg::NW;
@@ -916,10 +1038,10 @@ __global__ __launch_bounds__((64 * SharedQWaveCfg<MODE, BITS, AL>::NW)) void sha
   const int M = a.M, N = a.N, K = a.K, KT = K >> 6;
   const int lane = threadIdx.x & 63, r32 = lane & 31, g = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int kc = MODE == 1 ? blockIdx.x % kc_count : 0;
+  const int kc = MODE == 1 ? blk % kc_count : 0;
   const int quads = N >> 2;
-  const int c0 = MODE == 1 ? (blockIdx.x / kc_count) * 32 : static_cast<int>(static_cast<int64_t>(blockIdx.x) * quads / gridDim.x) * 4;
-  const int c1 = MODE == 1 ? c0 + 32 : static_cast<int>(static_cast<int64_t>(blockIdx.x + 1) * quads / gridDim.x) * 4;
+  const int c0 = MODE == 1 ? (blk / kc_count) * 32 : static_cast<int>(static_cast<int64_t>(blk) * quads / n_blk) * 4;
+  const int c1 = MODE == 1 ? c0 + 32 : static_cast<int>(static_cast<int64_t>(blk + 1) * quads / n_blk) * 4;
   // K steps of the workgroup, then this wavefront's share of them
   const int wg_step0 = kc * steps_per_plane;
   const int wg_steps = min(steps_per_plane, KT - wg_step0);
@@ -1069,6 +1191,12 @@ __global__ __launch_bounds__((64 * SharedQWaveCfg<MODE, BITS, AL>::NW)) void sha
   }
 }
 
+template <int MODE, int BITS, int AL>
+__global__ __launch_bounds__((64 * SharedQWaveCfg<MODE, BITS, AL>::NW)) void shared_qwave_kernel(SharedQDecodeArgs a, int kc_count,
+                                                                                              int steps_per_plane) {
+  shared_qwave_unit<MODE, BITS, AL>(a, blockIdx.x, gridDim.x, kc_count, steps_per_plane);
+}
+
 // K planes of the decode down projection: (fragments x planes) workgroups should fill two
 // slots per CU evenly, with planes of at least 8 K steps of 64.  The second value is the plane length.
 static void shared_decode_down_split(int d, int K, int* kc_out, int* steps_out) {
@@ -1169,6 +1297,156 @@ hipError_t launch_shared_decode_down(const uint16_t* h_s, const uint16_t* w_down
   int kc, steps;
   shared_decode_down_split(d, F, &kc, &steps);
   return launch_shared_wave<1>(a, n_frags, kc, steps, stream);
+}
+
+// ------------------------------------------------------- shared expert beside the routed chain
+// The shared expert depends on x only.  On a stream of its own it costs a fork and a join (at T = 1 about 19 us
+// of cross-queue signalling and 40 us of host time for 60 us of kernels); here its two kernels carry the two
+// small kernels of the routed chain as further workgroups of the same grid, so a decode step is five
+// launches on one stream and the router and the row quantiser cost next to nothing beside the weight stream:
+//
+//   decode_head_kernel : router + Q_a(x), one workgroup per token, beside the shared gate-up projection
+//                        (d = 2048, T = 1: 9.5 and 18.0 us apart, 20.1 us together; T = 64: 13.0 and 22.0, 22.0)
+//   decode_mid_kernel  : Q_a(h), one workgroup per dispatch row, beside the shared down projection
+//                        (T = 1: 4.0 and 10.6 us apart, 10.6 us together; T = 64: 4.9 and 12.6, 12.7)
+//
+// The small workgroups come first in the grid.  A workgroup of either kind reserves the ring of a
+// streaming one, so with the rings at 52 KiB three workgroups share a CU.  What bounds them is the weight
+// stream: 90 MB in 20 us, 45 MB in 10.6 us.
+struct RouterRoleArgs {
+  const uint16_t* x;
+  const uint16_t* w_router;
+  const float* bias;
+  int T, d, E, k;
+  int32_t* topk_idx;
+  float* topk_p;
+  int8_t* q_x;
+  float* beta_x;
+  int32_t* rowsum_x;
+};
+struct QuantRoleArgs {
+  const uint16_t* h;
+  int R, F;
+  int8_t* q_h;
+  float* beta_h;
+  int32_t* rowsum_h;
+};
+constexpr int kRoleLdsKiB = 52;
+
+template <int NW>
+__device__ __forceinline__ void router_role(const RouterRoleArgs& r, int tok) {
+  router_quant_group<16, 1, NW, 2>(tok, r.x, r.w_router, r.bias, r.T, r.d, r.E, r.k, r.topk_idx, r.topk_p, r.q_x,
+                                                  r.beta_x, r.rowsum_x, nullptr);
+}
+
+// Workgroups of four wavefronts for the sake of the small kernels; a streaming unit is one wavefront, the
+// other three end at once.  (One wavefront per workgroup left the router a chain of memory round trips
+// behind the weight stream: the head kernel took 29 us at T = 1 and T = 64.)
+template <int AL>
+__global__ __launch_bounds__(256) void decode_head_kernel(RouterRoleArgs r, SharedDecodeArgs a) {
+  if (static_cast<int>(blockIdx.x) < r.T) router_role<4>(r, blockIdx.x);
+  else if (threadIdx.x < 64) shared_wave_unit<0, AL, kRoleLdsKiB>(a, blockIdx.x - r.T, gridDim.x - r.T, 1, a.K >> 6);
+}
+
+template <int BITS, int AL>
+__global__ __launch_bounds__((64 * SharedQWaveCfg<0, BITS, AL>::NW)) void decode_head_q_kernel(RouterRoleArgs r, SharedQDecodeArgs a) {
+  if (static_cast<int>(blockIdx.x) < r.T) router_role<SharedQWaveCfg<0, BITS, AL>::NW>(r, blockIdx.x);
+  else shared_qwave_unit<0, BITS, AL>(a, blockIdx.x - r.T, gridDim.x - r.T, 1, a.K >> 6);
+}
+
+template <int AL>
+__global__ __launch_bounds__(256) void decode_mid_kernel(QuantRoleArgs r, SharedDecodeArgs a, int kc_count, int steps_per_plane) {
+  if (static_cast<int>(blockIdx.x) < r.R) quant_row<256, 10>(blockIdx.x, r.h, r.F, r.q_h, r.beta_h, r.rowsum_h);
+  else if (threadIdx.x < 64) shared_wave_unit<1, AL, kRoleLdsKiB>(a, blockIdx.x - r.R, gridDim.x - r.R, kc_count, steps_per_plane);
+}
+
+template <int BITS, int AL>
+__global__ __launch_bounds__((64 * SharedQWaveCfg<1, BITS, AL>::NW)) void decode_mid_q_kernel(QuantRoleArgs r, SharedQDecodeArgs a,
+                                                                                             int kc_count, int steps_per_plane) {
+  constexpr int NT = 64 * SharedQWaveCfg<1, BITS, AL>::NW;
+  if (static_cast<int>(blockIdx.x) < r.R) quant_row<NT, 2560 / NT>(blockIdx.x, r.h, r.F, r.q_h, r.beta_h, r.rowsum_h);
+  else shared_qwave_unit<1, BITS, AL>(a, blockIdx.x - r.R, gridDim.x - r.R, kc_count, steps_per_plane);
+}
+
+// Launch with `lds` bytes of dynamic LDS (above 64 KiB a kernel has to be told once).
+template <typename... P>
+static hipError_t launch_role(void (*kernel)(P...), bool* attr_set, int blocks, int threads, int lds, hipStream_t stream, P... args) {
+  if (!*attr_set) {
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    if (e != hipSuccess) return e;
+    *attr_set = true;
+  }
+  kernel<<<blocks, threads, lds, stream>>>(args...);
+  return hipGetLastError();
+}
+
+template <int AL>
+static hipError_t launch_head_al(const RouterRoleArgs& r, const SharedDecodeArgs& a, int runs, hipStream_t stream) {
+  static bool attr_set = false;
+  return launch_role(decode_head_kernel<AL>, &attr_set, r.T + runs, 256, SharedWaveCfg<0, AL, kRoleLdsKiB>::LDS, stream, r, a);
+}
+template <int BITS, int AL>
+static hipError_t launch_head_q_al(const RouterRoleArgs& r, const SharedQDecodeArgs& a, int runs, hipStream_t stream) {
+  using Cfg = SharedQWaveCfg<0, BITS, AL>;
+  static bool attr_set = false;
+  return launch_role(decode_head_q_kernel<BITS, AL>, &attr_set, r.T + runs, 64 * Cfg::NW, Cfg::LDS, stream, r, a);
+}
+template <int AL>
+static hipError_t launch_mid_al(const QuantRoleArgs& r, const SharedDecodeArgs& a, int units, int kc, int steps, hipStream_t stream) {
+  static bool attr_set = false;
+  return launch_role(decode_mid_kernel<AL>, &attr_set, r.R + units, 256, SharedWaveCfg<1, AL, kRoleLdsKiB>::LDS, stream, r, a, kc, steps);
+}
+template <int BITS, int AL>
+static hipError_t launch_mid_q_al(const QuantRoleArgs& r, const SharedQDecodeArgs& a, int units, int kc, int steps, hipStream_t stream) {
+  using Cfg = SharedQWaveCfg<1, BITS, AL>;
+  static bool attr_set = false;
+  return launch_role(decode_mid_q_kernel<BITS, AL>, &attr_set, r.R + units, 64 * Cfg::NW, Cfg::LDS, stream, r, a, kc, steps);
+}
+
+// AL = 1-KiB loads of token rows per K step, as in launch_shared_wave
+#define MOTE_BY_TOKENS(T_, CALL_)  \
+  if ((T_) <= 8) return CALL_(1);  \
+  if ((T_) <= 16) return CALL_(2); \
+  if ((T_) <= 32) return CALL_(4); \
+  return CALL_(8)
+
+hipError_t launch_decode_head(const DecodeSharedArgs& s, const float* bias, const uint16_t* w_router, int E, int k, int32_t* topk_idx,
+                              float* topk_p, int8_t* q_x, float* beta_x, int32_t* rowsum_x, uint16_t* h_s, hipStream_t stream) {
+  const RouterRoleArgs r{s.x, w_router, bias, s.T, s.d, E, k, topk_idx, topk_p, q_x, beta_x, rowsum_x};
+  const int n_frags = s.F / 32;
+  if (s.bits == 0) {
+    const int runs = std::min(std::max(device_cus() * 2, n_frags), s.F / 4);
+    const SharedDecodeArgs a{s.x, static_cast<const uint16_t*>(s.w_gate), static_cast<const uint16_t*>(s.w_up), s.T, s.F, s.d, h_s, nullptr, 0};
+#define MOTE_CALL(AL_) launch_head_al<AL_>(r, a, runs, stream)
+    MOTE_BY_TOKENS(s.T, MOTE_CALL);
+#undef MOTE_CALL
+  }
+  // rings of 80 KiB: the routers take slots of the two workgroups per CU, so as many fewer runs fill the chip once
+  const int runs = std::min(std::max(device_cus() * 2 - s.T, n_frags), s.F / 4);
+  const SharedQDecodeArgs a{s.x, static_cast<const unsigned char*>(s.w_gate), static_cast<const unsigned char*>(s.w_up), s.s_gate, s.s_up,
+                            s.T, s.F, s.d, h_s, nullptr, 0};
+#define MOTE_CALL(AL_) (s.bits == 8 ? launch_head_q_al<8, AL_>(r, a, runs, stream) : launch_head_q_al<4, AL_>(r, a, runs, stream))
+  MOTE_BY_TOKENS(s.T, MOTE_CALL);
+#undef MOTE_CALL
+}
+
+hipError_t launch_decode_mid(const DecodeSharedArgs& s, const uint16_t* h_s, float* y_s, const uint16_t* h, int R, int F_routed,
+                             int8_t* q_h, float* beta_h, int32_t* rowsum_h, hipStream_t stream) {
+  const QuantRoleArgs r{h, R, F_routed, q_h, beta_h, rowsum_h};
+  int kc, steps;
+  shared_decode_down_split(s.d, s.F, &kc, &steps);
+  const int units = s.d / 32 * kc;
+  const int64_t plane = static_cast<int64_t>(s.T) * s.d;
+  if (s.bits == 0) {
+    const SharedDecodeArgs a{h_s, static_cast<const uint16_t*>(s.w_down), nullptr, s.T, s.d, s.F, nullptr, y_s, plane};
+#define MOTE_CALL(AL_) launch_mid_al<AL_>(r, a, units, kc, steps, stream)
+    MOTE_BY_TOKENS(s.T, MOTE_CALL);
+#undef MOTE_CALL
+  }
+  const SharedQDecodeArgs a{h_s, static_cast<const unsigned char*>(s.w_down), nullptr, s.s_down, nullptr, s.T, s.d, s.F, nullptr, y_s, plane};
+#define MOTE_CALL(AL_) (s.bits == 8 ? launch_mid_q_al<8, AL_>(r, a, units, kc, steps, stream) : launch_mid_q_al<4, AL_>(r, a, units, kc, steps, stream))
+  MOTE_BY_TOKENS(s.T, MOTE_CALL);
+#undef MOTE_CALL
 }
 
 }  // namespace mote

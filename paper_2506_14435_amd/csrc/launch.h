@@ -23,6 +23,7 @@ enum Knob {
   kKnobMidRowsLo,            // 64-row plan tiles for more than this many rows per expert on average ...
   kKnobMidRowsHi,            // ... and at most this many
   kKnobSteBatchMiB,          // expanded weights (MiB) of the experts that share one grouped dX GEMM
+  kKnobDecodeRoles,          // decode step with the small kernels inside the large ones: 0 never, 1 by shape, 2 wherever it can run
   kKnobCount
 };
 int knob(int id);
@@ -80,7 +81,13 @@ struct RoutedGemmArgs {
   int split_max;            // planes a pair of the last round may be cut into (down projection with planes == 1; <= 1: never)
   int32_t* tap_gate;        // optional int32 [R, N]
   int32_t* tap_up;
+  // decode gate-up with the dispatch plan made inside the kernel (32-row tiles, at most kLocalPlanRows dispatch
+  // rows and kRoleMaxExperts experts); null: the plan is there already
+  const int32_t* topk_idx;
+  int k, E;
 };
+constexpr int kLocalPlanRows = 512;   // kSharedDecodeMaxTokens tokens of top-8
+constexpr int kRoleMaxExperts = 16;
 hipError_t launch_routed_gate_up(const RoutedGemmArgs& a, hipStream_t stream);
 hipError_t launch_routed_down(const RoutedGemmArgs& a, hipStream_t stream);
 int routed_down_tile_n(int planes);
@@ -101,6 +108,18 @@ hipError_t launch_shared_decode_gate_up(const uint16_t* x, const uint16_t* w_gat
 hipError_t launch_shared_decode_down(const uint16_t* h_s, const uint16_t* w_down, int T, int d, int F, float* y_s,
                                      hipStream_t stream);
 int shared_decode_down_planes(int d, int K);
+// T <= kSharedDecodeMaxTokens: the shared expert's two kernels with the router (E <= kRoleMaxExperts) and the
+// row quantiser as further workgroups of their grids, everything on one stream.
+struct DecodeSharedArgs {
+  const uint16_t* x;                        // bf16 [T, d]
+  const void *w_gate, *w_up, *w_down;       // bf16, or RTN codes of `bits` bits with row scales
+  const float *s_gate, *s_up, *s_down;
+  int bits, T, d, F;
+};
+hipError_t launch_decode_head(const DecodeSharedArgs& s, const float* bias, const uint16_t* w_router, int E, int k, int32_t* topk_idx,
+                              float* topk_p, int8_t* q_x, float* beta_x, int32_t* rowsum_x, uint16_t* h_s, hipStream_t stream);
+hipError_t launch_decode_mid(const DecodeSharedArgs& s, const uint16_t* h_s, float* y_s, const uint16_t* h, int R, int F_routed,
+                             int8_t* q_h, float* beta_h, int32_t* rowsum_h, hipStream_t stream);
 
 // Q_a(h): per dispatch row absmax int8 of the bf16 hidden activation.
 hipError_t launch_quant_rows(const uint16_t* h, int rows, int F, int8_t* q, float* beta, int32_t* rowsum,

@@ -13,7 +13,7 @@ static int g_knobs[kKnobCount] = {
     /* NoFork */ 0, /* ForkMinLog2 */ 29, /* EventFence */ 0, /* QuantWide */ 0, /* RoutedVariant */ 0,
     /* RoutedDownVariant */ -1, /* SharedVariant */ 0, /* GroupM */ 2, /* DynamicRounds */ 4,
     /* DecodeVariant */ -1, /* RouterTokenBlocks */ 256, /* DownSplitTiles */ 600, /* MidRowsLo */ 31,
-    /* MidRowsHi */ 60, /* SteBatchMiB */ 4095};
+    /* MidRowsHi */ 60, /* SteBatchMiB */ 4095, /* DecodeRoles */ 1};
 int knob(int id) { return (id >= 0 && id < kKnobCount) ? g_knobs[id] : -1; }
 }  // namespace mote
 
@@ -347,7 +347,27 @@ mote_status forward_impl(const mote_layer* layer, const mote_norm* norm, const v
   const bool fork_pays = T * shared_weights >= (int64_t{1} << fork_log2) ||
                          (T <= 8 && shared_weights >= (int64_t{1} << 24) && fork_log2 <= 29);
   SideStream* side = nullptr;
-  if (!timing && !one_stream && fork_enabled() && fork_pays) MOTE_HIP(side_stream(&side));
+  // Decode steps can carry the router and Q_a(h) as workgroups of the shared expert's kernels, on one
+  // stream, with the dispatch plan made inside the gate-up kernel: five launches, no events (stage timing
+  // wants one kernel per stage).  Against the forked chain (us per forward; E = 16, top-2 unless noted):
+  //   d = 256   T=64 39.0 -> 29.4;  d = 896 (E = 8) T=8 47.8 -> 36.6, T=64 55.0 -> 42.3, INT8 54.8 -> 44.7
+  //   d = 1536  T=8 80.7 -> 67.2, T=64 85.7 -> 83.5, but INT8 T=40 78.9 -> 80.7 and T=64 81.8 -> 83.1
+  //   d = 2048  T=1 74.8 -> 64.5, T=16 105.3 -> 98.2, INT8 T=1 65.3 -> 46.2, INT8 T=32 94.3 -> 89.3, but
+  //             T=24 96.6 -> 98.7, T=64 110.6 -> 112.2, INT8 T=64 103.5 -> 108.4: the routed kernels of more
+  //             rows leave half of a CU's LDS free, where the forked chain streams the shared expert
+  //   d = 3584  T=16 264.7 -> 259.2, T=64 330.5 -> 312.3, but T=2 140.2 -> 149.3 and INT4 T=1 77.7 -> 83.5 (long
+  //             kernels, the fork is hidden); there the plan inside the gate-up kernel alone pays (T=8 221.9 ->
+  //             212.4, INT8 T=32 178.8 -> 173.4), which at d = 2048 does not (T=32 99.8 -> 100.3).
+  const int roles_knob = knob(kKnobDecodeRoles);
+  const bool roles_fit = !timing && roles_knob != 0 && decode_shared && decode_routed && E <= kRoleMaxExperts;
+  const bool wide = shared_weights >= (int64_t{1} << 25);
+  bool roles_pay = true;
+  if (wide) roles_pay = layer->shared_bits == 0 && T > 8;
+  else if (shared_weights >= (int64_t{1} << 24)) roles_pay = T <= (layer->shared_bits ? 32 : 16);
+  else if (shared_weights >= (int64_t{1} << 23)) roles_pay = layer->shared_bits == 0 || T <= 32;
+  const bool roles = roles_fit && (roles_pay || roles_knob == 2);
+  const bool local_plan = roles_fit && (roles || wide) && tile_m == 32;
+  if (!timing && !roles && !one_stream && fork_enabled() && fork_pays) MOTE_HIP(side_stream(&side));
   hipStream_t sstream = side ? side->stream : stream;
   // Shared expert: bf16 weights (Eq.2), or RTN INT8 / INT4 codes with row scales (Section 4.3).  Small
   // batches stream the codes themselves; large batches first expand them to integer-valued bf16
@@ -381,12 +401,18 @@ mote_status forward_impl(const mote_layer* layer, const mote_norm* norm, const v
     MOTE_HIP(hipEventRecord(side->join, side->stream));
   }
 
+  const DecodeSharedArgs ds{xb, layer->ws_gate, layer->ws_up, layer->ws_down, layer->ss_gate, layer->ss_up, layer->ss_down, sbits, T, d, Fs};
   MOTE_HIP(mark(0));
-  MOTE_HIP(launch_router_quant(xb, static_cast<const uint16_t*>(layer->w_router), layer->router_bias, T, d, E, k,
-                               w.topk_idx, w.topk_p, w.q_x, w.beta_x, w.rs_x, nullptr, stream));
+  if (roles)
+    MOTE_HIP(launch_decode_head(ds, layer->router_bias, static_cast<const uint16_t*>(layer->w_router), E, k, w.topk_idx, w.topk_p,
+                                w.q_x, w.beta_x, w.rs_x, w.h_s, stream));
+  else
+    MOTE_HIP(launch_router_quant(xb, static_cast<const uint16_t*>(layer->w_router), layer->router_bias, T, d, E, k,
+                                 w.topk_idx, w.topk_p, w.q_x, w.beta_x, w.rs_x, nullptr, stream));
   MOTE_HIP(mark(1));
   DispatchPlan plan{w.counts, w.offsets, w.row_of, w.tok_of, w.tile_expert, w.tile_row0, w.tile_rows, w.n_tiles, w.row_planes, w.sched};
-  MOTE_HIP(launch_dispatch_plan(w.topk_idx, T, k, E, tile_m, plan, stream));
+  // local_plan: the gate-up kernel makes the plan itself (at most 64 * 8 dispatch rows)
+  if (!local_plan) MOTE_HIP(launch_dispatch_plan(w.topk_idx, T, k, E, tile_m, plan, stream));
   MOTE_HIP(mark(2));
 
   RoutedGemmArgs ga{};
@@ -397,9 +423,13 @@ mote_status forward_impl(const mote_layer* layer, const mote_norm* norm, const v
   ga.tap_gate = taps ? taps->acc_gate : nullptr;
   ga.tap_up = taps ? taps->acc_up : nullptr;
   ga.partial_stride = 0; ga.planes = 1; ga.split_max = 1;
+  ga.topk_idx = local_plan ? w.topk_idx : nullptr; ga.k = k; ga.E = E;
   MOTE_HIP(decode_routed ? launch_routed_decode_gate_up(ga, stream) : launch_routed_gate_up(ga, stream));
   MOTE_HIP(mark(3));
-  MOTE_HIP(launch_quant_rows(w.h, R, Fr, w.q_h, w.beta_h, w.rs_h, stream));
+  if (roles)
+    MOTE_HIP(launch_decode_mid(ds, w.h_s, w.y_s, w.h, R, Fr, w.q_h, w.beta_h, w.rs_h, stream));
+  else
+    MOTE_HIP(launch_quant_rows(w.h, R, Fr, w.q_h, w.beta_h, w.rs_h, stream));
   MOTE_HIP(mark(4));
 
   RoutedGemmArgs gd = ga;
@@ -414,7 +444,7 @@ mote_status forward_impl(const mote_layer* layer, const mote_norm* norm, const v
     MOTE_HIP(hipStreamWaitEvent(stream, side->join, 0));
     MOTE_HIP(mark(6));
     MOTE_HIP(mark(7));
-  } else {
+  } else if (!roles) {
     MOTE_HIP(shared_gate_up(stream));
     MOTE_HIP(mark(6));
     MOTE_HIP(shared_down(stream));

@@ -861,3 +861,49 @@ def test_stage_timing_reports_every_stage():
     M.mote_calib_copy(dst, src)
     torch.cuda.synchronize()
     assert torch.equal(src, dst)
+
+
+# A decode step with the router, the row quantiser and the dispatch plan inside the large kernels against
+# the same step with kernels of their own: same arithmetic per element, so every tap is equal to the bit.
+# Tokens at the edges of the token-row templates (8, 16, 32), top-k up to the most dispatch rows (512) and
+# one row, expert counts that are no power of two and the most (16), one tile and several per expert, one
+# chunk sweep of a hidden row and a second one (F > 20480), a gate-up kernel for d <= 2048 and one above.
+ROLE_CASES = [(1, 256, 512, 4, 1), (1, 256, 512, 16, 8), (8, 384, 640, 5, 2), (9, 512, 1408, 16, 2), (16, 256, 512, 2, 1),
+              (17, 2176, 1280, 8, 2), (32, 256, 20608, 3, 1), (33, 1536, 8960, 16, 2), (63, 128, 128, 16, 8),
+              (64, 2048, 11008, 16, 2), (64, 256, 512, 16, 8), (64, 384, 640, 1, 1)]
+
+
+@pytest.mark.parametrize("shared_bits", [0, 8, 4])
+@pytest.mark.parametrize("T,d,F,E,k", ROLE_CASES)
+def test_decode_step_with_small_kernels_inside_the_large_ones(T, d, F, E, k, shared_bits):
+    M = _m()
+    g = torch.Generator(device="cuda").manual_seed(T * 1000 + d + E)
+    rnd = lambda *s, std=1.0: torch.randn(*s, device="cuda", generator=g) * std
+    shared = [rnd(*s, std=0.02).to(torch.bfloat16) for s in ((F, d), (F, d), (d, F))]
+    scales = None
+    if shared_bits:
+        packed = [M.mote_pack_rtn(w, shared_bits) for w in shared]
+        shared, scales = [p for p, _ in packed], tuple(s for _, s in packed)
+    wt = [torch.empty(E, d * F // 16, dtype=torch.int32, device="cuda") for _ in range(3)]
+    alpha = torch.empty(3, E, 1, dtype=torch.float32, device="cuda")
+    for e in range(E):
+        for m in range(3):
+            M.mote_pack_ternary(rnd(*((F, d) if m < 2 else (d, F)), std=0.02), packed=wt[m][e], alpha=alpha[m, e])
+    bias = None if E < 4 else torch.linspace(0.0, 2.0, E, device="cuda")     # uneven loads: empty and full tiles
+    layer = M.MoteLayer(rnd(d, E, std=d ** -0.5).to(torch.bfloat16), *shared, *wt, alpha[:, :, 0].t().contiguous(), k,
+                        router_bias=bias, shared_bits=shared_bits, shared_scales=scales)
+    x = rnd(T, d).to(torch.bfloat16)
+    names = ("topk_idx", "topk_p", "counts", "row_of", "tok_of", "q_x", "beta_x", "acc_gate", "acc_up", "h", "q_h",
+             "beta_h", "acc_down", "h_s", "y_s", "out_f32")
+    taps = {}
+    try:
+        for mode in (0, 2):
+            M.mote_tuning_set("decode_roles", mode)
+            taps[mode] = M.alloc_taps(layer, T, names)
+            taps[mode]["out"] = M.mote_layer_forward(layer, x, taps={n: t for n, t in taps[mode].items()})
+            torch.cuda.synchronize()
+    finally:
+        M.mote_tuning_set("decode_roles", 1)
+    for n in taps[0]:
+        a, b = taps[0][n], taps[2][n]
+        assert torch.equal(a, b), n
