@@ -177,7 +177,7 @@ hipError_t launch_gemm_tn_f32_kgroups(const uint16_t* act, const uint16_t* w, in
                                       int n_groups, float* out, hipStream_t stream);
 // groups of rows with a weight matrix (and scale vector) each; row0_host: host int32 [n_groups + 1]
 int grouped_gemm_planes(const int32_t* row0_host, int n_groups, int N, int K, int max_planes);
-hipError_t launch_gemm_grouped_f32(const uint16_t* act, const uint16_t* w, const int32_t* row0_host, int n_groups, int N,
+hipError_t launch_gemm_grouped_f32(const uint16_t* act, const uint32_t* w, const int32_t* row0_host, int n_groups, int N,
                                    int K, float* out, const float* scale, int planes, hipStream_t stream);
 // straight-through gradients of a grouped ternary linear layer (ste_backward.hip); offsets_host: host int32 [E + 1]
 size_t ste_backward_workspace_bytes(int R, int N, int K, int E);

@@ -23,8 +23,17 @@
 
 namespace mote {
 
-template <int MODE_, int BM_W_, int BN_W_, int WAVES_M_, int WAVES_N_, int MIN_BLOCKS_ = 1, int STAGES_ = 3>
+template <int MODE_, int BM_W_, int BN_W_, int WAVES_M_, int WAVES_N_, int MIN_BLOCKS_ = 1, int STAGES_ = 3, bool TERN_ = false>
 struct SharedCfg {
+  // Weights as 2-bit ternary codes (grouped GEMM of the straight-through gradients): blocks of 32 channels x 32
+  // K elements = 256 bytes, block (channel block, K step) row-major; in a block word 2c + g holds channel c, K
+  // elements 8g .. 8g+7 and 16+8g .. of the step, element pair J (0..7 in that order) at bits 15-2J,14-2J (even
+  // element) and 31-2J,30-2J (odd element), sign above non-zero.  (word << 2J) & 0xC000C000 is then an operand
+  // register: the pair as bf16 values 0, 2, -2.  The factor of two is exact (the channel scale takes it back)
+  // for sums below 2^127.  What the GEMM is bound by is operand traffic: with bf16 weights 96 KiB of LDS reads and
+  // 32 KiB of loads per K step and CU, with codes 40 and 18 KiB: 16 groups of about 1024 rows, N = 2048,
+  // K = 11008: 875 -> 714 us (0.84 -> 1.03 PFLOP/s).
+  static constexpr bool TERN = TERN_;
   static constexpr int MIN_BLOCKS = MIN_BLOCKS_;
   static constexpr int STAGES = STAGES_;   // LDS ring: 3, or 4 with the fragment reads of a K step moved half a step ahead
   static constexpr int MODE = MODE_;  // 0 gate-up (two matrices, SwiGLU epilogue), 1 down
@@ -37,9 +46,9 @@ struct SharedCfg {
   static constexpr int KSTEP = 32;                   // bf16 elements per K step: 64-byte tile rows
   static constexpr int ROWS_PER_PASS = 16 * WAVES;   // a wavefront load fills 16 tile rows
   static constexpr int A_PASSES = BM / ROWS_PER_PASS;
-  static constexpr int B_PASSES = NMAT * BN / ROWS_PER_PASS;
+  static constexpr int B_PASSES = TERN_ ? 1 : NMAT * BN / ROWS_PER_PASS;   // ternary: a wavefront brings one block
   static constexpr int A_BYTES = BM * 64;
-  static constexpr int B_BYTES = BN * 64;            // per matrix
+  static constexpr int B_BYTES = BN * (TERN_ ? 8 : 64);   // per matrix
   static constexpr int STAGE_BYTES = A_BYTES + NMAT * B_BYTES;
   static constexpr int OUT_BYTES = MODE_ == 0 ? 2 : 4;
   static constexpr int PATCH_F = MODE_ == 0 ? BN_W_ : 1;   // fragments per epilogue pass (128-byte output rows for 2 / 1)
@@ -51,6 +60,7 @@ struct SharedCfg {
   static constexpr int LDS_BYTES = STAGES * STAGE_BYTES + ((PATCH_IN_STAGE || PATCH_IN_TWO) ? 0 : WAVES * PATCH_BYTES);
   static_assert(STAGES == 3 || STAGES == 4, "ring of three or four stages");
   static_assert(STAGES == 3 || PATCH_IN_TWO, "the ring of four keeps the epilogue patches in its two free stages");
+  static_assert(!TERN_ || (NMAT == 1 && STAGES_ == 4 && BN == 32 * WAVES && A_PASSES == 2), "what the ternary K loop is written for");
   static_assert(BM % ROWS_PER_PASS == 0 && (NMAT * BN) % ROWS_PER_PASS == 0 && BN % ROWS_PER_PASS == 0,
                 "loaders cover the tiles in whole passes, a pass stays inside one matrix");
   static_assert(64 % (PATCH_F * 32 * OUT_BYTES / 16) == 0, "an epilogue read covers whole rows");
@@ -61,9 +71,16 @@ struct SharedCfg {
 // a quarter wavefront read one chunk of 16 consecutive rows = all 64 banks exactly once.
 __device__ __forceinline__ int lds_tile_offset(int row, int chunk) { return row * 64 + ((chunk ^ ((row >> 2) & 3)) << 4); }
 
+// Half h of the ternary word of a lane (see SharedCfg): eight K elements as bf16 values 0, 2, -2.
+__device__ __forceinline__ bf16x8 ternary_operand(uint32_t w, int h) {
+  const u4 r = {(w << (8 * h)) & 0xC000C000u, (w << (8 * h + 2)) & 0xC000C000u, (w << (8 * h + 4)) & 0xC000C000u,
+                (w << (8 * h + 6)) & 0xC000C000u};
+  return __builtin_bit_cast(bf16x8, r);
+}
+
 struct SharedGemmArgs {
   const uint16_t* act;   // [M, K] bf16
-  const uint16_t* w0;    // [N, K] bf16 (gate / down)
+  const uint16_t* w0;    // [N, K] bf16 (gate / down), or ternary blocks (Cfg::TERN)
   const uint16_t* w1;    // [N, K] bf16 (up)
   int M, N, K;
   uint16_t* h_out;       // gate-up: bf16 [M, N]
@@ -141,7 +158,8 @@ __device__ __forceinline__ void shared_gemm_body(const SharedGemmArgs& a, const 
     return r;
   };
   const v4i rsrc_a = make_rsrc(a.act, static_cast<int64_t>(M) * K * 2);
-  const v4i rsrc_b0 = make_rsrc(a.w0, static_cast<int64_t>(GROUPED == 1 ? rg->n : 1) * N * K * 2);
+  const v4i rsrc_b0 = make_rsrc(a.w0, Cfg::TERN ? static_cast<int64_t>(GROUPED == 1 ? rg->n : 1) * N * K / 4
+                                                : static_cast<int64_t>(GROUPED == 1 ? rg->n : 1) * N * K * 2);
   const v4i rsrc_b1 = make_rsrc(NMAT == 2 ? a.w1 : a.w0, static_cast<int64_t>(N) * K * 2);
   // lane l of a wavefront load lands at byte 16*l of a 1-KiB block = tile row l/4, physical
   // chunk l%4, and therefore fetches logical chunk (l%4) ^ swizzle(row)
@@ -197,7 +215,11 @@ __device__ __forceinline__ void shared_gemm_body(const SharedGemmArgs& a, const 
       const int row_ = min((mrow_) + p * Cfg::ROWS_PER_PASS + ld_row, M - 1);                      \
       a_off[p] = static_cast<uint32_t>(row_) * static_cast<uint32_t>(K) * 2u + k0_;                \
     }                                                                                              \
-    _Pragma("unroll") for (int p = 0; p < Cfg::B_PASSES; ++p) {                                    \
+    if constexpr (Cfg::TERN) {                                                                     \
+      const int blk_ = min((nt_) * (BN / 32) + wave_u, (N >> 5) - 1) + (grp_) * (N >> 5);          \
+      b_off[0] = static_cast<uint32_t>(blk_) * static_cast<uint32_t>(K) * 8u + (kb_) * 4u + lane * 4u; \
+    }                                                                                              \
+    else _Pragma("unroll") for (int p = 0; p < Cfg::B_PASSES; ++p) {                               \
       const int row_ = min((nt_) * BN + (p * Cfg::ROWS_PER_PASS) % BN + ld_row, N - 1) + (grp_) * N; \
       b_off[p] = static_cast<uint32_t>(row_) * static_cast<uint32_t>(K) * 2u + k0_;                \
     }                                                                                              \
@@ -210,8 +232,14 @@ __device__ __forceinline__ void shared_gemm_body(const SharedGemmArgs& a, const 
   MOTE_DMA(lds0 + (stage_) + ((p_) * Cfg::ROWS_PER_PASS + wave_u * 16) * 64, a_off[p_], rsrc_a, (ks_) * 64)
   // loader pass p_ of the weights: matrix (p_*ROWS_PER_PASS)/BN, rows (p_*ROWS_PER_PASS)%BN ... of it
 #define MOTE_DMA_B(stage_, ks_, p_)                                                                \
-  MOTE_DMA(lds0 + (stage_) + A_BYTES + ((p_) * Cfg::ROWS_PER_PASS + wave_u * 16) * 64, b_off[p_],  \
-           (((p_) * Cfg::ROWS_PER_PASS) / BN == 0 ? rsrc_b0 : rsrc_b1), (ks_) * 64)
+  {                                                                                                \
+    if constexpr (Cfg::TERN)                                                                       \
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, %3 offen lds"         \
+                   :: "s"(lds0 + (stage_) + A_BYTES + wave_u * 256), "v"(b_off[p_]), "s"(rsrc_b0), "s"((ks_) * 256) : "memory"); \
+    else                                                                                           \
+      MOTE_DMA(lds0 + (stage_) + A_BYTES + ((p_) * Cfg::ROWS_PER_PASS + wave_u * 16) * 64, b_off[p_], \
+               (((p_) * Cfg::ROWS_PER_PASS) / BN == 0 ? rsrc_b0 : rsrc_b1), (ks_) * 64);           \
+  }
 #define MOTE_ISSUE_STEP(stage_, ks_)                                                               \
   {                                                                                                \
     _Pragma("unroll") for (int p = 0; p < Cfg::A_PASSES; ++p) MOTE_DMA_A(stage_, ks_, p);          \
@@ -260,7 +288,62 @@ __device__ __forceinline__ void shared_gemm_body(const SharedGemmArgs& a, const 
 #pragma unroll
           for (int v = 0; v < 16; ++v) acc[m][i][f][v] = 0.0f;
 
-    if constexpr (Cfg::STAGES == 4) {
+    if constexpr (Cfg::TERN) {
+      // The loop below (ring of four, one barrier in the middle of a step) with the weights unpacked from one
+      // word per lane and fragment: seven or eight vector instructions per two MFMAs in place of a
+      // 16-byte LDS read, an eighth of the weight bytes through L2 and LDS.
+      bf16x8 af0[BM_W], af1[BM_W];
+      uint32_t wq[BN_W], wx[BN_W];
+      const int w_lds = A_BYTES + (wn * BN_W * 64 + r32 * 2 + g) * 4;
+#pragma unroll
+      for (int i = 0; i < BM_W; ++i)
+        af0[i] = *reinterpret_cast<const bf16x8*>(s_lds + st_cur + lds_tile_offset(a_row_base + i * 32, g));
+#pragma unroll
+      for (int f = 0; f < BN_W; ++f) wq[f] = *reinterpret_cast<const uint32_t*>(s_lds + st_cur + w_lds + f * 256);
+      for (int kt = 0; kt < ktl; ++kt) {
+        const bool pf = kt + 3 < ktl;
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int f = 0; f < BN_W; ++f) {
+          const bf16x8 wf = ternary_operand(wq[f], 0);
+#pragma unroll
+          for (int i = 0; i < BM_W; ++i)
+            acc[0][i][f] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf, af0[i], acc[0][i][f], 0, 0, 0);
+          if (f == 0) {
+#pragma unroll
+            for (int i = 0; i < BM_W; ++i)
+              af1[i] = *reinterpret_cast<const bf16x8*>(s_lds + st_cur + lds_tile_offset(a_row_base + i * 32, 2 + g));
+            if (pf) MOTE_DMA_A(st_nx3, kt + 3, 0);
+          }
+          if (f == 1 && pf) MOTE_DMA_B(st_nx3, kt + 3, 0);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        // as below: K step kt+1 has landed, kt+2 and two of the three loads of kt+3 stay in flight
+        if (pf) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"(NLOAD + 2) : "memory");
+        else if (kt + 2 < ktl) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"(NLOAD) : "memory");
+        else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+        asm volatile("s_barrier" ::: "memory");
+#pragma unroll
+        for (int f = 0; f < BN_W; ++f) {
+          const bf16x8 wf = ternary_operand(wq[f], 1);
+#pragma unroll
+          for (int i = 0; i < BM_W; ++i)
+            acc[0][i][f] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf, af1[i], acc[0][i][f], 0, 0, 0);
+          if (f == 0) {
+#pragma unroll
+            for (int i = 0; i < BM_W; ++i)
+              af0[i] = *reinterpret_cast<const bf16x8*>(s_lds + st_nxt + lds_tile_offset(a_row_base + i * 32, g));
+#pragma unroll
+            for (int j = 0; j < BN_W; ++j) wx[j] = *reinterpret_cast<const uint32_t*>(s_lds + st_nxt + w_lds + j * 256);
+          }
+          if (f == 1 && pf) MOTE_DMA_A(st_nx3, kt + 3, 1);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll
+        for (int f = 0; f < BN_W; ++f) wq[f] = wx[f];
+        const int t = st_cur; st_cur = st_nxt; st_nxt = st_nx2; st_nx2 = st_nx3; st_nx3 = t;
+      }
+    } else if constexpr (Cfg::STAGES == 4) {
       // Ring of four stages, loads three K steps ahead, ONE barrier per K step placed in the middle
       // of the step: after it the next step's stage is visible, and its first-half fragments are
       // read while the MFMAs of this step's second half run; the second-half fragments of a step
@@ -728,19 +811,19 @@ int grouped_gemm_planes(const int32_t* row0_host, int n_groups, int N, int K, in
 
 // Grouped GEMM for other callers: rows row0_host[e] .. row0_host[e+1]-1 of act (row0_host: n_groups + 1
 // ascending HOST integers; act, out and the rows are counted from row0_host[0], which act and out point at)
-// are contracted with matrix e of w ([n_groups][N, K] bf16) and scaled per channel by row e of scale
-// ([n_groups][N], optional): out[r, n] = scale[e][n] * sum_k act[r, k] * w[e][n, k].  planes as given by
+// are contracted with matrix e of w ([n_groups] matrices of [N, K] ternary blocks, SharedCfg) and scaled per
+// channel by row e of scale ([n_groups][N]): out[r, n] = scale[e][n] * sum_k act[r, k] * 2 t[e][n, k].  planes as given by
 // grouped_gemm_planes: plane p writes its partial sums to out + p * rows * N and the caller adds them.
-// n_groups <= 64, n_groups * N * K * 2 bytes and rows * K * 2 bytes below 4 GiB, K a multiple of 64.
-hipError_t launch_gemm_grouped_f32(const uint16_t* act, const uint16_t* w, const int32_t* row0_host, int n_groups, int N,
+// n_groups <= 64, n_groups * N * K / 4 bytes and rows * K * 2 bytes below 4 GiB, K a multiple of 64.
+hipError_t launch_gemm_grouped_f32(const uint16_t* act, const uint32_t* w, const int32_t* row0_host, int n_groups, int N,
                                    int K, float* out, const float* scale, int planes, hipStream_t stream) {
   if (n_groups < 1 || n_groups > kMaxRowGroups) return hipErrorInvalidValue;
   const int M = row0_host[n_groups] - row0_host[0];
   if (M == 0 || N == 0) return hipSuccess;
-  SharedGemmArgs a{act, w, nullptr, M, N, K, nullptr, out, static_cast<int64_t>(M) * N, scale, nullptr};
+  SharedGemmArgs a{act, reinterpret_cast<const uint16_t*>(w), nullptr, M, N, K, nullptr, out, static_cast<int64_t>(M) * N, scale, nullptr};
   if (grouped_row_tiles(row0_host, n_groups, 256) * ((N + 255) / 256) >= (3 * shared_cu_count()) / 4)
-    return launch_grouped_cfg<SharedCfg<1, 2, 4, 4, 2, 1, 4>>(a, row0_host, n_groups, planes, stream);   // 256 x 256
-  return launch_grouped_cfg<SharedCfg<1, 2, 2, 2, 2, 2>>(a, row0_host, n_groups, planes, stream);        // 128 x 128
+    return launch_grouped_cfg<SharedCfg<1, 2, 4, 4, 2, 1, 4, true>>(a, row0_host, n_groups, planes, stream);   // 256 x 256
+  return launch_grouped_cfg<SharedCfg<1, 2, 2, 2, 2, 2, 4, true>>(a, row0_host, n_groups, planes, stream);     // 128 x 128
 }
 
 template <typename Cfg>

@@ -11,11 +11,12 @@
 // with its own weight matrix; dW of all experts as one launch whose K ranges are the experts.  The
 // kernels here bring the operands into that form, each in one launch over all experts:
 //
-//   expand_ternary_t_kernel : packed 2-bit codes of W_e [N, K] -> bf16 matrix [K, N] of t_e^T
+//   reblock_ternary_t_kernel: packed 2-bit codes of W_e [N, K] -> 2-bit blocks of t_e^T along the contraction;
+//                             the GEMM unpacks them in registers
 //   transpose_groups_kernel : dY [R, N] bf16, scaled by beta_r / 127 and rounded once -> [N, sum_pad],
 //                             q [R, K] int8 -> bf16 [K, sum_pad]; expert e in the columns pad0[e] ..,
 //                             its rows rounded up to 64 with zeros
-//   fill_alpha_kernel       : alpha_e broadcast over the K output channels of dX (the GEMM
+//   fill_alpha_kernel       : alpha_e / 2 broadcast over the K output channels of dX (the GEMM
 //                             epilogue multiplies per output channel)
 #include <algorithm>
 
@@ -26,55 +27,69 @@ namespace mote {
 
 constexpr int kSteThreads = 256;
 
-// One workgroup expands four packed tiles (32 output rows x 128 input channels each, consecutive
-// row tiles nt = 4 b .. 4 b + 3 of one K tile) into a 128 x 128 block of the transposed matrix:
-// out[(128 kt + c) * N + 128 b + n] = t[128 b + n][128 kt + c].
-__device__ __forceinline__ void expand_ternary_t_body(const uint32_t* __restrict__ packed, int N, int K,
-                                                      uint16_t* __restrict__ out) {
-  __shared__ uint16_t s_t[128][128 + 2];   // [c][n], two bf16 of padding per row
-  const int tiles_k = K >> 7;
-  const int kt = blockIdx.x % tiles_k, nb = blockIdx.x / tiles_k;
-  const int tid = threadIdx.x;
+// Codes t+1 (2-bit fields of a word) -> sign above non-zero: 0 -> 11, 1 -> 00, 2 -> 01.
+__device__ __forceinline__ uint32_t sign_nonzero(uint32_t w) {
+  const uint32_t nz = ~w & 0x55555555u;                       // low bit of t+1 is set for t = 0 only
+  return nz | ((nz & ~(w >> 1)) << 1);                        // high bit of t+1 is set for t = +1 only
+}
+
+// One wavefront re-blocks one packed tile (32 output rows x 128 input channels): the operand of dX contracts over
+// the rows, so its blocks (SharedCfg in shared_ffn.hip) are [channel block 4][this row tile] of 32 x 32 codes.
+// Lane (s, g', b, g) takes the channels 32s + 16g' + 4b .. +3, byte-parallel, and the sixteen rows 8g .. 8g+7
+// and 16+8g .. of its words.  Memory-bound: 90 MB in and out for 16 experts of 11008 x 2048, where the bf16
+// matrices they replaced were 721 MB (136 us to write, and the GEMM read them back).
+__device__ __forceinline__ void reblock_ternary_t_tile(const uint32_t* __restrict__ tile, uint32_t* __restrict__ out, int64_t block_stride,
+                                                       uint32_t* s_in, uint32_t* s_out) {
+  const int lane = threadIdx.x & 63;
+  reinterpret_cast<u4*>(s_in)[lane] = reinterpret_cast<const u4*>(tile)[lane];
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  const int g = lane & 1, b = (lane >> 1) & 3, gc = (lane >> 3) & 1, s = lane >> 4;
+  uint32_t x[4] = {0u, 0u, 0u, 0u};   // byte j of x[m]: channel 4b + j, byte m of its word
+#pragma unroll
+  for (int m = 0; m < 4; ++m) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      // byte 1 / 3: pairs 0..3 (K half 0), byte 0 / 2: pairs 4..7 (K half 1); bytes 2, 3: odd elements
+      const int row = ((m & 1) ? 0 : 16) + 8 * g + 2 * i + (m >> 1);
+      const uint32_t w = (s_in[(32 * gc + row) * 4 + s] >> (2 * b)) & 0x03030303u;
+      x[m] |= w << (6 - 2 * i);
+    }
+    x[m] = sign_nonzero(x[m]);
+  }
+  // 4 x 4 byte transpose: word j = bytes j of x[0..3]
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
-    const int nt = nb * 4 + j;
-    const uint32_t word = packed[(static_cast<int64_t>(nt) * tiles_k + kt) * 256 + tid];
-    const int lane = tid >> 2, s = tid & 3;
-    const int r = lane & 31, g = lane >> 5;
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const int code = (word >> (8 * (i & 3) + 2 * (i >> 2))) & 3;
-      // t = code - 1 as bf16: -1 = 0xBF80, 0 = 0, +1 = 0x3F80
-      s_t[32 * s + 16 * g + i][32 * j + r] = code == 1 ? 0 : (code == 0 ? 0xBF80 : 0x3F80);
-    }
+    const uint32_t w = ((x[0] >> (8 * j)) & 0xFFu) | (((x[1] >> (8 * j)) & 0xFFu) << 8) | (((x[2] >> (8 * j)) & 0xFFu) << 16) |
+                       ((x[3] >> (8 * j)) << 24);
+    s_out[s * 64 + (16 * gc + 4 * b + j) * 2 + g] = w;
   }
-  __syncthreads();
-  // row c of the block: 128 bf16 = 256 bytes, written by 16 threads of 16 bytes
-  for (int i = tid; i < 128 * 16; i += kSteThreads) {
-    const int c = i >> 4, part = i & 15;
-    u4 v;
-    const uint16_t* src = &s_t[c][part * 8];
-    v.x = src[0] | (static_cast<uint32_t>(src[1]) << 16);
-    v.y = src[2] | (static_cast<uint32_t>(src[3]) << 16);
-    v.z = src[4] | (static_cast<uint32_t>(src[5]) << 16);
-    v.w = src[6] | (static_cast<uint32_t>(src[7]) << 16);
-    *reinterpret_cast<u4*>(out + (static_cast<int64_t>(kt) * 128 + c) * N + nb * 128 + part * 8) = v;
-  }
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  // block c of the four: 256 bytes, sixteen lanes of 16 bytes
+  reinterpret_cast<u4*>(out + (lane >> 4) * block_stride)[lane & 15] = reinterpret_cast<const u4*>(s_out)[lane];
 }
 
 // Expert e0 + blockIdx.y of `packed` ([experts][N, K] packed) into matrix blockIdx.y of `out`; experts
-// without rows (row0[e] == row0[e + 1]) are skipped, their matrices are never read.
+// without rows (row0[e] == row0[e + 1]) are skipped, their matrices are never read.  A workgroup takes four
+// consecutive row tiles of one channel tile (consecutive K steps: 1 KiB runs of the output).
 struct SteGroups {
   int n;
   int row0[65];
   int col0[65];   // first column of the expert's block in the transposed operands (rows padded to 64 per expert)
 };
-__global__ __launch_bounds__(kSteThreads) void expand_ternary_t_kernel(const uint32_t* __restrict__ packed, int N, int K,
-                                                                       SteGroups grp, int e0, uint16_t* __restrict__ out) {
+__global__ __launch_bounds__(kSteThreads) void reblock_ternary_t_kernel(const uint32_t* __restrict__ packed, int N, int K,
+                                                                        SteGroups grp, int e0, uint32_t* __restrict__ out) {
+  __shared__ __attribute__((aligned(16))) uint32_t s_in[4][256], s_out[4][256];
   const int e = e0 + blockIdx.y;
   if (grp.row0[e] == grp.row0[e + 1]) return;
-  expand_ternary_t_body(packed + static_cast<int64_t>(e) * (static_cast<int64_t>(N) * K / 16), N, K,
-                        out + static_cast<int64_t>(blockIdx.y) * K * N);
+  const int tiles_k = K >> 7, wave = threadIdx.x >> 6;
+  const int kt = blockIdx.x % tiles_k, nt = (blockIdx.x / tiles_k) * 4 + wave;
+  const int64_t words = static_cast<int64_t>(N) * K / 16, block_stride = static_cast<int64_t>(N >> 5) * 64;
+  reblock_ternary_t_tile(packed + e * words + (static_cast<int64_t>(nt) * tiles_k + kt) * 256,
+                         out + blockIdx.y * words + kt * 4 * block_stride + nt * 64, block_stride, s_in[wave], s_out[wave]);
 }
 
 // in [rows, C] (bf16 bit patterns scaled by beta[r] / 127, or int8 codes) -> out [C, ld] bf16, columns
@@ -154,7 +169,7 @@ __global__ __launch_bounds__(kSteThreads) void transpose_groups_kernel(const voi
 __global__ __launch_bounds__(kSteThreads) void fill_alpha_kernel(const float* __restrict__ alpha, int alpha_stride, int E,
                                                                  int K, float* __restrict__ out) {
   const int i = blockIdx.x * kSteThreads + threadIdx.x;
-  if (i < E * K) out[i] = alpha[(i / K) * alpha_stride];
+  if (i < E * K) out[i] = 0.5f * alpha[(i / K) * alpha_stride];   // the GEMM's operand is 2 t
 }
 
 __global__ __launch_bounds__(kSteThreads) void fill_zero_kernel(float* __restrict__ out, int64_t n4) {
@@ -180,9 +195,9 @@ __global__ __launch_bounds__(kSteThreads) void sum_planes_kernel(const float* __
 
 static inline size_t ste_align(size_t v) { return (v + 255) / 256 * 256; }
 
-// K planes of the dX contraction at most; dX runs as one grouped GEMM over as many experts as have
-// their expanded weights below 4 GiB together (the kernel addresses them with 32-bit byte offsets;
-// the limit is a tuning knob so that tests reach the loop over batches with small matrices).
+// K planes of the dX contraction at most; dX runs as one grouped GEMM over as many experts as have their
+// weights, counted as bf16, below 4 GiB together (the kernel addresses the blocks, an eighth of that, with 32-bit
+// byte offsets; the limit is a tuning knob so that tests reach the loop over batches with small matrices).
 constexpr int kSteMaxPlanes = 8;
 static int ste_dx_batch(int N, int K, int E) {
   const int64_t per = static_cast<int64_t>(N) * K * 2;
@@ -191,7 +206,7 @@ static int ste_dx_batch(int N, int K, int E) {
   return static_cast<int>(std::max<int64_t>(1, std::min<int64_t>(g, E)));
 }
 
-// Workspace: the expanded transposed weights of one batch of experts [experts][K, N], the transposed
+// Workspace: the re-blocked transposed weights of one batch of experts [experts][K, N] (2 bits each), the transposed
 // scaled gradient rows and codes of every expert (sum of rows_pad_e <= R + 63 E columns, a sixteenth
 // more when near-equal blocks are padded to the longest), alpha
 // broadcast [E, K], partial planes of dX.
@@ -199,7 +214,7 @@ static size_t ste_pad_rows(int R, int E) { return (static_cast<size_t>(R) + 64 *
 size_t ste_backward_workspace_bytes(int R, int N, int K, int E) {
   const size_t rp = ste_pad_rows(R, E);
   const size_t plane_bytes = static_cast<size_t>(kSteMaxPlanes) * R * K * 4;
-  return ste_align(static_cast<size_t>(ste_dx_batch(N, K, E)) * K * N * 2) + ste_align(rp * N * 2) + ste_align(rp * K * 2) +
+  return ste_align(static_cast<size_t>(ste_dx_batch(N, K, E)) * K * N / 4) + ste_align(rp * N * 2) + ste_align(rp * K * 2) +
          ste_align(static_cast<size_t>(E) * K * 4) + ste_align(plane_bytes);
 }
 
@@ -209,8 +224,8 @@ hipError_t launch_ste_backward(const uint16_t* dy, const int32_t* offsets_host, 
   char* ws = static_cast<char*>(workspace);
   const size_t rp_total = ste_pad_rows(R, E);
   const int batch = ste_dx_batch(N, K, E);
-  uint16_t* wt = reinterpret_cast<uint16_t*>(ws);
-  ws += ste_align(static_cast<size_t>(batch) * K * N * 2);
+  uint32_t* wt = reinterpret_cast<uint32_t*>(ws);
+  ws += ste_align(static_cast<size_t>(batch) * K * N / 4);
   uint16_t* dyt = reinterpret_cast<uint16_t*>(ws);
   ws += ste_align(rp_total * N * 2);
   uint16_t* qt = reinterpret_cast<uint16_t*>(ws);
@@ -240,12 +255,12 @@ hipError_t launch_ste_backward(const uint16_t* dy, const int32_t* offsets_host, 
   }
 
   fill_alpha_kernel<<<(E * K + kSteThreads - 1) / kSteThreads, kSteThreads, 0, stream>>>(alpha, alpha_stride, E, K, alpha_vec);
-  // dX: t^T of a batch of experts expanded to bf16, then one grouped GEMM over their rows, scaled by alpha
+  // dX: the codes of a batch of experts re-blocked along the contraction, then one grouped GEMM over their rows, scaled by alpha
   for (int e0 = 0; e0 < E; e0 += batch) {
     const int nb = std::min(batch, E - e0);
     const int row0 = offsets_host[e0], rows = offsets_host[e0 + nb] - row0;
     if (rows == 0) continue;
-    expand_ternary_t_kernel<<<dim3((N / 128) * (K / 128), nb), kSteThreads, 0, stream>>>(packed, N, K, grp, e0, wt);
+    reblock_ternary_t_kernel<<<dim3((N / 128) * (K / 128), nb), kSteThreads, 0, stream>>>(packed, N, K, grp, e0, wt);
     const int planes = grouped_gemm_planes(offsets_host + e0, nb, K, N, kSteMaxPlanes);
     const uint16_t* dy_b = dy + static_cast<int64_t>(row0) * N;
     float* dx_b = dx + static_cast<int64_t>(row0) * K;

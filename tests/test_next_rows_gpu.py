@@ -450,3 +450,22 @@ def test_ste_linear_backward_arguments_are_validated():
     assert call(offs, 9, 128, 128, 2, 16) == 3               # workspace too small
     assert lib.mote_ste_backward_workspace_bytes(9, 128, 128, 2) > 0
     assert lib.mote_ste_backward_workspace_bytes(9, 100, 128, 2) == 0
+
+
+# The 2-bit operand of dX: exact sums (integer gradients, sums below 2^24) make every code's place visible.
+# 128 channels: half a 256-wide tile; 640: a last tile of half a width, on 256-row tiles; 128 output rows: one
+# workgroup of the re-blocking kernel; a group of one row and an empty one.
+@pytest.mark.parametrize("R,N,K,E,cuts", [(70, 128, 128, 3, [1, 1]), (300, 384, 640, 2, [130]), (16700, 128, 640, 2, [16600]),
+                                          (129, 1408, 256, 4, [0, 64, 128])])
+def test_ste_dx_of_integer_gradients_is_exact(R, N, K, E, cuts):
+    M = _m()
+    p = _ste_problem(R, N, K, E, seed=77 + R, cuts=cuts)
+    dy = torch.randint(-8, 9, (R, N), generator=torch.Generator().manual_seed(R)).float()
+    dx, _ = M.mote_ste_linear_backward(dy.to(torch.bfloat16).cuda(), p["offsets"], p["packed"].cuda(), p["alpha"].cuda(), 1,
+                                       torch.from_numpy(p["q"]).cuda(), torch.from_numpy(p["beta"]).cuda(), N, K)
+    torch.cuda.synchronize()
+    alpha = p["alpha"].cpu().numpy().reshape(-1)
+    for e in range(E):
+        a, b = int(p["offsets"][e]), int(p["offsets"][e + 1])
+        ref = (dy[a:b].numpy() @ p["experts"][e][0].astype(np.float32)).astype(np.float32)   # |sums| <= 8 N: exact
+        assert np.array_equal(dx[a:b].cpu().numpy(), ref * np.float32(alpha[e]))
