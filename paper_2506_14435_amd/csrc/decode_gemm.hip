@@ -1194,6 +1194,12 @@ __device__ __forceinline__ void shared_qwave_unit(const SharedQDecodeArgs& a, in
 template <int MODE, int BITS, int AL>
 __global__ __launch_bounds__((64 * SharedQWaveCfg<MODE, BITS, AL>::NW)) void shared_qwave_kernel(SharedQDecodeArgs a, int kc_count,
                                                                                               int steps_per_plane) {
+  // blockIdx.y: 64 tokens each (more than 64 tokens: the weights are streamed once per 64, from HBM the first time)
+  const int64_t t0 = static_cast<int64_t>(blockIdx.y) * kSharedDecodeMaxTokens;
+  a.act += t0 * a.K;
+  if constexpr (MODE == 0) a.h_out += t0 * a.N;
+  else a.y_out += t0 * a.N;
+  a.M = min(a.M - static_cast<int>(t0), kSharedDecodeMaxTokens);
   shared_qwave_unit<MODE, BITS, AL>(a, blockIdx.x, gridDim.x, kc_count, steps_per_plane);
 }
 
@@ -1257,7 +1263,8 @@ static hipError_t launch_shared_qwave_al(const SharedQDecodeArgs& a, int n_block
     if (e != hipSuccess) return e;
     attr_set = true;
   }
-  shared_qwave_kernel<MODE, BITS, AL><<<n_blocks, 64 * SharedQWaveCfg<MODE, BITS, AL>::NW, lds, stream>>>(a, kc, steps_per_plane);
+  const unsigned chunks = static_cast<unsigned>((a.M + kSharedDecodeMaxTokens - 1) / kSharedDecodeMaxTokens);
+  shared_qwave_kernel<MODE, BITS, AL><<<dim3(n_blocks, chunks), 64 * SharedQWaveCfg<MODE, BITS, AL>::NW, lds, stream>>>(a, kc, steps_per_plane);
   return hipGetLastError();
 }
 

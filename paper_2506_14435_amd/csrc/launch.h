@@ -23,6 +23,7 @@ enum Knob {
   kKnobMidRowsLo,            // 64-row plan tiles for more than this many rows per expert on average ...
   kKnobMidRowsHi,            // ... and at most this many
   kKnobSteBatchMiB,          // expanded weights (MiB) of the experts that share one grouped dX GEMM
+  kKnobSharedQTokens,        // RTN shared expert: largest T at which the codes are streamed, 64 tokens at a time (-1: by shape)
   kKnobDecodeRoles,          // decode step with the small kernels inside the large ones: 0 never, 1 by shape, 2 wherever it can run
   kKnobCount
 };
@@ -137,7 +138,7 @@ hipError_t launch_shared_gate_up_scaled(const uint16_t* x, const uint16_t* w_gat
                                         hipStream_t stream);
 hipError_t launch_shared_down_scaled(const uint16_t* h_s, const uint16_t* w_down, const float* s_down, int T, int d,
                                      int F, float* y_s, hipStream_t stream);
-// RTN-quantised shared expert, decode (T <= kSharedDecodeMaxTokens): packed INT8 / INT4 codes
+// RTN-quantised shared expert, few tokens: packed INT8 / INT4 codes, streamed once per kSharedDecodeMaxTokens
 hipError_t launch_shared_q_decode_gate_up(const uint16_t* x, const void* w_gate, const void* w_up, const float* s_gate,
                                           const float* s_up, int bits, int T, int d, int F, uint16_t* h_s,
                                           hipStream_t stream);

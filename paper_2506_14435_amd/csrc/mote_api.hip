@@ -13,7 +13,7 @@ static int g_knobs[kKnobCount] = {
     /* NoFork */ 0, /* ForkMinLog2 */ 29, /* EventFence */ 0, /* QuantWide */ 0, /* RoutedVariant */ 0,
     /* RoutedDownVariant */ -1, /* SharedVariant */ 0, /* GroupM */ 2, /* DynamicRounds */ 4,
     /* DecodeVariant */ -1, /* RouterTokenBlocks */ 256, /* DownSplitTiles */ 600, /* MidRowsLo */ 31,
-    /* MidRowsHi */ 60, /* SteBatchMiB */ 4095, /* DecodeRoles */ 1};
+    /* MidRowsHi */ 60, /* SteBatchMiB */ 4095, /* SharedQTokens */ -1, /* DecodeRoles */ 1};
 int knob(int id) { return (id >= 0 && id < kKnobCount) ? g_knobs[id] : -1; }
 }  // namespace mote
 
@@ -62,6 +62,24 @@ bool layer_shape_ok(const mote_layer* l) {
   return true;
 }
 
+// Whether the shared expert's weights are streamed (decode kernels) instead of tiled.  RTN codes are streamed
+// up to a few times 64 tokens: the tiled GEMMs want them expanded to bf16 in every forward (39 us at d = 2048) and
+// have a tile or two per CU there.  Expanded and tiled -> streamed, us per INT8 forward (E = 16, top-2):
+//   d = 256 (E = 4)  T=128 84.3 -> 48.9, T=512 72.7 -> 58.0;   d = 896 (E = 8) T=128 76.7 -> 64.8, T=256 72.3 -> 88.0
+//   d = 1536         T=128 131.0 -> 105.6, T=256 145.5 -> 153.8
+//   d = 2048         T=65 185.5 -> 127.5, T=128 198.3 -> 139.5, T=192 194.0 -> 170.2, T=256 194.4 -> 207.5
+//   d = 3584         T=128 473.0 -> 352.2, T=384 885.0 -> 779.9, T=512 697.1 -> 757.1
+int shared_q_tokens(const mote_layer* l) {
+  if (knob(kKnobSharedQTokens) >= 0) return knob(kKnobSharedQTokens);
+  const int64_t weights = static_cast<int64_t>(l->d_model) * l->d_ff_shared;
+  if (weights < (int64_t{1} << 20)) return 512;
+  if (weights < (int64_t{1} << 23)) return 128;
+  return weights < (int64_t{1} << 25) ? 192 : 384;
+}
+bool shared_streams(const mote_layer* l, int T) {
+  return T <= kSharedDecodeMaxTokens || (l->shared_bits != 0 && T <= shared_q_tokens(l));
+}
+
 // Carves the workspace; with base == nullptr only the size is computed.
 Workspace carve(const mote_layer* l, int T, char* base) {
   Workspace w{};
@@ -78,7 +96,7 @@ Workspace carve(const mote_layer* l, int T, char* base) {
   w.d_planes = w.tile_m != 128 ? routed_decode_down_planes(l->d_ff_routed)
                               : routed_down_planes(T, l->top_k, l->n_experts, l->d_model, l->d_ff_routed);
   w.d_split = (w.tile_m == 128 && w.d_planes == 1) ? kSplitMaxPlanes : 1;
-  w.y_planes = T <= kSharedDecodeMaxTokens ? shared_decode_down_planes(l->d_model, l->d_ff_shared)
+  w.y_planes = shared_streams(l, T) ? shared_decode_down_planes(l->d_model, l->d_ff_shared)
                                            : shared_down_planes(T, l->d_model, l->d_ff_shared);
   w.topk_idx = reinterpret_cast<int32_t*>(take(R * 4));
   w.topk_p = reinterpret_cast<float*>(take(R * 4));
@@ -103,7 +121,7 @@ Workspace carve(const mote_layer* l, int T, char* base) {
   w.h_s = reinterpret_cast<uint16_t*>(take(static_cast<size_t>(T) * Fs * 2));
   w.y_s = reinterpret_cast<float*>(take(static_cast<size_t>(T) * d * 4 * static_cast<size_t>(w.y_planes)));
   w.xn = reinterpret_cast<uint16_t*>(take(static_cast<size_t>(T) * d * 2));
-  if (l->shared_bits != 0 && T > kSharedDecodeMaxTokens) {
+  if (l->shared_bits != 0 && !shared_streams(l, T)) {
     w.deq_gate = reinterpret_cast<uint16_t*>(take(d * Fs * 2));
     w.deq_up = reinterpret_cast<uint16_t*>(take(d * Fs * 2));
     w.deq_down = reinterpret_cast<uint16_t*>(take(d * Fs * 2));
@@ -276,6 +294,7 @@ size_t mote_layer_workspace_bytes(const mote_layer* layer, int T_max) {
   };
   need = carve(layer, T_max, nullptr).bytes;
   consider(kSharedDecodeMaxTokens);
+  if (layer->shared_bits != 0) consider(shared_q_tokens(layer));
   consider(int64_t{48} * E / k);
   consider(static_cast<int64_t>(knob(kKnobMidRowsLo)) * E / k);
   consider(static_cast<int64_t>(knob(kKnobMidRowsHi)) * E / k);
@@ -377,7 +396,7 @@ mote_status forward_impl(const mote_layer* layer, const mote_norm* norm, const v
     if (sbits == 0)
       return decode_shared ? launch_shared_decode_gate_up(xb, sg, su, T, d, Fs, w.h_s, s)
                            : launch_shared_gate_up(xb, sg, su, T, d, Fs, w.h_s, s);
-    if (decode_shared)
+    if (shared_streams(layer, T))
       return launch_shared_q_decode_gate_up(xb, layer->ws_gate, layer->ws_up, layer->ss_gate, layer->ss_up, sbits, T, d,
                                             Fs, w.h_s, s);
     hipError_t e = launch_rtn_dequant(layer->ws_gate, Fs, d, sbits, w.deq_gate, s);
@@ -390,7 +409,7 @@ mote_status forward_impl(const mote_layer* layer, const mote_norm* norm, const v
     if (sbits == 0)
       return decode_shared ? launch_shared_decode_down(w.h_s, sd, T, d, Fs, w.y_s, s)
                            : launch_shared_down(w.h_s, sd, T, d, Fs, w.y_s, s);
-    if (decode_shared) return launch_shared_q_decode_down(w.h_s, layer->ws_down, layer->ss_down, sbits, T, d, Fs, w.y_s, s);
+    if (shared_streams(layer, T)) return launch_shared_q_decode_down(w.h_s, layer->ws_down, layer->ss_down, sbits, T, d, Fs, w.y_s, s);
     return launch_shared_down_scaled(w.h_s, w.deq_down, layer->ss_down, T, d, Fs, w.y_s, s);
   };
   if (side) {

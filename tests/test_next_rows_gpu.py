@@ -469,3 +469,21 @@ def test_ste_dx_of_integer_gradients_is_exact(R, N, K, E, cuts):
         a, b = int(p["offsets"][e]), int(p["offsets"][e + 1])
         ref = (dy[a:b].numpy() @ p["experts"][e][0].astype(np.float32)).astype(np.float32)   # |sums| <= 8 N: exact
         assert np.array_equal(dx[a:b].cpu().numpy(), ref * np.float32(alpha[e]))
+
+
+# More than 64 tokens through the streaming kernels of a quantised shared expert, 64 at a time: one token in the
+# last chunk, whole chunks, a last chunk of few rows, the most tokens a shape takes this way and one more.
+@pytest.mark.parametrize("bits_", [8, 4])
+@pytest.mark.parametrize("d,F,Ts", [(256, 512, (65, 128, 200, 512, 513)), (896, 4864, (128, 129)), (1536, 8960, (192, 193))])
+def test_rtn_shared_expert_streamed_in_chunks_of_64_tokens(d, F, Ts, bits_):
+    M = _m()
+    for T in Ts:
+        cfg = W.MoteConfig(f"rtn_chunks_{d}_{T}", d, F, 4, 1, T, seed=T + d)
+        gp, op = GpuProblem(cfg, shared_bits=bits_), OracleProblem(cfg, shared_bits=bits_)
+        tokens = None if d == 256 else sorted({0, 63, 64, T // 2, T - 2, T - 1})
+        out = _check_rtn_layer(cfg, bits_, gp, op, tokens=tokens)
+        # one workspace sized for more tokens serves this batch with the same result
+        ws = torch.empty(gp.layer.workspace_bytes(T + 70), dtype=torch.uint8, device="cuda")
+        again = M.mote_layer_forward(gp.layer, gp.x, workspace=ws)
+        torch.cuda.synchronize()
+        assert torch.equal(out, again)
