@@ -323,9 +323,15 @@ enum {
                                         average more than this many rows (31) ...                      */
   MOTE_KNOB_MID_ROWS_HI = 13,        /* ... and at most this many (60); lo >= hi switches them off     */
   MOTE_KNOB_STE_BATCH_MIB = 14,      /* mote_ste_linear_backward: the experts of one grouped dX GEMM have at
-                                        most this many MiB of expanded weights together, 1 .. 4095 (4095);
+                                        most this many MiB of weights together, counted as bf16, 1 .. 4095 (4095);
                                         mote_ste_backward_workspace_bytes depends on it                 */
-  MOTE_N_KNOBS = 15
+  MOTE_KNOB_SHARED_Q_TOKENS = 15,    /* quantised shared expert: largest T at which the codes are streamed, 64
+                                        tokens at a time (-1: by shape)                                */
+  MOTE_KNOB_DECODE_ROWS = 16,        /* largest average number of rows per expert on 32-row plan tiles
+                                        (-1: by shape)                                                 */
+  MOTE_KNOB_DECODE_ROLES = 17,       /* decode step with its small kernels inside the large ones: 0 never,
+                                        1 by shape, 2 wherever it can run (1)                          */
+  MOTE_N_KNOBS = 18
 };
 mote_status mote_tuning_set(int knob, int value);
 

@@ -24,6 +24,7 @@ enum Knob {
   kKnobMidRowsHi,            // ... and at most this many
   kKnobSteBatchMiB,          // expanded weights (MiB) of the experts that share one grouped dX GEMM
   kKnobSharedQTokens,        // RTN shared expert: largest T at which the codes are streamed, 64 tokens at a time (-1: by shape)
+  kKnobDecodeRows,           // largest average number of rows per expert on 32-row plan tiles (-1: by shape)
   kKnobDecodeRoles,          // decode step with the small kernels inside the large ones: 0 never, 1 by shape, 2 wherever it can run
   kKnobCount
 };
@@ -96,6 +97,7 @@ int routed_down_planes(int T, int k, int E, int d, int F);   // large-batch down
 int shared_down_planes(int T, int d, int F);
 int tile_group_m();                      // row tiles per band of the large-batch tile order
 int routed_tile_m(int T, int k, int E, int d, int F);  // plan tile size chosen for a workload (32, 64: decode kernels)
+int routed_decode_rows(int d);                         // largest average number of rows per expert on 32-row tiles
 bool routed_mid_kernel_fits(int d, int F);             // the 64-row wave-streaming kernel serves this shape
 
 // Decode (small batch) variants: weights streamed once, K split across wavefronts and, for the

@@ -13,7 +13,7 @@ static int g_knobs[kKnobCount] = {
     /* NoFork */ 0, /* ForkMinLog2 */ 29, /* EventFence */ 0, /* QuantWide */ 0, /* RoutedVariant */ 0,
     /* RoutedDownVariant */ -1, /* SharedVariant */ 0, /* GroupM */ 2, /* DynamicRounds */ 4,
     /* DecodeVariant */ -1, /* RouterTokenBlocks */ 256, /* DownSplitTiles */ 600, /* MidRowsLo */ 31,
-    /* MidRowsHi */ 60, /* SteBatchMiB */ 4095, /* SharedQTokens */ -1, /* DecodeRoles */ 1};
+    /* MidRowsHi */ 60, /* SteBatchMiB */ 4095, /* SharedQTokens */ -1, /* DecodeRows */ -1, /* DecodeRoles */ 1};
 int knob(int id) { return (id >= 0 && id < kKnobCount) ? g_knobs[id] : -1; }
 }  // namespace mote
 
@@ -295,7 +295,7 @@ size_t mote_layer_workspace_bytes(const mote_layer* layer, int T_max) {
   need = carve(layer, T_max, nullptr).bytes;
   consider(kSharedDecodeMaxTokens);
   if (layer->shared_bits != 0) consider(shared_q_tokens(layer));
-  consider(int64_t{48} * E / k);
+  consider(static_cast<int64_t>(routed_decode_rows(layer->d_model)) * E / k);
   consider(static_cast<int64_t>(knob(kKnobMidRowsLo)) * E / k);
   consider(static_cast<int64_t>(knob(kKnobMidRowsHi)) * E / k);
   for (int64_t m = 1;; ++m) {   // largest T with floor(T*k/128) == m - 1

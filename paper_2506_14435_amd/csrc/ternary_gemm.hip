@@ -701,8 +701,16 @@ static int routed_variant() { return knob(kKnobRoutedVariant); }
 int routed_tile_m(int T, int k, int E, int d, int F) {
   const int64_t avg = (static_cast<int64_t>(T) * k + E - 1) / E;
   if (avg > knob(kKnobMidRowsLo) && avg <= knob(kKnobMidRowsHi) && routed_mid_kernel_fits(d, F)) return 64;
-  if (avg <= 48) return 32;
-  return 128;
+  return avg <= routed_decode_rows(d) ? 32 : 128;
+}
+int routed_decode_rows(int d) {
+  if (knob(kKnobDecodeRows) >= 0) return knob(kKnobDecodeRows);
+  // Rows longer than one 16-step plane (d > 2048) have no wave-streaming gate-up kernel, and the register-ring
+  // kernel streams the weights once per 32 rows behind a gather per unit: from 17 rows per expert on the 128-row
+  // kernel is as fast or faster (d = 3584, E = 16, top-2, us per forward: T=130 390 and 390, T=180 421 -> 402,
+  // T=250 546 -> 430, T=380 802 -> 521; T=96 354 against 398).  Below, the 32-row kernels win longer (d = 2048,
+  // E = 8, T=100 113.8 against 121; d = 896, T=190 69.8 against 72.2).
+  return d > 2048 ? 16 : 48;
 }
 
 hipError_t launch_routed_gate_up(const RoutedGemmArgs& a, hipStream_t stream) {

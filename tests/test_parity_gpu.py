@@ -907,3 +907,25 @@ def test_decode_step_with_small_kernels_inside_the_large_ones(T, d, F, E, k, sha
     for n in taps[0]:
         a, b = taps[0][n], taps[2][n]
         assert torch.equal(a, b), n
+
+
+@pytest.mark.parametrize("T", [32, 34, 36, 94, 96, 98])
+def test_layer_rows_longer_than_a_plane_on_either_tile_height(T):
+    """d > 2048 with 16, 17 and 47 to 49 rows per expert: the 128-row kernel from 17 rows on, equal to the bit to the
+    32-row kernels (integer accumulators; the shared expert runs the same kernels either way)."""
+    M = _m()
+    cfg = W.MoteConfig(f"wide_T{T}", 2304, 640, 4, 2, T, seed=500 + T)
+    gp = GpuProblem(cfg)
+    names = ("topk_idx", "row_of", "acc_gate", "acc_up", "h", "q_h", "acc_down", "y_s", "out_f32")
+    taps = {}
+    try:
+        for rows in (48, 16, -1):
+            M.mote_tuning_set("decode_rows", rows)
+            taps[rows] = M.alloc_taps(gp.layer, T, names)
+            out = M.mote_layer_forward(gp.layer, gp.x, taps=taps[rows])
+            torch.cuda.synchronize()
+            taps[rows]["out"] = out
+    finally:
+        M.mote_tuning_set("decode_rows", -1)
+    for n in taps[48]:
+        assert torch.equal(taps[48][n], taps[16][n]) and torch.equal(taps[48][n], taps[-1][n]), n
