@@ -96,8 +96,11 @@ int routed_down_tile_n(int planes);
 int routed_down_planes(int T, int k, int E, int d, int F);   // large-batch down: K planes for a shape
 int shared_down_planes(int T, int d, int F);
 int tile_group_m();                      // row tiles per band of the large-batch tile order
-int routed_tile_m(int T, int k, int E, int d, int F);  // plan tile size chosen for a workload (32, 64: decode kernels)
-int routed_decode_rows(int d);                         // largest average number of rows per expert on 32-row tiles
+// plan tile size chosen for a workload (32, 64: decode kernels); decode_rows: largest average number of rows per
+// expert on 32-row tiles, by choice and where the scratch asks for it
+int routed_tile_m(int T, int k, int E, int d, int F, int decode_rows);
+int routed_decode_rows(int d);
+int routed_decode_rows_max(int d);
 bool routed_mid_kernel_fits(int d, int F);             // the 64-row wave-streaming kernel serves this shape
 
 // Decode (small batch) variants: weights streamed once, K split across wavefronts and, for the

@@ -698,11 +698,12 @@ static int routed_variant() { return knob(kKnobRoutedVariant); }
 // (decode kernels), 64-row tiles for some tens of rows where the wave-streaming kernel fits the
 // shape (the weights are then streamed once per 64 rows; the large-batch kernel would run half-empty
 // 128-row tiles and re-read the activations for every channel tile), else 128.
-int routed_tile_m(int T, int k, int E, int d, int F) {
+int routed_tile_m(int T, int k, int E, int d, int F, int decode_rows) {
   const int64_t avg = (static_cast<int64_t>(T) * k + E - 1) / E;
   if (avg > knob(kKnobMidRowsLo) && avg <= knob(kKnobMidRowsHi) && routed_mid_kernel_fits(d, F)) return 64;
-  return avg <= routed_decode_rows(d) ? 32 : 128;
+  return avg <= decode_rows ? 32 : 128;
 }
+int routed_decode_rows_max(int d) { return std::max(routed_decode_rows(d), knob(kKnobDecodeRows) >= 0 ? 0 : 48); }
 int routed_decode_rows(int d) {
   if (knob(kKnobDecodeRows) >= 0) return knob(kKnobDecodeRows);
   // Rows longer than one 16-step plane (d > 2048) have no wave-streaming gate-up kernel, and the register-ring

@@ -75,3 +75,22 @@ def test_static_entry_point_refuses_batches_beyond_its_array():
     assert lib.mote_layer_forward_static(ctypes.byref(L), None, 0, None, None, None) == 0      # T == 0: no-op
     L.d_model = 900
     assert lib.mote_layer_forward_static(ctypes.byref(L), ctypes.c_void_p(256), 4, ctypes.c_void_p(256), None, None) == 2
+
+
+def test_static_entry_point_on_the_smaller_layout_of_the_32_row_kernels():
+    """d > 2048, 46 rows per expert: the 128-row kernel's layout is beyond the array, the 32-row kernels' is not, and
+    both give the same bits.  The same batch in a workspace of the array's size."""
+    import paper_2506_14435_amd as M
+    T = 185
+    gp = GpuProblem(W.MoteConfig("wide_static", 2304, 640, 32, 8, T, seed=23), shared_bits=8)
+    assert gp.layer.workspace_bytes(T) > M.binding.STATIC_WORKSPACE_BYTES
+    want_taps, got_taps = M.alloc_taps(gp.layer, T, TAPS), M.alloc_taps(gp.layer, T, TAPS)
+    want = M.mote_layer_forward(gp.layer, gp.x, taps=want_taps)
+    got = torch.zeros_like(gp.x)
+    assert _raw_forward_static(M, gp.layer, gp.x, got, got_taps) == 0
+    torch.cuda.synchronize()
+    assert torch.equal(got, want)
+    for n in TAPS:
+        assert torch.equal(got_taps[n], want_taps[n]), n
+    ws = torch.empty(M.binding.STATIC_WORKSPACE_BYTES, dtype=torch.uint8, device="cuda")
+    assert torch.equal(M.mote_layer_forward(gp.layer, gp.x, workspace=ws), want)
