@@ -27,12 +27,13 @@ template <int MODE_, int BM_W_, int BN_W_, int WAVES_M_, int WAVES_N_, int MIN_B
 struct SharedCfg {
   // Weights as 2-bit ternary codes (grouped GEMM of the straight-through gradients): blocks of 32 channels x 32
   // K elements = 256 bytes, block (channel block, K step) row-major; in a block word 2c + g holds channel c, K
-  // elements 8g .. 8g+7 and 16+8g .. of the step, element pair J (0..7 in that order) at bits 15-2J,14-2J (even
-  // element) and 31-2J,30-2J (odd element), sign above non-zero.  (word << 2J) & 0xC000C000 is then an operand
-  // register: the pair as bf16 values 0, 2, -2.  The factor of two is exact (the channel scale takes it back)
-  // for sums below 2^127.  What the GEMM is bound by is operand traffic: with bf16 weights 96 KiB of LDS reads and
-  // 32 KiB of loads per K step and CU, with codes 40 and 18 KiB: 16 groups of about 1024 rows, N = 2048,
-  // K = 11008: 875 -> 714 us (0.84 -> 1.03 PFLOP/s).
+  // elements 8g .. 8g+7 and 16+8g .. of the step, element pair J (0..7 in that order) with its even element's
+  // "non-zero" at bit J and sign at bit 8+J, its odd element's at bits 16+J and 24+J.  In each 16-bit half of
+  // word & (0x01010101 << J), multiplied by 127 << (7 - J), "non-zero" becomes 0x3F80 and the sign 0x8000 (modulo 2^16;
+  // 127 is odd): the pair as bf16 values 0, 1, -1 after one and and one packed 16-bit multiplication (a shift and an
+  // and give 0, 2, -2 instead, whose sums overflow from 2^127 on).  What the GEMM is bound by is operand traffic: with
+  // bf16 weights 96 KiB of LDS reads and 32 KiB of loads per K step and CU, with codes 40 and 18 KiB: 16 groups of
+  // about 1024 rows, N = 2048, K = 11008: 875 -> 714 us (0.84 -> 1.03 PFLOP/s).
   static constexpr bool TERN = TERN_;
   static constexpr int MIN_BLOCKS = MIN_BLOCKS_;
   static constexpr int STAGES = STAGES_;   // LDS ring: 3, or 4 with the fragment reads of a K step moved half a step ahead
@@ -71,11 +72,17 @@ struct SharedCfg {
 // a quarter wavefront read one chunk of 16 consecutive rows = all 64 banks exactly once.
 __device__ __forceinline__ int lds_tile_offset(int row, int chunk) { return row * 64 + ((chunk ^ ((row >> 2) & 3)) << 4); }
 
-// Half h of the ternary word of a lane (see SharedCfg): eight K elements as bf16 values 0, 2, -2.
+// Half h of the ternary word of a lane (see SharedCfg): eight K elements as bf16 values 0, 1, -1.
 __device__ __forceinline__ bf16x8 ternary_operand(uint32_t w, int h) {
-  const u4 r = {(w << (8 * h)) & 0xC000C000u, (w << (8 * h + 2)) & 0xC000C000u, (w << (8 * h + 4)) & 0xC000C000u,
-                (w << (8 * h + 6)) & 0xC000C000u};
-  return __builtin_bit_cast(bf16x8, r);
+  typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+  uint32_t r[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int j = 4 * h + i;
+    const uint16_t c = static_cast<uint16_t>(127u << (7 - j));
+    r[i] = __builtin_bit_cast(uint32_t, __builtin_bit_cast(u16x2, w & (0x01010101u << j)) * u16x2{c, c});
+  }
+  return __builtin_bit_cast(bf16x8, u4{r[0], r[1], r[2], r[3]});
 }
 
 struct SharedGemmArgs {
@@ -290,8 +297,9 @@ __device__ __forceinline__ void shared_gemm_body(const SharedGemmArgs& a, const 
 
     if constexpr (Cfg::TERN) {
       // The loop below (ring of four, one barrier in the middle of a step) with the weights unpacked from one
-      // word per lane and fragment: seven or eight vector instructions per two MFMAs in place of a
-      // 16-byte LDS read, an eighth of the weight bytes through L2 and LDS.
+      // word per lane and fragment: eight vector instructions per two MFMAs in place of a 16-byte LDS read, an eighth
+      // of the weight bytes through L2 and LDS.  The next fragment is unpacked between the two MFMAs of this one (in
+      // front of its own it cost 4 % of the GEMM).
       bf16x8 af0[BM_W], af1[BM_W];
       uint32_t wq[BN_W], wx[BN_W];
       const int w_lds = A_BYTES + (wn * BN_W * 64 + r32 * 2 + g) * 4;
@@ -300,15 +308,18 @@ __device__ __forceinline__ void shared_gemm_body(const SharedGemmArgs& a, const 
         af0[i] = *reinterpret_cast<const bf16x8*>(s_lds + st_cur + lds_tile_offset(a_row_base + i * 32, g));
 #pragma unroll
       for (int f = 0; f < BN_W; ++f) wq[f] = *reinterpret_cast<const uint32_t*>(s_lds + st_cur + w_lds + f * 256);
+      bf16x8 wf = ternary_operand(wq[0], 0);
       for (int kt = 0; kt < ktl; ++kt) {
         const bool pf = kt + 3 < ktl;
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int f = 0; f < BN_W; ++f) {
-          const bf16x8 wf = ternary_operand(wq[f], 0);
+          acc[0][0][f] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf, af0[0], acc[0][0][f], 0, 0, 0);
+          const bf16x8 wn = f + 1 < BN_W ? ternary_operand(wq[(f + 1) % BN_W], 0) : ternary_operand(wq[0], 1);
 #pragma unroll
-          for (int i = 0; i < BM_W; ++i)
+          for (int i = 1; i < BM_W; ++i)
             acc[0][i][f] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf, af0[i], acc[0][i][f], 0, 0, 0);
+          wf = wn;
           if (f == 0) {
 #pragma unroll
             for (int i = 0; i < BM_W; ++i)
@@ -325,10 +336,12 @@ __device__ __forceinline__ void shared_gemm_body(const SharedGemmArgs& a, const 
         asm volatile("s_barrier" ::: "memory");
 #pragma unroll
         for (int f = 0; f < BN_W; ++f) {
-          const bf16x8 wf = ternary_operand(wq[f], 1);
+          acc[0][0][f] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf, af1[0], acc[0][0][f], 0, 0, 0);
+          const bf16x8 wn = f + 1 < BN_W ? ternary_operand(wq[(f + 1) % BN_W], 1) : ternary_operand(wx[0], 0);
 #pragma unroll
-          for (int i = 0; i < BM_W; ++i)
+          for (int i = 1; i < BM_W; ++i)
             acc[0][i][f] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf, af1[i], acc[0][i][f], 0, 0, 0);
+          wf = wn;
           if (f == 0) {
 #pragma unroll
             for (int i = 0; i < BM_W; ++i)
@@ -812,7 +825,7 @@ int grouped_gemm_planes(const int32_t* row0_host, int n_groups, int N, int K, in
 // Grouped GEMM for other callers: rows row0_host[e] .. row0_host[e+1]-1 of act (row0_host: n_groups + 1
 // ascending HOST integers; act, out and the rows are counted from row0_host[0], which act and out point at)
 // are contracted with matrix e of w ([n_groups] matrices of [N, K] ternary blocks, SharedCfg) and scaled per
-// channel by row e of scale ([n_groups][N]): out[r, n] = scale[e][n] * sum_k act[r, k] * 2 t[e][n, k].  planes as given by
+// channel by row e of scale ([n_groups][N]): out[r, n] = scale[e][n] * sum_k act[r, k] * t[e][n, k].  planes as given by
 // grouped_gemm_planes: plane p writes its partial sums to out + p * rows * N and the caller adds them.
 // n_groups <= 64, n_groups * N * K / 4 bytes and rows * K * 2 bytes below 4 GiB, K a multiple of 64.
 hipError_t launch_gemm_grouped_f32(const uint16_t* act, const uint32_t* w, const int32_t* row0_host, int n_groups, int N,

@@ -16,7 +16,7 @@
 //   transpose_groups_kernel : dY [R, N] bf16, scaled by beta_r / 127 and rounded once -> [N, sum_pad],
 //                             q [R, K] int8 -> bf16 [K, sum_pad]; expert e in the columns pad0[e] ..,
 //                             its rows rounded up to 64 with zeros
-//   fill_alpha_kernel       : alpha_e / 2 broadcast over the K output channels of dX (the GEMM
+//   fill_alpha_kernel       : alpha_e broadcast over the K output channels of dX (the GEMM
 //                             epilogue multiplies per output channel)
 #include <algorithm>
 
@@ -26,12 +26,6 @@
 namespace mote {
 
 constexpr int kSteThreads = 256;
-
-// Codes t+1 (2-bit fields of a word) -> sign above non-zero: 0 -> 11, 1 -> 00, 2 -> 01.
-__device__ __forceinline__ uint32_t sign_nonzero(uint32_t w) {
-  const uint32_t nz = ~w & 0x55555555u;                       // low bit of t+1 is set for t = 0 only
-  return nz | ((nz & ~(w >> 1)) << 1);                        // high bit of t+1 is set for t = +1 only
-}
 
 // One wavefront re-blocks one packed tile (32 output rows x 128 input channels): the operand of dX contracts over
 // the rows, so its blocks (SharedCfg in shared_ffn.hip) are [channel block 4][this row tile] of 32 x 32 codes.
@@ -46,17 +40,20 @@ __device__ __forceinline__ void reblock_ternary_t_tile(const uint32_t* __restric
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   const int g = lane & 1, b = (lane >> 1) & 3, gc = (lane >> 3) & 1, s = lane >> 4;
-  uint32_t x[4] = {0u, 0u, 0u, 0u};   // byte j of x[m]: channel 4b + j, byte m of its word
+  // codes t + 1 = 0, 1, 2: the low bit is set for t = 0 only, the high bit for t = +1 only
+  uint32_t x[4];   // byte j of x[m]: channel 4b + j, byte m of its word (bit J: element pair J)
 #pragma unroll
-  for (int m = 0; m < 4; ++m) {
+  for (int odd = 0; odd < 2; ++odd) {
+    uint32_t lo = 0u, hi = 0u;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      // byte 1 / 3: pairs 0..3 (K half 0), byte 0 / 2: pairs 4..7 (K half 1); bytes 2, 3: odd elements
-      const int row = ((m & 1) ? 0 : 16) + 8 * g + 2 * i + (m >> 1);
-      const uint32_t w = (s_in[(32 * gc + row) * 4 + s] >> (2 * b)) & 0x03030303u;
-      x[m] |= w << (6 - 2 * i);
+    for (int J = 0; J < 8; ++J) {
+      const int row = 16 * (J >> 2) + 8 * g + 2 * (J & 3) + odd;
+      const uint32_t w = s_in[(32 * gc + row) * 4 + s] >> (2 * b);
+      lo |= (w & 0x01010101u) << J;
+      hi |= ((w >> 1) & 0x01010101u) << J;
     }
-    x[m] = sign_nonzero(x[m]);
+    x[2 * odd] = ~lo;                 // non-zero
+    x[2 * odd + 1] = ~(lo | hi);      // negative
   }
   // 4 x 4 byte transpose: word j = bytes j of x[0..3]
 #pragma unroll
@@ -169,7 +166,7 @@ __global__ __launch_bounds__(kSteThreads) void transpose_groups_kernel(const voi
 __global__ __launch_bounds__(kSteThreads) void fill_alpha_kernel(const float* __restrict__ alpha, int alpha_stride, int E,
                                                                  int K, float* __restrict__ out) {
   const int i = blockIdx.x * kSteThreads + threadIdx.x;
-  if (i < E * K) out[i] = 0.5f * alpha[(i / K) * alpha_stride];   // the GEMM's operand is 2 t
+  if (i < E * K) out[i] = alpha[(i / K) * alpha_stride];
 }
 
 __global__ __launch_bounds__(kSteThreads) void fill_zero_kernel(float* __restrict__ out, int64_t n4) {

@@ -471,6 +471,28 @@ def test_ste_dx_of_integer_gradients_is_exact(R, N, K, E, cuts):
         assert np.array_equal(dx[a:b].cpu().numpy(), ref * np.float32(alpha[e]))
 
 
+# Sums near both ends of the fp32 range: the contraction and the scale keep the exponents of dy, t and alpha.  Every
+# row of dy follows the signs of one channel at 2^120, so its own sum is 2^120 times that channel's number of
+# non-zero codes (above 2^127 for more than 128 of 256); every product and partial sum is exact, as is alpha's value.
+@pytest.mark.parametrize("alpha", [0.0173, float(np.float32(2.0 ** -126) * np.float32(1 + 2.0 ** -23))])
+def test_ste_dx_keeps_the_fp32_range(alpha):
+    M = _m()
+    R, N, K = 40, 256, 128
+    p = _ste_problem(R, N, K, 1, seed=5)
+    t = p["experts"][0][0].astype(np.float64)
+    own = np.arange(R) % K
+    dy = t[:, own].T * 2.0 ** 120
+    sums = dy @ t
+    mine = sums[np.arange(R), own]
+    assert (mine >= 2.0 ** 127).all() and (np.abs(sums) < 2.0 ** 128).all()
+    dx, _ = M.mote_ste_linear_backward(torch.from_numpy(dy).to(torch.bfloat16).cuda(), p["offsets"], p["packed"].cuda(),
+                                       torch.tensor([alpha], device="cuda"), 1, torch.from_numpy(p["q"]).cuda(),
+                                       torch.from_numpy(p["beta"]).cuda(), N, K)
+    torch.cuda.synchronize()
+    ref = (sums.astype(np.float32) * np.float32(alpha)).astype(np.float32)
+    assert np.isfinite(ref).all() and np.array_equal(dx.cpu().numpy(), ref)
+
+
 # More than 64 tokens through the streaming kernels of a quantised shared expert, 64 at a time: one token in the
 # last chunk, whole chunks, a last chunk of few rows, the most tokens a shape takes this way and one more.
 @pytest.mark.parametrize("bits_", [8, 4])
