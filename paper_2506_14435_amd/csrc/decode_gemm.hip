@@ -1318,8 +1318,9 @@ hipError_t launch_shared_decode_down(const uint16_t* h_s, const uint16_t* w_down
 //                        (T = 1: 4.0 and 10.6 us apart, 10.6 us together; T = 64: 4.9 and 12.6, 12.7)
 //
 // The small workgroups come first in the grid.  A workgroup of either kind reserves the ring of a
-// streaming one, so with the rings at 52 KiB three workgroups share a CU.  What bounds them is the weight
-// stream: 90 MB in 20 us, 45 MB in 10.6 us.
+// streaming one; the small ones keep their few bytes of LDS inside it (as arrays of their own beside it they took
+// the third, or of the quantised kernels' 80 KiB the second, workgroup from a CU).  With the rings of the bf16 kernels
+// at 52 KiB three workgroups share a CU.  What bounds them is the weight stream: 90 MB in 20 us, 45 MB in 10.6 us.
 struct RouterRoleArgs {
   const uint16_t* x;
   const uint16_t* w_router;
@@ -1340,38 +1341,56 @@ struct QuantRoleArgs {
 };
 constexpr int kRoleLdsKiB = 52;
 
-template <int NW>
+// `blocks` workgroups of `lds` bytes fit the 160 KiB of a CU, handed out in units of 1280 bytes.
+constexpr bool lds_fits(int blocks, int lds) { return blocks * ((lds + 1279) / 1280) <= 128; }
+
+template <int NW, int RING>
 __device__ __forceinline__ void router_role(const RouterRoleArgs& r, int tok) {
-  router_quant_group<16, 1, NW, 2>(tok, r.x, r.w_router, r.bias, r.T, r.d, r.E, r.k, r.topk_idx, r.topk_p, r.q_x,
-                                                  r.beta_x, r.rowsum_x, nullptr);
+  extern __shared__ __attribute__((aligned(16))) unsigned char s_ring[];
+  static_assert(sizeof(RouterScratch<1, NW>) <= RING, "");
+  router_quant_group<16, 1, NW, 2>(*reinterpret_cast<RouterScratch<1, NW>*>(s_ring), tok, r.x, r.w_router, r.bias, r.T, r.d, r.E, r.k,
+                                   r.topk_idx, r.topk_p, r.q_x, r.beta_x, r.rowsum_x, nullptr);
+}
+template <int NT, int RING>
+__device__ __forceinline__ void quant_role(const QuantRoleArgs& r, int row) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char s_ring[];
+  static_assert(sizeof(QuantRowScratch<NT>) <= RING, "");
+  quant_row<NT, 2560 / NT>(*reinterpret_cast<QuantRowScratch<NT>*>(s_ring), row, r.h, r.F, r.q_h, r.beta_h, r.rowsum_h);
 }
 
 // Workgroups of four wavefronts for the sake of the small kernels; a streaming unit is one wavefront, the
 // other three end at once.  (One wavefront per workgroup left the router a chain of memory round trips
 // behind the weight stream: the head kernel took 29 us at T = 1 and T = 64.)
 template <int AL>
-__global__ __launch_bounds__(256) void decode_head_kernel(RouterRoleArgs r, SharedDecodeArgs a) {
-  if (static_cast<int>(blockIdx.x) < r.T) router_role<4>(r, blockIdx.x);
+__global__ __launch_bounds__(256, 3) void decode_head_kernel(RouterRoleArgs r, SharedDecodeArgs a) {
+  constexpr int LDS = SharedWaveCfg<0, AL, kRoleLdsKiB>::LDS;
+  static_assert(lds_fits(3, LDS), "three workgroups per CU");
+  if (static_cast<int>(blockIdx.x) < r.T) router_role<4, LDS>(r, blockIdx.x);
   else if (threadIdx.x < 64) shared_wave_unit<0, AL, kRoleLdsKiB>(a, blockIdx.x - r.T, gridDim.x - r.T, 1, a.K >> 6);
 }
 
 template <int BITS, int AL>
 __global__ __launch_bounds__((64 * SharedQWaveCfg<0, BITS, AL>::NW)) void decode_head_q_kernel(RouterRoleArgs r, SharedQDecodeArgs a) {
-  if (static_cast<int>(blockIdx.x) < r.T) router_role<SharedQWaveCfg<0, BITS, AL>::NW>(r, blockIdx.x);
+  using Cfg = SharedQWaveCfg<0, BITS, AL>;
+  static_assert(lds_fits(2, Cfg::LDS), "two workgroups per CU");
+  if (static_cast<int>(blockIdx.x) < r.T) router_role<Cfg::NW, Cfg::LDS>(r, blockIdx.x);
   else shared_qwave_unit<0, BITS, AL>(a, blockIdx.x - r.T, gridDim.x - r.T, 1, a.K >> 6);
 }
 
 template <int AL>
 __global__ __launch_bounds__(256) void decode_mid_kernel(QuantRoleArgs r, SharedDecodeArgs a, int kc_count, int steps_per_plane) {
-  if (static_cast<int>(blockIdx.x) < r.R) quant_row<256, 10>(blockIdx.x, r.h, r.F, r.q_h, r.beta_h, r.rowsum_h);
+  constexpr int LDS = SharedWaveCfg<1, AL, kRoleLdsKiB>::LDS;
+  static_assert(lds_fits(3, LDS), "three workgroups per CU");
+  if (static_cast<int>(blockIdx.x) < r.R) quant_role<256, LDS>(r, blockIdx.x);
   else if (threadIdx.x < 64) shared_wave_unit<1, AL, kRoleLdsKiB>(a, blockIdx.x - r.R, gridDim.x - r.R, kc_count, steps_per_plane);
 }
 
 template <int BITS, int AL>
 __global__ __launch_bounds__((64 * SharedQWaveCfg<1, BITS, AL>::NW)) void decode_mid_q_kernel(QuantRoleArgs r, SharedQDecodeArgs a,
                                                                                              int kc_count, int steps_per_plane) {
-  constexpr int NT = 64 * SharedQWaveCfg<1, BITS, AL>::NW;
-  if (static_cast<int>(blockIdx.x) < r.R) quant_row<NT, 2560 / NT>(blockIdx.x, r.h, r.F, r.q_h, r.beta_h, r.rowsum_h);
+  using Cfg = SharedQWaveCfg<1, BITS, AL>;
+  static_assert(lds_fits(2, Cfg::LDS), "two workgroups per CU");
+  if (static_cast<int>(blockIdx.x) < r.R) quant_role<64 * Cfg::NW, Cfg::LDS>(r, blockIdx.x);
   else shared_qwave_unit<1, BITS, AL>(a, blockIdx.x - r.R, gridDim.x - r.R, kc_count, steps_per_plane);
 }
 

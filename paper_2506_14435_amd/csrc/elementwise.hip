@@ -15,7 +15,8 @@ template <int THREADS>
 __global__ __launch_bounds__(THREADS) void quant_rows_kernel(const uint16_t* __restrict__ h, int F,
                                                              int8_t* __restrict__ q, float* __restrict__ beta,
                                                              int32_t* __restrict__ rowsum) {
-  quant_row<THREADS, kRowChunks>(blockIdx.x, h, F, q, beta, rowsum);
+  __shared__ QuantRowScratch<THREADS> lds;
+  quant_row<THREADS, kRowChunks>(lds, blockIdx.x, h, F, q, beta, rowsum);
 }
 
 hipError_t launch_quant_rows(const uint16_t* h, int rows, int F, int8_t* q, float* beta, int32_t* rowsum,

@@ -48,12 +48,16 @@ __device__ __forceinline__ int chunk_quant(const uint4& p, float s, uint2* o) {
   return q0 + q1 + q2 + q3 + q4 + q5 + q6 + q7;
 }
 
+template <int THREADS>
+struct QuantRowScratch {   // LDS of a workgroup
+  float f[THREADS / kWave];
+  int i[THREADS / kWave];
+};
+
 // One row by a workgroup of THREADS threads, CHUNKS 16-byte chunks per thread in registers.
 template <int THREADS, int CHUNKS>
-__device__ __forceinline__ void quant_row(int64_t row, const uint16_t* __restrict__ h, int F, int8_t* __restrict__ q,
+__device__ __forceinline__ void quant_row(QuantRowScratch<THREADS>& lds, int64_t row, const uint16_t* __restrict__ h, int F, int8_t* __restrict__ q,
                                           float* __restrict__ beta, int32_t* __restrict__ rowsum) {
-  __shared__ float s_f[THREADS / kWave];
-  __shared__ int s_i[THREADS / kWave];
   const uint16_t* hp = h + row * F;
   const int n_chunks = F >> 3;
   uint4 keep[CHUNKS];
@@ -67,7 +71,7 @@ __device__ __forceinline__ void quant_row(int64_t row, const uint16_t* __restric
   for (int i = 0; i < CHUNKS; ++i) amax = fmaxf(amax, chunk_absmax(keep[i]));
   for (int ch = threadIdx.x + CHUNKS * THREADS; ch < n_chunks; ch += THREADS)
     amax = fmaxf(amax, chunk_absmax(*reinterpret_cast<const uint4*>(hp + ch * 8)));
-  const float b = fmaxf(block_max<THREADS>(amax, s_f), kEps);
+  const float b = fmaxf(block_max<THREADS>(amax, lds.f), kEps);
   const float s = 127.0f / b;
   int rs = 0;
 #pragma unroll
@@ -85,7 +89,7 @@ __device__ __forceinline__ void quant_row(int64_t row, const uint16_t* __restric
     rs += chunk_quant(*reinterpret_cast<const uint4*>(hp + ch * 8), s, &o);
     *reinterpret_cast<uint2*>(q + row * F + ch * 8) = o;
   }
-  const int total = block_sum<THREADS>(rs, s_i);
+  const int total = block_sum<THREADS>(rs, lds.i);
   if (threadIdx.x == 0) {
     beta[row] = b;
     rowsum[row] = total;

@@ -23,7 +23,8 @@ __global__ __launch_bounds__(64 * NW) void router_quant_kernel(
     float* __restrict__ beta_x, int32_t* __restrict__ rowsum_x, float* __restrict__ gate_p) {
   const int t0 = blockIdx.x * TPW;   // the NW wavefronts of a workgroup split the channels of TPW tokens
   if (t0 >= T) return;
-  router_quant_group<EMAX, TPW, NW, (EMAX > 16 ? 1 : 2)>(t0, x, w_router, bias, T, d, E, k, topk_idx, topk_p, q_x, beta_x,
+  __shared__ RouterScratch<TPW, NW> lds;
+  router_quant_group<EMAX, TPW, NW, (EMAX > 16 ? 1 : 2)>(lds, t0, x, w_router, bias, T, d, E, k, topk_idx, topk_p, q_x, beta_x,
                                                         rowsum_x, gate_p);
 }
 

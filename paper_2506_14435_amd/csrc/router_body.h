@@ -93,20 +93,24 @@ __device__ __forceinline__ void gate_topk(double l, int e, bool store, int tok, 
   }
 }
 
+template <int TPW, int NW>
+struct RouterScratch {   // LDS of a workgroup
+  double logit[NW][64];
+  float amax[NW][TPW];
+  int rsum[NW][TPW];
+};
+
 // One token group = TPW tokens from t0 on; the NW wavefronts of the workgroup split its channels.
 // ROWS: router rows of a chunk requested together (registers against latency).
 template <int EMAX, int TPW, int NW, int ROWS>
 __device__ __forceinline__ void router_quant_group(
-    int t0, const uint16_t* __restrict__ x, const uint16_t* __restrict__ w_router, const float* __restrict__ bias, int T,
+    RouterScratch<TPW, NW>& lds, int t0, const uint16_t* __restrict__ x, const uint16_t* __restrict__ w_router, const float* __restrict__ bias, int T,
     int d, int E, int k, int32_t* __restrict__ topk_idx, float* __restrict__ topk_p, int8_t* __restrict__ q_x,
     float* __restrict__ beta_x, int32_t* __restrict__ rowsum_x, float* __restrict__ gate_p) {
   constexpr int NV = EMAX * TPW;           // logits of a token group; lane l ends up with logit l % NV
   static_assert(NV <= 64 && 64 % NV == 0, "at most one finished logit per lane");
   constexpr int kWaves = NW;               // wavefronts that split the channels of one token group
   constexpr int kThreads = 64 * NW;
-  __shared__ double s_logit[kWaves][64];
-  __shared__ float s_amax[kWaves][TPW];
-  __shared__ int s_rsum[kWaves][TPW];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int n_chunks = d >> 3;
   const bool vec_ok = (E & 7) == 0;
@@ -157,26 +161,26 @@ __device__ __forceinline__ void router_quant_group(
   if constexpr (NV > 1) reduce_scatter_step<NV / 2, NV>(acc, lane);
 #pragma unroll
   for (int off = NV; off < 64; off <<= 1) acc[0] += __shfl_xor(acc[0], off, kWave);
-  s_logit[wave][lane] = acc[0];
+  lds.logit[wave][lane] = acc[0];
 #pragma unroll
   for (int t = 0; t < TPW; ++t) {
     amax[t] = wave_max(amax[t]);
-    if (lane == 0) s_amax[wave][t] = amax[t];
+    if (lane == 0) lds.amax[wave][t] = amax[t];
   }
   __syncthreads();
   if (wave == 0) {   // fixed summation order over the channel slices
-    double l = s_logit[0][lane];
+    double l = lds.logit[0][lane];
 #pragma unroll
-    for (int w = 1; w < kWaves; ++w) l += s_logit[w][lane];
+    for (int w = 1; w < kWaves; ++w) l += lds.logit[w][lane];
     const int e = lane % EMAX;
     const int tok = t0 + (lane % NV) / EMAX;
     gate_topk<EMAX>(l, e, lane < NV && tok < T, tok, bias, E, k, topk_idx, topk_p, gate_p);
   }
 #pragma unroll
   for (int t = 0; t < TPW; ++t) {
-    float m = s_amax[0][t];
+    float m = lds.amax[0][t];
 #pragma unroll
-    for (int w = 1; w < kWaves; ++w) m = fmaxf(m, s_amax[w][t]);
+    for (int w = 1; w < kWaves; ++w) m = fmaxf(m, lds.amax[w][t]);
     amax[t] = m;
   }
 
@@ -214,16 +218,16 @@ __device__ __forceinline__ void router_quant_group(
 #pragma unroll
   for (int t = 0; t < TPW; ++t) {
     const int part = wave_sum(rs[t]);
-    if (lane == 0) s_rsum[wave][t] = part;
+    if (lane == 0) lds.rsum[wave][t] = part;
   }
   __syncthreads();
   if (threadIdx.x < TPW && t0 + threadIdx.x < T) {
     int total = 0;
 #pragma unroll
-    for (int w = 0; w < kWaves; ++w) total += s_rsum[w][threadIdx.x];
-    float m = s_amax[0][threadIdx.x];
+    for (int w = 0; w < kWaves; ++w) total += lds.rsum[w][threadIdx.x];
+    float m = lds.amax[0][threadIdx.x];
 #pragma unroll
-    for (int w = 1; w < kWaves; ++w) m = fmaxf(m, s_amax[w][threadIdx.x]);
+    for (int w = 1; w < kWaves; ++w) m = fmaxf(m, lds.amax[w][threadIdx.x]);
     beta_x[t0 + threadIdx.x] = fmaxf(m, kEps);
     rowsum_x[t0 + threadIdx.x] = total;
   }

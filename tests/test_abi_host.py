@@ -141,3 +141,43 @@ def test_batches_that_fit_on_32_row_tiles_are_not_refused(lib, d, F, E, k, bits,
     call = lambda t: lib.mote_layer_forward_static(ctypes.byref(L), None, t, ctypes.c_void_p(p), None, None)
     assert call(T) in (1, 4)      # invalid argument, or no GPU for the scratch array
     assert call(8 * T) == 3
+
+
+def _device_kernels(path):
+    """Metadata of the kernels in the gfx950 code objects inside the library: {name: {key: value}} from the
+    AMDGPU notes (a msgpack map each) of the ELF files embedded in it."""
+    import struct
+    import msgpack
+    data, out = open(path, "rb").read(), {}
+    at = data.find(b"\x7fELF", 1)
+    while at >= 0:
+        machine, = struct.unpack_from("<H", data, at + 18)
+        shoff, = struct.unpack_from("<Q", data, at + 40)
+        shentsize, shnum = struct.unpack_from("<HH", data, at + 58)
+        for i in range(shnum if machine == 224 else 0):     # EM_AMDGPU
+            _, kind, _, _, off, size = struct.unpack_from("<IIQQQQ", data, at + shoff + i * shentsize)
+            pos, end = at + off, at + off + size
+            while kind == 7 and pos < end:                  # SHT_NOTE
+                namesz, descsz, ntype = struct.unpack_from("<III", data, pos)
+                desc = pos + 12 + (namesz + 3) // 4 * 4
+                if ntype == 32:                             # NT_AMDGPU_METADATA
+                    for k in msgpack.unpackb(data[desc:desc + descsz])["amdhsa.kernels"]:
+                        out[k[".name"]] = k
+                pos = desc + (descsz + 3) // 4 * 4
+        at = data.find(b"\x7fELF", at + 1)
+    return out
+
+
+def test_combined_decode_kernels_reserve_nothing_beside_their_ring(lib):
+    """The rings of the decode step's two combined kernels are cut so that a whole number of workgroups fills a CU's
+    LDS; static LDS of the small kernels inside them would come on top and take one of those workgroups away.  Nor do
+    they need so many registers that fewer workgroups fit (four wavefronts, one per SIMD: 512 / 3 and 512 / 2)."""
+    kernels = _device_kernels(M.LIB_PATH)
+    assert any("routed_wave_kernel" in n for n in kernels)
+    combined = {n: k for n, k in kernels.items() if re.search(r"decode_(head|mid)(_q)?_kernel", n)}
+    assert len(combined) == 2 * 4 + 2 * 2 * 4      # by token rows, and for the quantised expert by bits
+    for n, k in combined.items():
+        assert k[".group_segment_fixed_size"] == 0, n
+        assert k[".private_segment_fixed_size"] == 0 and k[".vgpr_spill_count"] == 0, n
+        per_simd = 2 if "_q_kernel" in n else 3
+        assert k[".vgpr_count"] <= 512 // per_simd // 8 * 8, n
