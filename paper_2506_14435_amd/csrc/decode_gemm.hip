@@ -755,10 +755,10 @@ hipError_t launch_routed_decode_gate_up(const RoutedGemmArgs& a, hipStream_t str
   if (a.max_tiles == 0) return hipSuccess;
   const int n_frags = a.N / 32, KT = a.K >> 7;
   const int64_t max_units = static_cast<int64_t>(a.max_tiles) * n_frags;
-  int64_t blocks = static_cast<int64_t>(device_cus()) * 4;
+  const bool local = a.topk_idx != nullptr;
+  int64_t blocks = static_cast<int64_t>(device_cus()) * a.wg_per_cu;
   if (blocks > max_units) blocks = max_units;
   if (a.tile_m == 64) return launch_wave<0, 2, 8, false>(a, n_frags, 1, stream);
-  const bool local = a.topk_idx != nullptr;
   if (KT <= 16) {
     if (use_wave_kernel(a, n_frags, 1)) {
       if (knob(kKnobDecodeVariant) == 1)

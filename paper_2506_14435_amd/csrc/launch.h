@@ -87,6 +87,7 @@ struct RoutedGemmArgs {
   // rows and kRoleMaxExperts experts); null: the plan is there already
   const int32_t* topk_idx;
   int k, E;
+  int wg_per_cu;            // grid of the K-split decode kernel (d > 2048), of which two workgroups per CU are resident
 };
 constexpr int kLocalPlanRows = 512;   // kSharedDecodeMaxTokens tokens of top-8
 constexpr int kRoleMaxExperts = 16;

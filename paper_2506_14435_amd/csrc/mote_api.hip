@@ -378,28 +378,49 @@ mote_status forward_impl(const mote_layer* layer, const mote_norm* norm, const v
   const int64_t shared_weights = static_cast<int64_t>(d) * Fs;
   const bool fork_pays = T * shared_weights >= (int64_t{1} << fork_log2) ||
                          (T <= 8 && shared_weights >= (int64_t{1} << 24) && fork_log2 <= 29);
-  SideStream* side = nullptr;
+  const bool fork = !timing && !one_stream && fork_enabled() && fork_pays;
   // Decode steps can carry the router and Q_a(h) as workgroups of the shared expert's kernels, on one
   // stream, with the dispatch plan made inside the gate-up kernel: five launches, no events (stage timing
-  // wants one kernel per stage).  Against the forked chain (us per forward; E = 16, top-2 unless noted):
-  //   d = 256   T=64 39.0 -> 29.4;  d = 896 (E = 8) T=8 47.8 -> 36.6, T=64 55.0 -> 42.3, INT8 54.8 -> 44.7
-  //   d = 1536  T=8 80.7 -> 67.2, T=64 85.7 -> 83.5, but INT8 T=40 78.9 -> 80.7 and T=64 81.8 -> 83.1
-  //   d = 2048  T=1 74.8 -> 64.5, T=16 105.3 -> 98.2, INT8 T=1 65.3 -> 46.2, INT8 T=32 94.3 -> 89.3, but
-  //             T=24 96.6 -> 98.7, T=64 110.6 -> 112.2, INT8 T=64 103.5 -> 108.4: the routed kernels of more
-  //             rows leave half of a CU's LDS free, where the forked chain streams the shared expert
-  //   d = 3584  T=16 264.7 -> 259.2, T=64 330.5 -> 312.3, but T=2 140.2 -> 149.3 and INT4 T=1 77.7 -> 83.5 (long
-  //             kernels, the fork is hidden); there the plan inside the gate-up kernel alone pays (T=8 221.9 ->
-  //             212.4, INT8 T=32 178.8 -> 173.4), which at d = 2048 does not (T=32 99.8 -> 100.3).
+  // wants one kernel per stage).  Where the forward would not fork, this is always the faster form (us per forward,
+  // E = 16, top-2 unless noted; eight launches on one stream -> five):
+  //   d = 256 (E = 4) T=1 33.8 -> 25.7, T=64 38.9 -> 29.7;  d = 896 (E = 8) T=64 56.2 -> 43.5, INT4 58.6 -> 45.9
+  //   d = 1536 INT8 T=33 93.5 -> 79.8;  d = 2048 T=16 98.7 -> 88.3, T=20 102.3 -> 89.9, INT4 T=16 93.3 -> 77.4
+  //   and with the helper stream switched off d = 2048 T=64 118 -> 106, d = 3584 T=1 165 -> 126, INT4 T=64 315 -> 293
+  // Where it would fork, the shared expert's stream is partly hidden already and the answer depends on the shape
+  // (forked, in brackets with the plan inside the gate-up kernel -> five launches):
+  //   below 2^24 weights (d = 1536, F = 8960)   T=64 85.7 -> 83.6, INT8 T=64 85.1 -> 83.7, INT4 T=64 91.0 -> 85.2
+  //   2^24 (d = 2048, F = 11008)  T=1 65.8 -> 57.5, T=8 92.9 -> 87.8, but T=24 89.6 -> 90.5, T=64 106.9 -> 111.1;
+  //     INT8 T=32 90.2 -> 84.0, T=64 102.5 -> 101.9 (F = 8320 94.4 -> 89.1), but from 1.5 * 2^24 on, d = 1536,
+  //     F = 18944: T=64 131 -> 132;  INT4 T=32 94.2 -> 83.8, but T=64 103.2 -> 104.7
+  //   2^25 and 2^26 (d = 4096, F = 14336 and d = 3584, F = 18944)
+  //     E = 16  T=1 127 (128) -> 126, T=4 172 (164) -> 172, T=16 263 -> 254, T=64 328 -> 308, but at 4096 T=16 204 -> 212,
+  //             T=24 222 -> 222, T=64 261 -> 251;   E = 8  T=4 150 (150) -> 156, T=16 182 -> 185, T=33 207 -> 196;
+  //             E = 4  T=64 169 -> 178
+  //     INT8    E = 16 T=4 147 (136) -> 137, T=8 191 -> 182, T=24 248 (251) -> 243, T=64 304 (288) -> 299, but at 4096
+  //             T=64 239 (252) -> 238;   E = 8 T=4 129 (122) -> 127, T=8 153 -> 148, T=24 173 (167) -> 175, T=64 202 (202) -> 229
+  //     INT4    E = 16 T=4 131 (124) -> 127, T=16 217 -> 208, T=64 276 (275) -> 292;   E = 8 T=4 114 (113) -> 118,
+  //             T=16 144 -> 141, T=64 194 (201) -> 218
+  // These are even loads.  At 2^26 weights a router that sends all tokens of a larger step to two or four of sixteen
+  // experts leaves so little routed work that the fork would hide it (two experts, T=64: 182 -> 190, INT8 163 -> 168);
+  // the host does not know the loads.
   const int roles_knob = knob(kKnobDecodeRoles);
   const bool roles_fit = !timing && roles_knob != 0 && decode_shared && decode_routed && E <= kRoleMaxExperts;
   const bool wide = shared_weights >= (int64_t{1} << 25);
-  bool roles_pay = true;
-  if (wide) roles_pay = layer->shared_bits == 0 && T > 8;
-  else if (shared_weights >= (int64_t{1} << 24)) roles_pay = T <= (layer->shared_bits ? 32 : 16);
-  else if (shared_weights >= (int64_t{1} << 23)) roles_pay = layer->shared_bits == 0 || T <= 32;
+  const int bits = layer->shared_bits;
+  bool roles_pay = true, plan_pays = false;   // five launches; forked, with the plan inside the gate-up kernel
+  if (fork && wide) {
+    if (bits == 0) roles_pay = T > 32 ? E >= 8 : T > 8 && E >= 16 && shared_weights >= (int64_t{1} << 26);
+    else if (bits == 8) roles_pay = T >= 8 && T <= (E >= 16 ? 32 : 16);
+    else roles_pay = T > 8 && T <= 32;
+    plan_pays = T <= 8 ? bits != 0 || T > 1 : bits == 8 && (T <= 32 || shared_weights >= (int64_t{1} << 26));
+  } else if (fork && shared_weights >= (int64_t{1} << 24)) {
+    if (bits == 0) roles_pay = T <= 16;
+    else roles_pay = T <= 32 || (bits == 8 && shared_weights < (int64_t{3} << 23));
+  }
   const bool roles = roles_fit && (roles_pay || roles_knob == 2);
-  const bool local_plan = roles_fit && (roles || wide) && tile_m == 32;
-  if (!timing && !roles && !one_stream && fork_enabled() && fork_pays) MOTE_HIP(side_stream(&side));
+  const bool local_plan = roles_fit && (roles || plan_pays) && tile_m == 32;
+  SideStream* side = nullptr;
+  if (fork && !roles) MOTE_HIP(side_stream(&side));
   hipStream_t sstream = side ? side->stream : stream;
   // Shared expert: bf16 weights (Eq.2), or RTN INT8 / INT4 codes with row scales (Section 4.3).  Small
   // batches stream the codes themselves; large batches first expand them to integer-valued bf16
@@ -456,6 +477,11 @@ mote_status forward_impl(const mote_layer* layer, const mote_norm* norm, const v
   ga.tap_up = taps ? taps->acc_up : nullptr;
   ga.partial_stride = 0; ga.planes = 1; ga.split_max = 1;
   ga.topk_idx = local_plan ? w.topk_idx : nullptr; ga.k = k; ga.E = E;
+  // A workgroup that makes the plan itself should not do so twice per slot: two per CU, all resident, take the units in
+  // turn (d = 3584, E = 16, INT8 T=4 145 -> 137 us, T=8 184 -> 183; two experts active of 16, bf16 T=16 134 -> 132).
+  // Beside the forked bf16 kernels, or those of more than 32 tokens, the hardware's dealing out of four pays more
+  // (E = 8: T=4 157 -> 150; d = 4096, E = 8, INT8 T=64 177 -> 169).
+  ga.wg_per_cu = !local_plan || (side && (bits == 0 || T > 32)) ? 4 : 2;
   MOTE_HIP(decode_routed ? launch_routed_decode_gate_up(ga, stream) : launch_routed_gate_up(ga, stream));
   MOTE_HIP(mark(3));
   if (roles)

@@ -509,3 +509,49 @@ def test_rtn_shared_expert_streamed_in_chunks_of_64_tokens(d, F, Ts, bits_):
         again = M.mote_layer_forward(gp.layer, gp.x, workspace=ws)
         torch.cuda.synchronize()
         assert torch.equal(out, again)
+
+
+# Kernel launches of a decode step: five with the router, the row quantiser and the dispatch plan inside the large
+# kernels, seven with only the plan inside the gate-up kernel, eight otherwise.  Wherever the forward does not fork it
+# takes the five: between the batches that fork for their few tokens and those that fork for their work (3B width, T = 17
+# to 23; quantised 1.5B width, T = 33 to 38), with the helper stream switched off, and on the static scratch.
+LAUNCH_CASES = [(2048, 11008, 4, 0, 16, "", 5), (2048, 11008, 4, 0, 20, "", 5), (2048, 11008, 4, 0, 24, "", 8),
+                (2048, 11008, 4, 0, 32, "no_fork", 5), (2048, 11008, 4, 0, 33, "static", 5), (1536, 8960, 4, 8, 33, "", 5),
+                (1536, 8960, 4, 4, 64, "", 5), (2048, 11008, 4, 4, 33, "", 8), (256, 512, 17, 0, 8, "", 8),
+                (3584, 18944, 4, 0, 1, "", 8), (3584, 18944, 4, 0, 8, "", 7), (3584, 18944, 4, 0, 64, "", 8),
+                (3584, 18944, 4, 8, 33, "", 7), (3584, 18944, 4, 4, 16, "", 5), (3584, 18944, 4, 4, 33, "", 8),
+                (3584, 18944, 4, 8, 64, "no_fork", 5)]
+
+
+@pytest.mark.parametrize("d,F,E,bits_,T,how,launches", LAUNCH_CASES)
+def test_decode_step_kernel_launches(d, F, E, bits_, T, how, launches):
+    import ctypes
+    M = _m()
+    lib = M.load_library()
+    z = lambda *s, dtype=torch.bfloat16: torch.zeros(*s, dtype=dtype, device="cuda")
+    shared, scales = [z(F, d), z(F, d), z(d, F)], None
+    if bits_:
+        shared = [z(F * d * bits_ // 8, dtype=torch.uint8) for _ in range(3)]
+        scales = tuple(z(n, dtype=torch.float32) for n in (F, F, d))
+    layer = M.MoteLayer(z(d, E), *shared, *[z(E, d * F // 16, dtype=torch.int32) for _ in range(3)],
+                        z(E, 3, dtype=torch.float32), 1, shared_bits=bits_, shared_scales=scales)
+    x, out = z(T, d), z(T, d)
+    ws = layer.workspace(T)
+    call = lambda: (M.mote_layer_forward_static(layer, x, out) if how == "static"
+                    else M.mote_layer_forward(layer, x, out=out, workspace=ws))
+    stream, graph, n = torch.cuda.Stream(), ctypes.c_void_p(), ctypes.c_size_t()
+    try:
+        M.mote_tuning_set("no_fork", int(how == "no_fork"))
+        with torch.cuda.stream(stream):
+            call()                                  # helper stream and kernel attributes exist from here on
+            torch.cuda.synchronize()
+            handle = ctypes.c_void_p(stream.cuda_stream)
+            assert lib.hipStreamBeginCapture(handle, 2) == 0
+            call()
+            assert lib.hipStreamEndCapture(handle, ctypes.byref(graph)) == 0
+        assert lib.hipGraphGetNodes(graph, None, ctypes.byref(n)) == 0
+        assert n.value == launches
+    finally:
+        M.mote_tuning_set("no_fork", 0)
+        if graph:
+            lib.hipGraphDestroy(graph)
