@@ -929,3 +929,40 @@ def test_layer_rows_longer_than_a_plane_on_either_tile_height(T):
         M.mote_tuning_set("decode_rows", -1)
     for n in taps[48]:
         assert torch.equal(taps[48][n], taps[16][n]) and torch.equal(taps[48][n], taps[-1][n]), n
+
+
+# From 2^25 shared weights on a small step keeps the forked shared expert and makes only the dispatch plan inside the
+# gate-up kernel (the K-split one, d > 2048): against the plan kernel, by the default rule, with the shared chain on the
+# helper stream.  Two, eight and 32 tokens, one and several tiles per expert, experts without rows (bias).
+@pytest.mark.parametrize("T,k,shared_bits", [(2, 1, 0), (8, 2, 0), (1, 2, 8), (7, 2, 8), (32, 2, 8), (3, 2, 4), (8, 4, 4)])
+def test_decode_step_with_the_plan_alone_inside_the_gate_up_kernel(T, k, shared_bits):
+    M = _m()
+    d, F, E = 2304, 14592, 4
+    g = torch.Generator(device="cuda").manual_seed(T * 100 + k)
+    rnd = lambda *s, std=1.0: torch.randn(*s, device="cuda", generator=g) * std
+    shared, scales = [rnd(*s, std=0.01).to(torch.bfloat16) for s in ((F, d), (F, d), (d, F))], None
+    if shared_bits:
+        packed = [M.mote_pack_rtn(w, shared_bits) for w in shared]
+        shared, scales = [p for p, _ in packed], tuple(s for _, s in packed)
+    wt = [torch.empty(E, d * F // 16, dtype=torch.int32, device="cuda") for _ in range(3)]
+    alpha = torch.empty(3, E, 1, dtype=torch.float32, device="cuda")
+    for e in range(E):
+        for m in range(3):
+            M.mote_pack_ternary(rnd(*((F, d) if m < 2 else (d, F)), std=0.02), packed=wt[m][e], alpha=alpha[m, e])
+    layer = M.MoteLayer(rnd(d, E, std=d ** -0.5).to(torch.bfloat16), *shared, *wt, alpha[:, :, 0].t().contiguous(), k,
+                        router_bias=torch.tensor([0.0, 3.0, 30.0, 0.0], device="cuda"), shared_bits=shared_bits, shared_scales=scales)
+    x = rnd(T, d).to(torch.bfloat16)
+    names = ("topk_idx", "topk_p", "counts", "row_of", "tok_of", "acc_gate", "acc_up", "h", "q_h", "acc_down", "h_s", "y_s", "out_f32")
+    taps = {}
+    try:
+        for mode in (0, 1):
+            M.mote_tuning_set("decode_roles", mode)
+            for again in range(3):      # a step right behind the last one: the two streams meet different kernels
+                taps[mode] = M.alloc_taps(layer, T, names)
+                taps[mode]["out"] = M.mote_layer_forward(layer, x, taps=dict(taps[mode]))
+            torch.cuda.synchronize()
+    finally:
+        M.mote_tuning_set("decode_roles", 1)
+    assert taps[0]["counts"].sum() == T * k
+    for n in taps[0]:
+        assert torch.equal(taps[0][n], taps[1][n]), n
