@@ -264,7 +264,8 @@ mote_status mote_block_forward(const mote_layer* layer, const mote_norm* norm, c
  * mote_layer_forward (the results are bit-identical).  A batch whose layout needs more than the
  * array is refused with MOTE_ERR_WORKSPACE_TOO_SMALL before anything is launched (none with
  * mote_layer_workspace_bytes(layer, T) <= MOTE_STATIC_WORKSPACE_BYTES; where two layouts can serve a
- * batch, the smaller is taken if only that fits); 64 MiB serve the 3B-width layer
+ * batch, the smaller is taken if only that fits: the one difference in results is then that a quantised
+ * shared expert of a few hundred tokens may have its fp32 sums in another order); 64 MiB serve the 3B-width layer
  * (d = 2048, F = 11008, 16 experts, top-2) up to 256 tokens and the 7B width up to 128.  All calls
  * on one GPU share that GPU's array, which keeps the previous call's contents: calls must be
  * ordered on one stream (or otherwise not overlap), two that overlap on one GPU race. */

@@ -40,6 +40,7 @@ struct Workspace {
   size_t bytes;
   int max_tiles;
   int tile_m;        // 32, 64: decode kernels, 128: large-batch kernels
+  bool shared_streams;   // the shared expert's weights are streamed (decode kernels) instead of tiled
   int d_planes;      // uniform partial planes of the routed down accumulators
   int d_split;       // planes a tile of the last round may be cut into instead (large batch, d_planes == 1)
   int y_planes;      // partial planes of the shared expert output
@@ -62,27 +63,38 @@ bool layer_shape_ok(const mote_layer* l) {
   return true;
 }
 
-// Whether the shared expert's weights are streamed (decode kernels) instead of tiled.  RTN codes are streamed
-// up to a few times 64 tokens: the tiled GEMMs want them expanded to bf16 in every forward (39 us at d = 2048) and
-// have a tile or two per CU there.  Expanded and tiled -> streamed, us per INT8 forward (E = 16, top-2):
-//   d = 256 (E = 4)  T=128 84.3 -> 48.9, T=512 72.7 -> 58.0;   d = 896 (E = 8) T=128 76.7 -> 64.8, T=256 72.3 -> 88.0
-//   d = 1536         T=128 131.0 -> 105.6, T=256 145.5 -> 153.8
-//   d = 2048         T=65 185.5 -> 127.5, T=128 198.3 -> 139.5, T=192 194.0 -> 170.2, T=256 194.4 -> 207.5
-//   d = 3584         T=128 473.0 -> 352.2, T=384 885.0 -> 779.9, T=512 697.1 -> 757.1
+// Largest batch at which the RTN codes of a quantised shared expert are streamed (decode kernels) instead of tiled, a
+// few times 64 tokens: the tiled GEMMs want them expanded to bf16 in every forward (39 us at d = 2048) and
+// have a tile or two per CU there.  Expanded and tiled -> streamed, us per forward (top-2, INT8 / INT4):
+//   below 2^20 weights  d = 256, F = 512 (E = 4) T=128 84 -> 49, T=512 73 -> 59;  d = 2048, F = 384 (E = 8) T=512 132 -> 93;
+//                       d = 896, F = 1024 T=384 125 -> 81, but T=512 86 -> 90;  d = 384, F = 2560 T=384 99 -> 84, T=512 84 -> 96
+//   2^20                d = 896, F = 4864 (E = 8) T=128 79 -> 66, T=192 81 -> 80, T=256 72 -> 89
+//   2^23                d = 2048, F = 4352 T=192 136 -> 114 / 138 -> 122, T=256 145 -> 142 / 148 -> 159;  d = 1536, F = 8960 T=192
+//                       133 -> 133, T=193 133 -> 148;  F = 11008, d = 2048 T=128 188 -> 142, T=192 194 -> 176, T=256 190 -> 215;
+//                       but d = 1024, F = 8192 T=128 92 -> 79 / 96 -> 80, T=192 96 -> 100 / 97 -> 104
+//   2^25                d = 3584, F = 18944 T=128 473 -> 352 / 478 -> 372, T=256 550 -> 528 / 566 -> 494, T=320 615 -> 606 /
+//                       616 -> 572, T=384 640 -> 664 / 643 -> 654;  E = 8 T=320 511 -> 487, T=384 543 -> 550;
+//                       d = 4096, F = 14336 (E = 8) T=320 448 -> 426, T=384 477 -> 487
 int shared_q_tokens(const mote_layer* l) {
+  if (knob(kKnobSharedQTokens) >= 0) return knob(kKnobSharedQTokens);
+  const int64_t weights = static_cast<int64_t>(l->d_model) * l->d_ff_shared;
+  if (weights < (int64_t{1} << 20)) return weights < (int64_t{7} << 17) ? 512 : 384;
+  if (weights < (int64_t{1} << 23)) return 128;
+  if (weights < (int64_t{1} << 25)) return l->d_model >= 1536 ? 192 : 128;
+  return 320;
+}
+// ... and where the scratch has no room for the expanded matrices.
+int shared_q_tokens_max(const mote_layer* l) {
   if (knob(kKnobSharedQTokens) >= 0) return knob(kKnobSharedQTokens);
   const int64_t weights = static_cast<int64_t>(l->d_model) * l->d_ff_shared;
   if (weights < (int64_t{1} << 20)) return 512;
   if (weights < (int64_t{1} << 23)) return 128;
   return weights < (int64_t{1} << 25) ? 192 : 384;
 }
-bool shared_streams(const mote_layer* l, int T) {
-  return T <= kSharedDecodeMaxTokens || (l->shared_bits != 0 && T <= shared_q_tokens(l));
-}
 
 // Carves the workspace; with base == nullptr only the size is computed.  decode_rows: largest average number of
-// rows per expert on 32-row plan tiles.
-Workspace carve(const mote_layer* l, int T, char* base, int decode_rows) {
+// rows per expert on 32-row plan tiles; q_tokens: largest T at which a quantised shared expert is streamed.
+Workspace carve(const mote_layer* l, int T, char* base, int decode_rows, int q_tokens) {
   Workspace w{};
   size_t off = 0;
   auto take = [&](size_t bytes) -> char* {
@@ -97,8 +109,9 @@ Workspace carve(const mote_layer* l, int T, char* base, int decode_rows) {
   w.d_planes = w.tile_m != 128 ? routed_decode_down_planes(l->d_ff_routed)
                               : routed_down_planes(T, l->top_k, l->n_experts, l->d_model, l->d_ff_routed);
   w.d_split = (w.tile_m == 128 && w.d_planes == 1) ? kSplitMaxPlanes : 1;
-  w.y_planes = shared_streams(l, T) ? shared_decode_down_planes(l->d_model, l->d_ff_shared)
-                                           : shared_down_planes(T, l->d_model, l->d_ff_shared);
+  w.shared_streams = T <= kSharedDecodeMaxTokens || (l->shared_bits != 0 && T <= q_tokens);
+  w.y_planes = w.shared_streams ? shared_decode_down_planes(l->d_model, l->d_ff_shared)
+                                : shared_down_planes(T, l->d_model, l->d_ff_shared);
   w.topk_idx = reinterpret_cast<int32_t*>(take(R * 4));
   w.topk_p = reinterpret_cast<float*>(take(R * 4));
   w.counts = reinterpret_cast<int32_t*>(take(64 * 4));
@@ -122,7 +135,7 @@ Workspace carve(const mote_layer* l, int T, char* base, int decode_rows) {
   w.h_s = reinterpret_cast<uint16_t*>(take(static_cast<size_t>(T) * Fs * 2));
   w.y_s = reinterpret_cast<float*>(take(static_cast<size_t>(T) * d * 4 * static_cast<size_t>(w.y_planes)));
   w.xn = reinterpret_cast<uint16_t*>(take(static_cast<size_t>(T) * d * 2));
-  if (l->shared_bits != 0 && !shared_streams(l, T)) {
+  if (l->shared_bits != 0 && !w.shared_streams) {
     w.deq_gate = reinterpret_cast<uint16_t*>(take(d * Fs * 2));
     w.deq_up = reinterpret_cast<uint16_t*>(take(d * Fs * 2));
     w.deq_down = reinterpret_cast<uint16_t*>(take(d * Fs * 2));
@@ -130,17 +143,24 @@ Workspace carve(const mote_layer* l, int T, char* base, int decode_rows) {
   w.bytes = off;
   return w;
 }
-Workspace carve(const mote_layer* l, int T, char* base) { return carve(l, T, base, routed_decode_rows(l->d_model)); }
+Workspace carve(const mote_layer* l, int T, char* base) {
+  return carve(l, T, base, routed_decode_rows(l->d_model), shared_q_tokens(l));
+}
 
-// The layout for `bytes` of scratch.  The 128-row kernel that a wide layer prefers from 17 rows per expert on keeps up
-// to four planes of the routed down accumulators, the 32-row kernels ceil(F / 2048): where only the latter fit
-// (d = 2176, F = 1280, E = 32, top-2, T = 674: 66.8 and 33.2 MiB), the batch runs on 32-row tiles, with the same result to
-// the bit, and is not refused.
+// The layout for `bytes` of scratch.  Two routes that are faster need more of it than the other way to the result; where
+// only the other fits, the batch goes that way and is not refused:
+//   - the 128-row kernel that a wide layer prefers from 17 rows per expert on keeps up to four planes of the routed down
+//     accumulators, the 32-row kernels ceil(F / 2048) (d = 2176, F = 1280, E = 32, top-2, T = 674: 66.8 and 33.2 MiB); the
+//     result is the same to the bit;
+//   - the tiled GEMMs of a quantised shared expert want its matrices expanded to bf16.
 Workspace carve_to_fit(const mote_layer* l, int T, char* base, size_t bytes) {
-  const Workspace w = carve(l, T, base);
-  if (w.bytes <= bytes) return w;
-  const Workspace small = carve(l, T, base, routed_decode_rows_max(l->d_model));
-  return small.bytes <= bytes ? small : w;
+  const int rows[2] = {routed_decode_rows(l->d_model), routed_decode_rows_max(l->d_model)};
+  const int q_tokens[2] = {shared_q_tokens(l), shared_q_tokens_max(l)};
+  for (int i = 0; i < 4; ++i) {
+    const Workspace w = carve(l, T, base, rows[i & 1], q_tokens[i >> 1]);
+    if (w.bytes <= bytes) return w;
+  }
+  return carve(l, T, base);
 }
 
 // ---- stage timing state (host side) ----
@@ -430,7 +450,7 @@ mote_status forward_impl(const mote_layer* layer, const mote_norm* norm, const v
     if (sbits == 0)
       return decode_shared ? launch_shared_decode_gate_up(xb, sg, su, T, d, Fs, w.h_s, s)
                            : launch_shared_gate_up(xb, sg, su, T, d, Fs, w.h_s, s);
-    if (shared_streams(layer, T))
+    if (w.shared_streams)
       return launch_shared_q_decode_gate_up(xb, layer->ws_gate, layer->ws_up, layer->ss_gate, layer->ss_up, sbits, T, d,
                                             Fs, w.h_s, s);
     hipError_t e = launch_rtn_dequant(layer->ws_gate, Fs, d, sbits, w.deq_gate, s);
@@ -443,7 +463,7 @@ mote_status forward_impl(const mote_layer* layer, const mote_norm* norm, const v
     if (sbits == 0)
       return decode_shared ? launch_shared_decode_down(w.h_s, sd, T, d, Fs, w.y_s, s)
                            : launch_shared_down(w.h_s, sd, T, d, Fs, w.y_s, s);
-    if (shared_streams(layer, T)) return launch_shared_q_decode_down(w.h_s, layer->ws_down, layer->ss_down, sbits, T, d, Fs, w.y_s, s);
+    if (w.shared_streams) return launch_shared_q_decode_down(w.h_s, layer->ws_down, layer->ss_down, sbits, T, d, Fs, w.y_s, s);
     return launch_shared_down_scaled(w.h_s, w.deq_down, layer->ss_down, T, d, Fs, w.y_s, s);
   };
   if (side) {

@@ -555,3 +555,59 @@ def test_decode_step_kernel_launches(d, F, E, bits_, T, how, launches):
         M.mote_tuning_set("no_fork", 0)
         if graph:
             lib.hipGraphDestroy(graph)
+
+
+def _captured_kernels(call):
+    """Names of the kernels that call() launches, in no particular order: the kernel nodes of a captured graph."""
+    import ctypes
+
+    class Params(ctypes.Structure):      # hipKernelNodeParams
+        _fields_ = [("block", ctypes.c_uint * 3), ("extra", ctypes.c_void_p), ("func", ctypes.c_void_p),
+                    ("grid", ctypes.c_uint * 3), ("args", ctypes.c_void_p), ("lds", ctypes.c_uint)]
+    lib = _m().load_library()
+    lib.hipKernelNameRefByPtr.restype = ctypes.c_char_p
+    stream, graph, n = torch.cuda.Stream(), ctypes.c_void_p(), ctypes.c_size_t()
+    with torch.cuda.stream(stream):
+        call()                           # helper stream and kernel attributes exist from here on
+        torch.cuda.synchronize()
+        handle = ctypes.c_void_p(stream.cuda_stream)
+        assert lib.hipStreamBeginCapture(handle, 2) == 0
+        call()
+        assert lib.hipStreamEndCapture(handle, ctypes.byref(graph)) == 0
+    try:
+        assert lib.hipGraphGetNodes(graph, None, ctypes.byref(n)) == 0
+        nodes = (ctypes.c_void_p * n.value)()
+        assert lib.hipGraphGetNodes(graph, nodes, ctypes.byref(n)) == 0
+        names = []
+        for node in nodes:
+            p = Params()
+            assert lib.hipGraphKernelNodeGetParams(ctypes.c_void_p(node), ctypes.byref(p)) == 0
+            names.append(lib.hipKernelNameRefByPtr(ctypes.c_void_p(p.func), handle).decode())
+        return names
+    finally:
+        lib.hipGraphDestroy(graph)
+
+
+def _zero_layer(M, d, F, E, k, bits_):
+    z = lambda *s, dtype=torch.bfloat16: torch.zeros(*s, dtype=dtype, device="cuda")
+    shared, scales = [z(F, d), z(F, d), z(d, F)], None
+    if bits_:
+        shared = [z(F * d * bits_ // 8, dtype=torch.uint8) for _ in range(3)]
+        scales = tuple(z(n, dtype=torch.float32) for n in (F, F, d))
+    return M.MoteLayer(z(d, E), *shared, *[z(E, d * F // 16, dtype=torch.int32) for _ in range(3)],
+                       z(E, 3, dtype=torch.float32), k, shared_bits=bits_, shared_scales=scales)
+
+
+# The batches up to which a quantised shared expert's codes are streamed, on both sides of each limit.
+@pytest.mark.parametrize("d,F,T,streamed", [(256, 512, 512, True), (256, 512, 513, False), (896, 1024, 384, True),
+                                            (896, 1024, 385, False), (1024, 8192, 128, True), (1024, 8192, 129, False),
+                                            (1536, 8960, 192, True), (1536, 8960, 193, False), (2304, 14592, 320, True),
+                                            (2304, 14592, 321, False)])
+def test_quantised_shared_expert_is_streamed_up_to_a_limit_by_shape(d, F, T, streamed):
+    M = _m()
+    layer = _zero_layer(M, d, F, 8, 1, 8)
+    x = torch.zeros(T, d, dtype=torch.bfloat16, device="cuda")
+    out, ws = torch.empty_like(x), layer.workspace(T)
+    names = _captured_kernels(lambda: M.mote_layer_forward(layer, x, out=out, workspace=ws))
+    assert any("shared_qwave_kernel" in n for n in names) == streamed
+    assert any("rtn_dequant_kernel" in n for n in names) == (not streamed)

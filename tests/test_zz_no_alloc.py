@@ -94,3 +94,22 @@ def test_static_entry_point_on_the_smaller_layout_of_the_32_row_kernels():
         assert torch.equal(got_taps[n], want_taps[n]), n
     ws = torch.empty(M.binding.STATIC_WORKSPACE_BYTES, dtype=torch.uint8, device="cuda")
     assert torch.equal(M.mote_layer_forward(gp.layer, gp.x, workspace=ws), want)
+
+
+def test_static_entry_point_streams_a_quantised_expert_that_does_not_fit_expanded():
+    import paper_2506_14435_amd as M
+    T = 420
+    gp = GpuProblem(W.MoteConfig("rtn_static", 896, 1024, 8, 8, T, seed=29), shared_bits=8)
+    assert gp.layer.workspace_bytes(T) > M.binding.STATIC_WORKSPACE_BYTES
+    got = torch.zeros_like(gp.x)
+    M.mote_layer_forward_static(gp.layer, gp.x, got)
+    tiled = M.mote_layer_forward(gp.layer, gp.x)
+    try:
+        M.mote_tuning_set("shared_q_tokens", T)
+        streamed = M.mote_layer_forward(gp.layer, gp.x)
+    finally:
+        M.mote_tuning_set("shared_q_tokens", -1)
+    torch.cuda.synchronize()
+    assert torch.equal(got, streamed)
+    # fp32 sums in another order: bf16 values of h_s and of the output may round the other way (2^-8 each)
+    assert (got.float() - tiled.float()).norm() <= 2.0 ** -8 * tiled.float().norm()
