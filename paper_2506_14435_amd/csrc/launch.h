@@ -100,8 +100,9 @@ int tile_group_m();                      // row tiles per band of the large-batc
 // plan tile size chosen for a workload (32, 64: decode kernels); decode_rows: largest average number of rows per
 // expert on 32-row tiles, by choice and where the scratch asks for it
 int routed_tile_m(int T, int k, int E, int d, int F, int decode_rows);
-int routed_decode_rows(int d);
-int routed_decode_rows_max(int d);
+int routed_decode_rows(int T, int E, int d, int F, bool shared_quantised);
+int routed_decode_rows_max();
+int routed_decode_rows_min(int d);
 bool routed_mid_kernel_fits(int d, int F);             // the 64-row wave-streaming kernel serves this shape
 
 // Decode (small batch) variants: weights streamed once, K split across wavefronts and, for the

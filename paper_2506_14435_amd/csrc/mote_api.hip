@@ -143,23 +143,25 @@ Workspace carve(const mote_layer* l, int T, char* base, int decode_rows, int q_t
   w.bytes = off;
   return w;
 }
-Workspace carve(const mote_layer* l, int T, char* base) {
-  return carve(l, T, base, routed_decode_rows(l->d_model), shared_q_tokens(l));
+int decode_rows(const mote_layer* l, int T) {
+  return routed_decode_rows(T, l->n_experts, l->d_model, l->d_ff_routed, l->shared_bits != 0);
 }
+Workspace carve(const mote_layer* l, int T, char* base) { return carve(l, T, base, decode_rows(l, T), shared_q_tokens(l)); }
 
-// The layout for `bytes` of scratch.  Two routes that are faster need more of it than the other way to the result; where
-// only the other fits, the batch goes that way and is not refused:
-//   - the 128-row kernel that a wide layer prefers from 17 rows per expert on keeps up to four planes of the routed down
+// The layout for `bytes` of scratch.  The faster of two routes may need more of it than the other; where only the other
+// fits, the batch goes that way and is not refused:
+//   - a wide layer with 17 to 48 rows per expert: the 128-row kernel keeps up to four planes of the routed down
 //     accumulators, the 32-row kernels ceil(F / 2048) (d = 2176, F = 1280, E = 32, top-2, T = 674: 66.8 and 33.2 MiB); the
 //     result is the same to the bit;
 //   - the tiled GEMMs of a quantised shared expert want its matrices expanded to bf16.
 Workspace carve_to_fit(const mote_layer* l, int T, char* base, size_t bytes) {
-  const int rows[2] = {routed_decode_rows(l->d_model), routed_decode_rows_max(l->d_model)};
+  const int rows[3] = {decode_rows(l, T), routed_decode_rows_max(), routed_decode_rows_min(l->d_model)};
   const int q_tokens[2] = {shared_q_tokens(l), shared_q_tokens_max(l)};
-  for (int i = 0; i < 4; ++i) {
-    const Workspace w = carve(l, T, base, rows[i & 1], q_tokens[i >> 1]);
-    if (w.bytes <= bytes) return w;
-  }
+  for (int q : q_tokens)
+    for (int r : rows) {
+      const Workspace w = carve(l, T, base, r, q);
+      if (w.bytes <= bytes) return w;
+    }
   return carve(l, T, base);
 }
 
@@ -328,7 +330,9 @@ size_t mote_layer_workspace_bytes(const mote_layer* layer, int T_max) {
   need = carve(layer, T_max, nullptr).bytes;
   consider(kSharedDecodeMaxTokens);
   if (layer->shared_bits != 0) consider(shared_q_tokens(layer));
-  consider(static_cast<int64_t>(routed_decode_rows(layer->d_model)) * E / k);
+  // the largest T on 32-row tiles, among the batches whose shared expert is streamed and among the others
+  consider(std::min<int64_t>(kSharedDecodeMaxTokens, static_cast<int64_t>(decode_rows(layer, 1)) * E / k));
+  consider(static_cast<int64_t>(decode_rows(layer, T_max)) * E / k);
   consider(static_cast<int64_t>(knob(kKnobMidRowsLo)) * E / k);
   consider(static_cast<int64_t>(knob(kKnobMidRowsHi)) * E / k);
   for (int64_t m = 1;; ++m) {   // largest T with floor(T*k/128) == m - 1

@@ -703,15 +703,26 @@ int routed_tile_m(int T, int k, int E, int d, int F, int decode_rows) {
   if (avg > knob(kKnobMidRowsLo) && avg <= knob(kKnobMidRowsHi) && routed_mid_kernel_fits(d, F)) return 64;
   return avg <= decode_rows ? 32 : 128;
 }
-int routed_decode_rows_max(int d) { return std::max(routed_decode_rows(d), knob(kKnobDecodeRows) >= 0 ? 0 : 48); }
-int routed_decode_rows(int d) {
+int routed_decode_rows_max() { return knob(kKnobDecodeRows) >= 0 ? knob(kKnobDecodeRows) : 48; }
+int routed_decode_rows_min(int d) { return knob(kKnobDecodeRows) >= 0 ? knob(kKnobDecodeRows) : d > 2048 ? 16 : 48; }
+// Rows longer than one 16-step plane (d > 2048) have no wave-streaming gate-up kernel, and the register-ring kernel
+// streams the weights once per 32 rows behind a gather per unit: from some 20 to 30 rows per expert on the 128-row
+// kernel is faster.  us per forward on 32-row -> on 128-row tiles, r rows per expert (top-2 unless noted):
+//   few narrow experts (F = 640, E = 8, d = 2304)  r = 17 255 -> 271, r = 48 178 -> 195;  F = 2560 r = 17 103 -> 114, r = 48 121 -> 124
+//   F = 5120, d = 3072, E = 16  r = 24 143 -> 150, r = 28 150 -> 154, r = 32 168 -> 160, r = 40 210 -> 160;  F = 6912, d = 2560
+//     r = 24 143 -> 152, r = 30 166 -> 160;  INT8 shared expert r = 24 170 -> 178, r = 30 190 -> 189
+//   F = 18944, d = 3584, E = 16  r = 20 403 -> 408, r = 24 427 -> 412, r = 32 544 -> 445;  E = 4, top-1 r = 24 203 -> 192;  INT8
+//     r = 20 422 -> 430, r = 24 447 -> 442;  but up to 64 tokens (E = 4), where the shared expert is streamed, r = 20
+//     169 -> 189, r = 28 186 -> 193, r = 32 204 -> 190
+//   E = 64, top-4, d = 3072, F = 1920  r = 24 228 -> 267, r = 28 231 -> 225;  F = 4096 r = 24 295 -> 335, r = 28 352 -> 313;
+//     top-8, d = 2560, F = 6912 r = 17 364 -> 329, r = 24 433 -> 339, INT8 r = 20 396 -> 407, r = 24 420 -> 413
+// Up to d = 2048 the 32-row kernels win longer (E = 8, T=100 113.8 against 121; d = 896, T=190 69.8 against 72.2).
+int routed_decode_rows(int T, int E, int d, int F, bool shared_quantised) {
   if (knob(kKnobDecodeRows) >= 0) return knob(kKnobDecodeRows);
-  // Rows longer than one 16-step plane (d > 2048) have no wave-streaming gate-up kernel, and the register-ring
-  // kernel streams the weights once per 32 rows behind a gather per unit: from 17 rows per expert on the 128-row
-  // kernel is as fast or faster (d = 3584, E = 16, top-2, us per forward: T=130 390 and 390, T=180 421 -> 402,
-  // T=250 546 -> 430, T=380 802 -> 521; T=96 354 against 398).  Below, the 32-row kernels win longer (d = 2048,
-  // E = 8, T=100 113.8 against 121; d = 896, T=190 69.8 against 72.2).
-  return d > 2048 ? 16 : 48;
+  if (d <= 2048 || (F < 4096 && E < 32)) return 48;
+  if (E >= 32) return E >= 64 && F >= 6144 && !shared_quantised ? 16 : 24;
+  if (F >= 12288) return shared_quantised ? 24 : T > kSharedDecodeMaxTokens ? 20 : 28;
+  return 28;
 }
 
 hipError_t launch_routed_gate_up(const RoutedGemmArgs& a, hipStream_t stream) {

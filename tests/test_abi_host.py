@@ -130,12 +130,12 @@ def test_tuning_knobs_are_validated(lib):
         assert "getenv" not in open(os.path.join(srcs, f)).read(), f
 
 
-@pytest.mark.parametrize("d,F,E,k,bits,T", [(2176, 1280, 32, 2, 0, 674), (2304, 640, 32, 8, 8, 185), (2304, 640, 64, 1, 8, 1100),
-                                            (8192, 1024, 16, 2, 0, 200), (8192, 1024, 16, 8, 4, 60),
+@pytest.mark.parametrize("d,F,E,k,bits,T", [(2176, 1280, 32, 2, 0, 674), (2304, 640, 32, 8, 8, 185), (2304, 640, 64, 1, 8, 1700),
+                                            (2304, 14592, 32, 8, 4, 80), (3584, 18944, 16, 2, 0, 150),
                                             (896, 1024, 8, 8, 8, 420), (1024, 8192, 4, 2, 4, 150)])
 def test_batches_that_fit_in_the_smaller_of_two_layouts_are_not_refused(lib, d, F, E, k, bits, T):
-    """17 to 48 rows per expert at d > 2048: the layout of the 128-row kernel is larger than the static array, that of
-    the 32-row kernels is not; a quantised shared expert expanded to bf16 is, its streamed codes are not.  x == NULL ends
+    """17 to 48 rows per expert at d > 2048: the layout of the preferred tile height is larger than the static array, that
+    of the other is not; a quantised shared expert expanded to bf16 is, its streamed codes are not.  x == NULL ends
     the call behind the size check, before any launch."""
     p = 256
     L = M.binding.MoteLayerStruct(d, F, F, E, k, p, None, *([p] * 7), bits, p, p, p)

@@ -611,3 +611,19 @@ def test_quantised_shared_expert_is_streamed_up_to_a_limit_by_shape(d, F, T, str
     names = _captured_kernels(lambda: M.mote_layer_forward(layer, x, out=out, workspace=ws))
     assert any("shared_qwave_kernel" in n for n in names) == streamed
     assert any("rtn_dequant_kernel" in n for n in names) == (not streamed)
+
+
+# Rows per expert (T * k / E) up to which a layer with d > 2048 runs on 32-row tiles, on both sides of each limit.
+@pytest.mark.parametrize("F,E,k,bits_,T,decode", [(640, 4, 2, 0, 96, True), (640, 4, 2, 8, 98, False), (5760, 4, 1, 0, 112, True),
+                                                  (5760, 4, 1, 0, 113, False), (14592, 4, 1, 0, 80, True), (14592, 4, 1, 0, 81, False),
+                                                  (14592, 2, 1, 0, 56, True), (14592, 2, 1, 0, 57, False), (14592, 4, 1, 8, 96, True),
+                                                  (14592, 4, 1, 8, 97, False), (640, 32, 4, 0, 192, True), (640, 32, 4, 0, 193, False),
+                                                  (6144, 64, 8, 0, 128, True), (6144, 64, 8, 0, 129, False), (6144, 64, 8, 4, 192, True)])
+def test_tile_height_of_wide_layers(F, E, k, bits_, T, decode):
+    M = _m()
+    layer = _zero_layer(M, 2304, F, E, k, bits_)
+    x = torch.zeros(T, 2304, dtype=torch.bfloat16, device="cuda")
+    out, ws = torch.empty_like(x), layer.workspace(T)
+    names = _captured_kernels(lambda: M.mote_layer_forward(layer, x, out=out, workspace=ws))
+    assert any("routed_decode_kernel" in n for n in names) == decode
+    assert any("routed_gemm_kernel" in n for n in names) == (not decode)

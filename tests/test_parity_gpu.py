@@ -911,8 +911,8 @@ def test_decode_step_with_small_kernels_inside_the_large_ones(T, d, F, E, k, sha
 
 @pytest.mark.parametrize("T", [32, 34, 36, 94, 96, 98])
 def test_layer_rows_longer_than_a_plane_on_either_tile_height(T):
-    """d > 2048 with 16, 17 and 47 to 49 rows per expert: the 128-row kernel from 17 rows on, equal to the bit to the
-    32-row kernels (integer accumulators; the shared expert runs the same kernels either way)."""
+    """d > 2048 with 16, 17 and 47 to 49 rows per expert: the 128-row kernel from 17 and from 49 rows on, equal to the bit to
+    the 32-row kernels (integer accumulators; the shared expert runs the same kernels either way)."""
     M = _m()
     cfg = W.MoteConfig(f"wide_T{T}", 2304, 640, 4, 2, T, seed=500 + T)
     gp = GpuProblem(cfg)
