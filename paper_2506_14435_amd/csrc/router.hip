@@ -21,10 +21,10 @@ __global__ __launch_bounds__(64 * NW) void router_quant_kernel(
     const uint16_t* __restrict__ x, const uint16_t* __restrict__ w_router, const float* __restrict__ bias, int T,
     int d, int E, int k, int32_t* __restrict__ topk_idx, float* __restrict__ topk_p, int8_t* __restrict__ q_x,
     float* __restrict__ beta_x, int32_t* __restrict__ rowsum_x, float* __restrict__ gate_p) {
-  const int t0 = blockIdx.x * TPW;   // the NW wavefronts of a workgroup split the channels of TPW tokens
-  if (t0 >= T) return;
+  // The grid is exact, ceil(T / TPW) workgroups: with a check in front the arguments are kept in spilled scalar registers
+  // over the 64-expert body (d = 896, T = 64: 17.6 -> 19.0 us).
   __shared__ RouterScratch<TPW, NW> lds;
-  router_quant_group<EMAX, TPW, NW, (EMAX > 16 ? 1 : 2)>(lds, t0, x, w_router, bias, T, d, E, k, topk_idx, topk_p, q_x, beta_x,
+  router_quant_group<EMAX, TPW, NW, (EMAX > 16 ? 1 : 2)>(lds, blockIdx.x * TPW, x, w_router, bias, T, d, E, k, topk_idx, topk_p, q_x, beta_x,
                                                         rowsum_x, gate_p);
 }
 
