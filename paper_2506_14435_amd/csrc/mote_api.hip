@@ -433,10 +433,12 @@ mote_status forward_impl(const mote_layer* layer, const mote_norm* norm, const v
   const int bits = layer->shared_bits;
   bool roles_pay = true, plan_pays = false;   // five launches; forked, with the plan inside the gate-up kernel
   if (fork && wide) {
-    if (bits == 0) roles_pay = T > 32 ? E >= 8 : T > 8 && E >= 16 && shared_weights >= (int64_t{1} << 26);
+    const bool widest = shared_weights >= (int64_t{1} << 26);
+    if (bits == 0) roles_pay = T > 32 ? E >= 8 : T > 8 && E >= 16 && widest;
     else if (bits == 8) roles_pay = T >= 8 && T <= (E >= 16 ? 32 : 16);
     else roles_pay = T > 8 && T <= 32;
-    plan_pays = T <= 8 ? bits != 0 || T > 1 : bits == 8 && (T <= 32 || shared_weights >= (int64_t{1} << 26));
+    if (T <= 8) plan_pays = bits != 0 || (T > 1 && (E >= 16 || !widest));
+    else plan_pays = bits == 8 && (T <= 32 || widest);
   } else if (fork && shared_weights >= (int64_t{1} << 24)) {
     if (bits == 0) roles_pay = T <= 16;
     else roles_pay = T <= 32 || (bits == 8 && shared_weights < (int64_t{3} << 23));

@@ -518,7 +518,7 @@ def test_rtn_shared_expert_streamed_in_chunks_of_64_tokens(d, F, Ts, bits_):
 LAUNCH_CASES = [(2048, 11008, 4, 0, 16, "", 5), (2048, 11008, 4, 0, 20, "", 5), (2048, 11008, 4, 0, 24, "", 8),
                 (2048, 11008, 4, 0, 32, "no_fork", 5), (2048, 11008, 4, 0, 33, "static", 5), (1536, 8960, 4, 8, 33, "", 5),
                 (1536, 8960, 4, 4, 64, "", 5), (2048, 11008, 4, 4, 33, "", 8), (256, 512, 17, 0, 8, "", 8),
-                (3584, 18944, 4, 0, 1, "", 8), (3584, 18944, 4, 0, 8, "", 7), (3584, 18944, 4, 0, 64, "", 8),
+                (3584, 18944, 4, 0, 1, "", 8), (3584, 18944, 4, 0, 8, "", 8), (2304, 14592, 4, 0, 8, "", 7), (3584, 18944, 4, 0, 64, "", 8),
                 (3584, 18944, 4, 8, 33, "", 7), (3584, 18944, 4, 4, 16, "", 5), (3584, 18944, 4, 4, 33, "", 8),
                 (3584, 18944, 4, 8, 64, "no_fork", 5)]
 
