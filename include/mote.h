@@ -17,7 +17,7 @@
  *     runs the shared expert on a helper stream of its own (created on first use, default
  *     priority) that it forks from and joins back into `hip_stream` with events, so to the
  *     caller the call behaves like work on `hip_stream` alone; mote_tuning_set(MOTE_KNOB_NO_FORK, 1)
- *     keeps everything on one stream.  The library reads no environment variable.  Host-side
+ *     keeps everything on one stream.  Most decode steps are five kernels on `hip_stream`.  The library reads no environment variable.  Host-side
  *     state (helper stream, timing events, knobs) is not thread-safe.
  *     Inputs and outputs must not alias.
  *   - Matrices are row-major.  A weight matrix is [n_out, n_in] and acts on a column
@@ -127,9 +127,8 @@ mote_status mote_pack_rtn(const void* w, int64_t n_out, int64_t n_in, int bits, 
  * dx           out: fp32 [R, K]
  * dw           out: fp32 [E, N, K] (zero for an expert without rows)
  * workspace       : device, >= mote_ste_backward_workspace_bytes(R, N, K, E) bytes, 256-byte aligned
- *                   (the transposed ternary weights of all experts as bf16, at most 4 GiB of them at a
- *                   time, the transposed gradient rows and codes, partial sums of dx: about
- *                   2 E N K + 2 R (N + K) + 32 R K bytes)
+ *                   (the re-blocked 2-bit codes of the experts that share a launch, the transposed gradient
+ *                   rows and codes, partial sums of dx: about E N K / 4 + 2 R (N + K) + 32 R K bytes)
  * Limits: N % 128 == 0, K % 128 == 0, 1 <= E <= 64, R >= 0; every operand of one expert below
  * 2 GiB.  Enqueued on hip_stream; the host array is read before the call returns.
  * Returns MOTE_ERR_INVALID_ARG for NULL pointers or offsets that are not ascending from 0 to R,
@@ -289,7 +288,10 @@ enum {
 };
 
 /* enable != 0: every following mote_layer_forward brackets each stage with HIP events on
- * the caller's stream (created on first use, host-side state, not thread-safe). */
+ * the caller's stream (created on first use, host-side state, not thread-safe).  A timed forward runs
+ * one kernel per stage, one after the other on that stream: no helper stream, and none of the combined
+ * kernels of a decode step (MOTE_KNOB_DECODE_ROLES), so the stage times of a small batch add up to more
+ * than the forward takes otherwise. */
 mote_status mote_stage_timing(int enable);
 
 /* Waits for the last timed forward and writes the MOTE_N_STAGES stage durations in
@@ -330,7 +332,7 @@ enum {
   MOTE_KNOB_SHARED_Q_TOKENS = 15,    /* quantised shared expert: largest T at which the codes are streamed, 64
                                         tokens at a time (-1: by shape)                                */
   MOTE_KNOB_DECODE_ROWS = 16,        /* largest average number of rows per expert on 32-row plan tiles
-                                        (-1: by shape)                                                 */
+                                        (-1: by shape and batch)                                       */
   MOTE_KNOB_DECODE_ROLES = 17,       /* decode step with its small kernels inside the large ones: 0 never,
                                         1 by shape, 2 wherever it can run (1)                          */
   MOTE_N_KNOBS = 18

@@ -398,7 +398,7 @@ def mote_layer_forward_static(layer: MoteLayer, x: torch.Tensor, out: torch.Tens
 
 class ForwardGraph:
     """One mote_layer_forward call (fixed layer, x, out and workspace buffers) captured into a HIP
-    graph: replay() re-runs the same kernels with one launch instead of eight plus the fork/join
+    graph: replay() re-runs the same kernels with one launch instead of five, or of eight plus the fork/join
     events.  The buffers must stay alive and keep their addresses; x may be refilled in place."""
 
     def __init__(self, layer: MoteLayer, x: torch.Tensor, out: torch.Tensor, workspace: torch.Tensor):

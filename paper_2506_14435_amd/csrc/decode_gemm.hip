@@ -41,8 +41,8 @@ constexpr int kDecThreads = 256;
 // The dispatch plan of a small decode step (at most 512 dispatch rows, 16 experts, 32-row tiles), made by every
 // workgroup of the gate-up kernel for itself: one load of the selected experts, then a histogram and a stable
 // compaction by ballots.  It takes the place of the two dependent loads of a finished plan, so the gate-up
-// kernel takes about as long as before (d = 2048: T = 1 12.0 -> 12.2 us, T = 64 36.6 -> 38.0) and the plan kernel
-// (5.2 us) with its launch is gone: forward 68.3 -> 64.3 us at T = 1.  Workgroup 0 writes the plan for the kernels that follow.
+// kernel takes about as long as before (d = 2048: T = 1 11.9 -> 12.1 us, T = 64 38.8 -> 37.7) and the plan kernel (4.5
+// and 6.7 us) with its launch is gone.  Workgroup 0 writes the plan for the kernels that follow.
 struct LocalPlan {
   int n_tiles;
   int tok[kLocalPlanRows];
@@ -1310,17 +1310,20 @@ hipError_t launch_shared_decode_down(const uint16_t* h_s, const uint16_t* w_down
 // The shared expert depends on x only.  On a stream of its own it costs a fork and a join (at T = 1 about 19 us
 // of cross-queue signalling and 40 us of host time for 60 us of kernels); here its two kernels carry the two
 // small kernels of the routed chain as further workgroups of the same grid, so a decode step is five
-// launches on one stream and the router and the row quantiser cost next to nothing beside the weight stream:
+// launches on one stream (d = 2048, bf16, weights from HBM, us):
 //
 //   decode_head_kernel : router + Q_a(x), one workgroup per token, beside the shared gate-up projection
-//                        (d = 2048, T = 1: 9.5 and 18.0 us apart, 20.1 us together; T = 64: 13.0 and 22.0, 22.0)
+//                        (T = 1: 10.8 and 22.2 apart, 26.4 together; T = 16: 9.5 and 21.9, 27.7; from the memory-side
+//                        cache T = 1 9.5 and 18.0, 20.6)
 //   decode_mid_kernel  : Q_a(h), one workgroup per dispatch row, beside the shared down projection
-//                        (T = 1: 4.0 and 10.6 us apart, 10.6 us together; T = 64: 4.9 and 12.6, 12.7)
+//                        (T = 1: 3.9 and 11.5 apart, 10.9 together; T = 16: 4.6 and 11.5, 11.6; T = 64: 4.8 and 15.0, 15.0)
 //
 // The small workgroups come first in the grid.  A workgroup of either kind reserves the ring of a
 // streaming one; the small ones keep their few bytes of LDS inside it (as arrays of their own beside it they took
-// the third, or of the quantised kernels' 80 KiB the second, workgroup from a CU).  With the rings of the bf16 kernels
-// at 52 KiB three workgroups share a CU.  What bounds them is the weight stream: 90 MB in 20 us, 45 MB in 10.6 us.
+// the third, or of the quantised kernels' 80 KiB the second, workgroup from a CU).  With rings
+// of 52 KiB three workgroups of the bf16 kernels share a CU (above 32 tokens the head kernel's registers leave two at the start, until the
+// three idle wavefronts of each have ended; held to a third of the register file it is as fast: T = 64 d = 1536 78.5 against
+// 78.0 us, d = 3584 309.6 against 310.9).  What bounds them is the weight stream: 90 MB in 26 us, 45 MB in 11.
 struct RouterRoleArgs {
   const uint16_t* x;
   const uint16_t* w_router;
@@ -1339,7 +1342,7 @@ struct QuantRoleArgs {
   float* beta_h;
   int32_t* rowsum_h;
 };
-constexpr int kRoleLdsKiB = 52;
+constexpr int kRoleLdsKiB = 52, kHeadLdsKiB = 64;
 
 // `blocks` workgroups of `lds` bytes fit the 160 KiB of a CU, handed out in units of 1280 bytes.
 constexpr bool lds_fits(int blocks, int lds) { return blocks * ((lds + 1279) / 1280) <= 128; }
@@ -1361,12 +1364,12 @@ __device__ __forceinline__ void quant_role(const QuantRoleArgs& r, int row) {
 // Workgroups of four wavefronts for the sake of the small kernels; a streaming unit is one wavefront, the
 // other three end at once.  (One wavefront per workgroup left the router a chain of memory round trips
 // behind the weight stream: the head kernel took 29 us at T = 1 and T = 64.)
-template <int AL>
-__global__ __launch_bounds__(256, 3) void decode_head_kernel(RouterRoleArgs r, SharedDecodeArgs a) {
-  constexpr int LDS = SharedWaveCfg<0, AL, kRoleLdsKiB>::LDS;
-  static_assert(lds_fits(3, LDS), "three workgroups per CU");
+template <int AL, int KIB>
+__global__ __launch_bounds__(256) void decode_head_kernel(RouterRoleArgs r, SharedDecodeArgs a) {
+  constexpr int LDS = SharedWaveCfg<0, AL, KIB>::LDS;
+  static_assert(lds_fits(KIB == kRoleLdsKiB ? 3 : 2, LDS), "three workgroups per CU, or two with the longer ring");
   if (static_cast<int>(blockIdx.x) < r.T) router_role<4, LDS>(r, blockIdx.x);
-  else if (threadIdx.x < 64) shared_wave_unit<0, AL, kRoleLdsKiB>(a, blockIdx.x - r.T, gridDim.x - r.T, 1, a.K >> 6);
+  else if (threadIdx.x < 64) shared_wave_unit<0, AL, KIB>(a, blockIdx.x - r.T, gridDim.x - r.T, 1, a.K >> 6);
 }
 
 template <int BITS, int AL>
@@ -1406,10 +1409,22 @@ static hipError_t launch_role(void (*kernel)(P...), bool* attr_set, int blocks, 
   return hipGetLastError();
 }
 
+template <int AL, int KIB>
+static hipError_t launch_head_ring(const RouterRoleArgs& r, const SharedDecodeArgs& a, int runs, hipStream_t stream) {
+  static bool attr_set = false;
+  return launch_role(decode_head_kernel<AL, KIB>, &attr_set, r.T + runs, 256, SharedWaveCfg<0, AL, KIB>::LDS, stream, r, a);
+}
+// Channel runs of the bf16 head kernel.  Two workgroups per CU where the routers and the runs fit that way: with slots for
+// three some CUs get three runs and others one (d = 2048, F = 11008, E = 16, us per forward with weights from HBM: T=1 64.0 ->
+// 58.3, T=16 97.0 -> 92.1; d = 1536 T=4 61.7 -> 58.8).  Wider layers have more runs than that and need the third slot
+// (d = 3584, F = 18944 T=16 254 against 259, T=64 311 against 326).
+static int head_runs(int T, int F) { return std::min(std::max(device_cus() * 2 - T, F / 32), F / 4); }
+bool decode_head_fits_twice(int T, int F) { return T + head_runs(T, F) <= device_cus() * 2; }
+
 template <int AL>
 static hipError_t launch_head_al(const RouterRoleArgs& r, const SharedDecodeArgs& a, int runs, hipStream_t stream) {
-  static bool attr_set = false;
-  return launch_role(decode_head_kernel<AL>, &attr_set, r.T + runs, 256, SharedWaveCfg<0, AL, kRoleLdsKiB>::LDS, stream, r, a);
+  return decode_head_fits_twice(r.T, a.N) ? launch_head_ring<AL, kHeadLdsKiB>(r, a, runs, stream)
+                                        : launch_head_ring<AL, kRoleLdsKiB>(r, a, runs, stream);
 }
 template <int BITS, int AL>
 static hipError_t launch_head_q_al(const RouterRoleArgs& r, const SharedQDecodeArgs& a, int runs, hipStream_t stream) {
@@ -1439,16 +1454,15 @@ static hipError_t launch_mid_q_al(const QuantRoleArgs& r, const SharedQDecodeArg
 hipError_t launch_decode_head(const DecodeSharedArgs& s, const float* bias, const uint16_t* w_router, int E, int k, int32_t* topk_idx,
                               float* topk_p, int8_t* q_x, float* beta_x, int32_t* rowsum_x, uint16_t* h_s, hipStream_t stream) {
   const RouterRoleArgs r{s.x, w_router, bias, s.T, s.d, E, k, topk_idx, topk_p, q_x, beta_x, rowsum_x};
-  const int n_frags = s.F / 32;
   if (s.bits == 0) {
-    const int runs = std::min(std::max(device_cus() * 2, n_frags), s.F / 4);
+    const int runs = head_runs(s.T, s.F);
     const SharedDecodeArgs a{s.x, static_cast<const uint16_t*>(s.w_gate), static_cast<const uint16_t*>(s.w_up), s.T, s.F, s.d, h_s, nullptr, 0};
 #define MOTE_CALL(AL_) launch_head_al<AL_>(r, a, runs, stream)
     MOTE_BY_TOKENS(s.T, MOTE_CALL);
 #undef MOTE_CALL
   }
-  // rings of 80 KiB: the routers take slots of the two workgroups per CU, so as many fewer runs fill the chip once
-  const int runs = std::min(std::max(device_cus() * 2 - s.T, n_frags), s.F / 4);
+  // rings of 80 KiB: the routers take slots of the two workgroups per CU here too
+  const int runs = head_runs(s.T, s.F);
   const SharedQDecodeArgs a{s.x, static_cast<const unsigned char*>(s.w_gate), static_cast<const unsigned char*>(s.w_up), s.s_gate, s.s_up,
                             s.T, s.F, s.d, h_s, nullptr, 0};
 #define MOTE_CALL(AL_) (s.bits == 8 ? launch_head_q_al<8, AL_>(r, a, runs, stream) : launch_head_q_al<4, AL_>(r, a, runs, stream))

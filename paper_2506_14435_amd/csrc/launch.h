@@ -124,6 +124,7 @@ struct DecodeSharedArgs {
   const float *s_gate, *s_up, *s_down;
   int bits, T, d, F;
 };
+bool decode_head_fits_twice(int T, int F);   // routers and channel runs of the bf16 head kernel: two per CU
 hipError_t launch_decode_head(const DecodeSharedArgs& s, const float* bias, const uint16_t* w_router, int E, int k, int32_t* topk_idx,
                               float* topk_p, int8_t* q_x, float* beta_x, int32_t* rowsum_x, uint16_t* h_s, hipStream_t stream);
 hipError_t launch_decode_mid(const DecodeSharedArgs& s, const uint16_t* h_s, float* y_s, const uint16_t* h, int R, int F_routed,

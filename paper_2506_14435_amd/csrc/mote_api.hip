@@ -410,38 +410,38 @@ mote_status forward_impl(const mote_layer* layer, const mote_norm* norm, const v
   //   d = 256 (E = 4) T=1 33.8 -> 25.7, T=64 38.9 -> 29.7;  d = 896 (E = 8) T=64 56.2 -> 43.5, INT4 58.6 -> 45.9
   //   d = 1536 INT8 T=33 93.5 -> 79.8;  d = 2048 T=16 98.7 -> 88.3, T=20 102.3 -> 89.9, INT4 T=16 93.3 -> 77.4
   //   and with the helper stream switched off d = 2048 T=64 118 -> 106, d = 3584 T=1 165 -> 126, INT4 T=64 315 -> 293
-  // Where it would fork, the shared expert's stream is partly hidden already and the answer depends on the shape
-  // (forked, in brackets with the plan inside the gate-up kernel -> five launches):
-  //   below 2^24 weights (d = 1536, F = 8960)   T=64 85.7 -> 83.6, INT8 T=64 85.1 -> 83.7, INT4 T=64 91.0 -> 85.2
-  //   2^24 (d = 2048, F = 11008)  T=1 65.8 -> 57.5, T=8 92.9 -> 87.8, but T=24 89.6 -> 90.5, T=64 106.9 -> 111.1;
-  //     INT8 T=32 90.2 -> 84.0, T=64 102.5 -> 101.9 (F = 8320 94.4 -> 89.1), but from 1.5 * 2^24 on, d = 1536,
-  //     F = 18944: T=64 131 -> 132;  INT4 T=32 94.2 -> 83.8, but T=64 103.2 -> 104.7
-  //   2^25 and 2^26 (d = 4096, F = 14336 and d = 3584, F = 18944)
-  //     E = 16  T=1 127 (128) -> 126, T=4 172 (164) -> 172, T=16 263 -> 254, T=64 328 -> 308, but at 4096 T=16 204 -> 212,
-  //             T=24 222 -> 222, T=64 261 -> 251;   E = 8  T=4 150 (150) -> 156, T=16 182 -> 185, T=33 207 -> 196;
-  //             E = 4  T=64 169 -> 178
-  //     INT8    E = 16 T=4 147 (136) -> 137, T=8 191 -> 182, T=24 248 (251) -> 243, T=64 304 (288) -> 299, but at 4096
-  //             T=64 239 (252) -> 238;   E = 8 T=4 129 (122) -> 127, T=8 153 -> 148, T=24 173 (167) -> 175, T=64 202 (202) -> 229
-  //     INT4    E = 16 T=4 131 (124) -> 127, T=16 217 -> 208, T=64 276 (275) -> 292;   E = 8 T=4 114 (113) -> 118,
-  //             T=16 144 -> 141, T=64 194 (201) -> 218
+  // Where it would fork, the answer depends on the shape (forked, in brackets with the plan inside the gate-up kernel ->
+  // five launches).  bf16, while the head kernel's workgroups fit two per CU, or below 2^25 weights: always
+  //     d = 2048, F = 11008  T=1 69 -> 53, T=8 93 -> 84, T=24 88 -> 87, T=64 105 -> 102 (weights from HBM T=1 65 -> 60, T=24
+  //     96 -> 96, T=64 110 -> 106);  F = 12288 T=32 102 -> 102, T=64 122 -> 108;  d = 4096, F = 14336 T=8 175 -> 171, T=64 263 -> 252
+  //     d = 1536, F = 18944  T=8 127 -> 111, T=64 150 -> 138
+  //   bf16 with more runs than that (d = 3584, F = 18944)
+  //     E = 16  T=1 127 (128) -> 124, T=4 171 (162) -> 171, T=8 223 (212) -> 216, T=16 264 -> 254, T=64 331 -> 310
+  //     E = 8   T=4 150 (150) -> 157, T=16 181 -> 184, T=33 208 -> 197;   E = 4  T=64 169 -> 178
+  //   INT8
+  //     d = 2048, F = 11008 T=32 90.2 -> 84.0, T=64 102.5 -> 101.9;  F = 8320 T=64 94.4 -> 89.1;  but from 1.5 * 2^24 weights
+  //     on, d = 1536, F = 18944: T=64 131 -> 132
+  //     d = 3584  E = 16 T=4 147 (136) -> 137, T=8 191 -> 182, T=24 248 (251) -> 243, T=64 304 (288) -> 299;  E = 8 T=4 129 (122)
+  //     -> 127, T=8 153 -> 148, T=24 173 (167) -> 175, T=64 202 (202) -> 229;  d = 4096, F = 14336 E = 16 T=64 239 (252) -> 238
+  //   INT4
+  //     d = 2048 T=32 94.2 -> 83.8, but T=64 103.2 -> 104.7
+  //     d = 3584  E = 16 T=4 131 (124) -> 127, T=16 217 -> 208, T=64 276 (275) -> 292;  E = 8 T=4 114 (113) -> 118, T=16 144 -> 141,
+  //     T=64 194 (201) -> 218
   // These are even loads.  At 2^26 weights a router that sends all tokens of a larger step to two or four of sixteen
   // experts leaves so little routed work that the fork would hide it (two experts, T=64: 182 -> 190, INT8 163 -> 168);
   // the host does not know the loads.
   const int roles_knob = knob(kKnobDecodeRoles);
   const bool roles_fit = !timing && roles_knob != 0 && decode_shared && decode_routed && E <= kRoleMaxExperts;
-  const bool wide = shared_weights >= (int64_t{1} << 25);
   const int bits = layer->shared_bits;
   bool roles_pay = true, plan_pays = false;   // five launches; forked, with the plan inside the gate-up kernel
-  if (fork && wide) {
-    const bool widest = shared_weights >= (int64_t{1} << 26);
-    if (bits == 0) roles_pay = T > 32 ? E >= 8 : T > 8 && E >= 16 && widest;
-    else if (bits == 8) roles_pay = T >= 8 && T <= (E >= 16 ? 32 : 16);
-    else roles_pay = T > 8 && T <= 32;
-    if (T <= 8) plan_pays = bits != 0 || (T > 1 && (E >= 16 || !widest));
-    else plan_pays = bits == 8 && (T <= 32 || widest);
+  if (fork && bits == 0) {
+    if (!decode_head_fits_twice(T, Fs) && shared_weights >= (int64_t{1} << 25)) roles_pay = T > 32 ? E >= 8 : T > 8 && E >= 16;
+    plan_pays = T > 1 && T <= 8 && E >= 16;
+  } else if (fork && shared_weights >= (int64_t{1} << 25)) {
+    roles_pay = bits == 8 ? T >= 8 && T <= (E >= 16 ? 32 : 16) : T > 8 && T <= 32;
+    plan_pays = T <= 8 || (bits == 8 && (T <= 32 || shared_weights >= (int64_t{1} << 26)));
   } else if (fork && shared_weights >= (int64_t{1} << 24)) {
-    if (bits == 0) roles_pay = T <= 16;
-    else roles_pay = T <= 32 || (bits == 8 && shared_weights < (int64_t{3} << 23));
+    roles_pay = T <= 32 || (bits == 8 && shared_weights < (int64_t{3} << 23));
   }
   const bool roles = roles_fit && (roles_pay || roles_knob == 2);
   const bool local_plan = roles_fit && (roles || plan_pays) && tile_m == 32;

@@ -512,13 +512,14 @@ def test_rtn_shared_expert_streamed_in_chunks_of_64_tokens(d, F, Ts, bits_):
 
 
 # Kernel launches of a decode step: five with the router, the row quantiser and the dispatch plan inside the large
-# kernels, seven with only the plan inside the gate-up kernel, eight otherwise.  Wherever the forward does not fork it
+# kernels, seven with only the plan inside the gate-up kernel, eight otherwise.  Wherever the forward would not fork it
 # takes the five: between the batches that fork for their few tokens and those that fork for their work (3B width, T = 17
-# to 23; quantised 1.5B width, T = 33 to 38), with the helper stream switched off, and on the static scratch.
-LAUNCH_CASES = [(2048, 11008, 4, 0, 16, "", 5), (2048, 11008, 4, 0, 20, "", 5), (2048, 11008, 4, 0, 24, "", 8),
+# to 23; quantised 1.5B width, T = 33 to 38), with the helper stream switched off, and on the static scratch; and in bf16
+# wherever the head kernel's workgroups fit two per CU.
+LAUNCH_CASES = [(2048, 11008, 4, 0, 16, "", 5), (2048, 11008, 4, 0, 20, "", 5), (2048, 11008, 4, 0, 24, "", 5),
                 (2048, 11008, 4, 0, 32, "no_fork", 5), (2048, 11008, 4, 0, 33, "static", 5), (1536, 8960, 4, 8, 33, "", 5),
                 (1536, 8960, 4, 4, 64, "", 5), (2048, 11008, 4, 4, 33, "", 8), (256, 512, 17, 0, 8, "", 8),
-                (3584, 18944, 4, 0, 1, "", 8), (3584, 18944, 4, 0, 8, "", 8), (2304, 14592, 4, 0, 8, "", 7), (3584, 18944, 4, 0, 64, "", 8),
+                (3584, 18944, 4, 0, 1, "", 8), (3584, 18944, 4, 0, 8, "", 8), (2304, 16384, 16, 0, 8, "", 7), (2304, 14592, 4, 0, 8, "", 5), (3584, 18944, 4, 0, 64, "", 8),
                 (3584, 18944, 4, 8, 33, "", 7), (3584, 18944, 4, 4, 16, "", 5), (3584, 18944, 4, 4, 33, "", 8),
                 (3584, 18944, 4, 8, 64, "no_fork", 5)]
 

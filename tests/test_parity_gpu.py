@@ -866,11 +866,11 @@ def test_stage_timing_reports_every_stage():
 # A decode step with the router, the row quantiser and the dispatch plan inside the large kernels against
 # the same step with kernels of their own: same arithmetic per element, so every tap is equal to the bit.
 # Tokens at the edges of the token-row templates (8, 16, 32), top-k up to the most dispatch rows (512) and
-# one row, expert counts that are no power of two and the most (16), one tile and several per expert, one
+# one row, expert counts that are no power of two and the most (16), one tile and several per expert (and 64-row tiles), one
 # chunk sweep of a hidden row and a second one (F > 20480), a gate-up kernel for d <= 2048 and one above.
 ROLE_CASES = [(1, 256, 512, 4, 1), (1, 256, 512, 16, 8), (8, 384, 640, 5, 2), (9, 512, 1408, 16, 2), (16, 256, 512, 2, 1),
               (17, 2176, 1280, 8, 2), (32, 256, 20608, 3, 1), (33, 1536, 8960, 16, 2), (63, 128, 128, 16, 8),
-              (64, 2048, 11008, 16, 2), (64, 256, 512, 16, 8), (64, 384, 640, 1, 1)]
+              (64, 2048, 11008, 16, 2), (64, 256, 512, 16, 8), (64, 384, 640, 1, 1), (64, 1536, 8960, 4, 2)]
 
 
 @pytest.mark.parametrize("shared_bits", [0, 8, 4])
@@ -931,13 +931,13 @@ def test_layer_rows_longer_than_a_plane_on_either_tile_height(T):
         assert torch.equal(taps[48][n], taps[16][n]) and torch.equal(taps[48][n], taps[-1][n]), n
 
 
-# From 2^25 shared weights on a small step keeps the forked shared expert and makes only the dispatch plan inside the
-# gate-up kernel (the K-split one, d > 2048): against the plan kernel, by the default rule, with the shared chain on the
+# Steps of the widest layers keep the forked shared expert and make only the dispatch plan inside the gate-up kernel (the
+# K-split one, d > 2048): against the plan kernel, by the default rule, with the shared chain on the
 # helper stream.  Two, eight and 32 tokens, one and several tiles per expert, experts without rows (bias).
 @pytest.mark.parametrize("T,k,shared_bits", [(2, 1, 0), (8, 2, 0), (1, 2, 8), (7, 2, 8), (32, 2, 8), (3, 2, 4), (8, 4, 4)])
 def test_decode_step_with_the_plan_alone_inside_the_gate_up_kernel(T, k, shared_bits):
     M = _m()
-    d, F, E = 2304, 14592, 4
+    d, F, E = 2304, 16384, 16
     g = torch.Generator(device="cuda").manual_seed(T * 100 + k)
     rnd = lambda *s, std=1.0: torch.randn(*s, device="cuda", generator=g) * std
     shared, scales = [rnd(*s, std=0.01).to(torch.bfloat16) for s in ((F, d), (F, d), (d, F))], None
@@ -950,7 +950,7 @@ def test_decode_step_with_the_plan_alone_inside_the_gate_up_kernel(T, k, shared_
         for m in range(3):
             M.mote_pack_ternary(rnd(*((F, d) if m < 2 else (d, F)), std=0.02), packed=wt[m][e], alpha=alpha[m, e])
     layer = M.MoteLayer(rnd(d, E, std=d ** -0.5).to(torch.bfloat16), *shared, *wt, alpha[:, :, 0].t().contiguous(), k,
-                        router_bias=torch.tensor([0.0, 3.0, 30.0, 0.0], device="cuda"), shared_bits=shared_bits, shared_scales=scales)
+                        router_bias=torch.tensor([0.0, 3.0, 30.0] + 13 * [-2.0], device="cuda"), shared_bits=shared_bits, shared_scales=scales)
     x = rnd(T, d).to(torch.bfloat16)
     names = ("topk_idx", "topk_p", "counts", "row_of", "tok_of", "acc_gate", "acc_up", "h", "q_h", "acc_down", "h_s", "y_s", "out_f32")
     taps = {}
