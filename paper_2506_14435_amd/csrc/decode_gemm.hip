@@ -1313,17 +1313,16 @@ hipError_t launch_shared_decode_down(const uint16_t* h_s, const uint16_t* w_down
 // launches on one stream (d = 2048, bf16, weights from HBM, us):
 //
 //   decode_head_kernel : router + Q_a(x), one workgroup per token, beside the shared gate-up projection
-//                        (T = 1: 10.8 and 22.2 apart, 26.4 together; T = 16: 9.5 and 21.9, 27.7; from the memory-side
-//                        cache T = 1 9.5 and 18.0, 20.6)
+//                        (T = 1: 10.8 and 22.2 apart, 22.5 together; T = 16: 9.5 and 21.9, 25.4; T = 64: 20.6 and 27.3,
+//                        25.7; from the memory-side cache T = 1 9.5 and 18.0, 17.6)
 //   decode_mid_kernel  : Q_a(h), one workgroup per dispatch row, beside the shared down projection
-//                        (T = 1: 3.9 and 11.5 apart, 10.9 together; T = 16: 4.6 and 11.5, 11.6; T = 64: 4.8 and 15.0, 15.0)
+//                        (T = 1: 3.9 and 11.5 apart, 10.9 together; T = 16: 4.6 and 11.5, 11.6; T = 64: 4.8 and 15.0, 14.8)
 //
 // The small workgroups come first in the grid.  A workgroup of either kind reserves the ring of a
 // streaming one; the small ones keep their few bytes of LDS inside it (as arrays of their own beside it they took
-// the third, or of the quantised kernels' 80 KiB the second, workgroup from a CU).  With rings
-// of 52 KiB three workgroups of the bf16 kernels share a CU (above 32 tokens the head kernel's registers leave two at the start, until the
-// three idle wavefronts of each have ended; held to a third of the register file it is as fast: T = 64 d = 1536 78.5 against
-// 78.0 us, d = 3584 309.6 against 310.9).  What bounds them is the weight stream: 90 MB in 26 us, 45 MB in 11.
+// the third, or of the quantised kernels' 80 KiB the second, workgroup from a CU).  With rings of 52 KiB three workgroups
+// of the bf16 kernels share a CU; the head kernel takes rings of 64 KiB and two workgroups where its grid fits that way
+// (head_runs).  What bounds them is the weight stream: 90 MB in 22.5 us, 45 MB in 11.
 struct RouterRoleArgs {
   const uint16_t* x;
   const uint16_t* w_router;

@@ -173,7 +173,8 @@ def _device_kernels(path):
 def test_combined_decode_kernels_reserve_nothing_beside_their_ring(lib):
     """The rings of the decode step's two combined kernels are cut so that a whole number of workgroups fills a CU's
     LDS; static LDS of the small kernels inside them would come on top and take one of those workgroups away.  Nor do
-    their registers take one, of one wavefront per SIMD (but for the head kernel of more than 32 tokens: two fit)."""
+    their registers take one, of one wavefront per SIMD (but for the head kernel of more than 32 tokens: two fit; its
+    form with the longer ring wants two)."""
     kernels = _device_kernels(M.LIB_PATH)
     assert any("routed_wave_kernel" in n for n in kernels)
     combined = {n: k for n, k in kernels.items() if re.search(r"decode_(head|mid)(_q)?_kernel", n)}
