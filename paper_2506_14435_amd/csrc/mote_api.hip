@@ -392,7 +392,7 @@ mote_status forward_impl(const mote_layer* layer, const mote_norm* norm, const v
   // Shared expert: on the helper stream, unless stage timing wants one stage after the other.
   // Forking and joining costs the host about 40 us per call (two event records, two stream waits)
   // and the GPU a few us at the join, and two kernels that stream weights at the same time share
-  // the HBM.  Measured in steady state (ms per forward, one stream vs forked): C1 0.040 vs 0.055,
+  // the HBM.  Measured in steady state (ms per forward of eight launches, one stream vs forked): C1 0.040 vs 0.055,
   // decode shape T=16 0.1155 vs 0.1206 the one way; T=1 0.075 vs 0.0695, T=4 0.089 vs 0.081 (few
   // routed experts stream, the shared expert's weights dominate), T=32 0.1157 vs 0.112, T=64
   // 0.1229 vs 0.1155, C2 0.1896 vs 0.1644 the other.  Hence: fork when the shared expert has
@@ -617,8 +617,9 @@ mote_status mote_layer_forward_static(const mote_layer* layer, const void* x, in
   if (carve_to_fit(layer, T, nullptr, MOTE_STATIC_WORKSPACE_BYTES).bytes > MOTE_STATIC_WORKSPACE_BYTES) return MOTE_ERR_WORKSPACE_TOO_SMALL;
   void* ws = nullptr;
   MOTE_HIP(static_scratch(&ws));
-  // Nothing in the array has to start at zero: the dispatch plan kernel of every forward zeroes
-  // the tile counters and the plane words it uses, everything else is written before it is read.
+  // Nothing in the array has to start at zero: the dispatch plan kernel zeroes the tile counters and the plane words for
+  // the large-batch kernels (a step that makes its plan inside the gate-up kernel uses neither), everything else is
+  // written before it is read.
   return forward_impl(layer, nullptr, x, T, out, ws, MOTE_STATIC_WORKSPACE_BYTES, taps, hip_stream, true);
 }
 
