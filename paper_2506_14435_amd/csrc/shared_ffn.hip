@@ -1,5 +1,5 @@
 // Shared expert FFN(x) of Eq.2: the dense checkpoint's full-precision SwiGLU FFN, active
-// for every token.  bf16 operands on v_mfma_f32_32x32x16_bf16, fp32 accumulation.
+// for every token.  bf16 operands on v_mfma_f32_16x16x32_bf16, fp32 accumulation.
 //
 //   gate-up mode : g = x W_gate^T, u = x W_up^T, h_s = bf16(u * SiLU(g))     [T, F]
 //   down mode    : y_s = h_s W_down^T (fp32)                                 [T, d]
@@ -12,10 +12,13 @@
 // barrier waits of one overlap with the MFMAs of the other.  Persistent workgroups walk an
 // XCD-aware list of (row tile, channel tile, K plane) triples as the ternary GEMM does.
 //
-// MFMA operand mapping (32x32x16 bf16): first operand = weights (lane l: output channel
-// l%32, 8 consecutive K elements of half l/32), second = activations (lane l: token row
-// l%32); result register v of lane l is output channel 8*(v/4) + 4*(l/32) + v%4 of token
-// row l%32.
+// MFMA operand mapping (16x16x32 bf16): first operand = weights (lane l: output channel
+// l%16, 8 consecutive K elements of quarter l/16), second = activations (lane l: token row
+// l%16); result register v of lane l is output channel 4*(l/16) + v of token row l%16.
+//
+// Why 16x16 and not 32x32 tiles: the chip is power-limited inside these GEMMs.  Register-only loops over random
+// operands on all CUs sustain 2.00 PFLOP/s with v_mfma_f32_16x16x32_bf16 and 1.74 with v_mfma_f32_32x32x16_bf16
+// (half as many accumulator registers read and written per flop), fed from LDS as here 1.75 and 1.55.
 #include <stdlib.h>
 
 #include "common.h"
@@ -26,9 +29,9 @@ namespace mote {
 template <int MODE_, int BM_W_, int BN_W_, int WAVES_M_, int WAVES_N_, int MIN_BLOCKS_ = 1, int STAGES_ = 3, bool TERN_ = false>
 struct SharedCfg {
   // Weights as 2-bit ternary codes (grouped GEMM of the straight-through gradients): blocks of 32 channels x 32
-  // K elements = 256 bytes, block (channel block, K step) row-major; in a block word 2c + g holds channel c, K
-  // elements 8g .. 8g+7 and 16+8g .. of the step, element pair J (0..7 in that order) with its even element's
-  // "non-zero" at bit J and sign at bit 8+J, its odd element's at bits 16+J and 24+J.  In each 16-bit half of
+  // K elements = 256 bytes, block (channel block, K step) row-major; in a block word 16Q + c holds the K elements
+  // 8Q .. 8Q+7 of channel c (pairs J = 0..3) and of channel 16 + c (J = 4..7), the operands of one lane for two
+  // fragments: pair J has its even element's "non-zero" at bit J and sign at bit 8+J, its odd element's at bits 16+J and 24+J.  In each 16-bit half of
   // word & (0x01010101 << J), multiplied by 127 << (7 - J), "non-zero" becomes 0x3F80 and the sign 0x8000 (modulo 2^16;
   // 127 is odd): the pair as bf16 values 0, 1, -1 after one and and one packed 16-bit multiplication (a shift and an
   // and give 0, 2, -2 instead, whose sums overflow from 2^127 on).  What the GEMM is bound by is operand traffic: with
@@ -72,7 +75,7 @@ struct SharedCfg {
 // a quarter wavefront read one chunk of 16 consecutive rows = all 64 banks exactly once.
 __device__ __forceinline__ int lds_tile_offset(int row, int chunk) { return row * 64 + ((chunk ^ ((row >> 2) & 3)) << 4); }
 
-// Half h of the ternary word of a lane (see SharedCfg): eight K elements as bf16 values 0, 1, -1.
+// Half h of the ternary word of a lane (see SharedCfg): eight K elements of fragment h as bf16 values 0, 1, -1.
 __device__ __forceinline__ bf16x8 ternary_operand(uint32_t w, int h) {
   typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
   uint32_t r[4];
@@ -124,9 +127,11 @@ __device__ __forceinline__ void shared_gemm_body(const SharedGemmArgs& a, const 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wave_u = __builtin_amdgcn_readfirstlane(wave);
   const int wm = wave % Cfg::WAVES_M, wn = wave / Cfg::WAVES_M;
-  const int r32 = lane & 31, g = lane >> 5;
-  const int a_row_base = wm * BM_W * 32 + r32;
-  const int b_row_base = wn * BN_W * 32 + r32;
+  const int r16 = lane & 15, quart = lane >> 4;
+  constexpr int A16 = 2 * BM_W, B16 = 2 * BN_W, NB = NMAT * B16;   // 16-row / 16-channel fragments of a wavefront
+  // this lane's 16 bytes of the wavefront's first activation / weight fragment inside a stage
+  const int a_lds = lds_tile_offset(wm * BM_W * 32 + r16, quart);
+  const int b_lds = A_BYTES + lds_tile_offset(wn * BN_W * 32 + r16, quart);
   // LDS byte address of the stage area (what M0 takes for a direct-to-LDS load)
   const uint32_t lds0 = (uint32_t)(uintptr_t)((__attribute__((address_space(3))) unsigned char*)s_lds);
 
@@ -285,114 +290,75 @@ __device__ __forceinline__ void shared_gemm_body(const SharedGemmArgs& a, const 
       if (ktl > 2) MOTE_ISSUE_STEP(st_nx2, 2);
     }
 
-    v16f acc[NMAT][BM_W][BN_W];
+    v4f acc[A16][NB];   // token rows 16i .., channels 16b .. of the wavefront's block (gate first, then up)
 #pragma unroll
-    for (int m = 0; m < NMAT; ++m)
+    for (int i = 0; i < A16; ++i)
 #pragma unroll
-      for (int i = 0; i < BM_W; ++i)
-#pragma unroll
-        for (int f = 0; f < BN_W; ++f)
-#pragma unroll
-          for (int v = 0; v < 16; ++v) acc[m][i][f][v] = 0.0f;
+      for (int b = 0; b < NB; ++b) acc[i][b] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
 
     if constexpr (Cfg::TERN) {
-      // The loop below (ring of four, one barrier in the middle of a step) with the weights unpacked from one
-      // word per lane and fragment: eight vector instructions per two MFMAs in place of a 16-byte LDS read, an eighth
-      // of the weight bytes through L2 and LDS.  The next fragment is unpacked between the two MFMAs of this one (in
-      // front of its own it cost 4 % of the GEMM).
-      bf16x8 af0[BM_W], af1[BM_W];
-      uint32_t wq[BN_W], wx[BN_W];
-      const int w_lds = A_BYTES + (wn * BN_W * 64 + r32 * 2 + g) * 4;
-#pragma unroll
-      for (int i = 0; i < BM_W; ++i)
-        af0[i] = *reinterpret_cast<const bf16x8*>(s_lds + st_cur + lds_tile_offset(a_row_base + i * 32, g));
-#pragma unroll
-      for (int f = 0; f < BN_W; ++f) wq[f] = *reinterpret_cast<const uint32_t*>(s_lds + st_cur + w_lds + f * 256);
-      bf16x8 wf = ternary_operand(wq[0], 0);
-      for (int kt = 0; kt < ktl; ++kt) {
-        const bool pf = kt + 3 < ktl;
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int f = 0; f < BN_W; ++f) {
-          acc[0][0][f] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf, af0[0], acc[0][0][f], 0, 0, 0);
-          const bf16x8 wn = f + 1 < BN_W ? ternary_operand(wq[(f + 1) % BN_W], 0) : ternary_operand(wq[0], 1);
-#pragma unroll
-          for (int i = 1; i < BM_W; ++i)
-            acc[0][i][f] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf, af0[i], acc[0][i][f], 0, 0, 0);
-          wf = wn;
-          if (f == 0) {
-#pragma unroll
-            for (int i = 0; i < BM_W; ++i)
-              af1[i] = *reinterpret_cast<const bf16x8*>(s_lds + st_cur + lds_tile_offset(a_row_base + i * 32, 2 + g));
-            if (pf) MOTE_DMA_A(st_nx3, kt + 3, 0);
-          }
-          if (f == 1 && pf) MOTE_DMA_B(st_nx3, kt + 3, 0);
-          __builtin_amdgcn_sched_barrier(0);
-        }
-        // as below: K step kt+1 has landed, kt+2 and two of the three loads of kt+3 stay in flight
-        if (pf) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"(NLOAD + 2) : "memory");
-        else if (kt + 2 < ktl) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"(NLOAD) : "memory");
-        else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
-        asm volatile("s_barrier" ::: "memory");
-#pragma unroll
-        for (int f = 0; f < BN_W; ++f) {
-          acc[0][0][f] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf, af1[0], acc[0][0][f], 0, 0, 0);
-          const bf16x8 wn = f + 1 < BN_W ? ternary_operand(wq[(f + 1) % BN_W], 1) : ternary_operand(wx[0], 0);
-#pragma unroll
-          for (int i = 1; i < BM_W; ++i)
-            acc[0][i][f] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf, af1[i], acc[0][i][f], 0, 0, 0);
-          wf = wn;
-          if (f == 0) {
-#pragma unroll
-            for (int i = 0; i < BM_W; ++i)
-              af0[i] = *reinterpret_cast<const bf16x8*>(s_lds + st_nxt + lds_tile_offset(a_row_base + i * 32, g));
-#pragma unroll
-            for (int j = 0; j < BN_W; ++j) wx[j] = *reinterpret_cast<const uint32_t*>(s_lds + st_nxt + w_lds + j * 256);
-          }
-          if (f == 1 && pf) MOTE_DMA_A(st_nx3, kt + 3, 1);
-          __builtin_amdgcn_sched_barrier(0);
-        }
-#pragma unroll
-        for (int f = 0; f < BN_W; ++f) wq[f] = wx[f];
-        const int t = st_cur; st_cur = st_nxt; st_nxt = st_nx2; st_nx2 = st_nx3; st_nx3 = t;
+      // The ring of four below with the weights unpacked from one word per lane and two fragments: eight vector
+      // instructions per four MFMAs in place of a 16-byte LDS read, an eighth of the weight bytes through L2 and LDS.  The
+      // next fragment is unpacked between the MFMAs of this one (in front of its own it cost 4 % of the GEMM).  A plane
+      // is a whole number of 64 elements, so the steps go in pairs that swap the fragment registers by name.
+      bf16x8 afx[A16], afy[A16];
+      uint32_t wx[BN_W], wy[BN_W];
+      const int w_lds = A_BYTES + (wn * BN_W * 64 + lane) * 4;
+#define MOTE_TERN_READ(af_, w_, stage_)                                                                   \
+      {                                                                                                   \
+        _Pragma("unroll") for (int i = 0; i < A16; ++i)                                                   \
+          af_[i] = *reinterpret_cast<const bf16x8*>(s_lds + (stage_) + a_lds + i * 1024);                 \
+        _Pragma("unroll") for (int f = 0; f < BN_W; ++f)                                                  \
+          w_[f] = *reinterpret_cast<const uint32_t*>(s_lds + (stage_) + w_lds + f * 256);                 \
       }
+      // K step ks_ with the fragments (af_, w_); (afn_, wn_) take those of the next step once it has landed
+#define MOTE_TERN_STEP(ks_, af_, w_, afn_, wn_)                                                           \
+      {                                                                                                   \
+        const bool pf_ = (ks_) + 3 < ktl;                                                                 \
+        __builtin_amdgcn_sched_barrier(0);                                                                \
+        _Pragma("unroll") for (int b = 0; b < NB; ++b) {                                                  \
+          if (b == NB / 2) {                                                                              \
+            /* as below: K step ks_+1 has landed, ks_+2 and two of the three loads of ks_+3 stay in flight */ \
+            if (pf_) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"(NLOAD + 2) : "memory");          \
+            else if ((ks_) + 2 < ktl) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"(NLOAD) : "memory"); \
+            else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");                              \
+            asm volatile("s_barrier" ::: "memory");                                                       \
+          }                                                                                               \
+          acc[0][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf, af_[0], acc[0][b], 0, 0, 0);            \
+          const bf16x8 wnext_ = b + 1 < NB ? ternary_operand(w_[((b + 1) % NB) / 2], (b + 1) & 1) : ternary_operand(wn_[0], 0); \
+          _Pragma("unroll") for (int i = 1; i < A16; ++i)                                                 \
+            acc[i][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf, af_[i], acc[i][b], 0, 0, 0);          \
+          wf = wnext_;                                                                                    \
+          if (b == 0 && pf_) MOTE_DMA_A(st_nx3, (ks_) + 3, 0);                                            \
+          if (b == 1 && pf_) MOTE_DMA_B(st_nx3, (ks_) + 3, 0);                                            \
+          if (b == NB / 2) MOTE_TERN_READ(afn_, wn_, st_nxt)                                              \
+          if (b == NB / 2 + 1 && pf_) MOTE_DMA_A(st_nx3, (ks_) + 3, 1);                                   \
+          __builtin_amdgcn_sched_barrier(0);                                                              \
+        }                                                                                                 \
+        const int t_ = st_cur; st_cur = st_nxt; st_nxt = st_nx2; st_nx2 = st_nx3; st_nx3 = t_;            \
+      }
+      MOTE_TERN_READ(afx, wx, st_cur)
+      bf16x8 wf = ternary_operand(wx[0], 0);
+      for (int kt = 0; kt < ktl; kt += 2) {
+        MOTE_TERN_STEP(kt, afx, wx, afy, wy)
+        MOTE_TERN_STEP(kt + 1, afy, wy, afx, wx)
+      }
+#undef MOTE_TERN_STEP
+#undef MOTE_TERN_READ
     } else if constexpr (Cfg::STAGES == 4) {
       // Ring of four stages, loads three K steps ahead, ONE barrier per K step placed in the middle
-      // of the step: after it the next step's stage is visible, and its first-half fragments are
-      // read while the MFMAs of this step's second half run; the second-half fragments of a step
-      // are read at its start, under the MFMAs of the first half.  The wavefronts of the single
-      // workgroup of a CU all stop at the same barrier, so without this every K step began with
-      // the matrix pipe idle for an LDS round trip.
+      // of the step, which contracts the first half of the weight fragments in front of it and the second half
+      // behind it.  The second half's fragments are read under the MFMAs of the first; behind the barrier the
+      // next step's stage is visible, and its first half of the weights and its activations are read under the
+      // MFMAs of the second half, an activation fragment as soon as its last MFMA of this step has been issued.  The
+      // wavefronts of the single workgroup of a CU all stop at the same barrier: reads or loads in a block of their own
+      // would leave the matrix pipe idle on every SIMD at once, so they go one by one between the MFMAs.
       constexpr int NH0 = (Cfg::A_PASSES + 1) / 2 + (Cfg::B_PASSES + 1) / 2;   // loads issued in the first half of a step
-      bf16x8 af0[BM_W], bf0[NMAT][BN_W], af1[BM_W], bf1[NMAT][BN_W];
-#define MOTE_READ_HALF(af_, bf_, stage_, s_)                                                              \
-      {                                                                                                   \
-        const unsigned char* const st_ = s_lds + (stage_);                                                \
-        _Pragma("unroll") for (int i = 0; i < BM_W; ++i)                                                  \
-          af_[i] = *reinterpret_cast<const bf16x8*>(st_ + lds_tile_offset(a_row_base + i * 32, 2 * (s_) + g)); \
-        _Pragma("unroll") for (int m = 0; m < NMAT; ++m)                                                  \
-          _Pragma("unroll") for (int f = 0; f < BN_W; ++f)                                                \
-            bf_[m][f] = *reinterpret_cast<const bf16x8*>(st_ + A_BYTES + m * B_BYTES +                    \
-                                                         lds_tile_offset(b_row_base + f * 32, 2 * (s_) + g)); \
-      }
-      // One half of a K step: the MFMAs of fragments (ua_, ub_), and between them - so that the matrix
-      // pipe never waits for this wavefront to get through a block of other instructions - the reads of
-      // the next half's fragments (fa_, fb_) from (fstage_, sub-step fs_), two per MFMA, then the
-      // direct loads of parity par_ of K step ks_ into dstage_, one per MFMA.  Every wavefront of the
-      // workgroup is in the same half at the same time, so nothing else would cover such a block.
-      constexpr int NM = NMAT * BN_W * BM_W;          // MFMAs of a half
-      constexpr int NR = BM_W + NMAT * BN_W;          // fragment reads of a half
-      constexpr int RPS = 2;                          // fragment reads per MFMA (1: C3 shared down 5 % slower, 3: the same)
-      constexpr int RSLOTS = (NR + RPS - 1) / RPS;
-#define MOTE_SIDE_READ(r_, fa_, fb_, fstage_, fs_)                                                        \
-      if ((r_) < BM_W) {                                                                                  \
-        fa_[(r_) < BM_W ? (r_) : 0] = *reinterpret_cast<const bf16x8*>(                                   \
-            s_lds + (fstage_) + lds_tile_offset(a_row_base + ((r_) < BM_W ? (r_) : 0) * 32, 2 * (fs_) + g)); \
-      } else if ((r_) < NR) {                                                                             \
-        const int b_ = (r_) < NR && (r_) >= BM_W ? (r_) - BM_W : 0;                                       \
-        fb_[b_ / BN_W][b_ % BN_W] = *reinterpret_cast<const bf16x8*>(                                     \
-            s_lds + (fstage_) + A_BYTES + (b_ / BN_W) * B_BYTES + lds_tile_offset(b_row_base + (b_ % BN_W) * 32, 2 * (fs_) + g)); \
-      }
+      constexpr int HB = NB / 2;        // weight fragments of a half
+      constexpr int NM = A16 * HB;      // MFMAs of a half
+      bf16x8 af[A16], bl[HB], bh[HB];
+#define MOTE_A_FRAG(stage_, i_) *reinterpret_cast<const bf16x8*>(s_lds + (stage_) + a_lds + (i_) * 1024)
+#define MOTE_B_FRAG(stage_, b_) *reinterpret_cast<const bf16x8*>(s_lds + (stage_) + b_lds + ((b_) / B16) * B_BYTES + ((b_) % B16) * 1024)
       // the d_-th direct load of parity par_: the A passes par_, par_ + 2, ..., then the B passes
 #define MOTE_SIDE_DMA(d_, par_, dstage_, ks_)                                                             \
       {                                                                                                   \
@@ -400,91 +366,79 @@ __device__ __forceinline__ void shared_gemm_body(const SharedGemmArgs& a, const 
         if ((d_) >= 0 && (d_) < NA_) { MOTE_DMA_A(dstage_, ks_, ((d_) >= 0 && (d_) < NA_ ? 2 * (d_) + (par_) : 0)); } \
         else if ((d_) >= NA_ && (d_) < NA_ + NB_) { MOTE_DMA_B(dstage_, ks_, ((d_) >= NA_ && (d_) < NA_ + NB_ ? 2 * ((d_) - NA_) + (par_) : 0)); } \
       }
-#define MOTE_HALF(ua_, ub_, fill_, fa_, fb_, fstage_, fs_, dma_, par_, dstage_, ks_)                      \
-      {                                                                                                   \
-        _Pragma("unroll") for (int m_ = 0; m_ < NMAT; ++m_)                                               \
-          _Pragma("unroll") for (int f_ = 0; f_ < BN_W; ++f_)                                             \
-            _Pragma("unroll") for (int i_ = 0; i_ < BM_W; ++i_) {                                         \
-              const int j_ = (m_ * BN_W + f_) * BM_W + i_;                                                \
-              acc[m_][i_][f_] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ub_[m_][f_], ua_[i_], acc[m_][i_][f_], 0, 0, 0); \
-              if (fill_) {                                                                                \
-                _Pragma("unroll") for (int r_ = 0; r_ < RPS; ++r_)                                        \
-                  MOTE_SIDE_READ(RPS * j_ + r_, fa_, fb_, fstage_, fs_)                                   \
-              }                                                                                           \
-              if (dma_) MOTE_SIDE_DMA(j_ - RSLOTS, par_, dstage_, ks_)                                    \
-              __builtin_amdgcn_sched_barrier(0);                                                          \
-            }                                                                                             \
-        /* more side work than MFMAs (small tiles): the rest at the end */                                \
-        _Pragma("unroll") for (int j_ = NM; j_ < RSLOTS + (Cfg::A_PASSES + Cfg::B_PASSES + 1) / 2; ++j_) { \
-          if (fill_) {                                                                                    \
-            _Pragma("unroll") for (int r_ = 0; r_ < RPS; ++r_)                                            \
-              MOTE_SIDE_READ(RPS * j_ + r_, fa_, fb_, fstage_, fs_)                                       \
-          }                                                                                               \
-          if (dma_) MOTE_SIDE_DMA(j_ - RSLOTS, par_, dstage_, ks_)                                        \
-        }                                                                                                 \
-        __builtin_amdgcn_sched_barrier(0);                                                                \
-      }
-      MOTE_READ_HALF(af0, bf0, st_cur, 0);
+#pragma unroll
+      for (int i = 0; i < A16; ++i) af[i] = MOTE_A_FRAG(st_cur, i);
+#pragma unroll
+      for (int b = 0; b < HB; ++b) bl[b] = MOTE_B_FRAG(st_cur, b);
       for (int kt = 0; kt < ktl; ++kt) {
         const bool pf = kt + 3 < ktl;
         __builtin_amdgcn_sched_barrier(0);
-        // first half: fragments of sub-step 1 of this step; first half of the loads of K step kt+3,
-        // into the stage that step kt-1 used
-        MOTE_HALF(af0, bf0, true, af1, bf1, st_cur, 1, pf, 0, st_nx3, kt + 3)
+        // the loads of K step kt+3 go into the stage that step kt-1 used
+#pragma unroll
+        for (int i = 0; i < A16; ++i)
+#pragma unroll
+          for (int b = 0; b < HB; ++b) {
+            const int j = i * HB + b;
+            acc[i][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bl[b], af[i], acc[i][b], 0, 0, 0);
+            if (j < HB) bh[j] = MOTE_B_FRAG(st_cur, HB + j);
+            if (pf && j >= HB && ((j - HB) & 1) == 0) MOTE_SIDE_DMA((j - HB) / 2, 0, st_nx3, kt + 3)
+            __builtin_amdgcn_sched_barrier(0);
+          }
         // K step kt+1 has landed everywhere (kt+2 and the half of kt+3 stay in flight); every
         // wavefront has finished its reads of this step's stage
         if (pf) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"(NLOAD + NH0) : "memory");
         else if (kt + 2 < ktl) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"(NLOAD) : "memory");
         else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
         asm volatile("s_barrier" ::: "memory");
-        // second half: fragments of sub-step 0 of the next step (after the last step: of a stage nobody
-        // uses, read and dropped); the other half of the loads
-        MOTE_HALF(af1, bf1, true, af0, bf0, st_nxt, 0, pf, 1, st_nx3, kt + 3)
+        // after the last step the reads are of a stage nobody uses, and dropped
+#pragma unroll
+        for (int i = 0; i < A16; ++i)
+#pragma unroll
+          for (int b = 0; b < HB; ++b) {
+            const int j = i * HB + b;
+            acc[i][HB + b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bh[b], af[i], acc[i][HB + b], 0, 0, 0);
+            if (j < HB) bl[j] = MOTE_B_FRAG(st_nxt, j);
+            if (b == HB - 1) af[i] = MOTE_A_FRAG(st_nxt, i);
+            if (pf && j >= HB && ((j - HB) & 1) == 0) MOTE_SIDE_DMA((j - HB) / 2, 1, st_nx3, kt + 3)
+            __builtin_amdgcn_sched_barrier(0);
+          }
         const int t = st_cur; st_cur = st_nxt; st_nxt = st_nx2; st_nx2 = st_nx3; st_nx3 = t;
       }
-#undef MOTE_HALF
+      static_assert(NM >= HB + Cfg::A_PASSES + Cfg::B_PASSES, "every load of a half finds an MFMA to follow");
 #undef MOTE_SIDE_DMA
-#undef MOTE_SIDE_READ
-#undef MOTE_READ_HALF
+#undef MOTE_A_FRAG
+#undef MOTE_B_FRAG
     } else {
       // K loop.  K step kt contracts stage st_cur while the loads of kt+2 are issued, half of them
-      // per 16-element sub-step, into the stage that the barrier at the end of step kt-1 released.
+      // in front of each half of the MFMAs, into the stage that the barrier at the end of step kt-1 released.
       for (int kt = 0; kt < ktl; ++kt) {
         const bool pf = kt + 2 < ktl;
         const unsigned char* const st = s_lds + st_cur;
-        // all fragments of the step are requested at once: the MFMAs of the first half run while
-        // those of the second half are still on their way
-        bf16x8 af[2][BM_W], bfr[2][NMAT][BN_W];
-  #pragma unroll
-        for (int s = 0; s < 2; ++s) {
-  #pragma unroll
-          for (int i = 0; i < BM_W; ++i)
-            af[s][i] = *reinterpret_cast<const bf16x8*>(st + lds_tile_offset(a_row_base + i * 32, 2 * s + g));
-  #pragma unroll
-          for (int m = 0; m < NMAT; ++m)
-  #pragma unroll
-            for (int f = 0; f < BN_W; ++f)
-              bfr[s][m][f] = *reinterpret_cast<const bf16x8*>(st + A_BYTES + m * B_BYTES +
-                                                              lds_tile_offset(b_row_base + f * 32, 2 * s + g));
-        }
+        // all fragments of the step are requested at once: the first MFMAs run while
+        // the later fragments are still on their way
+        bf16x8 af[A16], bfr[NB];
+#pragma unroll
+        for (int b = 0; b < NB / 2; ++b) bfr[b] = *reinterpret_cast<const bf16x8*>(st + b_lds + (b / B16) * B_BYTES + (b % B16) * 1024);
+#pragma unroll
+        for (int i = 0; i < A16; ++i) af[i] = *reinterpret_cast<const bf16x8*>(st + a_lds + i * 1024);
+#pragma unroll
+        for (int b = NB / 2; b < NB; ++b) bfr[b] = *reinterpret_cast<const bf16x8*>(st + b_lds + (b / B16) * B_BYTES + (b % B16) * 1024);
         __builtin_amdgcn_sched_barrier(0);
-  #pragma unroll
+#pragma unroll
         for (int s = 0; s < 2; ++s) {
           if (pf) {   // half s of the loads of K step kt+2
-  #pragma unroll
+#pragma unroll
             for (int p = 0; p < Cfg::A_PASSES; ++p)
               if ((p & 1) == s) MOTE_DMA_A(st_nx2, kt + 2, p);
-  #pragma unroll
+#pragma unroll
             for (int p = 0; p < Cfg::B_PASSES; ++p)
               if ((p & 1) == s) MOTE_DMA_B(st_nx2, kt + 2, p);
           }
-  #pragma unroll
-          for (int m = 0; m < NMAT; ++m)
-  #pragma unroll
-            for (int f = 0; f < BN_W; ++f)
-  #pragma unroll
-              for (int i = 0; i < BM_W; ++i)
-                acc[m][i][f] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[s][m][f], af[s][i], acc[m][i][f], 0, 0, 0);
+#pragma unroll
+          for (int i = 0; i < A16; ++i)
+#pragma unroll
+            for (int b = s * (NB / 2); b < (s + 1) * (NB / 2); ++b)
+              acc[i][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bfr[b], af[i], acc[i][b], 0, 0, 0);
           __builtin_amdgcn_sched_barrier(0);  // keep each half's loads with its half
         }
         // K step kt+1 landed everywhere (kt+2 stays in flight); after the last step: every
@@ -503,8 +457,8 @@ __device__ __forceinline__ void shared_gemm_body(const SharedGemmArgs& a, const 
     }
 
     // ---- epilogue ----
-    // In registers lane l owns token row r32 and runs of four consecutive output channels
-    // (8q + 4g .. +3).  Each wavefront writes one 32-row block of PATCH_F fragments into its
+    // In registers lane l owns token row r16 and four consecutive output channels of every
+    // fragment (4 * quart .. +3).  Each wavefront writes one 32-row block of PATCH_F fragments into its
     // private LDS patch and reads it back row-major, 16 bytes per lane, so that a global store
     // instruction covers whole 128-byte rows of the block.
     constexpr int PATCH_F = Cfg::PATCH_F;
@@ -519,19 +473,17 @@ __device__ __forceinline__ void shared_gemm_body(const SharedGemmArgs& a, const 
     const int rd_row = lane / LANES_PER_ROW, rd_chunk = lane % LANES_PER_ROW;
     if (a.scale0 != nullptr) {   // row scales of quantised weights (uniform branch, not taken by the bf16 expert)
 #pragma unroll
-      for (int f = 0; f < BN_W; ++f) {
+      for (int b = 0; b < B16; ++b) {
+        const int ch = min(n_wave0 + b * 16 + 4 * quart, N - 4);
+        const float4 s0 = *reinterpret_cast<const float4*>(a.scale0 + static_cast<int64_t>(grp) * N + ch);
+        float4 s1 = s0;
+        if constexpr (NMAT == 2) s1 = *reinterpret_cast<const float4*>(a.scale1 + ch);
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int ch = min(n_wave0 + f * 32 + 8 * q + 4 * g, N - 4);
-          const float4 s0 = *reinterpret_cast<const float4*>(a.scale0 + static_cast<int64_t>(grp) * N + ch);
-          float4 s1 = s0;
-          if constexpr (NMAT == 2) s1 = *reinterpret_cast<const float4*>(a.scale1 + ch);
-#pragma unroll
-          for (int i = 0; i < BM_W; ++i) {
-            acc[0][i][f][4 * q] *= s0.x; acc[0][i][f][4 * q + 1] *= s0.y; acc[0][i][f][4 * q + 2] *= s0.z; acc[0][i][f][4 * q + 3] *= s0.w;
-            if constexpr (NMAT == 2) {
-              acc[1][i][f][4 * q] *= s1.x; acc[1][i][f][4 * q + 1] *= s1.y; acc[1][i][f][4 * q + 2] *= s1.z; acc[1][i][f][4 * q + 3] *= s1.w;
-            }
+        for (int i = 0; i < A16; ++i) {
+          acc[i][b].x *= s0.x; acc[i][b].y *= s0.y; acc[i][b].z *= s0.z; acc[i][b].w *= s0.w;
+          if constexpr (NMAT == 2) {
+            v4f& au = acc[i][(NMAT - 1) * B16 + b];
+            au.x *= s1.x; au.y *= s1.y; au.z *= s1.z; au.w *= s1.w;
           }
         }
       }
@@ -541,22 +493,20 @@ __device__ __forceinline__ void shared_gemm_body(const SharedGemmArgs& a, const 
 #pragma unroll
       for (int f0 = 0; f0 < BN_W; f0 += PATCH_F) {
 #pragma unroll
-        for (int ff = 0; ff < PATCH_F; ++ff) {
-          const int f = f0 + ff;
+        for (int bb = 0; bb < 2 * PATCH_F; ++bb) {
+          const int b = 2 * f0 + bb, pcol = bb * 16 + 4 * quart;   // channel inside the patch row
 #pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const int pcol = ff * 32 + 8 * q + 4 * g;   // channel inside the patch row
+          for (int r = 0; r < 2; ++r) {
+            const v4f v = acc[2 * i + r][b];
+            unsigned char* const dst = patch + (r * 16 + r16) * PATCH_ROW + pcol * Cfg::OUT_BYTES;
             if constexpr (Cfg::MODE == 0) {
-              float hv[4];
-#pragma unroll
-              for (int j = 0; j < 4; ++j) hv[j] = acc[NMAT - 1][i][f][4 * q + j] * silu_fast(acc[0][i][f][4 * q + j]);
+              const v4f u = acc[2 * i + r][(NMAT - 1) * B16 + b];
               uint2 packed;
-              packed.x = cvt_pk_bf16(hv[0], hv[1]);
-              packed.y = cvt_pk_bf16(hv[2], hv[3]);
-              *reinterpret_cast<uint2*>(patch + r32 * PATCH_ROW + pcol * 2) = packed;
+              packed.x = cvt_pk_bf16(u.x * silu_fast(v.x), u.y * silu_fast(v.y));
+              packed.y = cvt_pk_bf16(u.z * silu_fast(v.z), u.w * silu_fast(v.w));
+              *reinterpret_cast<uint2*>(dst) = packed;
             } else {
-              *reinterpret_cast<float4*>(patch + r32 * PATCH_ROW + pcol * 4) = make_float4(
-                  acc[0][i][f][4 * q], acc[0][i][f][4 * q + 1], acc[0][i][f][4 * q + 2], acc[0][i][f][4 * q + 3]);
+              *reinterpret_cast<float4*>(dst) = make_float4(v.x, v.y, v.z, v.w);
             }
           }
         }
@@ -616,6 +566,318 @@ __global__ __launch_bounds__(Cfg::THREADS, Cfg::MIN_BLOCKS) void kgrouped_gemm_k
   shared_gemm_body<Cfg, 2>(a, &rg, n_ntiles, rg.n, 0, group_m);
 }
 
+
+// Large problems: 256 x 256 tiles (256 x (128+128) in gate-up mode), one workgroup of eight wavefronts per CU, each
+// 64 rows x 128 channels.  K goes in chunks of 64 elements, so that a tile row in LDS is 128 bytes and a direct load
+// brings eight rows x one whole cache line: on 64-byte rows (the kernel above) a load needs twice the requests, and
+// loads alone, without any MFMA, peak at 14 TB/s over the chip where 128-byte rows reach 25 - this kernel asks for 10
+// to 13.
+//
+// LDS is a ring of five 32-KiB slots that take the operands in turn, A0 B0 A1 B1 A2 ...; chunk c is contracted out
+// of two of them while the other three hold or receive A and B of chunk c+1 and A of chunk c+2.  A chunk is four
+// quarters of 16 MFMAs per wavefront (half of the chunk's K x half of the weight fragments); every quarter reads the fragments of
+// the next one between its MFMAs (an activation fragment as soon as its last MFMA has been issued), so the last
+// quarter reads nothing of chunk c any more: in front of it stands the one barrier of the chunk, which publishes
+// chunk c+1 and frees the two slots for B of chunk c+2 and A of chunk c+3 (requested in the last quarter and in the
+// first one of chunk c+1: one and two chunks ahead of their use; spread evenly over all quarters, or all in the last one, the
+// kernel is 2-3 % slower).  The wavefronts of the single workgroup of a CU are
+// in step, so reads and loads in a block of their own would leave the matrix pipe idle on every SIMD at once: they
+// go one by one between the MFMAs.
+//
+// Measured (random operands, start: the ring of four 32-element steps on 32x32x16 MFMAs): gate-up 8192 x 2048 x 11008
+// 591 -> 511 us (1.44 PFLOP/s), down 314 -> 250 (1.48); 16384 x 3584 x 18944 3861 -> 3145, 1995 -> 1612.  What bounds it is
+// power: with operands of zeros the first takes 374 us at 2.4 GHz, with random ones the chip clocks at 1.75 GHz.
+//
+// GROUPED: 0 plain, 2 K ranges (as above).
+template <int MODE_>
+struct BigCfg {
+  static constexpr int MODE = MODE_;   // 0 gate-up, 1 down
+  static constexpr int NMAT = MODE_ == 0 ? 2 : 1;
+  static constexpr int BM = 256, BN = 256 / NMAT, WAVES = 8, THREADS = 512;
+  static constexpr int A16 = 4, NB = 8, B16 = NB / NMAT, HB = NB / 2;   // 16-row and 16-channel fragments of a wavefront
+  static constexpr int SLOT = 32768, LDS_BYTES = 5 * SLOT;
+  static constexpr int OUT_BYTES = MODE_ == 0 ? 2 : 4;
+  static constexpr int PATCH_ROW = 128 + 16, PATCH_BYTES = 32 * PATCH_ROW;   // epilogue: 32 rows of 128 bytes per wavefront
+  static_assert(4 * PATCH_BYTES <= SLOT, "the patches of four wavefronts fit a free slot");
+};
+
+template <typename Cfg, int GROUPED>
+__device__ __forceinline__ void big_gemm_body(const SharedGemmArgs& a, const RowGroups* rg, int n_ntiles, int kplanes, int ktp, int group_m) {
+  constexpr int NMAT = Cfg::NMAT, BM = Cfg::BM, BN = Cfg::BN, SLOT = Cfg::SLOT;
+  constexpr int A16 = Cfg::A16, NB = Cfg::NB, B16 = Cfg::B16, HB = Cfg::HB;
+  extern __shared__ __attribute__((aligned(16))) unsigned char s_lds[];
+  const int M = a.M, N = a.N, K = a.K;
+  const int KT = K >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int wave_u = __builtin_amdgcn_readfirstlane(wave);
+  const int wm = wave & 3, wn = wave >> 2;
+  const int r16 = lane & 15, quart = lane >> 4;
+  const uint32_t lds0 = (uint32_t)(uintptr_t)((__attribute__((address_space(3))) unsigned char*)s_lds);
+  // 128-byte rows of eight 16-byte chunks, chunk XOR-swizzled with row bits 1..3 (two rows span the banks once).  This
+  // lane's 16 bytes of the wavefront's first fragment, K half 0; half 1 is at ^ 64
+  const int frag = r16 * 128 + ((quart ^ (r16 >> 1)) << 4);
+  const int a_lds = wm * 64 * 128 + frag, b_lds = wn * (BN / 2) * 128 + frag;
+
+  // tile order: as in shared_gemm_body
+  n_ntiles *= kplanes;
+  const int n_mtiles = (M + BM - 1) / BM;
+  const int xcd = blockIdx.x & 7;
+  const bool split_n = n_ntiles >= 16;
+  const int xcd_ntiles = split_n ? (n_ntiles - xcd + 7) >> 3 : n_ntiles;
+  const int xcd_mtiles = split_n ? n_mtiles : (n_mtiles - xcd + 7) >> 3;
+  const int xcd_work = xcd_ntiles * xcd_mtiles;
+  const int per_group = group_m * xcd_ntiles;
+  const int stride = gridDim.x >> 3;
+  int slot = blockIdx.x >> 3;
+  if (slot >= xcd_work) return;
+
+  constexpr int kBufferFlags = 0x00020000;   // raw buffer, 32-bit data format
+  auto make_rsrc = [&](const void* base, int64_t bytes) {
+    const uint64_t p = reinterpret_cast<uint64_t>(base);
+    v4i r;
+    r.x = static_cast<int>(static_cast<uint32_t>(p));
+    r.y = static_cast<int>(static_cast<uint32_t>(p >> 32) & 0xFFFFu);
+    r.z = static_cast<int>(bytes);
+    r.w = kBufferFlags;
+    return r;
+  };
+  const v4i rsrc_a = make_rsrc(a.act, static_cast<int64_t>(M) * K * 2);
+  const v4i rsrc_b0 = make_rsrc(a.w0, static_cast<int64_t>(N) * K * 2);
+  const v4i rsrc_b1 = make_rsrc(NMAT == 2 ? a.w1 : a.w0, static_cast<int64_t>(N) * K * 2);
+  // lane l of a load lands at byte 16*l of a 1-KiB block = tile row l/8, physical chunk l%8; pass p covers the tile
+  // rows 64p + 8 * wavefront ..
+  const int ld_row = wave_u * 8 + (lane >> 3);
+  const uint32_t ld_chunk = static_cast<uint32_t>(((lane & 7) ^ ((ld_row >> 1) & 7)) << 4);
+  uint32_t a_off[4], b_off[4];   // byte offsets of this lane's 16 bytes, chunk 0 of the plane
+  int mt, nt, kc, ktl;
+  int s0 = 0, s1 = SLOT, s2 = 2 * SLOT, s3 = 3 * SLOT, s4 = 4 * SLOT;   // slots of A, B of chunk c, A, B of chunk c+1, A of chunk c+2
+
+#define MOTE_DECODE(slot_, mt_, nt_, kc_)                                       \
+  {                                                                             \
+    const int grp_ = (slot_) / per_group;                                       \
+    const int in_ = (slot_) - grp_ * per_group;                                 \
+    const int gsz_ = min(xcd_mtiles - grp_ * group_m, group_m);                 \
+    const int ni_ = in_ / gsz_, mi_ = grp_ * group_m + (in_ - ni_ * gsz_);      \
+    mt_ = split_n ? mi_ : xcd + 8 * mi_;                                        \
+    const int ntk_ = split_n ? xcd + 8 * ni_ : ni_;                             \
+    nt_ = ntk_ / kplanes;                                                       \
+    kc_ = ntk_ - nt_ * kplanes;                                                 \
+  }
+  // byte offset of plane kc_ in an operand row and its chunks
+#define MOTE_KRANGE(kc_, kb_, ktl_)                                             \
+  {                                                                             \
+    if constexpr (GROUPED == 2) {                                               \
+      kb_ = static_cast<uint32_t>(rg->row0[kc_]) * 2u;                          \
+      ktl_ = (rg->row0[(kc_) + 1] - rg->row0[kc_]) >> 6;                        \
+    } else {                                                                    \
+      kb_ = static_cast<uint32_t>((kc_) * ktp) * 128u;                          \
+      ktl_ = min(ktp, KT - (kc_) * ktp);                                        \
+    }                                                                           \
+  }
+#define MOTE_POINTERS(mt_, nt_, kb_)                                                               \
+  {                                                                                                \
+    const uint32_t k0_ = (kb_) + ld_chunk;                                                         \
+    _Pragma("unroll") for (int p = 0; p < 4; ++p) {                                                \
+      a_off[p] = static_cast<uint32_t>(min((mt_) * BM + p * 64 + ld_row, M - 1)) * static_cast<uint32_t>(K) * 2u + k0_; \
+      b_off[p] = static_cast<uint32_t>(min((nt_) * BN + (p * 64) % BN + ld_row, N - 1)) * static_cast<uint32_t>(K) * 2u + k0_; \
+    }                                                                                              \
+  }
+  // one 16-byte-per-lane direct load of pass p_ of chunk ks_ (M0: see ternary_gemm.hip)
+#define MOTE_DMA(lds_, voff_, rsrc_, soff_)                                                        \
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"           \
+               :: "s"(lds_), "v"(voff_), "s"(rsrc_), "s"(soff_) : "memory")
+#define MOTE_DMA_A(slot_, ks_, p_) MOTE_DMA(lds0 + (slot_) + ((p_) * 64 + wave_u * 8) * 128, a_off[p_], rsrc_a, (ks_) * 128)
+#define MOTE_DMA_B(slot_, ks_, p_) \
+  MOTE_DMA(lds0 + (slot_) + ((p_) * 64 + wave_u * 8) * 128, b_off[p_], (((p_) * 64) / BN == 0 ? rsrc_b0 : rsrc_b1), (ks_) * 128)
+#define MOTE_ISSUE_A(slot_, ks_) { _Pragma("unroll") for (int p = 0; p < 4; ++p) MOTE_DMA_A(slot_, ks_, p); }
+#define MOTE_ISSUE_B(slot_, ks_) { _Pragma("unroll") for (int p = 0; p < 4; ++p) MOTE_DMA_B(slot_, ks_, p); }
+#define MOTE_A_FRAG(slot_, h_, i_) *reinterpret_cast<const bf16x8*>(s_lds + (slot_) + (a_lds ^ ((h_) * 64)) + (i_) * 2048)
+#define MOTE_B_FRAG(slot_, h_, b_) \
+  *reinterpret_cast<const bf16x8*>(s_lds + (slot_) + (b_lds ^ ((h_) * 64)) + ((b_) / B16) * (BN * 128) + ((b_) % B16) * 2048)
+
+  // ---- first tile ----
+  MOTE_DECODE(slot, mt, nt, kc);
+  uint32_t kb;
+  MOTE_KRANGE(kc, kb, ktl);
+  MOTE_POINTERS(mt, nt, kb);
+  if (ktl > 0) {
+    MOTE_ISSUE_A(s0, 0);
+    MOTE_ISSUE_B(s1, 0);
+    if (ktl > 1) MOTE_ISSUE_A(s2, 1);
+  }
+
+  for (;;) {
+    const int nslot = slot + stride;
+    const bool has_next = nslot < xcd_work;
+    int mt2 = mt, nt2 = nt, kc2 = kc, ktl2 = ktl;
+    uint32_t kb2 = kb;
+    if (has_next) {
+      MOTE_DECODE(nslot, mt2, nt2, kc2);
+      MOTE_KRANGE(kc2, kb2, ktl2);
+    }
+    // chunk 0 visible to every wavefront, the patches of the previous tile done
+    if (ktl > 1) asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
+    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    asm volatile("s_barrier" ::: "memory");
+    if (ktl > 1) MOTE_ISSUE_B(s3, 1);   // this slot held patches
+
+    v4f acc[A16][NB];   // token rows 16i .., channels 16b .. of the wavefront's block (gate first, then up)
+#pragma unroll
+    for (int i = 0; i < A16; ++i)
+#pragma unroll
+      for (int b = 0; b < NB; ++b) acc[i][b] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+    bf16x8 af[A16], bl[HB], bh[HB];
+#pragma unroll
+    for (int b = 0; b < HB; ++b) bl[b] = MOTE_B_FRAG(s1, 0, b);
+#pragma unroll
+    for (int i = 0; i < A16; ++i) af[i] = MOTE_A_FRAG(s0, 0, i);
+    // a quarter: MFMAs of (af, b_) into the weight half o_; behind MFMA j the statement side_(i, b, j)
+#define MOTE_QUARTER(b_, o_, side_)                                                                \
+    _Pragma("unroll") for (int i = 0; i < A16; ++i)                                                \
+      _Pragma("unroll") for (int b = 0; b < HB; ++b) {                                             \
+        const int j = i * HB + b;                                                                  \
+        acc[i][(o_) + b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b_[b], af[i], acc[i][(o_) + b], 0, 0, 0); \
+        side_                                                                                      \
+        __builtin_amdgcn_sched_barrier(0);                                                         \
+      }
+    // chunk c; PF_: with the requests of A and B of chunk c+2.  In front of the barrier chunk c+1 has landed (A of chunk
+    // c+2 stays in flight) and this wavefront has read all of chunk c.  After the last chunk the last quarter's
+    // reads are of slots nobody uses, and dropped.
+#define MOTE_CHUNK(PF_)                                                                            \
+    {                                                                                              \
+      __builtin_amdgcn_sched_barrier(0);                                                           \
+      MOTE_QUARTER(bl, 0, {                                                                        \
+        if (j < HB) bh[j] = MOTE_B_FRAG(s1, 0, HB + j);                                            \
+        if (PF_ && (j & 3) == 2) MOTE_DMA_A(s4, c + 2, j / 4);                                     \
+      })                                                                                           \
+      MOTE_QUARTER(bh, HB, {                                                                       \
+        if (j < HB) bl[j] = MOTE_B_FRAG(s1, 1, j);                                                 \
+        if (b == HB - 1) af[i] = MOTE_A_FRAG(s0, 1, i);                                            \
+      })                                                                                           \
+      MOTE_QUARTER(bl, 0, {                                                                        \
+        if (j < HB) bh[j] = MOTE_B_FRAG(s1, 1, HB + j);                                            \
+      })                                                                                           \
+      asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"(PF_ ? 4 : 0) : "memory");               \
+      asm volatile("s_barrier" ::: "memory");                                                      \
+      MOTE_QUARTER(bh, HB, {                                                                       \
+        if (j < HB) bl[j] = MOTE_B_FRAG(s3, 0, j);                                                 \
+        if (b == HB - 1) af[i] = MOTE_A_FRAG(s2, 0, i);                                            \
+        if (PF_ && (j & 3) == 2) MOTE_DMA_B(s0, c + 2, j / 4);                                     \
+      })                                                                                           \
+      const int t0 = s0, t1 = s1;                                                                  \
+      s0 = s2; s1 = s3; s2 = s4; s3 = t0; s4 = t1;                                                 \
+    }
+    // two loops rather than a test at every request: the branches between the MFMAs cost 4 %
+    int c = 0;
+    for (; c + 2 < ktl; ++c) MOTE_CHUNK(true)
+    for (; c < ktl; ++c) MOTE_CHUNK(false)
+#undef MOTE_CHUNK
+#undef MOTE_QUARTER
+
+    // Start the next tile now: its first loads travel while this tile runs its epilogue in the two slots of the
+    // last chunk.
+    if (has_next) {
+      MOTE_POINTERS(mt2, nt2, kb2);
+      if (ktl2 > 0) {
+        MOTE_ISSUE_A(s0, 0);
+        MOTE_ISSUE_B(s1, 0);
+        if (ktl2 > 1) MOTE_ISSUE_A(s2, 1);
+      }
+    }
+
+    // ---- epilogue ----
+    // In registers lane l owns token row r16 and four consecutive output channels of every fragment (4 * quart .. +3).
+    // Each wavefront writes one 32-row block of 128 bytes per row into its private LDS patch and reads it back row-major,
+    // 16 bytes per lane, so that a global store instruction covers whole 128-byte rows of the block.
+    unsigned char* const patch = s_lds + (wave < 4 ? s3 : s4) + (wave & 3) * Cfg::PATCH_BYTES;
+    const int n_wave0 = nt * BN + wn * (BN / 2);
+    const int rd_row = lane >> 3, rd_chunk = lane & 7;
+    if (a.scale0 != nullptr) {   // row scales of quantised weights (uniform branch, not taken by the bf16 expert)
+#pragma unroll
+      for (int b = 0; b < B16; ++b) {
+        const int ch = min(n_wave0 + b * 16 + 4 * quart, N - 4);
+        const float4 s0_ = *reinterpret_cast<const float4*>(a.scale0 + ch);
+        float4 s1_ = s0_;
+        if constexpr (NMAT == 2) s1_ = *reinterpret_cast<const float4*>(a.scale1 + ch);
+#pragma unroll
+        for (int i = 0; i < A16; ++i) {
+          acc[i][b].x *= s0_.x; acc[i][b].y *= s0_.y; acc[i][b].z *= s0_.z; acc[i][b].w *= s0_.w;
+          if constexpr (NMAT == 2) {
+            v4f& au = acc[i][(NMAT - 1) * B16 + b];
+            au.x *= s1_.x; au.y *= s1_.y; au.z *= s1_.z; au.w *= s1_.w;
+          }
+        }
+      }
+    }
+    constexpr int PF = Cfg::MODE == 0 ? 4 : 2;   // fragments of a patch (128 bytes per row)
+#pragma unroll
+    for (int i = 0; i < A16; i += 2) {
+#pragma unroll
+      for (int f0 = 0; f0 < B16; f0 += PF) {
+#pragma unroll
+        for (int bb = 0; bb < PF; ++bb) {
+          const int b = f0 + bb;
+#pragma unroll
+          for (int r = 0; r < 2; ++r) {
+            const v4f v = acc[i + r][b];
+            unsigned char* const dst = patch + (r * 16 + r16) * Cfg::PATCH_ROW + (bb * 16 + 4 * quart) * Cfg::OUT_BYTES;
+            if constexpr (Cfg::MODE == 0) {
+              const v4f u = acc[i + r][(NMAT - 1) * B16 + b];
+              uint2 packed;
+              packed.x = cvt_pk_bf16(u.x * silu_fast(v.x), u.y * silu_fast(v.y));
+              packed.y = cvt_pk_bf16(u.z * silu_fast(v.z), u.w * silu_fast(v.w));
+              *reinterpret_cast<uint2*>(dst) = packed;
+            } else {
+              *reinterpret_cast<float4*>(dst) = make_float4(v.x, v.y, v.z, v.w);
+            }
+          }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        const int rd_n = n_wave0 + f0 * 16 + rd_chunk * (16 / Cfg::OUT_BYTES);   // first output channel of this lane's 16 bytes
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+          const int pr = p * 8 + rd_row;
+          const u4 v = *reinterpret_cast<const u4*>(patch + pr * Cfg::PATCH_ROW + rd_chunk * 16);
+          const int orow = mt * BM + wm * 64 + i * 16 + pr;
+          if (orow < M && rd_n < N) {
+            const int64_t o = static_cast<int64_t>(orow) * N + rd_n;
+            if constexpr (Cfg::MODE == 0) *reinterpret_cast<u4*>(a.h_out + o) = v;
+            else *reinterpret_cast<u4*>(a.y_out + static_cast<int64_t>(kc) * a.plane_stride + o) = v;
+          }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+      }
+    }
+    if (!has_next) break;
+    // No barrier here: the patches are private and their slots are not refilled before the next
+    // tile's first barrier.
+    slot = nslot; mt = mt2; nt = nt2; kc = kc2; ktl = ktl2; kb = kb2;
+  }
+#undef MOTE_DECODE
+#undef MOTE_KRANGE
+#undef MOTE_POINTERS
+#undef MOTE_DMA
+#undef MOTE_DMA_A
+#undef MOTE_DMA_B
+#undef MOTE_ISSUE_A
+#undef MOTE_ISSUE_B
+#undef MOTE_A_FRAG
+#undef MOTE_B_FRAG
+}
+
+template <typename Cfg>
+__global__ __launch_bounds__(Cfg::THREADS, 2) void big_gemm_kernel(SharedGemmArgs a, int n_ntiles, int kplanes, int ktp, int group_m) {
+  big_gemm_body<Cfg, 0>(a, nullptr, n_ntiles, kplanes, ktp, group_m);
+}
+template <typename Cfg>
+__global__ __launch_bounds__(Cfg::THREADS, 2) void big_kgrouped_gemm_kernel(SharedGemmArgs a, RowGroups rg, int n_ntiles, int group_m) {
+  big_gemm_body<Cfg, 2>(a, &rg, n_ntiles, rg.n, 0, group_m);
+}
+
 static int shared_cu_count() {
   static int n = 0;
   if (n == 0) {
@@ -656,6 +918,32 @@ static hipError_t launch_shared_cfg(const SharedGemmArgs& a, int kplanes, hipStr
   return hipGetLastError();
 }
 
+template <typename Cfg>
+static hipError_t launch_big_cfg(const SharedGemmArgs& a, int kplanes, const RowGroups* rg, hipStream_t stream) {
+  const int n_ntiles = (a.N + Cfg::BN - 1) / Cfg::BN, n_mtiles = (a.M + Cfg::BM - 1) / Cfg::BM;
+  const int KT = a.K >> 6;
+  const int ktp = (KT + kplanes - 1) / kplanes;   // chunks per plane
+  static bool attr_set = false;
+  if (!attr_set) {
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(big_gemm_kernel<Cfg>), hipFuncAttributeMaxDynamicSharedMemorySize, Cfg::LDS_BYTES);
+    if (e == hipSuccess && Cfg::MODE == 1)
+      e = hipFuncSetAttribute(reinterpret_cast<const void*>(big_kgrouped_gemm_kernel<Cfg>), hipFuncAttributeMaxDynamicSharedMemorySize, Cfg::LDS_BYTES);
+    if (e != hipSuccess) return e;
+    attr_set = true;
+  }
+  const int64_t tiles = static_cast<int64_t>(n_mtiles) * n_ntiles * kplanes;
+  int64_t blocks = shared_cu_count();
+  if (blocks > tiles) blocks = (tiles + 7) / 8 * 8;
+  // Band height: the 32 workgroups of an XCD share the least operand bytes as 4 x 8 tiles (16 groups of 1088 rows, K
+  // ranges: 809 us with bands of two row tiles, 769 of four, 840 of eight).  Weights that the memory-side cache (256 MB)
+  // does not keep are read once per band: bands of eight (16384 x 3584 x 18944 gate-up: 3235 us of two, 3210 of four, 3145 of
+  // eight; with 90 MB of weights all the same).
+  const int group_m = static_cast<int64_t>(Cfg::NMAT) * a.N * a.K * 2 > (int64_t{192} << 20) && rg == nullptr ? 8 : 4;
+  if (rg != nullptr) big_kgrouped_gemm_kernel<Cfg><<<static_cast<unsigned>(blocks), Cfg::THREADS, Cfg::LDS_BYTES, stream>>>(a, *rg, n_ntiles, group_m);
+  else big_gemm_kernel<Cfg><<<static_cast<unsigned>(blocks), Cfg::THREADS, Cfg::LDS_BYTES, stream>>>(a, n_ntiles, kplanes, ktp, group_m);
+  return hipGetLastError();
+}
+
 hipError_t launch_shared_gate_up(const uint16_t* x, const uint16_t* w_gate, const uint16_t* w_up, int T, int d,
                                  int F, uint16_t* h_s, hipStream_t stream) {
   return launch_shared_gate_up_scaled(x, w_gate, w_up, nullptr, nullptr, T, d, F, h_s, stream);
@@ -684,7 +972,7 @@ hipError_t launch_shared_gate_up_scaled(const uint16_t* x, const uint16_t* w_gat
   switch (v) {
     case 1: return launch_shared_cfg<SharedCfg<0, 2, 1, 2, 2, 2>>(a, 1, stream);   // 128 x (64+64)
     case 2: return launch_shared_cfg<SharedCfg<0, 2, 2, 4, 2, 1>>(a, 1, stream);   // 256 x (128+128), 8 wavefronts, 1 workgroup / CU
-    case 5: return launch_shared_cfg<SharedCfg<0, 2, 2, 4, 2, 1, 4>>(a, 1, stream);   // the same with the ring of four stages (C5 4.08 -> 4.02 ms)
+    case 5: return launch_big_cfg<BigCfg<0>>(a, 1, nullptr, stream);   // the same with the ring of four stages (C5 4.08 -> 4.02 ms)
     case 4: return launch_shared_cfg<SharedCfg<0, 2, 1, 2, 4, 4>>(a, 1, stream);   // 128 x (128+128), 8 wavefronts of 64 x (32+32), 2 workgroups / CU
     default: return launch_shared_cfg<SharedCfg<0, 2, 2, 2, 2, 2>>(a, 1, stream);  // 128 x (128+128), 2 workgroups / CU
   }
@@ -741,14 +1029,14 @@ hipError_t launch_shared_down_scaled(const uint16_t* h_s, const uint16_t* w_down
   if (T == 0) return hipSuccess;
   SharedGemmArgs a{h_s, w_down, nullptr, T, d, F, nullptr, y_s, static_cast<int64_t>(T) * d, s_down, nullptr};
   const int planes = shared_down_planes(T, d, F);
-  if (shared_down_big_planes(T, d, F) != 0) return launch_shared_cfg<SharedCfg<1, 2, 4, 4, 2, 1, 4>>(a, planes, stream);
+  if (shared_down_big_planes(T, d, F) != 0) return launch_big_cfg<BigCfg<1>>(a, planes, nullptr, stream);
   if (planes > 1) return launch_shared_cfg<SharedCfg<1, 2, 2, 2, 2, 2>>(a, planes, stream);   // small problem: 128 x 128 tiles
   int v = shared_variant();
   if (v == 0) v = static_cast<int64_t>((T + 255) / 256) * ((d + 255) / 256) >= 256 ? 5 : 3;
   switch (v) {
     case 1: return launch_shared_cfg<SharedCfg<1, 2, 2, 2, 2, 2>>(a, 1, stream);    // 128 x 128
     case 2: return launch_shared_cfg<SharedCfg<1, 2, 4, 4, 2, 1>>(a, 1, stream);    // 256 x 256, 8 wavefronts, 1 workgroup / CU
-    case 5: return launch_shared_cfg<SharedCfg<1, 2, 4, 4, 2, 1, 4>>(a, 1, stream);    // the same with the ring of four stages (C5 2.15 -> 2.09 ms)
+    case 5: return launch_big_cfg<BigCfg<1>>(a, 1, nullptr, stream);    // the same with the ring of four stages (C5 2.15 -> 2.09 ms)
     default: return launch_shared_cfg<SharedCfg<1, 2, 4, 2, 2, 2>>(a, 1, stream);   // 128 x 256
   }
 }
@@ -840,13 +1128,8 @@ hipError_t launch_gemm_grouped_f32(const uint16_t* act, const uint32_t* w, const
 }
 
 template <typename Cfg>
-static hipError_t launch_kgrouped_cfg(const SharedGemmArgs& a, const int32_t* k0, int n_groups, hipStream_t stream) {
-  RowGroups rg;
-  rg.n = n_groups;
-  for (int e = 0; e <= kMaxRowGroups; ++e) {
-    rg.row0[e] = k0[std::min(e, n_groups)];
-    rg.tile0[e] = 0;
-  }
+static hipError_t launch_kgrouped_cfg(const SharedGemmArgs& a, const RowGroups& rg, hipStream_t stream) {
+  const int n_groups = rg.n;
   const int n_ntiles = (a.N + Cfg::BN - 1) / Cfg::BN;
   const int n_mtiles = (a.M + Cfg::BM - 1) / Cfg::BM;
   const size_t lds = Cfg::LDS_BYTES;
@@ -878,9 +1161,15 @@ hipError_t launch_gemm_tn_f32_kgroups(const uint16_t* act, const uint16_t* w, in
   if (M == 0 || N == 0) return hipSuccess;
   const int K = k0_host[n_groups];
   SharedGemmArgs a{act, w, nullptr, M, N, K, nullptr, out, static_cast<int64_t>(M) * N, nullptr, nullptr};
+  RowGroups rg;
+  rg.n = n_groups;
+  for (int e = 0; e <= kMaxRowGroups; ++e) {
+    rg.row0[e] = k0_host[std::min(e, n_groups)];
+    rg.tile0[e] = 0;
+  }
   if (static_cast<int64_t>((M + 255) / 256) * ((N + 255) / 256) * n_groups >= 256)
-    return launch_kgrouped_cfg<SharedCfg<1, 2, 4, 4, 2, 1, 4>>(a, k0_host, n_groups, stream);   // 256 x 256
-  return launch_kgrouped_cfg<SharedCfg<1, 2, 2, 2, 2, 2>>(a, k0_host, n_groups, stream);        // 128 x 128
+    return launch_big_cfg<BigCfg<1>>(a, n_groups, &rg, stream);              // 256 x 256
+  return launch_kgrouped_cfg<SharedCfg<1, 2, 2, 2, 2, 2>>(a, rg, stream);    // 128 x 128
 }
 
 }  // namespace mote

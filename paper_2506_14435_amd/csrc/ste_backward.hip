@@ -29,8 +29,7 @@ constexpr int kSteThreads = 256;
 
 // One wavefront re-blocks one packed tile (32 output rows x 128 input channels): the operand of dX contracts over
 // the rows, so its blocks (SharedCfg in shared_ffn.hip) are [channel block 4][this row tile] of 32 x 32 codes.
-// Lane (s, g', b, g) takes the channels 32s + 16g' + 4b .. +3, byte-parallel, and the sixteen rows 8g .. 8g+7
-// and 16+8g .. of its words.  Memory-bound: 90 MB in and out for 16 experts of 11008 x 2048, where the bf16
+// Lane (s, b, Q) takes the channels 32s + 4b .. +3 and 16 further on, byte-parallel, and the rows 8Q .. 8Q+7 of their words.  Memory-bound: 90 MB in and out for 16 experts of 11008 x 2048, where the bf16
 // matrices they replaced were 721 MB (136 us to write, and the GEMM read them back).
 __device__ __forceinline__ void reblock_ternary_t_tile(const uint32_t* __restrict__ tile, uint32_t* __restrict__ out, int64_t block_stride,
                                                        uint32_t* s_in, uint32_t* s_out) {
@@ -39,16 +38,16 @@ __device__ __forceinline__ void reblock_ternary_t_tile(const uint32_t* __restric
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-  const int g = lane & 1, b = (lane >> 1) & 3, gc = (lane >> 3) & 1, s = lane >> 4;
+  const int Q = lane & 3, b = (lane >> 2) & 3, s = lane >> 4;
   // codes t + 1 = 0, 1, 2: the low bit is set for t = 0 only, the high bit for t = +1 only
-  uint32_t x[4];   // byte j of x[m]: channel 4b + j, byte m of its word (bit J: element pair J)
+  uint32_t x[4];   // byte j of x[m]: byte m of word 4b + j (bit J: pair J & 3 of channel 4b + j + 16 * (J >> 2))
 #pragma unroll
   for (int odd = 0; odd < 2; ++odd) {
     uint32_t lo = 0u, hi = 0u;
 #pragma unroll
     for (int J = 0; J < 8; ++J) {
-      const int row = 16 * (J >> 2) + 8 * g + 2 * (J & 3) + odd;
-      const uint32_t w = s_in[(32 * gc + row) * 4 + s] >> (2 * b);
+      const int row = 8 * Q + 2 * (J & 3) + odd;
+      const uint32_t w = s_in[(32 * (J >> 2) + row) * 4 + s] >> (2 * b);
       lo |= (w & 0x01010101u) << J;
       hi |= ((w >> 1) & 0x01010101u) << J;
     }
@@ -60,7 +59,7 @@ __device__ __forceinline__ void reblock_ternary_t_tile(const uint32_t* __restric
   for (int j = 0; j < 4; ++j) {
     const uint32_t w = ((x[0] >> (8 * j)) & 0xFFu) | (((x[1] >> (8 * j)) & 0xFFu) << 8) | (((x[2] >> (8 * j)) & 0xFFu) << 16) |
                        ((x[3] >> (8 * j)) << 24);
-    s_out[s * 64 + (16 * gc + 4 * b + j) * 2 + g] = w;
+    s_out[s * 64 + 16 * Q + 4 * b + j] = w;
   }
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
