@@ -70,7 +70,7 @@ __device__ __forceinline__ int quant_i8(float x, float s) {
 }
 
 // One 32-bit word of the packed ternary format = 16 codes t+1, code i at bit 8*(i%4) + 2*(i/4):
-// (w >> 2j) & 0x03030303 are the four int8 operand registers of one v_mfma_i32_32x32x32_i8.
+// (w >> 2j) & 0x03030303 are the four int8 operand registers of one v_mfma_i32_32x32x32_i8 or v_mfma_i32_16x16x64_i8.
 __device__ __forceinline__ v4i unpack_codes(uint32_t w) {
   v4i b;
   b.x = static_cast<int>(w & 0x03030303u);

@@ -11,15 +11,21 @@
 // into LDS (global_load_lds), 16-byte chunks XOR-swizzled by row so that ds_read_b128 of
 // 32 consecutive rows is conflict free; three stages, requested two K steps ahead.
 // Packed weights take the same road (global -> LDS directly, ring of three stages) and stay
-// packed in LDS: a tile of 32 rows x 128 channels is 1 KiB = one 16-byte LDS read per lane,
+// packed in LDS: a tile of 32 rows x 128 channels is 1 KiB = two 8-byte LDS reads per lane,
 // each 32-bit word expands in registers with (w >> 2j) & 0x03030303 into the four operand
-// registers of one v_mfma_i32_32x32x32_i8.  The codes are t+1, so the accumulator holds
+// registers of one v_mfma_i32_16x16x64_i8.  The codes are t+1, so the accumulator holds
 // sum (t+1) q; it starts at minus the row sum of q.
 //
-// MFMA operand mapping (32x32x32 i8): first operand = weights, lane l supplies output
-// channel l%32 and 16 consecutive input channels of half l/32; second operand =
-// activations, lane l supplies dispatch row l%32 and the same 16 channels.  Result register
-// v of lane l is output channel 8*(v/4) + 4*(l/32) + v%4 of dispatch row l%32.
+// MFMA operand mapping (16x16x64 i8): first operand = weights, lane l supplies output
+// channel l%16 and 16 consecutive input channels; second operand = activations, lane l supplies
+// dispatch row l%16 and the same 16 channels (which 16 of a 128-channel step a quarter l/16 takes is free as long as
+// both operands agree; it follows the packed format, see w_rd below).  Result register v of lane l is output channel
+// 4*(l/16) + v of dispatch row l%16.
+//
+// Why 16x16 and not 32x32 tiles: the chip is power-limited inside these GEMMs.  Register-only loops over random operands
+// on all CUs sustain 3.99 POP/s with v_mfma_i32_16x16x64_i8 and 3.37 with v_mfma_i32_32x32x32_i8, fed from LDS 3.49 and
+// 2.97.  On the small tiles (the same loop otherwise; 16 experts, top-2): T = 8192 at the 3B width gate-up 664 -> 619 us,
+// down 329 -> 298; T = 16384 at the 7B width, loads of 10x spread, 3560 -> 3217 and 1710 -> 1555 (2.87 POP/s).
 //
 // Epilogue: every wavefront transposes its result fragments through a private LDS patch so
 // that a global store instruction covers whole rows of a 32-row block.
@@ -65,16 +71,17 @@ __device__ unsigned long long g_trace[1024 * 32 * 8];
 #define MOTE_TP(k_)
 #endif
 
-// LDS tile geometry: 128-byte rows of eight 16-byte chunks, chunk index XOR-swizzled with
-// bits 1..3 of the row.  Two consecutive rows span the 64 banks once, so 16 lanes that read
-// the same chunk of 16 consecutive rows (one quarter of a ds_read_b128) hit 16 distinct
-// 4-bank groups: conflict free (measured 2x faster than swizzling with row bits 0..2).
-__device__ __forceinline__ int lds_a_offset(int row, int chunk) { return row * 128 + ((chunk ^ ((row >> 1) & 7)) << 4); }
+// LDS tile geometry: 128-byte rows of eight 16-byte chunks, chunk index XOR-swizzled with bits 1..3 of the row, bit 3
+// also into bit 2's place below.  Two consecutive rows span the 64 banks once, so 16 lanes that read the same chunk of 16
+// consecutive rows (one quarter of a ds_read_b128) hit 16 distinct 4-bank groups: conflict free (measured 2x faster
+// than swizzling with row bits 0..2).
+__device__ __forceinline__ int lds_a_swizzle(int row) { const int t = (row >> 1) & 7; return t ^ ((t >> 1) & 2); }
+__device__ __forceinline__ int lds_a_offset(int row, int chunk) { return row * 128 + ((chunk ^ lds_a_swizzle(row)) << 4); }
 
-// One 128-channel K step of a wavefront is four 32-channel sub-steps; each reads BM_W
-// activation fragments from LDS and, per weight fragment, unpacks 16 codes per lane and feeds
-// BM_W MFMAs (MOTE_KSTEP in the kernel).  The global loads of a later K step are spread over
-// the four sub-steps: issued in one burst right after the barrier, eight wavefronts x eight
+// One 128-channel K step of a wavefront is four quarters, half of its channels x half of its weight
+// fragments each; a quarter unpacks 16 codes per lane and fragment and feeds 2 BM_W MFMAs per
+// fragment.  The global loads of a later K step are spread over
+// the four quarters: issued in one burst right after the barrier, eight wavefronts x eight
 // 1-KiB loads fill the CU's vector-memory queue and every wavefront stalls in issue (measured:
 // about 800 cycles per K step) before it reaches its first MFMA.
 constexpr int kFixedShares = 1 << 20;   // n_static from which every tile of a workgroup is fixed
@@ -106,8 +113,13 @@ __global__ __launch_bounds__(Cfg::THREADS, Cfg::MIN_BLOCKS) void routed_gemm_ker
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wave_u = __builtin_amdgcn_readfirstlane(wave);
   const int wm = wave % Cfg::WAVES_M, wn = wave / Cfg::WAVES_M;
-  const int r32 = lane & 31, g = lane >> 5;
-  const int a_row_base = wm * BM_W * 32 + r32;
+  const int r16 = lane & 15, quart = lane >> 4;
+  constexpr int A16 = 2 * BM_W, B16 = 2 * BN_W, NF = NMAT * B16;   // 16-row / 16-channel fragments of a wavefront
+  // This lane's operand bytes in a stage.  Quarter q of the wavefront takes, in MFMA j = 0, 1 of a K step, the channels
+  // 32 (2 (q & 1) + j) + 16 (q / 2) .. +15 of its row: word 2 (q & 1) + j of 16-byte unit 32 (q / 2) + row of a packed tile,
+  // so one 8-byte read brings both MFMAs' words (and the reads of 32 lanes cover the banks once)
+  const int a_rd = lds_a_offset(wm * BM_W * 32 + r16, 4 * (quart & 1) + (quart >> 1));   // j = 1: ^ 32
+  const int w_rd = (32 * (quart >> 1) + r16) * 16 + (quart & 1) * 8;
   const int64_t expert_words = static_cast<int64_t>(N) * K / 16;
   // LDS byte address of the stage area (what M0 takes for a direct-to-LDS load)
   const uint32_t lds0 = (uint32_t)(uintptr_t)((__attribute__((address_space(3))) unsigned char*)s_lds);
@@ -253,7 +265,7 @@ __global__ __launch_bounds__(Cfg::THREADS, Cfg::MIN_BLOCKS) void routed_gemm_ker
   uint32_t w_soff[W_PER_WAVE];             // uniform: byte offset of that fragment's first tile in the plane
   uint32_t a_off[Cfg::A_PASSES];           // byte offset of this lane's 16 bytes inside q, K step 0 of the plane
   const uint32_t w_lane = lane * 16;
-  const uint32_t a_chunk = static_cast<uint32_t>(((tid & 7) ^ ((tid >> 4) & 7)) << 4);
+  const uint32_t a_chunk = static_cast<uint32_t>(((tid & 7) ^ lds_a_swizzle(tid >> 3)) << 4);
   int src_row[Cfg::A_PASSES];   // row of q (gathered) per loader pass, next tile
   int meta_row = 0;             // row of q whose beta (wavefronts 0-1) or row sum (2-3) this lane requests
   int mt, nt, kc, expert, row0, rows, ktl, ktp_t, planes_t;   // ktp_t: K steps per plane of this tile, planes_t: its planes
@@ -380,6 +392,18 @@ __global__ __launch_bounds__(Cfg::THREADS, Cfg::MIN_BLOCKS) void routed_gemm_ker
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
   }
 
+  // (3) start the next tile now: its first two K steps travel while this tile runs its
+  // epilogue.  The stage of the last K step (now st_nx2) is free until the next tile's
+  // first barrier: it holds the epilogue patches.
+#define MOTE_START_NEXT                                                                            \
+    if (has_next) {                                                                                \
+      ktl2 = min(ktp2, KT - kc2 * ktp2);                                                           \
+      MOTE_POINTERS(expert2, nt2, kc2, ktp2);                                                      \
+      MOTE_DMA_META(par ^ 1);                                                                      \
+      MOTE_ISSUE_STEP(st_cur, 0);                                                                  \
+      if (ktl2 > 1) MOTE_ISSUE_STEP(st_nxt, 1);                                                    \
+    }
+
 #ifdef MOTE_TRACE
   int tile_it = 0;
 #endif
@@ -404,84 +428,74 @@ __global__ __launch_bounds__(Cfg::THREADS, Cfg::MIN_BLOCKS) void routed_gemm_ker
     const float al0 = load_uniform(a.alpha + expert * 3 + (Cfg::MODE == 0 ? 0 : 2));
     const float al1 = Cfg::MODE == 0 ? load_uniform(a.alpha + expert * 3 + 1) : 0.0f;
 
-    // Accumulators start at -rowsum(q): the stored codes are t+1, so sum (t+1) q - sum q = sum t q.
-    v16i acc[NMAT][BM_W][BN_W];
-#pragma unroll
-    for (int i = 0; i < BM_W; ++i) {
-      const int nrs = kc == 0 ? -s_rs[par][wm * BM_W * 32 + i * 32 + r32] : 0;   // the correction enters plane 0 only
-#pragma unroll
-      for (int m = 0; m < NMAT; ++m)
-#pragma unroll
-        for (int f = 0; f < BN_W; ++f)
-#pragma unroll
-          for (int v = 0; v < 16; ++v) acc[m][i][f][v] = nrs;
-    }
     // row gather of the next tile: the indices are in registers when the K loop ends
     if (has_next) MOTE_GATHER(row02, rows2);
     // Rows of this wavefront's block that exist: the last row tile of an expert is half empty on
-    // average, and a 32-row fragment without rows is neither read nor contracted (its MFMA slots go
+    // average, and a pair of 16-row fragments without rows is neither read nor contracted (its MFMA slots go
     // to the other wavefronts of the SIMD).  Wavefront-uniform, so these are scalar branches.
     const int rows_w = SKIP_ != 0 ? __builtin_amdgcn_readfirstlane(rows - (wave_u % Cfg::WAVES_M) * BM_W * 32) : BM_W * 32;
 
     // (2) K loop.  K step kt contracts stage st_cur while the loads of kt+2 are issued, one
-    // quarter of them per 32-channel sub-step (a burst of loads right after the barrier fills
+    // quarter of them per quarter of the MFMAs (a burst of loads right after the barrier fills
     // the CU's vector-memory queue and stalls every wavefront in issue), into the stage that the
     // barrier at the end of step kt-1 released.
-    const int ktl_mm = (SKIP_ == 1 && rows_w <= 0) ? 0 : ktl;   // a wavefront without rows contracts nothing ...
-    for (int kt = 0; kt < ktl - ktl_mm; ++kt) {                  // ... it only issues its share of the loads and meets the barriers
-      const bool pf = kt + 2 < ktl;
-      if (pf) {
+    int ktl2 = ktl;
+    // Accumulators start at -rowsum(q): the stored codes are t+1, so sum (t+1) q - sum q = sum t q.
+    v4i acc[A16][NF];   // dispatch rows 16i .., channels of fragment n (gate first, then up)
 #pragma unroll
-        for (int p = 0; p < Cfg::A_PASSES; ++p) MOTE_DMA_A(st_nx2, kt + 2, p);
+    for (int i = 0; i < A16; ++i) {
+      const int nrs = kc == 0 ? -s_rs[par][wm * BM_W * 32 + i * 16 + r16] : 0;   // the correction enters plane 0 only
 #pragma unroll
-        for (int i = 0; i < W_PER_WAVE; ++i) MOTE_DMA_W(st_nx2, kt + 2, i);
-      }
-      MOTE_WAIT_BARRIER(pf);
-      const int t = st_cur; st_cur = st_nxt; st_nxt = st_nx2; st_nx2 = t;
+      for (int n = 0; n < NF; ++n) acc[i][n] = v4i{nrs, nrs, nrs, nrs};
     }
-    for (int kt = 0; kt < ktl_mm; ++kt) {
+    for (int kt = 0; kt < ktl; ++kt) {
       const bool pf = kt + 2 < ktl;
       const unsigned char* const st = s_lds + st_cur;
-      u4 wf[NMAT][BN_W];
-#pragma unroll
-      for (int m = 0; m < NMAT; ++m)
-#pragma unroll
-        for (int f = 0; f < BN_W; ++f)
-          wf[m][f] = *reinterpret_cast<const u4*>(st + A_BYTES + (m * NB + wn * BN_W + f) * 1024 + w_lane);
-      v4i af[2][BM_W];
-#pragma unroll
-      for (int i = 0; i < BM_W; ++i)
-        if (!SKIP || i * 32 < rows_w) af[0][i] = *reinterpret_cast<const v4i*>(st + lds_a_offset(a_row_base + i * 32, g));
-#pragma unroll
-      for (int s = 0; s < 4; ++s) {
-        if (pf) {   // quarter s of the loads of K step kt+2
-#pragma unroll
-          for (int p = 0; p < Cfg::A_PASSES; ++p)
-            if ((p & 3) == s) MOTE_DMA_A(st_nx2, kt + 2, p);
-#pragma unroll
-          for (int i = 0; i < W_PER_WAVE; ++i)
-            if (((i + 1) & 3) == s) MOTE_DMA_W(st_nx2, kt + 2, i);
-        }
-        if (s < 3) {
-#pragma unroll
-          for (int i = 0; i < BM_W; ++i)
-            if (!SKIP || i * 32 < rows_w)
-              af[(s + 1) & 1][i] = *reinterpret_cast<const v4i*>(st + lds_a_offset(a_row_base + i * 32, 2 * (s + 1) + g));
-        }
-        if (!SKIP || rows_w > 0) {
-#pragma unroll
-          for (int m = 0; m < NMAT; ++m)
-#pragma unroll
-            for (int f = 0; f < BN_W; ++f) {
-              const v4i bf = unpack_codes(wf[m][f][s]);
-#pragma unroll
-              for (int i = 0; i < BM_W; ++i)
-                if (!SKIP || i * 32 < rows_w)
-                  acc[m][i][f] = __builtin_amdgcn_mfma_i32_32x32x32_i8(bf, af[s & 1][i], acc[m][i][f], 0, 0, 0);
-            }
-        }
-        __builtin_amdgcn_sched_barrier(0);  // keep each quarter's loads with its quarter
+      // quarter s_ of the loads of K step kt+2
+#define MOTE_LOAD_QUARTER(s_)                                                                      \
+      if (pf) {                                                                                    \
+        _Pragma("unroll") for (int p = 0; p < Cfg::A_PASSES; ++p)                                  \
+          if ((p & 3) == (s_)) MOTE_DMA_A(st_nx2, kt + 2, p);                                      \
+        _Pragma("unroll") for (int i = 0; i < W_PER_WAVE; ++i)                                     \
+          if (((i + 1) & 3) == (s_)) MOTE_DMA_W(st_nx2, kt + 2, i);                                \
       }
+      // Where the wavefront's rows are tested: around the whole step, or, with 128 registers (the allocator then copies and
+      // spills accumulators behind the loop), around the MFMAs of every quarter.
+      constexpr bool PER_QUARTER = Cfg::MIN_BLOCKS >= 4;
+      if (PER_QUARTER || SKIP_ == 0 || rows_w > 0) {
+        // the packed words of both 64-channel halves of the step, and the activations of the first
+        uint2 wf[NF];
+#pragma unroll
+        for (int n = 0; n < NF; ++n)
+          wf[n] = *reinterpret_cast<const uint2*>(st + A_BYTES + ((n / B16) * NB + wn * BN_W + (n % B16) / 2) * 1024 + (n & 1) * 256 + w_rd);
+        v4i af[A16];
+#pragma unroll
+        for (int i = 0; i < A16; ++i)
+          if (!SKIP || (i & ~1) * 16 < rows_w) af[i] = *reinterpret_cast<const v4i*>(st + a_rd + i * 2048);
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {   // quarter s: half s / 2 of the channels, half s % 2 of the weight fragments
+          MOTE_LOAD_QUARTER(s)
+          if (!PER_QUARTER || SKIP_ == 0 || rows_w > 0) {
+            v4i bf[NF / 2];
+#pragma unroll
+            for (int n = 0; n < NF / 2; ++n) bf[n] = unpack_codes(s < 2 ? wf[(s & 1) * (NF / 2) + n].x : wf[(s & 1) * (NF / 2) + n].y);
+#pragma unroll
+            for (int i = 0; i < A16; ++i)
+              if (!SKIP || (i & ~1) * 16 < rows_w) {
+#pragma unroll
+                for (int n = 0; n < NF / 2; ++n)
+                  acc[i][(s & 1) * (NF / 2) + n] = __builtin_amdgcn_mfma_i32_16x16x64_i8(bf[n], af[i], acc[i][(s & 1) * (NF / 2) + n], 0, 0, 0);
+                // the second half's activations, a fragment behind its last MFMA of the first half
+                if (s == 1) af[i] = *reinterpret_cast<const v4i*>(st + (a_rd ^ 32) + i * 2048);
+              }
+          }
+          __builtin_amdgcn_sched_barrier(0);  // keep each quarter's loads with its quarter
+        }
+      } else {   // a wavefront without rows contracts nothing: it issues its share of the loads and meets the barriers
+#pragma unroll
+        for (int s = 0; s < 4; ++s) MOTE_LOAD_QUARTER(s)
+      }
+#undef MOTE_LOAD_QUARTER
       // K step kt+1 landed everywhere (kt+2 stays in flight); after the last step: every
       // wavefront has read its last stage
       MOTE_WAIT_BARRIER(pf);
@@ -489,17 +503,7 @@ __global__ __launch_bounds__(Cfg::THREADS, Cfg::MIN_BLOCKS) void routed_gemm_ker
     }
 
     MOTE_TP(2)
-    // (3) start the next tile now: its first two K steps travel while this tile runs its
-    // epilogue.  The stage of the last K step (now st_nx2) is free until the next tile's
-    // first barrier: it holds the epilogue patches.
-    int ktl2 = ktl;
-    if (has_next) {
-      ktl2 = min(ktp2, KT - kc2 * ktp2);
-      MOTE_POINTERS(expert2, nt2, kc2, ktp2);
-      MOTE_DMA_META(par ^ 1);
-      MOTE_ISSUE_STEP(st_cur, 0);
-      if (ktl2 > 1) MOTE_ISSUE_STEP(st_nxt, 1);
-    }
+    MOTE_START_NEXT
 
     MOTE_TP(3)
     // ---- epilogue ----
@@ -520,50 +524,49 @@ __global__ __launch_bounds__(Cfg::THREADS, Cfg::MIN_BLOCKS) void routed_gemm_ker
     // and not held in registers across the K loop (10-30 registers per configuration).
     int lane_e;
     asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(lane_e));
-    const int r32e = lane_e & 31, ge = lane_e >> 5;
+    const int r16e = lane_e & 15, qe = lane_e >> 4;
     unsigned char* const patch = s_lds + st_nx2 + wave * Cfg::PATCH_BYTES;
     const int rd_row = lane_e / LANES_PER_ROW, rd_chunk = lane_e % LANES_PER_ROW;
 #pragma unroll
     for (int i = 0; i < BM_W; ++i) {
       if ((SKIP && i * 32 >= rows_w) || (SKIP_ == 1 && rows_w <= 0)) continue;   // nothing to store
-      const int rl = wm * BM_W * 32 + i * 32 + r32e;
-      float sg = 0.0f, su = 0.0f;
+      float sg[2] = {0.0f, 0.0f}, su[2] = {0.0f, 0.0f};
       if constexpr (Cfg::MODE == 0) {
-        const float sx = s_beta[par][rl] / 127.0f;
-        sg = sx * al0;
-        su = sx * al1;
+#pragma unroll
+        for (int r = 0; r < 2; ++r) {
+          const float sx = s_beta[par][wm * BM_W * 32 + i * 32 + r * 16 + r16e] / 127.0f;
+          sg[r] = sx * al0;
+          su[r] = sx * al1;
+        }
       }
 #pragma unroll
       for (int f0 = 0; f0 < BN_W; f0 += PATCH_F) {
 #pragma unroll
-        for (int ff = 0; ff < PATCH_F; ++ff) {
-          const int f = f0 + ff;
+        for (int bb = 0; bb < 2 * PATCH_F; ++bb) {
+          const int n = 2 * f0 + bb;
+          const int pcol = bb * 16 + 4 * qe;             // channel inside the patch row
+          const int col = f0 * 32 + pcol;                // channel inside the wavefront's block
 #pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const int pcol = ff * 32 + 8 * q + 4 * ge;      // channel inside the patch row
-            const int col = f0 * 32 + pcol;                // channel inside the wavefront's block
+          for (int r = 0; r < 2; ++r) {
+            const v4i d0 = acc[2 * i + r][n];
+            unsigned char* const dst = patch + (r * 16 + r16e) * PATCH_ROW + pcol * Cfg::OUT_BYTES;
             if constexpr (Cfg::MODE == 0) {
+              const v4i d1 = acc[2 * i + r][(NMAT - 1) * B16 + n];
               float hv[4];
 #pragma unroll
-              for (int j = 0; j < 4; ++j)
-                hv[j] = (static_cast<float>(acc[1][i][f][4 * q + j]) * su) *
-                        silu_fast(static_cast<float>(acc[0][i][f][4 * q + j]) * sg);
+              for (int j = 0; j < 4; ++j) hv[j] = (static_cast<float>(d1[j]) * su[r]) * silu_fast(static_cast<float>(d0[j]) * sg[r]);
               uint2 packed;
               packed.x = cvt_pk_bf16(hv[0], hv[1]);
               packed.y = cvt_pk_bf16(hv[2], hv[3]);
-              *reinterpret_cast<uint2*>(patch + r32e * PATCH_ROW + pcol * 2) = packed;
+              *reinterpret_cast<uint2*>(dst) = packed;
+              const int rl = wm * BM_W * 32 + i * 32 + r * 16 + r16e;
               if ((a.tap_gate != nullptr || a.tap_up != nullptr) && rl < rows && n_wave0 + col < N) {   // parity taps (tests only), each optional
                 const int64_t o = static_cast<int64_t>(row0 + rl) * N + n_wave0 + col;
-                if (a.tap_gate != nullptr)
-                  *reinterpret_cast<int4*>(a.tap_gate + o) = make_int4(acc[0][i][f][4 * q], acc[0][i][f][4 * q + 1],
-                                                                       acc[0][i][f][4 * q + 2], acc[0][i][f][4 * q + 3]);
-                if (a.tap_up != nullptr)
-                  *reinterpret_cast<int4*>(a.tap_up + o) = make_int4(acc[1][i][f][4 * q], acc[1][i][f][4 * q + 1],
-                                                                     acc[1][i][f][4 * q + 2], acc[1][i][f][4 * q + 3]);
+                if (a.tap_gate != nullptr) *reinterpret_cast<v4i*>(a.tap_gate + o) = d0;
+                if (a.tap_up != nullptr) *reinterpret_cast<v4i*>(a.tap_up + o) = d1;
               }
             } else {
-              *reinterpret_cast<int4*>(patch + r32e * PATCH_ROW + pcol * 4) = make_int4(
-                  acc[0][i][f][4 * q], acc[0][i][f][4 * q + 1], acc[0][i][f][4 * q + 2], acc[0][i][f][4 * q + 3]);
+              *reinterpret_cast<v4i*>(dst) = d0;
             }
           }
         }
@@ -621,6 +624,7 @@ __global__ __launch_bounds__(Cfg::THREADS, Cfg::MIN_BLOCKS) void routed_gemm_ker
 #undef MOTE_DMA_W
 #undef MOTE_ISSUE_STEP
 #undef MOTE_WAIT_BARRIER
+#undef MOTE_START_NEXT
 }
 
 #ifdef MOTE_TRACE
