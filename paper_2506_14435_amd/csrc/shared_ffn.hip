@@ -588,17 +588,24 @@ __global__ __launch_bounds__(Cfg::THREADS, Cfg::MIN_BLOCKS) void kgrouped_gemm_k
 // 591 -> 511 us (1.44 PFLOP/s), down 314 -> 250 (1.48); 16384 x 3584 x 18944 3861 -> 3145, 1995 -> 1612.  What bounds it is
 // power: with operands of zeros the first takes 374 us at 2.4 GHz, with random ones the chip clocks at 1.75 GHz.
 //
-// GROUPED: 0 plain, 2 K ranges (as above).
-template <int MODE_>
+// GROUPED: 0 plain, 1 row groups, 2 K ranges (as above).
+// TERN: weights as 2-bit codes in the blocks described at SharedCfg, unpacked in registers (eight vector instructions per
+// four MFMAs).  The weights of a chunk are 4 KiB, so the ring is four whole stages (A, then weights) and the loads run
+// three chunks ahead; the fragments of a half chunk are read during the half before it, into the other one of two
+// register sets, and the barrier stands in the middle of the second half.
+template <int MODE_, bool TERN_ = false>
 struct BigCfg {
+  static constexpr bool TERN = TERN_;
   static constexpr int MODE = MODE_;   // 0 gate-up, 1 down
   static constexpr int NMAT = MODE_ == 0 ? 2 : 1;
   static constexpr int BM = 256, BN = 256 / NMAT, WAVES = 8, THREADS = 512;
   static constexpr int A16 = 4, NB = 8, B16 = NB / NMAT, HB = NB / 2;   // 16-row and 16-channel fragments of a wavefront
-  static constexpr int SLOT = 32768, LDS_BYTES = 5 * SLOT;
+  static constexpr int SLOT = 32768, STAGE = SLOT + 4096;   // STAGE: ternary weights
+  static constexpr int LDS_BYTES = TERN_ ? 4 * STAGE : 5 * SLOT;
   static constexpr int OUT_BYTES = MODE_ == 0 ? 2 : 4;
   static constexpr int PATCH_ROW = 128 + 16, PATCH_BYTES = 32 * PATCH_ROW;   // epilogue: 32 rows of 128 bytes per wavefront
-  static_assert(4 * PATCH_BYTES <= SLOT, "the patches of four wavefronts fit a free slot");
+  static_assert(4 * PATCH_BYTES <= SLOT && 8 * PATCH_BYTES <= STAGE, "the patches fit two free slots / one free stage");
+  static_assert(!TERN_ || MODE_ == 1, "ternary weights: one matrix");
 };
 
 template <typename Cfg, int GROUPED>
@@ -620,7 +627,8 @@ __device__ __forceinline__ void big_gemm_body(const SharedGemmArgs& a, const Row
 
   // tile order: as in shared_gemm_body
   n_ntiles *= kplanes;
-  const int n_mtiles = (M + BM - 1) / BM;
+  int n_mtiles = (M + BM - 1) / BM;
+  if constexpr (GROUPED == 1) n_mtiles = rg->tile0[rg->n];
   const int xcd = blockIdx.x & 7;
   const bool split_n = n_ntiles >= 16;
   const int xcd_ntiles = split_n ? (n_ntiles - xcd + 7) >> 3 : n_ntiles;
@@ -642,7 +650,7 @@ __device__ __forceinline__ void big_gemm_body(const SharedGemmArgs& a, const Row
     return r;
   };
   const v4i rsrc_a = make_rsrc(a.act, static_cast<int64_t>(M) * K * 2);
-  const v4i rsrc_b0 = make_rsrc(a.w0, static_cast<int64_t>(N) * K * 2);
+  const v4i rsrc_b0 = make_rsrc(a.w0, Cfg::TERN ? static_cast<int64_t>(GROUPED == 1 ? rg->n : 1) * N * K / 4 : static_cast<int64_t>(N) * K * 2);
   const v4i rsrc_b1 = make_rsrc(NMAT == 2 ? a.w1 : a.w0, static_cast<int64_t>(N) * K * 2);
   // lane l of a load lands at byte 16*l of a 1-KiB block = tile row l/8, physical chunk l%8; pass p covers the tile
   // rows 64p + 8 * wavefront ..
@@ -650,7 +658,10 @@ __device__ __forceinline__ void big_gemm_body(const SharedGemmArgs& a, const Row
   const uint32_t ld_chunk = static_cast<uint32_t>(((lane & 7) ^ ((ld_row >> 1) & 7)) << 4);
   uint32_t a_off[4], b_off[4];   // byte offsets of this lane's 16 bytes, chunk 0 of the plane
   int mt, nt, kc, ktl;
-  int s0 = 0, s1 = SLOT, s2 = 2 * SLOT, s3 = 3 * SLOT, s4 = 4 * SLOT;   // slots of A, B of chunk c, A, B of chunk c+1, A of chunk c+2
+  int mrow, mend = M, grp = 0;   // first row of the tile, one past the last row it may store, its group (0 without groups)
+  // slots of A, B of chunk c, A, B of chunk c+1, A of chunk c+2; ternary weights: stages of the chunks c .. c+3
+  constexpr int PITCH = Cfg::TERN ? Cfg::STAGE : SLOT;
+  int s0 = 0, s1 = PITCH, s2 = 2 * PITCH, s3 = 3 * PITCH, s4 = 4 * PITCH;
 
 #define MOTE_DECODE(slot_, mt_, nt_, kc_)                                       \
   {                                                                             \
@@ -674,12 +685,30 @@ __device__ __forceinline__ void big_gemm_body(const SharedGemmArgs& a, const Row
       ktl_ = min(ktp, KT - (kc_) * ktp);                                        \
     }                                                                           \
   }
-#define MOTE_POINTERS(mt_, nt_, kb_)                                                               \
+  // where row tile mt_ starts and ends (uniform; the group is found by walking the table)
+#define MOTE_ROWS(mt_, mrow_, mend_, grp_)                                      \
+  {                                                                             \
+    if constexpr (GROUPED == 1) {                                               \
+      int e_ = 0;                                                               \
+      while (e_ + 1 < rg->n && rg->tile0[e_ + 1] <= (mt_)) ++e_;                \
+      grp_ = e_;                                                                \
+      mrow_ = rg->row0[e_] + ((mt_) - rg->tile0[e_]) * BM;                      \
+      mend_ = rg->row0[e_ + 1];                                                 \
+    } else {                                                                    \
+      mrow_ = (mt_) * BM;                                                       \
+    }                                                                           \
+  }
+#define MOTE_POINTERS(mrow_, grp_, nt_, kb_)                                                       \
   {                                                                                                \
     const uint32_t k0_ = (kb_) + ld_chunk;                                                         \
     _Pragma("unroll") for (int p = 0; p < 4; ++p) {                                                \
-      a_off[p] = static_cast<uint32_t>(min((mt_) * BM + p * 64 + ld_row, M - 1)) * static_cast<uint32_t>(K) * 2u + k0_; \
-      b_off[p] = static_cast<uint32_t>(min((nt_) * BN + (p * 64) % BN + ld_row, N - 1)) * static_cast<uint32_t>(K) * 2u + k0_; \
+      a_off[p] = static_cast<uint32_t>(min((mrow_) + p * 64 + ld_row, M - 1)) * static_cast<uint32_t>(K) * 2u + k0_; \
+      if constexpr (!Cfg::TERN)                                                                    \
+        b_off[p] = static_cast<uint32_t>(min((nt_) * BN + (p * 64) % BN + ld_row, N - 1)) * static_cast<uint32_t>(K) * 2u + k0_; \
+    }                                                                                              \
+    if constexpr (Cfg::TERN) {                                                                     \
+      const int blk_ = min((nt_) * (BN / 32) + wave_u, (N >> 5) - 1) + (grp_) * (N >> 5);          \
+      b_off[0] = static_cast<uint32_t>(blk_) * static_cast<uint32_t>(K) * 8u + (kb_) * 4u + lane * 4u; \
     }                                                                                              \
   }
   // one 16-byte-per-lane direct load of pass p_ of chunk ks_ (M0: see ternary_gemm.hip)
@@ -689,6 +718,22 @@ __device__ __forceinline__ void big_gemm_body(const SharedGemmArgs& a, const Row
 #define MOTE_DMA_A(slot_, ks_, p_) MOTE_DMA(lds0 + (slot_) + ((p_) * 64 + wave_u * 8) * 128, a_off[p_], rsrc_a, (ks_) * 128)
 #define MOTE_DMA_B(slot_, ks_, p_) \
   MOTE_DMA(lds0 + (slot_) + ((p_) * 64 + wave_u * 8) * 128, b_off[p_], (((p_) * 64) / BN == 0 ? rsrc_b0 : rsrc_b1), (ks_) * 128)
+  // ternary: half h_ of the chunk of this wavefront's block of 32 channels
+#define MOTE_DMA_W(stage_, ks_, h_)                                                                \
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, %3 offen lds"             \
+               :: "s"(lds0 + (stage_) + SLOT + (h_) * 2048 + wave_u * 256), "v"(b_off[0]), "s"(rsrc_b0), "s"((ks_) * 512 + (h_) * 256) : "memory")
+#define MOTE_ISSUE_STAGE(stage_, ks_) { MOTE_ISSUE_A(stage_, ks_) MOTE_DMA_W(stage_, ks_, 0); MOTE_DMA_W(stage_, ks_, 1); }
+  // the first loads of a tile of ktl_ chunks
+#define MOTE_START(ktl_)                                                                           \
+  if constexpr (Cfg::TERN) {                                                                       \
+    if ((ktl_) > 0) MOTE_ISSUE_STAGE(s0, 0)                                                        \
+    if ((ktl_) > 1) MOTE_ISSUE_STAGE(s1, 1)                                                        \
+    if ((ktl_) > 2) MOTE_ISSUE_STAGE(s2, 2)                                                        \
+  } else if ((ktl_) > 0) {                                                                         \
+    MOTE_ISSUE_A(s0, 0);                                                                           \
+    MOTE_ISSUE_B(s1, 0);                                                                           \
+    if ((ktl_) > 1) MOTE_ISSUE_A(s2, 1);                                                           \
+  }
 #define MOTE_ISSUE_A(slot_, ks_) { _Pragma("unroll") for (int p = 0; p < 4; ++p) MOTE_DMA_A(slot_, ks_, p); }
 #define MOTE_ISSUE_B(slot_, ks_) { _Pragma("unroll") for (int p = 0; p < 4; ++p) MOTE_DMA_B(slot_, ks_, p); }
 #define MOTE_A_FRAG(slot_, h_, i_) *reinterpret_cast<const bf16x8*>(s_lds + (slot_) + (a_lds ^ ((h_) * 64)) + (i_) * 2048)
@@ -699,33 +744,84 @@ __device__ __forceinline__ void big_gemm_body(const SharedGemmArgs& a, const Row
   MOTE_DECODE(slot, mt, nt, kc);
   uint32_t kb;
   MOTE_KRANGE(kc, kb, ktl);
-  MOTE_POINTERS(mt, nt, kb);
-  if (ktl > 0) {
-    MOTE_ISSUE_A(s0, 0);
-    MOTE_ISSUE_B(s1, 0);
-    if (ktl > 1) MOTE_ISSUE_A(s2, 1);
-  }
+  MOTE_ROWS(mt, mrow, mend, grp);
+  MOTE_POINTERS(mrow, grp, nt, kb);
+  MOTE_START(ktl)
 
   for (;;) {
     const int nslot = slot + stride;
     const bool has_next = nslot < xcd_work;
-    int mt2 = mt, nt2 = nt, kc2 = kc, ktl2 = ktl;
+    int mt2 = mt, nt2 = nt, kc2 = kc, ktl2 = ktl, mrow2 = mrow, mend2 = mend, grp2 = grp;
     uint32_t kb2 = kb;
     if (has_next) {
       MOTE_DECODE(nslot, mt2, nt2, kc2);
+      MOTE_ROWS(mt2, mrow2, mend2, grp2);
       MOTE_KRANGE(kc2, kb2, ktl2);
     }
     // chunk 0 visible to every wavefront, the patches of the previous tile done
-    if (ktl > 1) asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
+    if (Cfg::TERN && ktl > 2) asm volatile("s_waitcnt vmcnt(12)" ::: "memory");
+    else if (!Cfg::TERN && ktl > 1) asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
     else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     asm volatile("s_barrier" ::: "memory");
-    if (ktl > 1) MOTE_ISSUE_B(s3, 1);   // this slot held patches
+    if (!Cfg::TERN && ktl > 1) MOTE_ISSUE_B(s3, 1);   // this slot held patches
 
     v4f acc[A16][NB];   // token rows 16i .., channels 16b .. of the wavefront's block (gate first, then up)
 #pragma unroll
     for (int i = 0; i < A16; ++i)
 #pragma unroll
       for (int b = 0; b < NB; ++b) acc[i][b] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+    if constexpr (Cfg::TERN) {
+      bf16x8 afx[A16], afy[A16];
+      uint32_t wx[4], wy[4];
+#define MOTE_TERN_READ(af_, w_, stage_, h_)                                                        \
+      {                                                                                            \
+        _Pragma("unroll") for (int i = 0; i < A16; ++i) af_[i] = MOTE_A_FRAG(stage_, h_, i);       \
+        _Pragma("unroll") for (int f = 0; f < 4; ++f)                                              \
+          w_[f] = *reinterpret_cast<const uint32_t*>(s_lds + (stage_) + SLOT + (h_) * 2048 + (wn * 4 + f) * 256 + lane * 4); \
+      }
+      // weight fragments b0_ .. of a half chunk with (af_, w_); the fragment behind the last one of w_ is the first of wn_;
+      // behind the MFMAs of fragment b the statement side_(b)
+#define MOTE_TERN_PART(b0_, b1_, af_, w_, wn_, side_)                                              \
+      _Pragma("unroll") for (int b = b0_; b < b1_; ++b) {                                          \
+        acc[0][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf, af_[0], acc[0][b], 0, 0, 0);       \
+        const bf16x8 wnext_ = b + 1 < NB ? ternary_operand(w_[((b + 1) % NB) / 2], (b + 1) & 1) : ternary_operand(wn_[0], 0); \
+        _Pragma("unroll") for (int i = 1; i < A16; ++i)                                            \
+          acc[i][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf, af_[i], acc[i][b], 0, 0, 0);     \
+        wf = wnext_;                                                                               \
+        side_                                                                                      \
+        __builtin_amdgcn_sched_barrier(0);                                                         \
+      }
+      // chunk c; PF_: with the requests of chunk c+3.  At the barrier chunk c+1 has landed (wait_), chunk c has been read
+#define MOTE_TERN_CHUNK(PF_, wait_)                                                                \
+      {                                                                                            \
+        __builtin_amdgcn_sched_barrier(0);                                                         \
+        MOTE_TERN_PART(0, NB, afx, wx, wy, {                                                       \
+          if (b == 0) MOTE_TERN_READ(afy, wy, s0, 1)                                               \
+          if (PF_ && (b & 1) == 1) MOTE_DMA_A(s3, c + 3, b / 2);                                   \
+        })                                                                                         \
+        MOTE_TERN_PART(0, NB / 2, afy, wy, wx, {                                                   \
+          if (PF_ && (b & 1) == 0) MOTE_DMA_W(s3, c + 3, b / 2);                                   \
+        })                                                                                         \
+        wait_                                                                                      \
+        asm volatile("s_barrier" ::: "memory");                                                    \
+        MOTE_TERN_PART(NB / 2, NB, afy, wy, wx, {                                                  \
+          if (b == NB / 2) MOTE_TERN_READ(afx, wx, s1, 0)                                          \
+        })                                                                                         \
+        const int t0 = s0;                                                                         \
+        s0 = s1; s1 = s2; s2 = s3; s3 = t0;                                                        \
+      }
+      MOTE_TERN_READ(afx, wx, s0, 0)
+      bf16x8 wf = ternary_operand(wx[0], 0);
+      int c = 0;
+      for (; c + 3 < ktl; ++c) MOTE_TERN_CHUNK(true, asm volatile("s_waitcnt vmcnt(12) lgkmcnt(0)" ::: "memory");)
+      for (; c < ktl; ++c) MOTE_TERN_CHUNK(false, {
+        if (c + 2 < ktl) asm volatile("s_waitcnt vmcnt(6) lgkmcnt(0)" ::: "memory");
+        else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+      })
+#undef MOTE_TERN_CHUNK
+#undef MOTE_TERN_PART
+#undef MOTE_TERN_READ
+    } else {
     bf16x8 af[A16], bl[HB], bh[HB];
 #pragma unroll
     for (int b = 0; b < HB; ++b) bl[b] = MOTE_B_FRAG(s1, 0, b);
@@ -773,30 +869,27 @@ __device__ __forceinline__ void big_gemm_body(const SharedGemmArgs& a, const Row
     for (; c < ktl; ++c) MOTE_CHUNK(false)
 #undef MOTE_CHUNK
 #undef MOTE_QUARTER
+    }
 
     // Start the next tile now: its first loads travel while this tile runs its epilogue in the two slots of the
     // last chunk.
     if (has_next) {
-      MOTE_POINTERS(mt2, nt2, kb2);
-      if (ktl2 > 0) {
-        MOTE_ISSUE_A(s0, 0);
-        MOTE_ISSUE_B(s1, 0);
-        if (ktl2 > 1) MOTE_ISSUE_A(s2, 1);
-      }
+      MOTE_POINTERS(mrow2, grp2, nt2, kb2);
+      MOTE_START(ktl2)
     }
 
     // ---- epilogue ----
     // In registers lane l owns token row r16 and four consecutive output channels of every fragment (4 * quart .. +3).
     // Each wavefront writes one 32-row block of 128 bytes per row into its private LDS patch and reads it back row-major,
     // 16 bytes per lane, so that a global store instruction covers whole 128-byte rows of the block.
-    unsigned char* const patch = s_lds + (wave < 4 ? s3 : s4) + (wave & 3) * Cfg::PATCH_BYTES;
+    unsigned char* const patch = Cfg::TERN ? s_lds + s3 + wave * Cfg::PATCH_BYTES : s_lds + (wave < 4 ? s3 : s4) + (wave & 3) * Cfg::PATCH_BYTES;
     const int n_wave0 = nt * BN + wn * (BN / 2);
     const int rd_row = lane >> 3, rd_chunk = lane & 7;
     if (a.scale0 != nullptr) {   // row scales of quantised weights (uniform branch, not taken by the bf16 expert)
 #pragma unroll
       for (int b = 0; b < B16; ++b) {
         const int ch = min(n_wave0 + b * 16 + 4 * quart, N - 4);
-        const float4 s0_ = *reinterpret_cast<const float4*>(a.scale0 + ch);
+        const float4 s0_ = *reinterpret_cast<const float4*>(a.scale0 + static_cast<int64_t>(grp) * N + ch);
         float4 s1_ = s0_;
         if constexpr (NMAT == 2) s1_ = *reinterpret_cast<const float4*>(a.scale1 + ch);
 #pragma unroll
@@ -840,8 +933,8 @@ __device__ __forceinline__ void big_gemm_body(const SharedGemmArgs& a, const Row
         for (int p = 0; p < 4; ++p) {
           const int pr = p * 8 + rd_row;
           const u4 v = *reinterpret_cast<const u4*>(patch + pr * Cfg::PATCH_ROW + rd_chunk * 16);
-          const int orow = mt * BM + wm * 64 + i * 16 + pr;
-          if (orow < M && rd_n < N) {
+          const int orow = mrow + wm * 64 + i * 16 + pr;
+          if (orow < mend && rd_n < N) {
             const int64_t o = static_cast<int64_t>(orow) * N + rd_n;
             if constexpr (Cfg::MODE == 0) *reinterpret_cast<u4*>(a.h_out + o) = v;
             else *reinterpret_cast<u4*>(a.y_out + static_cast<int64_t>(kc) * a.plane_stride + o) = v;
@@ -855,7 +948,7 @@ __device__ __forceinline__ void big_gemm_body(const SharedGemmArgs& a, const Row
     if (!has_next) break;
     // No barrier here: the patches are private and their slots are not refilled before the next
     // tile's first barrier.
-    slot = nslot; mt = mt2; nt = nt2; kc = kc2; ktl = ktl2; kb = kb2;
+    slot = nslot; mt = mt2; nt = nt2; kc = kc2; ktl = ktl2; kb = kb2; mrow = mrow2; mend = mend2; grp = grp2;
   }
 #undef MOTE_DECODE
 #undef MOTE_KRANGE
@@ -865,6 +958,10 @@ __device__ __forceinline__ void big_gemm_body(const SharedGemmArgs& a, const Row
 #undef MOTE_DMA_B
 #undef MOTE_ISSUE_A
 #undef MOTE_ISSUE_B
+#undef MOTE_ROWS
+#undef MOTE_DMA_W
+#undef MOTE_ISSUE_STAGE
+#undef MOTE_START
 #undef MOTE_A_FRAG
 #undef MOTE_B_FRAG
 }
@@ -876,6 +973,11 @@ __global__ __launch_bounds__(Cfg::THREADS, 2) void big_gemm_kernel(SharedGemmArg
 template <typename Cfg>
 __global__ __launch_bounds__(Cfg::THREADS, 2) void big_kgrouped_gemm_kernel(SharedGemmArgs a, RowGroups rg, int n_ntiles, int group_m) {
   big_gemm_body<Cfg, 2>(a, &rg, n_ntiles, rg.n, 0, group_m);
+}
+
+// ternary weights, groups of rows
+__global__ __launch_bounds__(512, 2) void big_grouped_gemm_kernel(SharedGemmArgs a, RowGroups rg, int n_ntiles, int kplanes, int ktp, int group_m) {
+  big_gemm_body<BigCfg<1, true>, 1>(a, &rg, n_ntiles, kplanes, ktp, group_m);
 }
 
 static int shared_cu_count() {
@@ -918,6 +1020,8 @@ static hipError_t launch_shared_cfg(const SharedGemmArgs& a, int kplanes, hipStr
   return hipGetLastError();
 }
 
+constexpr int kBigBand = 4;   // row tiles per band, see launch_big_cfg
+
 template <typename Cfg>
 static hipError_t launch_big_cfg(const SharedGemmArgs& a, int kplanes, const RowGroups* rg, hipStream_t stream) {
   const int n_ntiles = (a.N + Cfg::BN - 1) / Cfg::BN, n_mtiles = (a.M + Cfg::BM - 1) / Cfg::BM;
@@ -926,7 +1030,7 @@ static hipError_t launch_big_cfg(const SharedGemmArgs& a, int kplanes, const Row
   static bool attr_set = false;
   if (!attr_set) {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(big_gemm_kernel<Cfg>), hipFuncAttributeMaxDynamicSharedMemorySize, Cfg::LDS_BYTES);
-    if (e == hipSuccess && Cfg::MODE == 1)
+    if constexpr (Cfg::MODE == 1) if (e == hipSuccess)
       e = hipFuncSetAttribute(reinterpret_cast<const void*>(big_kgrouped_gemm_kernel<Cfg>), hipFuncAttributeMaxDynamicSharedMemorySize, Cfg::LDS_BYTES);
     if (e != hipSuccess) return e;
     attr_set = true;
@@ -938,9 +1042,12 @@ static hipError_t launch_big_cfg(const SharedGemmArgs& a, int kplanes, const Row
   // ranges: 809 us with bands of two row tiles, 769 of four, 840 of eight).  Weights that the memory-side cache (256 MB)
   // does not keep are read once per band: bands of eight (16384 x 3584 x 18944 gate-up: 3235 us of two, 3210 of four, 3145 of
   // eight; with 90 MB of weights all the same).
-  const int group_m = static_cast<int64_t>(Cfg::NMAT) * a.N * a.K * 2 > (int64_t{192} << 20) && rg == nullptr ? 8 : 4;
-  if (rg != nullptr) big_kgrouped_gemm_kernel<Cfg><<<static_cast<unsigned>(blocks), Cfg::THREADS, Cfg::LDS_BYTES, stream>>>(a, *rg, n_ntiles, group_m);
-  else big_gemm_kernel<Cfg><<<static_cast<unsigned>(blocks), Cfg::THREADS, Cfg::LDS_BYTES, stream>>>(a, n_ntiles, kplanes, ktp, group_m);
+  const int group_m = static_cast<int64_t>(Cfg::NMAT) * a.N * a.K * 2 > (int64_t{192} << 20) && rg == nullptr ? 8 : kBigBand;
+  if constexpr (Cfg::MODE == 1) if (rg != nullptr) {
+    big_kgrouped_gemm_kernel<Cfg><<<static_cast<unsigned>(blocks), Cfg::THREADS, Cfg::LDS_BYTES, stream>>>(a, *rg, n_ntiles, group_m);
+    return hipGetLastError();
+  }
+  big_gemm_kernel<Cfg><<<static_cast<unsigned>(blocks), Cfg::THREADS, Cfg::LDS_BYTES, stream>>>(a, n_ntiles, kplanes, ktp, group_m);
   return hipGetLastError();
 }
 
@@ -1044,6 +1151,7 @@ hipError_t launch_shared_down_scaled(const uint16_t* h_s, const uint16_t* w_down
 template <typename Cfg>
 static hipError_t launch_grouped_cfg(const SharedGemmArgs& a, const int32_t* row0, int n_groups, int kplanes,
                                      hipStream_t stream) {
+  constexpr bool BIG = Cfg::BM == 256;
   RowGroups rg;
   rg.n = n_groups;
   int tiles_m = 0;
@@ -1058,24 +1166,27 @@ static hipError_t launch_grouped_cfg(const SharedGemmArgs& a, const int32_t* row
   if (tiles_m == 0) return hipSuccess;
   const int n_ntiles = (a.N + Cfg::BN - 1) / Cfg::BN;
   const int KT64 = a.K >> 6;
-  const int ktp = 2 * ((KT64 + kplanes - 1) / kplanes);
+  const int ktp64 = (KT64 + kplanes - 1) / kplanes;
   const size_t lds = Cfg::LDS_BYTES;
   static bool attr_set = false;
-  static int resident = Cfg::MIN_BLOCKS;
+  static int resident = 1;
   if (!attr_set) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(grouped_gemm_kernel<Cfg>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
+    const void* kernel;
+    if constexpr (BIG) kernel = reinterpret_cast<const void*>(big_grouped_gemm_kernel);
+    else kernel = reinterpret_cast<const void*>(grouped_gemm_kernel<Cfg>);
+    hipError_t e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
     if (e != hipSuccess) return e;
     int n = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, grouped_gemm_kernel<Cfg>, Cfg::THREADS, lds) == hipSuccess && n > 0)
-      resident = n;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, kernel, Cfg::THREADS, lds) == hipSuccess && n > 0) resident = n;
     attr_set = true;
   }
   const int64_t tiles = static_cast<int64_t>(tiles_m) * n_ntiles * kplanes;
   int64_t blocks = static_cast<int64_t>(shared_cu_count()) * resident;
   if (blocks > tiles) blocks = (tiles + 7) / 8 * 8;
-  grouped_gemm_kernel<Cfg><<<static_cast<unsigned>(blocks), Cfg::THREADS, lds, stream>>>(a, rg, n_ntiles, kplanes, ktp,
-                                                                                        tile_group_m());
+  if constexpr (BIG)
+    big_grouped_gemm_kernel<<<static_cast<unsigned>(blocks), Cfg::THREADS, lds, stream>>>(a, rg, n_ntiles, kplanes, ktp64, kBigBand);
+  else
+    grouped_gemm_kernel<Cfg><<<static_cast<unsigned>(blocks), Cfg::THREADS, lds, stream>>>(a, rg, n_ntiles, kplanes, 2 * ktp64, tile_group_m());
   return hipGetLastError();
 }
 
@@ -1123,7 +1234,7 @@ hipError_t launch_gemm_grouped_f32(const uint16_t* act, const uint32_t* w, const
   if (M == 0 || N == 0) return hipSuccess;
   SharedGemmArgs a{act, reinterpret_cast<const uint16_t*>(w), nullptr, M, N, K, nullptr, out, static_cast<int64_t>(M) * N, scale, nullptr};
   if (grouped_row_tiles(row0_host, n_groups, 256) * ((N + 255) / 256) >= (3 * shared_cu_count()) / 4)
-    return launch_grouped_cfg<SharedCfg<1, 2, 4, 4, 2, 1, 4, true>>(a, row0_host, n_groups, planes, stream);   // 256 x 256
+    return launch_grouped_cfg<BigCfg<1, true>>(a, row0_host, n_groups, planes, stream);                          // 256 x 256
   return launch_grouped_cfg<SharedCfg<1, 2, 2, 2, 2, 2, 4, true>>(a, row0_host, n_groups, planes, stream);     // 128 x 128
 }
 
