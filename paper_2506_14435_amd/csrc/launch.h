@@ -185,9 +185,14 @@ hipError_t launch_combine(const CombineArgs& a, hipStream_t stream);
 hipError_t launch_gemm_tn_f32_kgroups(const uint16_t* act, const uint16_t* w, int M, int N, const int32_t* k0_host,
                                       int n_groups, float* out, hipStream_t stream);
 // groups of rows with a weight matrix (and scale vector) each; row0_host: host int32 [n_groups + 1]
-int grouped_gemm_planes(const int32_t* row0_host, int n_groups, int N, int K, int max_planes);
+struct GemmSplit {
+  int planes;      // K planes of the rows from split_row on (1: none)
+  int split_mt;    // row tiles in front of them (256-row tiles only) ...
+  int split_row;   // ... and rows, contracted in one plane
+};
+GemmSplit grouped_gemm_split(const int32_t* row0_host, int n_groups, int N, int K, int max_planes);
 hipError_t launch_gemm_grouped_f32(const uint16_t* act, const uint32_t* w, const int32_t* row0_host, int n_groups, int N,
-                                   int K, float* out, const float* scale, int planes, hipStream_t stream);
+                                   int K, float* out, float* planes_out, const float* scale, const GemmSplit& sp, hipStream_t stream);
 // straight-through gradients of a grouped ternary linear layer (ste_backward.hip); offsets_host: host int32 [E + 1]
 size_t ste_backward_workspace_bytes(int R, int N, int K, int E);
 hipError_t launch_ste_backward(const uint16_t* dy, const int32_t* offsets_host, const uint32_t* packed, const float* alpha,

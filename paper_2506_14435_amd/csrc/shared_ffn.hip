@@ -98,6 +98,7 @@ struct SharedGemmArgs {
   int64_t plane_stride;  // elements between partial planes
   const float* scale0;   // optional fp32 [N]: the sums of w0 (w1) are multiplied by scale0 (scale1)
   const float* scale1;   // per output channel (RTN-quantised weights held as integer-valued bf16)
+  float* y_split;        // row groups: where the planes of the row tiles from RowGroups::split_mt on go, counted like y_out
 };
 
 // Grouped rows: group e owns the rows row0[e] .. row0[e+1]-1 of act / the output and the row tiles
@@ -107,6 +108,8 @@ struct SharedGemmArgs {
 constexpr int kMaxRowGroups = 64;
 struct RowGroups {
   int n;
+  int split_mt;   // 256-row tiles: the row tiles below contract all of K in one plane
+
   int row0[kMaxRowGroups + 1];
   int tile0[kMaxRowGroups + 1];
 };
@@ -625,16 +628,17 @@ __device__ __forceinline__ void big_gemm_body(const SharedGemmArgs& a, const Row
   const int frag = r16 * 128 + ((quart ^ (r16 >> 1)) << 4);
   const int a_lds = wm * 64 * 128 + frag, b_lds = wn * (BN / 2) * 128 + frag;
 
-  // tile order: as in shared_gemm_body
-  n_ntiles *= kplanes;
+  // Tile order: as in shared_gemm_body; with row groups two such lists one after the other, the row tiles below
+  // rg->split_mt with one plane and the others with kplanes.
   int n_mtiles = (M + BM - 1) / BM;
   if constexpr (GROUPED == 1) n_mtiles = rg->tile0[rg->n];
+  const int mt1 = GROUPED == 1 ? rg->split_mt : 0;   // row tiles of the first list
+  const int nk1 = n_ntiles, nk2 = n_ntiles * kplanes, mt2n = n_mtiles - mt1;
   const int xcd = blockIdx.x & 7;
-  const bool split_n = n_ntiles >= 16;
-  const int xcd_ntiles = split_n ? (n_ntiles - xcd + 7) >> 3 : n_ntiles;
-  const int xcd_mtiles = split_n ? n_mtiles : (n_mtiles - xcd + 7) >> 3;
-  const int xcd_work = xcd_ntiles * xcd_mtiles;
-  const int per_group = group_m * xcd_ntiles;
+  auto list_nt = [&](int nk) { return nk >= 16 ? (nk - xcd + 7) >> 3 : nk; };
+  auto list_mt = [&](int nk, int mts) { return nk >= 16 ? mts : (mts - xcd + 7) >> 3; };
+  const int work1 = GROUPED == 1 ? list_nt(nk1) * list_mt(nk1, mt1) : 0;
+  const int xcd_work = work1 + list_nt(nk2) * list_mt(nk2, mt2n);
   const int stride = gridDim.x >> 3;
   int slot = blockIdx.x >> 3;
   if (slot >= xcd_work) return;
@@ -663,26 +667,32 @@ __device__ __forceinline__ void big_gemm_body(const SharedGemmArgs& a, const Row
   constexpr int PITCH = Cfg::TERN ? Cfg::STAGE : SLOT;
   int s0 = 0, s1 = PITCH, s2 = 2 * PITCH, s3 = 3 * PITCH, s4 = 4 * PITCH;
 
-#define MOTE_DECODE(slot_, mt_, nt_, kc_)                                       \
+#define MOTE_DECODE(slot_, mt_, nt_, kc_, kl_)                                  \
   {                                                                             \
-    const int grp_ = (slot_) / per_group;                                       \
-    const int in_ = (slot_) - grp_ * per_group;                                 \
-    const int gsz_ = min(xcd_mtiles - grp_ * group_m, group_m);                 \
+    const bool second_ = GROUPED != 1 || (slot_) >= work1;                      \
+    const int nk_ = second_ ? nk2 : nk1, mts_ = second_ ? mt2n : mt1;           \
+    const int kp_ = second_ ? kplanes : 1, s_ = second_ ? (slot_) - work1 : (slot_); \
+    const bool split_n_ = nk_ >= 16;                                            \
+    const int per_group_ = group_m * list_nt(nk_);                              \
+    const int grp_ = s_ / per_group_;                                           \
+    const int in_ = s_ - grp_ * per_group_;                                     \
+    const int gsz_ = min(list_mt(nk_, mts_) - grp_ * group_m, group_m);         \
     const int ni_ = in_ / gsz_, mi_ = grp_ * group_m + (in_ - ni_ * gsz_);      \
-    mt_ = split_n ? mi_ : xcd + 8 * mi_;                                        \
-    const int ntk_ = split_n ? xcd + 8 * ni_ : ni_;                             \
-    nt_ = ntk_ / kplanes;                                                       \
-    kc_ = ntk_ - nt_ * kplanes;                                                 \
+    mt_ = (second_ ? mt1 : 0) + (split_n_ ? mi_ : xcd + 8 * mi_);               \
+    const int ntk_ = split_n_ ? xcd + 8 * ni_ : ni_;                            \
+    nt_ = ntk_ / kp_;                                                           \
+    kc_ = ntk_ - nt_ * kp_;                                                     \
+    kl_ = second_ ? ktp : KT;                                                   \
   }
   // byte offset of plane kc_ in an operand row and its chunks
-#define MOTE_KRANGE(kc_, kb_, ktl_)                                             \
+#define MOTE_KRANGE(kc_, kl_, kb_, ktl_)                                        \
   {                                                                             \
     if constexpr (GROUPED == 2) {                                               \
       kb_ = static_cast<uint32_t>(rg->row0[kc_]) * 2u;                          \
       ktl_ = (rg->row0[(kc_) + 1] - rg->row0[kc_]) >> 6;                        \
     } else {                                                                    \
-      kb_ = static_cast<uint32_t>((kc_) * ktp) * 128u;                          \
-      ktl_ = min(ktp, KT - (kc_) * ktp);                                        \
+      kb_ = static_cast<uint32_t>((kc_) * (kl_)) * 128u;                        \
+      ktl_ = min((kl_), KT - (kc_) * (kl_));                                    \
     }                                                                           \
   }
   // where row tile mt_ starts and ends (uniform; the group is found by walking the table)
@@ -741,9 +751,10 @@ __device__ __forceinline__ void big_gemm_body(const SharedGemmArgs& a, const Row
   *reinterpret_cast<const bf16x8*>(s_lds + (slot_) + (b_lds ^ ((h_) * 64)) + ((b_) / B16) * (BN * 128) + ((b_) % B16) * 2048)
 
   // ---- first tile ----
-  MOTE_DECODE(slot, mt, nt, kc);
+  int kl;
+  MOTE_DECODE(slot, mt, nt, kc, kl);
   uint32_t kb;
-  MOTE_KRANGE(kc, kb, ktl);
+  MOTE_KRANGE(kc, kl, kb, ktl);
   MOTE_ROWS(mt, mrow, mend, grp);
   MOTE_POINTERS(mrow, grp, nt, kb);
   MOTE_START(ktl)
@@ -754,9 +765,10 @@ __device__ __forceinline__ void big_gemm_body(const SharedGemmArgs& a, const Row
     int mt2 = mt, nt2 = nt, kc2 = kc, ktl2 = ktl, mrow2 = mrow, mend2 = mend, grp2 = grp;
     uint32_t kb2 = kb;
     if (has_next) {
-      MOTE_DECODE(nslot, mt2, nt2, kc2);
+      int kl2;
+      MOTE_DECODE(nslot, mt2, nt2, kc2, kl2);
       MOTE_ROWS(mt2, mrow2, mend2, grp2);
-      MOTE_KRANGE(kc2, kb2, ktl2);
+      MOTE_KRANGE(kc2, kl2, kb2, ktl2);
     }
     // chunk 0 visible to every wavefront, the patches of the previous tile done
     if (Cfg::TERN && ktl > 2) asm volatile("s_waitcnt vmcnt(12)" ::: "memory");
@@ -937,6 +949,7 @@ __device__ __forceinline__ void big_gemm_body(const SharedGemmArgs& a, const Row
           if (orow < mend && rd_n < N) {
             const int64_t o = static_cast<int64_t>(orow) * N + rd_n;
             if constexpr (Cfg::MODE == 0) *reinterpret_cast<u4*>(a.h_out + o) = v;
+            else if (GROUPED == 1 && mt >= mt1) *reinterpret_cast<u4*>(a.y_split + static_cast<int64_t>(kc) * a.plane_stride + o) = v;
             else *reinterpret_cast<u4*>(a.y_out + static_cast<int64_t>(kc) * a.plane_stride + o) = v;
           }
         }
@@ -1149,10 +1162,11 @@ hipError_t launch_shared_down_scaled(const uint16_t* h_s, const uint16_t* w_down
 }
 
 template <typename Cfg>
-static hipError_t launch_grouped_cfg(const SharedGemmArgs& a, const int32_t* row0, int n_groups, int kplanes,
+static hipError_t launch_grouped_cfg(const SharedGemmArgs& a, const int32_t* row0, int n_groups, int kplanes, int split_mt,
                                      hipStream_t stream) {
   constexpr bool BIG = Cfg::BM == 256;
   RowGroups rg;
+  rg.split_mt = split_mt;
   rg.n = n_groups;
   int tiles_m = 0;
   for (int e = 0; e < n_groups; ++e) {
@@ -1180,7 +1194,7 @@ static hipError_t launch_grouped_cfg(const SharedGemmArgs& a, const int32_t* row
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, kernel, Cfg::THREADS, lds) == hipSuccess && n > 0) resident = n;
     attr_set = true;
   }
-  const int64_t tiles = static_cast<int64_t>(tiles_m) * n_ntiles * kplanes;
+  const int64_t tiles = (static_cast<int64_t>(split_mt) + static_cast<int64_t>(tiles_m - split_mt) * kplanes) * n_ntiles;
   int64_t blocks = static_cast<int64_t>(shared_cu_count()) * resident;
   if (blocks > tiles) blocks = (tiles + 7) / 8 * 8;
   if constexpr (BIG)
@@ -1197,45 +1211,76 @@ static int64_t grouped_row_tiles(const int32_t* row0, int n_groups, int bm) {
   return t;
 }
 
-// K planes of a grouped GEMM (pure function of the group sizes and the shape, at most max_planes).  256 x 256
-// tiles: two planes when one plane leaves more than 15 % of the last round of workgroups empty and two
-// leave less (16 groups of about 1024 rows, N = 2048, K = 11008: 576 tiles on 256 CUs; one / two / three /
-// four planes 2.39 / 2.32 / 2.37 / 2.35 ms for the whole backward call), else one.  Small problems
-// (128 x 128 tiles): as many as give two workgroups per CU, planes of at least 16 K steps of 64.
-int grouped_gemm_planes(const int32_t* row0_host, int n_groups, int N, int K, int max_planes) {
+// How a grouped GEMM cuts its contraction (pure function of the group sizes and the shape, at most max_planes planes).
+// 256 x 256 tiles: the row tiles that fill whole rounds of workgroups contract all of K, those of the last, partly
+// empty round are cut into as many planes as fill it.  16 groups of about 1024 rows, N = 2048, K = 11008: 576 tiles on
+// 256 CUs are two rounds of 512 and 64 tiles in four planes: 669 + 70 us (two planes for all rows, and their sum) -> 624 + 10.
+// With fewer than 16 channel tiles the row tiles are dealt to the XCDs, so whole rounds are whole rounds of every XCD.
+// Where no such cut exists: two planes for all rows when one plane leaves more than 15 % of the last round empty and two
+// leave less.  Small problems (128 x 128 tiles): as many planes as give two workgroups per CU, planes of at least 16 K
+// steps of 64.
+GemmSplit grouped_gemm_split(const int32_t* row0_host, int n_groups, int N, int K, int max_planes) {
+  GemmSplit sp{1, 0, 0};
   const int cus = shared_cu_count();
-  const int64_t t256 = grouped_row_tiles(row0_host, n_groups, 256) * ((N + 255) / 256);
+  const int nt = (N + 255) / 256;
+  const int mt = static_cast<int>(grouped_row_tiles(row0_host, n_groups, 256));
+  const int64_t t256 = static_cast<int64_t>(mt) * nt;
+  const int KT = K >> 6;
   if (t256 >= (3 * cus) / 4) {
     auto eff = [&](int p) {
       const int64_t rounds = (t256 * p + cus - 1) / cus;
       return static_cast<double>(t256 * p) / static_cast<double>(rounds * cus);
     };
-    if (eff(1) >= 0.85 || max_planes < 2 || (K >> 6) < 32) return 1;
-    return eff(2) > eff(1) + 0.05 ? 2 : 1;
+    if (eff(1) >= 0.85 || max_planes < 2 || KT < 32) return sp;
+    if (nt < 16 && cus % 8 == 0) {
+      int whole = mt / 8 * 8;
+      while (whole > 0 && (whole / 8 * nt) % (cus / 8) != 0) whole -= 8;
+      const int left = mt - whole;
+      int p = left > 0 ? cus / (left * nt) : 1;
+      p = std::min(std::min(p, max_planes), KT / 16);
+      if (whole > 0 && p >= 2) {
+        sp.planes = (KT + (KT + p - 1) / p - 1) / ((KT + p - 1) / p);   // every plane non-empty
+        sp.split_mt = whole;
+        int e = 0, t = 0;   // first row of row tile `whole`
+        for (; e < n_groups; ++e) {
+          const int te = (row0_host[e + 1] - row0_host[e] + 255) / 256;
+          if (t + te > whole) break;
+          t += te;
+        }
+        sp.split_row = row0_host[e] - row0_host[0] + (whole - t) * 256;
+        return sp;
+      }
+    }
+    if (eff(2) > eff(1) + 0.05) sp.planes = 2;
+    return sp;
   }
   const int64_t t128 = grouped_row_tiles(row0_host, n_groups, 128) * ((N + 127) / 128);
-  if (t128 == 0) return 1;
+  if (t128 == 0) return sp;
   int planes = static_cast<int>((2 * cus) / t128);
-  if (planes > (K >> 6) / 16) planes = (K >> 6) / 16;
+  if (planes > KT / 16) planes = KT / 16;
   if (planes > max_planes) planes = max_planes;
-  return planes < 1 ? 1 : planes;
+  sp.planes = planes < 1 ? 1 : planes;
+  return sp;
 }
 
 // Grouped GEMM for other callers: rows row0_host[e] .. row0_host[e+1]-1 of act (row0_host: n_groups + 1
 // ascending HOST integers; act, out and the rows are counted from row0_host[0], which act and out point at)
 // are contracted with matrix e of w ([n_groups] matrices of [N, K] ternary blocks, SharedCfg) and scaled per
-// channel by row e of scale ([n_groups][N]): out[r, n] = scale[e][n] * sum_k act[r, k] * t[e][n, k].  planes as given by
-// grouped_gemm_planes: plane p writes its partial sums to out + p * rows * N and the caller adds them.
+// channel by row e of scale ([n_groups][N]): out[r, n] = scale[e][n] * sum_k act[r, k] * t[e][n, k].  sp as given by
+// grouped_gemm_split: the rows below sp.split_row go to out; with more than one plane, plane p of the others writes its
+// partial sums to planes_out + p * (rows - split_row) * N (row split_row first) and the caller adds them.
 // n_groups <= 64, n_groups * N * K / 4 bytes and rows * K * 2 bytes below 4 GiB, K a multiple of 64.
 hipError_t launch_gemm_grouped_f32(const uint16_t* act, const uint32_t* w, const int32_t* row0_host, int n_groups, int N,
-                                   int K, float* out, const float* scale, int planes, hipStream_t stream) {
+                                   int K, float* out, float* planes_out, const float* scale, const GemmSplit& sp, hipStream_t stream) {
   if (n_groups < 1 || n_groups > kMaxRowGroups) return hipErrorInvalidValue;
   const int M = row0_host[n_groups] - row0_host[0];
   if (M == 0 || N == 0) return hipSuccess;
-  SharedGemmArgs a{act, reinterpret_cast<const uint16_t*>(w), nullptr, M, N, K, nullptr, out, static_cast<int64_t>(M) * N, scale, nullptr};
+  float* const y_split = sp.planes > 1 ? planes_out - static_cast<int64_t>(sp.split_row) * N : out;
+  SharedGemmArgs a{act, reinterpret_cast<const uint16_t*>(w), nullptr, M, N, K, nullptr, out, static_cast<int64_t>(M - sp.split_row) * N, scale, nullptr, y_split};
   if (grouped_row_tiles(row0_host, n_groups, 256) * ((N + 255) / 256) >= (3 * shared_cu_count()) / 4)
-    return launch_grouped_cfg<BigCfg<1, true>>(a, row0_host, n_groups, planes, stream);                          // 256 x 256
-  return launch_grouped_cfg<SharedCfg<1, 2, 2, 2, 2, 2, 4, true>>(a, row0_host, n_groups, planes, stream);     // 128 x 128
+    return launch_grouped_cfg<BigCfg<1, true>>(a, row0_host, n_groups, sp.planes, sp.split_mt, stream);          // 256 x 256
+  a.y_out = y_split;
+  return launch_grouped_cfg<SharedCfg<1, 2, 2, 2, 2, 2, 4, true>>(a, row0_host, n_groups, sp.planes, 0, stream);   // 128 x 128
 }
 
 template <typename Cfg>

@@ -257,17 +257,16 @@ hipError_t launch_ste_backward(const uint16_t* dy, const int32_t* offsets_host, 
     const int row0 = offsets_host[e0], rows = offsets_host[e0 + nb] - row0;
     if (rows == 0) continue;
     reblock_ternary_t_kernel<<<dim3((N / 128) * (K / 128), nb), kSteThreads, 0, stream>>>(packed, N, K, grp, e0, wt);
-    const int planes = grouped_gemm_planes(offsets_host + e0, nb, K, N, kSteMaxPlanes);
+    const GemmSplit sp = grouped_gemm_split(offsets_host + e0, nb, K, N, kSteMaxPlanes);
     const uint16_t* dy_b = dy + static_cast<int64_t>(row0) * N;
     float* dx_b = dx + static_cast<int64_t>(row0) * K;
     const float* alpha_b = alpha_vec + static_cast<int64_t>(e0) * K;
-    hipError_t err = launch_gemm_grouped_f32(dy_b, wt, offsets_host + e0, nb, K, N, planes == 1 ? dx_b : dx_planes, alpha_b,
-                                             planes, stream);
+    hipError_t err = launch_gemm_grouped_f32(dy_b, wt, offsets_host + e0, nb, K, N, dx_b, dx_planes, alpha_b, sp, stream);
     if (err != hipSuccess) return err;
-    if (planes > 1) {   // the contraction over N was cut into planes, added in order here
-      const int64_t n4 = static_cast<int64_t>(rows) * K / 4;
+    if (sp.planes > 1) {   // rows whose contraction over N was cut into planes, added in order here
+      const int64_t n4 = static_cast<int64_t>(rows - sp.split_row) * K / 4;
       sum_planes_kernel<<<static_cast<unsigned>(std::min<int64_t>((n4 + kSteThreads - 1) / kSteThreads, 2048)), kSteThreads,
-                          0, stream>>>(dx_planes, planes, n4, nullptr, dx_b);
+                          0, stream>>>(dx_planes, sp.planes, n4, nullptr, dx_b + static_cast<int64_t>(sp.split_row) * K);
     }
   }
   // dW: the scaled gradient rows and the codes of every expert transposed into [N, sum_pad] and [K, sum_pad]

@@ -454,9 +454,10 @@ def test_ste_linear_backward_arguments_are_validated():
 
 # The 2-bit operand of dX: exact sums (integer gradients, sums below 2^24) make every code's place visible.
 # 128 channels: half a 256-wide tile; 640: a last tile of half a width, on 256-row tiles; 128 output rows: one
-# workgroup of the re-blocking kernel; a group of one row and an empty one.
+# workgroup of the re-blocking kernel; a group of one row and an empty one; 36 row tiles x 8 channel tiles, of which the
+# last four row tiles (from the middle of a group on) go in four K planes.
 @pytest.mark.parametrize("R,N,K,E,cuts", [(70, 128, 128, 3, [1, 1]), (300, 384, 640, 2, [130]), (16700, 128, 640, 2, [16600]),
-                                          (129, 1408, 256, 4, [0, 64, 128])])
+                                          (129, 1408, 256, 4, [0, 64, 128]), (8700, 4096, 2048, 3, [2900, 5800])])
 def test_ste_dx_of_integer_gradients_is_exact(R, N, K, E, cuts):
     M = _m()
     p = _ste_problem(R, N, K, E, seed=77 + R, cuts=cuts)
