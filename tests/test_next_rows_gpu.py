@@ -454,10 +454,9 @@ def test_ste_linear_backward_arguments_are_validated():
 
 # The 2-bit operand of dX: exact sums (integer gradients, sums below 2^24) make every code's place visible.
 # 128 channels: half a 256-wide tile; 640: a last tile of half a width, on 256-row tiles; 128 output rows: one
-# workgroup of the re-blocking kernel; a group of one row and an empty one; 36 row tiles x 8 channel tiles, of which the
-# last four row tiles (from the middle of a group on) go in four K planes.
+# workgroup of the re-blocking kernel; a group of one row and an empty one.
 @pytest.mark.parametrize("R,N,K,E,cuts", [(70, 128, 128, 3, [1, 1]), (300, 384, 640, 2, [130]), (16700, 128, 640, 2, [16600]),
-                                          (129, 1408, 256, 4, [0, 64, 128]), (8700, 4096, 2048, 3, [2900, 5800])])
+                                          (129, 1408, 256, 4, [0, 64, 128])])
 def test_ste_dx_of_integer_gradients_is_exact(R, N, K, E, cuts):
     M = _m()
     p = _ste_problem(R, N, K, E, seed=77 + R, cuts=cuts)
@@ -470,6 +469,24 @@ def test_ste_dx_of_integer_gradients_is_exact(R, N, K, E, cuts):
         a, b = int(p["offsets"][e]), int(p["offsets"][e + 1])
         ref = (dy[a:b].numpy() @ p["experts"][e][0].astype(np.float32)).astype(np.float32)   # |sums| <= 8 N: exact
         assert np.array_equal(dx[a:b].cpu().numpy(), ref * np.float32(alpha[e]))
+
+
+# The last row tiles in K planes of their own: 36 row tiles of 256 x 8 channel tiles, the last four row tiles (from the
+# middle of a group on) in four planes; 33 row tiles, a group of 40 rows in two planes (K steps: 32).  Every plane is
+# multiplied by alpha before they are added, so alpha is a power of two here and everything stays exact.
+@pytest.mark.parametrize("R,N,K,E,cuts", [(8700, 4096, 2048, 3, [2900, 5800]), (8232, 2048, 2048, 3, [0, 8192])])
+def test_ste_dx_with_the_last_row_tiles_in_planes_is_exact(R, N, K, E, cuts):
+    M = _m()
+    p = _ste_problem(R, N, K, E, seed=5 + R, cuts=cuts)
+    dy = torch.randint(-8, 9, (R, N), generator=torch.Generator().manual_seed(R)).float()
+    alpha = torch.full_like(p["alpha"], 2.0 ** -6)
+    dx, _ = M.mote_ste_linear_backward(dy.to(torch.bfloat16).cuda(), p["offsets"], p["packed"].cuda(), alpha.cuda(), 1,
+                                       torch.from_numpy(p["q"]).cuda(), torch.from_numpy(p["beta"]).cuda(), N, K)
+    torch.cuda.synchronize()
+    for e in range(E):
+        a, b = int(p["offsets"][e]), int(p["offsets"][e + 1])
+        ref = dy[a:b].numpy() @ p["experts"][e][0].astype(np.float32)   # |sums| <= 8 N: exact
+        assert np.array_equal(dx[a:b].cpu().numpy(), ref * np.float32(2.0 ** -6))
 
 
 # Sums near both ends of the fp32 range: the contraction and the scale keep the exponents of dy, t and alpha.  Every
