@@ -5,12 +5,11 @@
 //   down mode    : y_s = h_s W_down^T (fp32)                                 [T, d]
 //
 // Both operands are K-contiguous ([rows, K] row-major) and are loaded straight into LDS
-// (buffer_load ... lds, 16 bytes per lane) in K steps of 32 elements: a tile row is 64
-// bytes = four 16-byte chunks, chunk index XOR-swizzled with bits 2..3 of the row so that a
-// ds_read_b128 of 16 consecutive rows touches every LDS bank once.  Three stages, requested
-// two K steps ahead; two workgroups of four wavefronts share a CU, so the epilogue and the
-// barrier waits of one overlap with the MFMAs of the other.  Persistent workgroups walk an
-// XCD-aware list of (row tile, channel tile, K plane) triples as the ternary GEMM does.
+// (buffer_load ... lds, 16 bytes per lane) in K chunks of 64 elements: a tile row is 128
+// bytes = eight 16-byte chunks, chunk index XOR-swizzled with bits 1..3 of the row so that a
+// ds_read_b128 of 16 consecutive rows touches every LDS bank once.  Two kernels: big_gemm (256 x 256
+// tiles, bound by the matrix pipe and power) and mid_gemm (128-row tiles, bound by latency); gemm_choice
+// says which takes a problem.
 //
 // MFMA operand mapping (16x16x32 bf16): first operand = weights (lane l: output channel
 // l%16, 8 consecutive K elements of quarter l/16), second = activations (lane l: token row
@@ -21,61 +20,24 @@
 // (half as many accumulator registers read and written per flop), fed from LDS as here 1.75 and 1.55.
 #include <stdlib.h>
 
+#include <algorithm>
+
 #include "common.h"
 #include "launch.h"
 
 namespace mote {
 
-template <int MODE_, int BM_W_, int BN_W_, int WAVES_M_, int WAVES_N_, int MIN_BLOCKS_ = 1, int STAGES_ = 3, bool TERN_ = false>
-struct SharedCfg {
-  // Weights as 2-bit ternary codes (grouped GEMM of the straight-through gradients): blocks of 32 channels x 32
-  // K elements = 256 bytes, block (channel block, K step) row-major; in a block word 16Q + c holds the K elements
-  // 8Q .. 8Q+7 of channel c (pairs J = 0..3) and of channel 16 + c (J = 4..7), the operands of one lane for two
-  // fragments: pair J has its even element's "non-zero" at bit J and sign at bit 8+J, its odd element's at bits 16+J and 24+J.  In each 16-bit half of
-  // word & (0x01010101 << J), multiplied by 127 << (7 - J), "non-zero" becomes 0x3F80 and the sign 0x8000 (modulo 2^16;
-  // 127 is odd): the pair as bf16 values 0, 1, -1 after one and and one packed 16-bit multiplication (a shift and an
-  // and give 0, 2, -2 instead, whose sums overflow from 2^127 on).  What the GEMM is bound by is operand traffic: with
-  // bf16 weights 96 KiB of LDS reads and 32 KiB of loads per K step and CU, with codes 40 and 18 KiB: 16 groups of
-  // about 1024 rows, N = 2048, K = 11008: 875 -> 714 us (0.84 -> 1.03 PFLOP/s).
-  static constexpr bool TERN = TERN_;
-  static constexpr int MIN_BLOCKS = MIN_BLOCKS_;
-  static constexpr int STAGES = STAGES_;   // LDS ring: 3, or 4 with the fragment reads of a K step moved half a step ahead
-  static constexpr int MODE = MODE_;  // 0 gate-up (two matrices, SwiGLU epilogue), 1 down
-  static constexpr int NMAT = MODE_ == 0 ? 2 : 1;
-  static constexpr int BM_W = BM_W_, BN_W = BN_W_, WAVES_M = WAVES_M_, WAVES_N = WAVES_N_;
-  static constexpr int BM = 32 * BM_W_ * WAVES_M_;
-  static constexpr int BN = 32 * BN_W_ * WAVES_N_;   // output channels per matrix
-  static constexpr int WAVES = WAVES_M_ * WAVES_N_;
-  static constexpr int THREADS = 64 * WAVES;
-  static constexpr int KSTEP = 32;                   // bf16 elements per K step: 64-byte tile rows
-  static constexpr int ROWS_PER_PASS = 16 * WAVES;   // a wavefront load fills 16 tile rows
-  static constexpr int A_PASSES = BM / ROWS_PER_PASS;
-  static constexpr int B_PASSES = TERN_ ? 1 : NMAT * BN / ROWS_PER_PASS;   // ternary: a wavefront brings one block
-  static constexpr int A_BYTES = BM * 64;
-  static constexpr int B_BYTES = BN * (TERN_ ? 8 : 64);   // per matrix
-  static constexpr int STAGE_BYTES = A_BYTES + NMAT * B_BYTES;
-  static constexpr int OUT_BYTES = MODE_ == 0 ? 2 : 4;
-  static constexpr int PATCH_F = MODE_ == 0 ? BN_W_ : 1;   // fragments per epilogue pass (128-byte output rows for 2 / 1)
-  static constexpr int PATCH_ROW = PATCH_F * 32 * OUT_BYTES + 16;
-  static constexpr int PATCH_BYTES = 32 * PATCH_ROW;
-  static constexpr bool PATCH_IN_STAGE = WAVES * PATCH_BYTES <= STAGE_BYTES;
-  // ring of four: two stages are free during the epilogue, each takes the patches of half the wavefronts
-  static constexpr bool PATCH_IN_TWO = STAGES_ == 4 && (WAVES / 2) * PATCH_BYTES <= STAGE_BYTES;
-  static constexpr int LDS_BYTES = STAGES * STAGE_BYTES + ((PATCH_IN_STAGE || PATCH_IN_TWO) ? 0 : WAVES * PATCH_BYTES);
-  static_assert(STAGES == 3 || STAGES == 4, "ring of three or four stages");
-  static_assert(STAGES == 3 || PATCH_IN_TWO, "the ring of four keeps the epilogue patches in its two free stages");
-  static_assert(!TERN_ || (NMAT == 1 && STAGES_ == 4 && BN == 32 * WAVES && A_PASSES == 2), "what the ternary K loop is written for");
-  static_assert(BM % ROWS_PER_PASS == 0 && (NMAT * BN) % ROWS_PER_PASS == 0 && BN % ROWS_PER_PASS == 0,
-                "loaders cover the tiles in whole passes, a pass stays inside one matrix");
-  static_assert(64 % (PATCH_F * 32 * OUT_BYTES / 16) == 0, "an epilogue read covers whole rows");
-  static_assert(A_PASSES + B_PASSES < 16, "fits the low vmcnt field");
-};
-
-// 64-byte rows of four 16-byte chunks, chunk XOR-swizzled with row bits 2..3: the 16 lanes of
-// a quarter wavefront read one chunk of 16 consecutive rows = all 64 banks exactly once.
-__device__ __forceinline__ int lds_tile_offset(int row, int chunk) { return row * 64 + ((chunk ^ ((row >> 2) & 3)) << 4); }
-
-// Half h of the ternary word of a lane (see SharedCfg): eight K elements of fragment h as bf16 values 0, 1, -1.
+// Weights as 2-bit ternary codes (grouped GEMM of the straight-through gradients): blocks of 32 channels x 32
+// K elements = 256 bytes, block (channel block, 32 K elements) row-major; in a block word 16Q + c holds the K elements
+// 8Q .. 8Q+7 of channel c (pairs J = 0..3) and of channel 16 + c (J = 4..7), the operands of one lane for two
+// fragments: pair J has its even element's "non-zero" at bit J and sign at bit 8+J, its odd element's at bits 16+J and 24+J.
+// In each 16-bit half of
+// word & (0x01010101 << J), multiplied by 127 << (7 - J), "non-zero" becomes 0x3F80 and the sign 0x8000 (modulo 2^16;
+// 127 is odd): the pair as bf16 values 0, 1, -1 after one and and one packed 16-bit multiplication (a shift and an
+// and give 0, 2, -2 instead, whose sums overflow from 2^127 on).  The codes are an eighth of the bytes of bf16 weights
+// through L2 and LDS.
+//
+// Half h of the ternary word of a lane: eight K elements of fragment h as bf16 values 0, 1, -1.
 __device__ __forceinline__ bf16x8 ternary_operand(uint32_t w, int h) {
   typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
   uint32_t r[4];
@@ -114,465 +76,23 @@ struct RowGroups {
   int tile0[kMaxRowGroups + 1];
 };
 
-// GROUPED: 0 plain, 1 row groups (above), 2 K ranges: plane p of the kplanes = rg->n planes contracts the
-// K range row0[p] .. row0[p+1]-1 (multiples of 64 elements; an empty range gives a plane of zeros).
-template <typename Cfg, int GROUPED>
-__device__ __forceinline__ void shared_gemm_body(const SharedGemmArgs& a, const RowGroups* rg, int n_ntiles, int kplanes,
-                                                 int ktp, int group_m) {
-  constexpr int NMAT = Cfg::NMAT, BM_W = Cfg::BM_W, BN_W = Cfg::BN_W;
-  constexpr int BM = Cfg::BM, BN = Cfg::BN;
-  constexpr int A_BYTES = Cfg::A_BYTES, B_BYTES = Cfg::B_BYTES, STAGE_BYTES = Cfg::STAGE_BYTES;
-  constexpr int NLOAD = Cfg::A_PASSES + Cfg::B_PASSES;   // vector-memory operations a wavefront issues per K step
-  extern __shared__ __attribute__((aligned(16))) unsigned char s_lds[];
-
-  const int M = a.M, N = a.N, K = a.K;
-  const int KT = K >> 5;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wave_u = __builtin_amdgcn_readfirstlane(wave);
-  const int wm = wave % Cfg::WAVES_M, wn = wave / Cfg::WAVES_M;
-  const int r16 = lane & 15, quart = lane >> 4;
-  constexpr int A16 = 2 * BM_W, B16 = 2 * BN_W, NB = NMAT * B16;   // 16-row / 16-channel fragments of a wavefront
-  // this lane's 16 bytes of the wavefront's first activation / weight fragment inside a stage
-  const int a_lds = lds_tile_offset(wm * BM_W * 32 + r16, quart);
-  const int b_lds = A_BYTES + lds_tile_offset(wn * BN_W * 32 + r16, quart);
-  // LDS byte address of the stage area (what M0 takes for a direct-to-LDS load)
-  const uint32_t lds0 = (uint32_t)(uintptr_t)((__attribute__((address_space(3))) unsigned char*)s_lds);
-
-  // Persistent workgroups, dealt to the 8 XCDs round-robin by linear id: XCD x owns the
-  // (channel tile, K plane) pairs x, x+8, ... (the row tiles x, x+8, ... when there are fewer
-  // than 16 pairs); inside an XCD the tiles are ordered in bands of group_m row tiles, row tile
-  // fastest, so the resident workgroups share both activation tiles and weight slices in L2.
-  // With kplanes > 1 (down projection of small problems) the contraction is cut into planes of
-  // ktp K steps; each plane writes its own partial output, added later in plane order.
-  n_ntiles *= kplanes;
-  int n_mtiles = (M + BM - 1) / BM;
-  if constexpr (GROUPED == 1) n_mtiles = rg->tile0[rg->n];
-  const int xcd = blockIdx.x & 7;
-  const bool split_n = n_ntiles >= 16;
-  const int xcd_ntiles = split_n ? (n_ntiles - xcd + 7) >> 3 : n_ntiles;
-  const int xcd_mtiles = split_n ? n_mtiles : (n_mtiles - xcd + 7) >> 3;
-  const int xcd_work = xcd_ntiles * xcd_mtiles;
-  const int per_group = group_m * xcd_ntiles;   // tiles of a band of group_m row tiles
-  const int stride = gridDim.x >> 3;
-  int slot = blockIdx.x >> 3;
-  if (slot >= xcd_work) return;
-
-  // Loader: raw buffer loads written in assembly (the compiler has no exact model of
-  // outstanding direct-to-LDS loads across this loop).  Vector-memory operations complete in
-  // issue order, so waiting for "all but the NLOAD youngest" retires the K step that is about
-  // to be contracted while the following one stays in flight; anything else issued since
-  // (stores of the previous epilogue) only makes that wait stricter.
-  constexpr int kBufferFlags = 0x00020000;   // raw buffer, 32-bit data format
-  auto make_rsrc = [&](const void* base, int64_t bytes) {
-    const uint64_t p = reinterpret_cast<uint64_t>(base);
-    v4i r;
-    r.x = static_cast<int>(static_cast<uint32_t>(p));
-    r.y = static_cast<int>(static_cast<uint32_t>(p >> 32) & 0xFFFFu);
-    r.z = static_cast<int>(bytes);
-    r.w = kBufferFlags;
-    return r;
-  };
-  const v4i rsrc_a = make_rsrc(a.act, static_cast<int64_t>(M) * K * 2);
-  const v4i rsrc_b0 = make_rsrc(a.w0, Cfg::TERN ? static_cast<int64_t>(GROUPED == 1 ? rg->n : 1) * N * K / 4
-                                                : static_cast<int64_t>(GROUPED == 1 ? rg->n : 1) * N * K * 2);
-  const v4i rsrc_b1 = make_rsrc(NMAT == 2 ? a.w1 : a.w0, static_cast<int64_t>(N) * K * 2);
-  // lane l of a wavefront load lands at byte 16*l of a 1-KiB block = tile row l/4, physical
-  // chunk l%4, and therefore fetches logical chunk (l%4) ^ swizzle(row)
-  const int ld_row = wave_u * 16 + (lane >> 2);
-  const uint32_t ld_chunk = static_cast<uint32_t>(((lane & 3) ^ ((lane >> 4) & 3)) << 4);
-  uint32_t a_off[Cfg::A_PASSES], b_off[Cfg::B_PASSES];   // byte offsets of this lane's 16 bytes, K step 0 of the plane
-  int mt, nt, kc, ktl;
-  // first row of the tile, one past the last row it may store, its group (0 without groups)
-  int mrow, mend = M, grp = 0;
-  int st_cur = 0, st_nxt = STAGE_BYTES, st_nx2 = 2 * STAGE_BYTES;   // stage of K step kt, kt+1, kt+2 (byte offsets)
-  int st_nx3 = 3 * STAGE_BYTES;                                      // ... and kt+3 (ring of four stages only)
-
-#define MOTE_DECODE(slot_, mt_, nt_, kc_)                                       \
-  {                                                                             \
-    const int grp_ = (slot_) / per_group;                                       \
-    const int in_ = (slot_) - grp_ * per_group;                                 \
-    const int gsz_ = min(xcd_mtiles - grp_ * group_m, group_m);                 \
-    const int ni_ = in_ / gsz_, mi_ = grp_ * group_m + (in_ - ni_ * gsz_);      \
-    mt_ = split_n ? mi_ : xcd + 8 * mi_;                                        \
-    const int ntk_ = split_n ? xcd + 8 * ni_ : ni_;                             \
-    nt_ = ntk_ / kplanes;                                                       \
-    kc_ = ntk_ - nt_ * kplanes;                                                 \
-  }
-  // where row tile mt_ starts and ends (uniform; the group is found by walking the table)
-#define MOTE_ROWS(mt_, mrow_, mend_, grp_)                                      \
-  {                                                                             \
-    if constexpr (GROUPED == 1) {                                               \
-      int e_ = 0;                                                               \
-      while (e_ + 1 < rg->n && rg->tile0[e_ + 1] <= (mt_)) ++e_;                \
-      grp_ = e_;                                                                \
-      mrow_ = rg->row0[e_] + ((mt_) - rg->tile0[e_]) * BM;                      \
-      mend_ = rg->row0[e_ + 1];                                                 \
-    } else {                                                                    \
-      mrow_ = (mt_) * BM;                                                       \
-    }                                                                           \
-  }
-  // byte offset of plane kc_ in an operand row and its K steps (uniform; GROUPED == 2 reads them from the
-  // table, early enough that the scalar loads are back when the tile starts)
-#define MOTE_KRANGE(kc_, kb_, ktl_)                                                                \
-  {                                                                                                \
-    if constexpr (GROUPED == 2) {                                                                  \
-      kb_ = static_cast<uint32_t>(rg->row0[kc_]) * 2u;                                             \
-      ktl_ = (rg->row0[(kc_) + 1] - rg->row0[kc_]) >> 5;                                           \
-    } else {                                                                                       \
-      kb_ = static_cast<uint32_t>((kc_) * ktp) * 64u;                                              \
-      ktl_ = min(ktp, KT - (kc_) * ktp);                                                           \
-    }                                                                                              \
-  }
-#define MOTE_POINTERS(mrow_, grp_, nt_, kb_)                                                       \
-  {                                                                                                \
-    const uint32_t k0_ = (kb_) + ld_chunk;                                                         \
-    _Pragma("unroll") for (int p = 0; p < Cfg::A_PASSES; ++p) {                                    \
-      const int row_ = min((mrow_) + p * Cfg::ROWS_PER_PASS + ld_row, M - 1);                      \
-      a_off[p] = static_cast<uint32_t>(row_) * static_cast<uint32_t>(K) * 2u + k0_;                \
-    }                                                                                              \
-    if constexpr (Cfg::TERN) {                                                                     \
-      const int blk_ = min((nt_) * (BN / 32) + wave_u, (N >> 5) - 1) + (grp_) * (N >> 5);          \
-      b_off[0] = static_cast<uint32_t>(blk_) * static_cast<uint32_t>(K) * 8u + (kb_) * 4u + lane * 4u; \
-    }                                                                                              \
-    else _Pragma("unroll") for (int p = 0; p < Cfg::B_PASSES; ++p) {                               \
-      const int row_ = min((nt_) * BN + (p * Cfg::ROWS_PER_PASS) % BN + ld_row, N - 1) + (grp_) * N; \
-      b_off[p] = static_cast<uint32_t>(row_) * static_cast<uint32_t>(K) * 2u + k0_;                \
-    }                                                                                              \
-  }
-  // one 16-byte-per-lane direct load: LDS byte address (uniform), lane offset, buffer, scalar offset
-#define MOTE_DMA(lds_, voff_, rsrc_, soff_)                                                        \
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"           \
-               :: "s"(lds_), "v"(voff_), "s"(rsrc_), "s"(soff_) : "memory")
-#define MOTE_DMA_A(stage_, ks_, p_)                                                                \
-  MOTE_DMA(lds0 + (stage_) + ((p_) * Cfg::ROWS_PER_PASS + wave_u * 16) * 64, a_off[p_], rsrc_a, (ks_) * 64)
-  // loader pass p_ of the weights: matrix (p_*ROWS_PER_PASS)/BN, rows (p_*ROWS_PER_PASS)%BN ... of it
-#define MOTE_DMA_B(stage_, ks_, p_)                                                                \
-  {                                                                                                \
-    if constexpr (Cfg::TERN)                                                                       \
-      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, %3 offen lds"         \
-                   :: "s"(lds0 + (stage_) + A_BYTES + wave_u * 256), "v"(b_off[p_]), "s"(rsrc_b0), "s"((ks_) * 256) : "memory"); \
-    else                                                                                           \
-      MOTE_DMA(lds0 + (stage_) + A_BYTES + ((p_) * Cfg::ROWS_PER_PASS + wave_u * 16) * 64, b_off[p_], \
-               (((p_) * Cfg::ROWS_PER_PASS) / BN == 0 ? rsrc_b0 : rsrc_b1), (ks_) * 64);           \
-  }
-#define MOTE_ISSUE_STEP(stage_, ks_)                                                               \
-  {                                                                                                \
-    _Pragma("unroll") for (int p = 0; p < Cfg::A_PASSES; ++p) MOTE_DMA_A(stage_, ks_, p);          \
-    _Pragma("unroll") for (int p = 0; p < Cfg::B_PASSES; ++p) MOTE_DMA_B(stage_, ks_, p);          \
-  }
-  // in_flight_: whether the loads of one more K step were issued after the ones needed now
-#define MOTE_WAIT_BARRIER(in_flight_)                                                              \
-  {                                                                                                \
-    if (in_flight_) asm volatile("s_waitcnt vmcnt(%0)" :: "n"(NLOAD) : "memory");                  \
-    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");                                          \
-    asm volatile("s_barrier" ::: "memory");                                                        \
-  }
-
-  // ---- first tile ----
-  MOTE_DECODE(slot, mt, nt, kc);
-  MOTE_ROWS(mt, mrow, mend, grp);
-  uint32_t kb;
-  MOTE_KRANGE(kc, kb, ktl);
-  MOTE_POINTERS(mrow, grp, nt, kb);
-  MOTE_ISSUE_STEP(st_cur, 0);
-  if (ktl > 1) MOTE_ISSUE_STEP(st_nxt, 1);
-
-  for (;;) {
-    const int nslot = slot + stride;
-    const bool has_next = nslot < xcd_work;
-    int mt2 = mt, nt2 = nt, kc2 = kc;
-    int mrow2 = mrow, mend2 = mend, grp2 = grp, ktl2 = ktl;
-    uint32_t kb2 = kb;
-    if (has_next) {
-      MOTE_DECODE(nslot, mt2, nt2, kc2);
-      MOTE_ROWS(mt2, mrow2, mend2, grp2);
-      MOTE_KRANGE(kc2, kb2, ktl2);
-    }
-    MOTE_WAIT_BARRIER(ktl > 1);   // K step 0 visible to every wavefront; the patches of the previous tile are done
-    if constexpr (Cfg::STAGES == 4) {   // the third K step goes where patches of the previous tile were
-      if (ktl > 2) MOTE_ISSUE_STEP(st_nx2, 2);
-    }
-
-    v4f acc[A16][NB];   // token rows 16i .., channels 16b .. of the wavefront's block (gate first, then up)
-#pragma unroll
-    for (int i = 0; i < A16; ++i)
-#pragma unroll
-      for (int b = 0; b < NB; ++b) acc[i][b] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
-
-    if constexpr (Cfg::TERN) {
-      // The ring of four below with the weights unpacked from one word per lane and two fragments: eight vector
-      // instructions per four MFMAs in place of a 16-byte LDS read, an eighth of the weight bytes through L2 and LDS.  The
-      // next fragment is unpacked between the MFMAs of this one (in front of its own it cost 4 % of the GEMM).  A plane
-      // is a whole number of 64 elements, so the steps go in pairs that swap the fragment registers by name.
-      bf16x8 afx[A16], afy[A16];
-      uint32_t wx[BN_W], wy[BN_W];
-      const int w_lds = A_BYTES + (wn * BN_W * 64 + lane) * 4;
-#define MOTE_TERN_READ(af_, w_, stage_)                                                                   \
-      {                                                                                                   \
-        _Pragma("unroll") for (int i = 0; i < A16; ++i)                                                   \
-          af_[i] = *reinterpret_cast<const bf16x8*>(s_lds + (stage_) + a_lds + i * 1024);                 \
-        _Pragma("unroll") for (int f = 0; f < BN_W; ++f)                                                  \
-          w_[f] = *reinterpret_cast<const uint32_t*>(s_lds + (stage_) + w_lds + f * 256);                 \
-      }
-      // K step ks_ with the fragments (af_, w_); (afn_, wn_) take those of the next step once it has landed
-#define MOTE_TERN_STEP(ks_, af_, w_, afn_, wn_)                                                           \
-      {                                                                                                   \
-        const bool pf_ = (ks_) + 3 < ktl;                                                                 \
-        __builtin_amdgcn_sched_barrier(0);                                                                \
-        _Pragma("unroll") for (int b = 0; b < NB; ++b) {                                                  \
-          if (b == NB / 2) {                                                                              \
-            /* as below: K step ks_+1 has landed, ks_+2 and two of the three loads of ks_+3 stay in flight */ \
-            if (pf_) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"(NLOAD + 2) : "memory");          \
-            else if ((ks_) + 2 < ktl) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"(NLOAD) : "memory"); \
-            else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");                              \
-            asm volatile("s_barrier" ::: "memory");                                                       \
-          }                                                                                               \
-          acc[0][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf, af_[0], acc[0][b], 0, 0, 0);            \
-          const bf16x8 wnext_ = b + 1 < NB ? ternary_operand(w_[((b + 1) % NB) / 2], (b + 1) & 1) : ternary_operand(wn_[0], 0); \
-          _Pragma("unroll") for (int i = 1; i < A16; ++i)                                                 \
-            acc[i][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf, af_[i], acc[i][b], 0, 0, 0);          \
-          wf = wnext_;                                                                                    \
-          if (b == 0 && pf_) MOTE_DMA_A(st_nx3, (ks_) + 3, 0);                                            \
-          if (b == 1 && pf_) MOTE_DMA_B(st_nx3, (ks_) + 3, 0);                                            \
-          if (b == NB / 2) MOTE_TERN_READ(afn_, wn_, st_nxt)                                              \
-          if (b == NB / 2 + 1 && pf_) MOTE_DMA_A(st_nx3, (ks_) + 3, 1);                                   \
-          __builtin_amdgcn_sched_barrier(0);                                                              \
-        }                                                                                                 \
-        const int t_ = st_cur; st_cur = st_nxt; st_nxt = st_nx2; st_nx2 = st_nx3; st_nx3 = t_;            \
-      }
-      MOTE_TERN_READ(afx, wx, st_cur)
-      bf16x8 wf = ternary_operand(wx[0], 0);
-      for (int kt = 0; kt < ktl; kt += 2) {
-        MOTE_TERN_STEP(kt, afx, wx, afy, wy)
-        MOTE_TERN_STEP(kt + 1, afy, wy, afx, wx)
-      }
-#undef MOTE_TERN_STEP
-#undef MOTE_TERN_READ
-    } else if constexpr (Cfg::STAGES == 4) {
-      // Ring of four stages, loads three K steps ahead, ONE barrier per K step placed in the middle
-      // of the step, which contracts the first half of the weight fragments in front of it and the second half
-      // behind it.  The second half's fragments are read under the MFMAs of the first; behind the barrier the
-      // next step's stage is visible, and its first half of the weights and its activations are read under the
-      // MFMAs of the second half, an activation fragment as soon as its last MFMA of this step has been issued.  The
-      // wavefronts of the single workgroup of a CU all stop at the same barrier: reads or loads in a block of their own
-      // would leave the matrix pipe idle on every SIMD at once, so they go one by one between the MFMAs.
-      constexpr int NH0 = (Cfg::A_PASSES + 1) / 2 + (Cfg::B_PASSES + 1) / 2;   // loads issued in the first half of a step
-      constexpr int HB = NB / 2;        // weight fragments of a half
-      constexpr int NM = A16 * HB;      // MFMAs of a half
-      bf16x8 af[A16], bl[HB], bh[HB];
-#define MOTE_A_FRAG(stage_, i_) *reinterpret_cast<const bf16x8*>(s_lds + (stage_) + a_lds + (i_) * 1024)
-#define MOTE_B_FRAG(stage_, b_) *reinterpret_cast<const bf16x8*>(s_lds + (stage_) + b_lds + ((b_) / B16) * B_BYTES + ((b_) % B16) * 1024)
-      // the d_-th direct load of parity par_: the A passes par_, par_ + 2, ..., then the B passes
-#define MOTE_SIDE_DMA(d_, par_, dstage_, ks_)                                                             \
-      {                                                                                                   \
-        constexpr int NA_ = (Cfg::A_PASSES - (par_) + 1) / 2, NB_ = (Cfg::B_PASSES - (par_) + 1) / 2;     \
-        if ((d_) >= 0 && (d_) < NA_) { MOTE_DMA_A(dstage_, ks_, ((d_) >= 0 && (d_) < NA_ ? 2 * (d_) + (par_) : 0)); } \
-        else if ((d_) >= NA_ && (d_) < NA_ + NB_) { MOTE_DMA_B(dstage_, ks_, ((d_) >= NA_ && (d_) < NA_ + NB_ ? 2 * ((d_) - NA_) + (par_) : 0)); } \
-      }
-#pragma unroll
-      for (int i = 0; i < A16; ++i) af[i] = MOTE_A_FRAG(st_cur, i);
-#pragma unroll
-      for (int b = 0; b < HB; ++b) bl[b] = MOTE_B_FRAG(st_cur, b);
-      for (int kt = 0; kt < ktl; ++kt) {
-        const bool pf = kt + 3 < ktl;
-        __builtin_amdgcn_sched_barrier(0);
-        // the loads of K step kt+3 go into the stage that step kt-1 used
-#pragma unroll
-        for (int i = 0; i < A16; ++i)
-#pragma unroll
-          for (int b = 0; b < HB; ++b) {
-            const int j = i * HB + b;
-            acc[i][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bl[b], af[i], acc[i][b], 0, 0, 0);
-            if (j < HB) bh[j] = MOTE_B_FRAG(st_cur, HB + j);
-            if (pf && j >= HB && ((j - HB) & 1) == 0) MOTE_SIDE_DMA((j - HB) / 2, 0, st_nx3, kt + 3)
-            __builtin_amdgcn_sched_barrier(0);
-          }
-        // K step kt+1 has landed everywhere (kt+2 and the half of kt+3 stay in flight); every
-        // wavefront has finished its reads of this step's stage
-        if (pf) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"(NLOAD + NH0) : "memory");
-        else if (kt + 2 < ktl) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"(NLOAD) : "memory");
-        else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
-        asm volatile("s_barrier" ::: "memory");
-        // after the last step the reads are of a stage nobody uses, and dropped
-#pragma unroll
-        for (int i = 0; i < A16; ++i)
-#pragma unroll
-          for (int b = 0; b < HB; ++b) {
-            const int j = i * HB + b;
-            acc[i][HB + b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bh[b], af[i], acc[i][HB + b], 0, 0, 0);
-            if (j < HB) bl[j] = MOTE_B_FRAG(st_nxt, j);
-            if (b == HB - 1) af[i] = MOTE_A_FRAG(st_nxt, i);
-            if (pf && j >= HB && ((j - HB) & 1) == 0) MOTE_SIDE_DMA((j - HB) / 2, 1, st_nx3, kt + 3)
-            __builtin_amdgcn_sched_barrier(0);
-          }
-        const int t = st_cur; st_cur = st_nxt; st_nxt = st_nx2; st_nx2 = st_nx3; st_nx3 = t;
-      }
-      static_assert(NM >= HB + Cfg::A_PASSES + Cfg::B_PASSES, "every load of a half finds an MFMA to follow");
-#undef MOTE_SIDE_DMA
-#undef MOTE_A_FRAG
-#undef MOTE_B_FRAG
-    } else {
-      // K loop.  K step kt contracts stage st_cur while the loads of kt+2 are issued, half of them
-      // in front of each half of the MFMAs, into the stage that the barrier at the end of step kt-1 released.
-      for (int kt = 0; kt < ktl; ++kt) {
-        const bool pf = kt + 2 < ktl;
-        const unsigned char* const st = s_lds + st_cur;
-        // all fragments of the step are requested at once: the first MFMAs run while
-        // the later fragments are still on their way
-        bf16x8 af[A16], bfr[NB];
-#pragma unroll
-        for (int b = 0; b < NB / 2; ++b) bfr[b] = *reinterpret_cast<const bf16x8*>(st + b_lds + (b / B16) * B_BYTES + (b % B16) * 1024);
-#pragma unroll
-        for (int i = 0; i < A16; ++i) af[i] = *reinterpret_cast<const bf16x8*>(st + a_lds + i * 1024);
-#pragma unroll
-        for (int b = NB / 2; b < NB; ++b) bfr[b] = *reinterpret_cast<const bf16x8*>(st + b_lds + (b / B16) * B_BYTES + (b % B16) * 1024);
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int s = 0; s < 2; ++s) {
-          if (pf) {   // half s of the loads of K step kt+2
-#pragma unroll
-            for (int p = 0; p < Cfg::A_PASSES; ++p)
-              if ((p & 1) == s) MOTE_DMA_A(st_nx2, kt + 2, p);
-#pragma unroll
-            for (int p = 0; p < Cfg::B_PASSES; ++p)
-              if ((p & 1) == s) MOTE_DMA_B(st_nx2, kt + 2, p);
-          }
-#pragma unroll
-          for (int i = 0; i < A16; ++i)
-#pragma unroll
-            for (int b = s * (NB / 2); b < (s + 1) * (NB / 2); ++b)
-              acc[i][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bfr[b], af[i], acc[i][b], 0, 0, 0);
-          __builtin_amdgcn_sched_barrier(0);  // keep each half's loads with its half
-        }
-        // K step kt+1 landed everywhere (kt+2 stays in flight); after the last step: every
-        // wavefront has read its last stage
-        MOTE_WAIT_BARRIER(pf);
-        const int t = st_cur; st_cur = st_nxt; st_nxt = st_nx2; st_nx2 = t;
-      }
-    }
-
-    // Start the next tile now: its first two K steps travel while this tile runs its epilogue.
-    // The stage of the last K step (now st_nx2) is free until the next tile's first barrier.
-    if (has_next) {
-      MOTE_POINTERS(mrow2, grp2, nt2, kb2);
-      MOTE_ISSUE_STEP(st_cur, 0);
-      if (ktl2 > 1) MOTE_ISSUE_STEP(st_nxt, 1);
-    }
-
-    // ---- epilogue ----
-    // In registers lane l owns token row r16 and four consecutive output channels of every
-    // fragment (4 * quart .. +3).  Each wavefront writes one 32-row block of PATCH_F fragments into its
-    // private LDS patch and reads it back row-major, 16 bytes per lane, so that a global store
-    // instruction covers whole 128-byte rows of the block.
-    constexpr int PATCH_F = Cfg::PATCH_F;
-    constexpr int PATCH_ROW = Cfg::PATCH_ROW;
-    constexpr int OUT_ROW_BYTES = PATCH_F * 32 * Cfg::OUT_BYTES;
-    constexpr int LANES_PER_ROW = OUT_ROW_BYTES / 16;
-    constexpr int ROWS_PER_READ = 64 / LANES_PER_ROW;
-    unsigned char* const patch =
-        Cfg::PATCH_IN_TWO ? s_lds + (wave < Cfg::WAVES / 2 ? st_nx2 : st_nx3) + (wave % (Cfg::WAVES / 2)) * Cfg::PATCH_BYTES
-                          : s_lds + (Cfg::PATCH_IN_STAGE ? st_nx2 : Cfg::STAGES * STAGE_BYTES) + wave * Cfg::PATCH_BYTES;
-    const int m0 = mrow, n_wave0 = nt * BN + wn * BN_W * 32;
-    const int rd_row = lane / LANES_PER_ROW, rd_chunk = lane % LANES_PER_ROW;
-    if (a.scale0 != nullptr) {   // row scales of quantised weights (uniform branch, not taken by the bf16 expert)
-#pragma unroll
-      for (int b = 0; b < B16; ++b) {
-        const int ch = min(n_wave0 + b * 16 + 4 * quart, N - 4);
-        const float4 s0 = *reinterpret_cast<const float4*>(a.scale0 + static_cast<int64_t>(grp) * N + ch);
-        float4 s1 = s0;
-        if constexpr (NMAT == 2) s1 = *reinterpret_cast<const float4*>(a.scale1 + ch);
-#pragma unroll
-        for (int i = 0; i < A16; ++i) {
-          acc[i][b].x *= s0.x; acc[i][b].y *= s0.y; acc[i][b].z *= s0.z; acc[i][b].w *= s0.w;
-          if constexpr (NMAT == 2) {
-            v4f& au = acc[i][(NMAT - 1) * B16 + b];
-            au.x *= s1.x; au.y *= s1.y; au.z *= s1.z; au.w *= s1.w;
-          }
-        }
-      }
-    }
-#pragma unroll
-    for (int i = 0; i < BM_W; ++i) {
-#pragma unroll
-      for (int f0 = 0; f0 < BN_W; f0 += PATCH_F) {
-#pragma unroll
-        for (int bb = 0; bb < 2 * PATCH_F; ++bb) {
-          const int b = 2 * f0 + bb, pcol = bb * 16 + 4 * quart;   // channel inside the patch row
-#pragma unroll
-          for (int r = 0; r < 2; ++r) {
-            const v4f v = acc[2 * i + r][b];
-            unsigned char* const dst = patch + (r * 16 + r16) * PATCH_ROW + pcol * Cfg::OUT_BYTES;
-            if constexpr (Cfg::MODE == 0) {
-              const v4f u = acc[2 * i + r][(NMAT - 1) * B16 + b];
-              uint2 packed;
-              packed.x = cvt_pk_bf16(u.x * silu_fast(v.x), u.y * silu_fast(v.y));
-              packed.y = cvt_pk_bf16(u.z * silu_fast(v.z), u.w * silu_fast(v.w));
-              *reinterpret_cast<uint2*>(dst) = packed;
-            } else {
-              *reinterpret_cast<float4*>(dst) = make_float4(v.x, v.y, v.z, v.w);
-            }
-          }
-        }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        const int rd_n = n_wave0 + f0 * 32 + rd_chunk * (16 / Cfg::OUT_BYTES);   // first output channel of this lane's 16 bytes
-#pragma unroll
-        for (int p = 0; p < 32 / ROWS_PER_READ; ++p) {
-          const int pr = p * ROWS_PER_READ + rd_row;
-          const u4 v = *reinterpret_cast<const u4*>(patch + pr * PATCH_ROW + rd_chunk * 16);
-          const int orow = m0 + wm * BM_W * 32 + i * 32 + pr;
-          if (orow < mend && rd_n < N) {
-            const int64_t o = static_cast<int64_t>(orow) * N + rd_n;
-            if constexpr (Cfg::MODE == 0) *reinterpret_cast<u4*>(a.h_out + o) = v;
-            else *reinterpret_cast<u4*>(a.y_out + static_cast<int64_t>(kc) * a.plane_stride + o) = v;
-          }
-        }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-      }
-    }
-    if (!has_next) break;
-    // No barrier here: the patches are private and their stage is not refilled before the next
-    // tile's first barrier.
-    slot = nslot; mt = mt2; nt = nt2; kc = kc2; ktl = ktl2;
-    mrow = mrow2; mend = mend2; grp = grp2; kb = kb2;
-  }
-#undef MOTE_DECODE
-#undef MOTE_ROWS
-#undef MOTE_KRANGE
-#undef MOTE_POINTERS
-#undef MOTE_DMA
-#undef MOTE_DMA_A
-#undef MOTE_DMA_B
-#undef MOTE_ISSUE_STEP
-#undef MOTE_WAIT_BARRIER
-}
-
-template <typename Cfg>
-__global__ __launch_bounds__(Cfg::THREADS, Cfg::MIN_BLOCKS) void shared_gemm_kernel(SharedGemmArgs a, int n_ntiles,
-                                                                                   int kplanes, int ktp, int group_m) {
-  shared_gemm_body<Cfg, 0>(a, nullptr, n_ntiles, kplanes, ktp, group_m);
-}
-
-template <typename Cfg>
-__global__ __launch_bounds__(Cfg::THREADS, Cfg::MIN_BLOCKS) void grouped_gemm_kernel(SharedGemmArgs a, RowGroups rg,
-                                                                                    int n_ntiles, int kplanes, int ktp,
-                                                                                    int group_m) {
-  shared_gemm_body<Cfg, 1>(a, &rg, n_ntiles, kplanes, ktp, group_m);
-}
-
-template <typename Cfg>
-__global__ __launch_bounds__(Cfg::THREADS, Cfg::MIN_BLOCKS) void kgrouped_gemm_kernel(SharedGemmArgs a, RowGroups rg,
-                                                                                     int n_ntiles, int group_m) {
-  shared_gemm_body<Cfg, 2>(a, &rg, n_ntiles, rg.n, 0, group_m);
-}
-
+// K ranges: plane p of the kplanes = rg->n planes contracts the K range row0[p] .. row0[p+1]-1 (multiples of 64
+// elements; an empty range gives a plane of zeros).
+//
+// Tile order of all kernels here.  Persistent workgroups, dealt to the 8 XCDs round-robin by linear id: XCD x owns the
+// (channel tile, K plane) pairs x, x+8, ... (the row tiles x, x+8, ... when there are fewer than 16 pairs); inside an XCD
+// the tiles are ordered in bands of group_m row tiles, row tile fastest, so the resident workgroups share both
+// activation tiles and weight slices in L2.  With kplanes > 1 the contraction is cut into planes of ktp K chunks; each
+// plane writes its own partial output, added later in plane order.
+//
+// Loads: raw buffer loads written in assembly (the compiler has no exact model of outstanding direct-to-LDS loads across
+// these loops).  Vector-memory operations complete in issue order, so waiting for "all but the N youngest" retires the
+// chunk that is about to be contracted while later ones stay in flight; anything else issued since (stores of the
+// previous epilogue) only makes that wait stricter.
 
 // Large problems: 256 x 256 tiles (256 x (128+128) in gate-up mode), one workgroup of eight wavefronts per CU, each
 // 64 rows x 128 channels.  K goes in chunks of 64 elements, so that a tile row in LDS is 128 bytes and a direct load
-// brings eight rows x one whole cache line: on 64-byte rows (the kernel above) a load needs twice the requests, and
+// brings eight rows x one whole cache line: on 64-byte rows a load needs twice the requests, and
 // loads alone, without any MFMA, peak at 14 TB/s over the chip where 128-byte rows reach 25 - this kernel asks for 10
 // to 13.
 //
@@ -591,8 +111,8 @@ __global__ __launch_bounds__(Cfg::THREADS, Cfg::MIN_BLOCKS) void kgrouped_gemm_k
 // 591 -> 511 us (1.44 PFLOP/s), down 314 -> 250 (1.48); 16384 x 3584 x 18944 3861 -> 3145, 1995 -> 1612.  What bounds it is
 // power: with operands of zeros the first takes 374 us at 2.4 GHz, with random ones the chip clocks at 1.75 GHz.
 //
-// GROUPED: 0 plain, 1 row groups, 2 K ranges (as above).
-// TERN: weights as 2-bit codes in the blocks described at SharedCfg, unpacked in registers (eight vector instructions per
+// GROUPED: 0 plain, 1 row groups, 2 K ranges.
+// TERN: weights as 2-bit codes in the blocks described above, unpacked in registers (eight vector instructions per
 // four MFMAs).  The weights of a chunk are 4 KiB, so the ring is four whole stages (A, then weights) and the loads run
 // three chunks ahead; the fragments of a half chunk are read during the half before it, into the other one of two
 // register sets, and the barrier stands in the middle of the second half.
@@ -628,7 +148,7 @@ __device__ __forceinline__ void big_gemm_body(const SharedGemmArgs& a, const Row
   const int frag = r16 * 128 + ((quart ^ (r16 >> 1)) << 4);
   const int a_lds = wm * 64 * 128 + frag, b_lds = wn * (BN / 2) * 128 + frag;
 
-  // Tile order: as in shared_gemm_body; with row groups two such lists one after the other, the row tiles below
+  // Tile order: as above; with row groups two such lists one after the other, the row tiles below
   // rg->split_mt with one plane and the others with kplanes.
   int n_mtiles = (M + BM - 1) / BM;
   if constexpr (GROUPED == 1) n_mtiles = rg->tile0[rg->n];
@@ -993,6 +513,333 @@ __global__ __launch_bounds__(512, 2) void big_grouped_gemm_kernel(SharedGemmArgs
   big_gemm_body<BigCfg<1, true>, 1>(a, &rg, n_ntiles, kplanes, ktp, group_m);
 }
 
+
+// Mid-size problems, where a CU has one or two tiles: 128-row tiles, one workgroup of eight wavefronts per CU, and a ring
+// deep enough to cover the latency of a load by itself: K chunks of 64 elements (128-byte LDS rows, as above), the loads
+// four (128 x 128) or two (128 x 256) chunks, some 2500 cycles, ahead.  A chunk is two halves of its K; the fragments of a
+// half are read during the half before it, into the other one of two register sets.  The one barrier of a chunk stands
+// between its halves: it publishes the next chunk and frees this one's stage, both its halves' fragments having been read.
+// BNT: channels of a tile, both matrices together.  GROUPED: 0 plain, 1 row groups, 2 K ranges.  TERN: ternary weights, a
+// half's fragments unpacked in front of its MFMAs.
+template <int MODE_, int BNT_, bool TERN_ = false>
+struct MidCfg {
+  static constexpr int MODE = MODE_;
+  static constexpr int NMAT = MODE_ == 0 ? 2 : 1;
+  static constexpr int BM = 128, BNT = BNT_, BN = BNT_ / NMAT, WAVES = 8, THREADS = 512;
+  static constexpr int WAVES_M = BNT_ == 128 ? 4 : 2, WAVES_N = 8 / WAVES_M;
+  static constexpr int A16 = BM / WAVES_M / 16, NB = BNT_ / WAVES_N / 16, B16 = NB / NMAT;   // fragments of a wavefront
+  static constexpr bool TERN = TERN_;
+  static constexpr int A_BYTES = BM * 128, STAGE = A_BYTES + BNT_ * (TERN_ ? 16 : 128);
+  static constexpr int STAGES = BNT_ == 128 ? 5 : 3, LDS_BYTES = STAGES * STAGE;
+  static constexpr int A_LOADS = BM / 64, B_LOADS = TERN_ ? 1 : BNT_ / 64, NLOAD = A_LOADS + B_LOADS;   // per wavefront and chunk
+  static constexpr int AHEAD = STAGES == 5 ? 3 : 2;   // chunks of the next tile requested in front of the epilogue; the patches have the other stages
+  static constexpr int OUT_BYTES = MODE_ == 0 ? 2 : 4;
+  static constexpr int PF = 2;                                        // fragments of a patch row
+  static constexpr int PATCH_ROW = PF * 16 * OUT_BYTES + 16, PATCH_BYTES = 32 * PATCH_ROW;
+  static_assert(B16 % PF == 0 && A16 % 2 == 0, "whole patches");
+  static_assert(STAGES == 5 ? 4 * PATCH_BYTES <= STAGE : 8 * PATCH_BYTES <= STAGE, "the patches fit the free stages");
+  static_assert(LDS_BYTES <= 163840 && (STAGES - 2) * NLOAD < 64, "LDS of a CU, vmcnt field");
+  static_assert(A16 * NB >= NLOAD, "every load of a chunk finds an MFMA to follow");
+  static_assert(!TERN_ || (MODE_ == 1 && BNT_ == 128), "ternary weights: four blocks of 32 channels, a wavefront brings one half of one");
+};
+
+template <typename Cfg, int GROUPED>
+__device__ __forceinline__ void mid_gemm_body(const SharedGemmArgs& a, const RowGroups* rg, int n_ntiles, int kplanes, int ktp, int group_m) {
+  constexpr int NMAT = Cfg::NMAT, BM = Cfg::BM, BN = Cfg::BN, STAGE = Cfg::STAGE, STAGES = Cfg::STAGES;
+  constexpr int A16 = Cfg::A16, NB = Cfg::NB, B16 = Cfg::B16, NLOAD = Cfg::NLOAD;
+  extern __shared__ __attribute__((aligned(16))) unsigned char s_lds[];
+  const int M = a.M, N = a.N, K = a.K;
+  const int KT = K >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int wave_u = __builtin_amdgcn_readfirstlane(wave);
+  const int wm = wave % Cfg::WAVES_M, wn = wave / Cfg::WAVES_M;
+  const int r16 = lane & 15, quart = lane >> 4;
+  const uint32_t lds0 = (uint32_t)(uintptr_t)((__attribute__((address_space(3))) unsigned char*)s_lds);
+  const int frag = r16 * 128 + ((quart ^ (r16 >> 1)) << 4);   // as in big_gemm_body; K half 1 at ^ 64
+  const int a_lds = wm * A16 * 2048 + frag, b_lds = Cfg::A_BYTES + wn * B16 * 2048 + frag;
+
+  n_ntiles *= kplanes;
+  int n_mtiles = (M + BM - 1) / BM;
+  if constexpr (GROUPED == 1) n_mtiles = rg->tile0[rg->n];
+  const int xcd = blockIdx.x & 7;
+  const bool split_n = n_ntiles >= 16;
+  const int xcd_ntiles = split_n ? (n_ntiles - xcd + 7) >> 3 : n_ntiles;
+  const int xcd_mtiles = split_n ? n_mtiles : (n_mtiles - xcd + 7) >> 3;
+  const int xcd_work = xcd_ntiles * xcd_mtiles;
+  const int per_group = group_m * xcd_ntiles;
+  const int stride = gridDim.x >> 3;
+  int slot = blockIdx.x >> 3;
+  if (slot >= xcd_work) return;
+
+  constexpr int kBufferFlags = 0x00020000;   // raw buffer, 32-bit data format
+  auto make_rsrc = [&](const void* base, int64_t bytes) {
+    const uint64_t p = reinterpret_cast<uint64_t>(base);
+    v4i r;
+    r.x = static_cast<int>(static_cast<uint32_t>(p));
+    r.y = static_cast<int>(static_cast<uint32_t>(p >> 32) & 0xFFFFu);
+    r.z = static_cast<int>(bytes);
+    r.w = kBufferFlags;
+    return r;
+  };
+  const v4i rsrc_a = make_rsrc(a.act, static_cast<int64_t>(M) * K * 2);
+  const v4i rsrc_b0 = make_rsrc(a.w0, Cfg::TERN ? static_cast<int64_t>(GROUPED == 1 ? rg->n : 1) * N * K / 4 : static_cast<int64_t>(N) * K * 2);
+  const v4i rsrc_b1 = make_rsrc(NMAT == 2 ? a.w1 : a.w0, static_cast<int64_t>(N) * K * 2);
+  const int ld_row = wave_u * 8 + (lane >> 3);   // row of a 64-row loader pass, physical chunk l % 8
+  const uint32_t ld_chunk = static_cast<uint32_t>(((lane & 7) ^ ((ld_row >> 1) & 7)) << 4);
+  uint32_t a_off[Cfg::A_LOADS], b_off[Cfg::B_LOADS];
+  int mt, nt, kc, ktl;
+  int mrow, mend = M, grp = 0;   // first row of the tile, one past the last row it may store, its group (0 without groups)
+  int st = 0;   // byte offset of the current chunk's stage; chunk c + i is at st + i stages, wrapped
+
+#define MOTE_STAGE(i_) (st + (i_) * STAGE >= STAGES * STAGE ? st + (i_) * STAGE - STAGES * STAGE : st + (i_) * STAGE)
+#define MOTE_DECODE(slot_, mt_, nt_, kc_)                                       \
+  {                                                                             \
+    const int grp_ = (slot_) / per_group;                                       \
+    const int in_ = (slot_) - grp_ * per_group;                                 \
+    const int gsz_ = min(xcd_mtiles - grp_ * group_m, group_m);                 \
+    const int ni_ = in_ / gsz_, mi_ = grp_ * group_m + (in_ - ni_ * gsz_);      \
+    mt_ = split_n ? mi_ : xcd + 8 * mi_;                                        \
+    const int ntk_ = split_n ? xcd + 8 * ni_ : ni_;                             \
+    nt_ = ntk_ / kplanes;                                                       \
+    kc_ = ntk_ - nt_ * kplanes;                                                 \
+  }
+#define MOTE_KRANGE(kc_, kb_, ktl_)                                             \
+  {                                                                             \
+    if constexpr (GROUPED == 2) {                                               \
+      kb_ = static_cast<uint32_t>(rg->row0[kc_]) * 2u;                          \
+      ktl_ = (rg->row0[(kc_) + 1] - rg->row0[kc_]) >> 6;                        \
+    } else {                                                                    \
+      kb_ = static_cast<uint32_t>((kc_) * ktp) * 128u;                          \
+      ktl_ = min(ktp, KT - (kc_) * ktp);                                        \
+    }                                                                           \
+  }
+#define MOTE_ROWS(mt_, mrow_, mend_, grp_)                                      \
+  {                                                                             \
+    if constexpr (GROUPED == 1) {                                               \
+      int e_ = 0;                                                               \
+      while (e_ + 1 < rg->n && rg->tile0[e_ + 1] <= (mt_)) ++e_;                \
+      grp_ = e_;                                                                \
+      mrow_ = rg->row0[e_] + ((mt_) - rg->tile0[e_]) * BM;                      \
+      mend_ = rg->row0[e_ + 1];                                                 \
+    } else {                                                                    \
+      mrow_ = (mt_) * BM;                                                       \
+    }                                                                           \
+  }
+#define MOTE_POINTERS(mrow_, grp_, nt_, kb_)                                                       \
+  {                                                                                                \
+    const uint32_t k0_ = (kb_) + ld_chunk;                                                         \
+    _Pragma("unroll") for (int p = 0; p < Cfg::A_LOADS; ++p)                                       \
+      a_off[p] = static_cast<uint32_t>(min((mrow_) + p * 64 + ld_row, M - 1)) * static_cast<uint32_t>(K) * 2u + k0_; \
+    if constexpr (Cfg::TERN) {                                                                     \
+      const int blk_ = min((nt_) * (BN / 32) + (wave_u & 3), (N >> 5) - 1) + (grp_) * (N >> 5);    \
+      b_off[0] = static_cast<uint32_t>(blk_) * static_cast<uint32_t>(K) * 8u + (kb_) * 4u + (wave_u >> 2) * 256u + lane * 4u; \
+    } else _Pragma("unroll") for (int p = 0; p < Cfg::B_LOADS; ++p)                                \
+      b_off[p] = static_cast<uint32_t>(min((nt_) * BN + (p * 64) % BN + ld_row, N - 1)) * static_cast<uint32_t>(K) * 2u + k0_; \
+  }
+  // load p_ of chunk ks_: the passes of A, then those of B (M0: see ternary_gemm.hip)
+#define MOTE_DMA(stage_, ks_, p_)                                                                  \
+  {                                                                                                \
+    if (Cfg::TERN && (p_) == Cfg::A_LOADS)                                                         \
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, %3 offen lds"         \
+                   :: "s"(lds0 + (stage_) + Cfg::A_BYTES + wave_u * 256), "v"(b_off[0]), "s"(rsrc_b0), "s"((ks_) * 512) : "memory"); \
+    else                                                                                           \
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"       \
+                   :: "s"(lds0 + (stage_) + ((p_) * 64 + wave_u * 8) * 128),                       \
+                      "v"((p_) < Cfg::A_LOADS ? a_off[(p_) < Cfg::A_LOADS ? (p_) : 0] : b_off[(p_) < Cfg::A_LOADS ? 0 : (p_) - Cfg::A_LOADS]), \
+                      "s"((p_) < Cfg::A_LOADS ? rsrc_a : (((p_) - Cfg::A_LOADS) * 64) / BN == 0 ? rsrc_b0 : rsrc_b1), "s"((ks_) * 128) : "memory"); \
+  }
+#define MOTE_ISSUE(stage_, ks_) { _Pragma("unroll") for (int p = 0; p < NLOAD; ++p) MOTE_DMA(stage_, ks_, p); }
+#define MOTE_A_FRAG(stage_, h_, i_) *reinterpret_cast<const bf16x8*>(s_lds + (stage_) + (a_lds ^ ((h_) * 64)) + (i_) * 2048)
+#define MOTE_B_FRAG(stage_, h_, b_) \
+  *reinterpret_cast<const bf16x8*>(s_lds + (stage_) + (b_lds ^ ((h_) * 64)) + ((b_) / B16) * (BN * 128) + ((b_) % B16) * 2048)
+  // fragment r_ of a half: the weights, then the activations
+#define MOTE_READ(af_, b_, w_, stage_, h_, r_)                                                     \
+  {                                                                                                \
+    if (Cfg::TERN && (r_) < NB) {                                                                  \
+      if (((r_) & 1) == 0)                                                                         \
+        w_[(r_) < NB ? (r_) / 2 : 0] = *reinterpret_cast<const uint32_t*>(                         \
+            s_lds + (stage_) + Cfg::A_BYTES + ((h_) * 4 + wn * (NB / 2) + ((r_) < NB ? (r_) / 2 : 0)) * 256 + lane * 4); \
+    } else if ((r_) < NB) b_[(r_) < NB ? (r_) : 0] = MOTE_B_FRAG(stage_, h_, (r_) < NB ? (r_) : 0);       \
+    else if ((r_) < NB + A16) af_[(r_) >= NB && (r_) < NB + A16 ? (r_) - NB : 0] = MOTE_A_FRAG(stage_, h_, (r_) >= NB && (r_) < NB + A16 ? (r_) - NB : 0); \
+  }
+
+  MOTE_DECODE(slot, mt, nt, kc);
+  uint32_t kb;
+  MOTE_KRANGE(kc, kb, ktl);
+  MOTE_ROWS(mt, mrow, mend, grp);
+  MOTE_POINTERS(mrow, grp, nt, kb);
+#pragma unroll
+  for (int i = 0; i < Cfg::AHEAD; ++i)
+    if (i < ktl) MOTE_ISSUE(MOTE_STAGE(i), i);
+
+  for (;;) {
+    const int nslot = slot + stride;
+    const bool has_next = nslot < xcd_work;
+    int mt2 = mt, nt2 = nt, kc2 = kc, ktl2 = ktl, mrow2 = mrow, mend2 = mend, grp2 = grp;
+    uint32_t kb2 = kb;
+    if (has_next) {
+      MOTE_DECODE(nslot, mt2, nt2, kc2);
+      MOTE_ROWS(mt2, mrow2, mend2, grp2);
+      MOTE_KRANGE(kc2, kb2, ktl2);
+    }
+    // chunk 0 visible to every wavefront, the patches of the previous tile done
+    if (ktl >= Cfg::AHEAD) asm volatile("s_waitcnt vmcnt(%0)" :: "n"((Cfg::AHEAD - 1) * NLOAD) : "memory");
+    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    asm volatile("s_barrier" ::: "memory");
+#pragma unroll
+    for (int i = Cfg::AHEAD; i < STAGES; ++i)
+      if (i < ktl) MOTE_ISSUE(MOTE_STAGE(i), i);
+
+    v4f acc[A16][NB];
+#pragma unroll
+    for (int i = 0; i < A16; ++i)
+#pragma unroll
+      for (int b = 0; b < NB; ++b) acc[i][b] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+    bf16x8 ax[A16], bx[NB], ay[A16], by[NB];
+    uint32_t wx[NB / 2], wy[NB / 2];
+#pragma unroll
+    for (int r = 0; r < NB + A16; ++r) MOTE_READ(ax, bx, wx, st, 0, r)
+    // a half: MFMAs of (af_, b_), behind MFMA j the statement side_(j)
+#define MOTE_HALF(af_, b_, w_, side_)                                                              \
+    if constexpr (Cfg::TERN) { _Pragma("unroll") for (int b = 0; b < NB; ++b) b_[b] = ternary_operand(w_[b / 2], b & 1); } \
+    _Pragma("unroll") for (int i = 0; i < A16; ++i)                                                \
+      _Pragma("unroll") for (int b = 0; b < NB; ++b) {                                             \
+        const int j = i * NB + b;                                                                  \
+        acc[i][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b_[b], af_[i], acc[i][b], 0, 0, 0);    \
+        side_                                                                                      \
+        __builtin_amdgcn_sched_barrier(0);                                                         \
+      }
+    // chunk c; PF_: with the requests of chunk c + STAGES into this chunk's stage.  After the last chunk the reads of the
+    // second half are of a stage nobody uses, and dropped.
+#define MOTE_CHUNK(PF_, wait_)                                                                     \
+    {                                                                                              \
+      const int nx = MOTE_STAGE(1);                                                                \
+      __builtin_amdgcn_sched_barrier(0);                                                           \
+      MOTE_HALF(ax, bx, wx, {                                                                          \
+        if (j < (NB + A16 + 1) / 2) { MOTE_READ(ay, by, wy, st, 1, 2 * j) MOTE_READ(ay, by, wy, st, 1, 2 * j + 1) } \
+      })                                                                                           \
+      wait_                                                                                        \
+      asm volatile("s_barrier" ::: "memory");                                                      \
+      MOTE_HALF(ay, by, wy, {                                                                          \
+        if (j < (NB + A16 + 1) / 2) { MOTE_READ(ax, bx, wx, nx, 0, 2 * j) MOTE_READ(ax, bx, wx, nx, 0, 2 * j + 1) } \
+        if (PF_ && j >= A16 * NB - NLOAD) MOTE_DMA(st, c + STAGES, j >= A16 * NB - NLOAD ? j - (A16 * NB - NLOAD) : 0); \
+      })                                                                                           \
+      st = nx;                                                                                     \
+    }
+    int c = 0;
+    for (; c + STAGES < ktl; ++c)
+      MOTE_CHUNK(true, asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"((STAGES - 2) * NLOAD) : "memory");)
+    for (; c < ktl; ++c)
+      MOTE_CHUNK(false, {
+        const int later = ktl - 2 - c;   // chunks behind the next one that are on their way
+        if (STAGES > 4 && later >= 3) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"(3 * NLOAD) : "memory");
+        else if (STAGES > 3 && later >= 2) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"(2 * NLOAD) : "memory");
+        else if (later >= 1) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"(NLOAD) : "memory");
+        else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+      })
+#undef MOTE_CHUNK
+#undef MOTE_HALF
+
+    if (has_next) {   // the next tile's first loads travel while this tile runs its epilogue in the stages behind them
+      MOTE_POINTERS(mrow2, grp2, nt2, kb2);
+#pragma unroll
+      for (int i = 0; i < Cfg::AHEAD; ++i)
+        if (i < ktl2) MOTE_ISSUE(MOTE_STAGE(i), i);
+    }
+
+    // ---- epilogue: as in big_gemm_body, patches of 32 rows x PF fragments ----
+    constexpr int PF = Cfg::PF, LANES_PER_ROW = PF * 16 * Cfg::OUT_BYTES / 16, ROWS_PER_READ = 64 / LANES_PER_ROW;
+    unsigned char* const patch = STAGES == 5 ? s_lds + (wave < 4 ? MOTE_STAGE(3) : MOTE_STAGE(4)) + (wave & 3) * Cfg::PATCH_BYTES
+                                             : s_lds + MOTE_STAGE(2) + wave * Cfg::PATCH_BYTES;
+    const int n_wave0 = nt * BN + wn * B16 * 16;
+    const int rd_row = lane / LANES_PER_ROW, rd_chunk = lane % LANES_PER_ROW;
+    if (a.scale0 != nullptr) {
+#pragma unroll
+      for (int b = 0; b < B16; ++b) {
+        const int ch = min(n_wave0 + b * 16 + 4 * quart, N - 4);
+        const float4 s0_ = *reinterpret_cast<const float4*>(a.scale0 + static_cast<int64_t>(grp) * N + ch);
+        float4 s1_ = s0_;
+        if constexpr (NMAT == 2) s1_ = *reinterpret_cast<const float4*>(a.scale1 + ch);
+#pragma unroll
+        for (int i = 0; i < A16; ++i) {
+          acc[i][b].x *= s0_.x; acc[i][b].y *= s0_.y; acc[i][b].z *= s0_.z; acc[i][b].w *= s0_.w;
+          if constexpr (NMAT == 2) {
+            v4f& au = acc[i][(NMAT - 1) * B16 + b];
+            au.x *= s1_.x; au.y *= s1_.y; au.z *= s1_.z; au.w *= s1_.w;
+          }
+        }
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < A16; i += 2) {
+#pragma unroll
+      for (int f0 = 0; f0 < B16; f0 += PF) {
+#pragma unroll
+        for (int bb = 0; bb < PF; ++bb) {
+          const int b = f0 + bb;
+#pragma unroll
+          for (int r = 0; r < 2; ++r) {
+            const v4f v = acc[i + r][b];
+            unsigned char* const dst = patch + (r * 16 + r16) * Cfg::PATCH_ROW + (bb * 16 + 4 * quart) * Cfg::OUT_BYTES;
+            if constexpr (Cfg::MODE == 0) {
+              const v4f u = acc[i + r][(NMAT - 1) * B16 + b];
+              uint2 packed;
+              packed.x = cvt_pk_bf16(u.x * silu_fast(v.x), u.y * silu_fast(v.y));
+              packed.y = cvt_pk_bf16(u.z * silu_fast(v.z), u.w * silu_fast(v.w));
+              *reinterpret_cast<uint2*>(dst) = packed;
+            } else {
+              *reinterpret_cast<float4*>(dst) = make_float4(v.x, v.y, v.z, v.w);
+            }
+          }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        const int rd_n = n_wave0 + f0 * 16 + rd_chunk * (16 / Cfg::OUT_BYTES);
+#pragma unroll
+        for (int p = 0; p < 32 / ROWS_PER_READ; ++p) {
+          const int pr = p * ROWS_PER_READ + rd_row;
+          const u4 v = *reinterpret_cast<const u4*>(patch + pr * Cfg::PATCH_ROW + rd_chunk * 16);
+          const int orow = mrow + wm * A16 * 16 + i * 16 + pr;
+          if (orow < mend && rd_n < N) {
+            const int64_t o = static_cast<int64_t>(orow) * N + rd_n;
+            if constexpr (Cfg::MODE == 0) *reinterpret_cast<u4*>(a.h_out + o) = v;
+            else *reinterpret_cast<u4*>(a.y_out + static_cast<int64_t>(kc) * a.plane_stride + o) = v;
+          }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+      }
+    }
+    if (!has_next) break;
+    slot = nslot; mt = mt2; nt = nt2; kc = kc2; ktl = ktl2; kb = kb2; mrow = mrow2; mend = mend2; grp = grp2;
+  }
+#undef MOTE_STAGE
+#undef MOTE_DECODE
+#undef MOTE_KRANGE
+#undef MOTE_POINTERS
+#undef MOTE_ROWS
+#undef MOTE_DMA
+#undef MOTE_ISSUE
+#undef MOTE_A_FRAG
+#undef MOTE_B_FRAG
+#undef MOTE_READ
+}
+
+template <typename Cfg>
+__global__ __launch_bounds__(Cfg::THREADS, 2) void mid_gemm_kernel(SharedGemmArgs a, int n_ntiles, int kplanes, int ktp, int group_m) {
+  mid_gemm_body<Cfg, 0>(a, nullptr, n_ntiles, kplanes, ktp, group_m);
+}
+template <typename Cfg>
+__global__ __launch_bounds__(Cfg::THREADS, 2) void mid_kgrouped_gemm_kernel(SharedGemmArgs a, RowGroups rg, int n_ntiles, int group_m) {
+  mid_gemm_body<Cfg, 2>(a, &rg, n_ntiles, rg.n, 0, group_m);
+}
+// ternary weights, groups of rows
+__global__ __launch_bounds__(512, 2) void mid_grouped_gemm_kernel(SharedGemmArgs a, RowGroups rg, int n_ntiles, int kplanes, int ktp, int group_m) {
+  mid_gemm_body<MidCfg<1, 128, true>, 1>(a, &rg, n_ntiles, kplanes, ktp, group_m);
+}
+
 static int shared_cu_count() {
   static int n = 0;
   if (n == 0) {
@@ -1006,35 +853,18 @@ static int shared_cu_count() {
 
 static int shared_variant() { return knob(kKnobSharedVariant); }
 
-// kplanes64 / the plane length are counted in 64-element units (the workspace layout depends
-// on shared_down_planes, which predates the 32-element K step).
-template <typename Cfg>
-static hipError_t launch_shared_cfg(const SharedGemmArgs& a, int kplanes, hipStream_t stream) {
-  const int n_ntiles = (a.N + Cfg::BN - 1) / Cfg::BN;
-  const int KT64 = a.K >> 6;
-  const int ktp = 2 * ((KT64 + kplanes - 1) / kplanes);   // K steps of 32 per plane
-  const int n_mtiles = (a.M + Cfg::BM - 1) / Cfg::BM;
-  const size_t lds = Cfg::LDS_BYTES;
-  static bool attr_set = false;
-  static int resident = Cfg::MIN_BLOCKS;
-  if (!attr_set) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(shared_gemm_kernel<Cfg>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
-    if (e != hipSuccess) return e;
-    int n = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, shared_gemm_kernel<Cfg>, Cfg::THREADS, lds) == hipSuccess && n > 0)
-      resident = n;
-    attr_set = true;
-  }
-  const int64_t tiles = static_cast<int64_t>(n_mtiles) * n_ntiles * kplanes;
-  int64_t blocks = static_cast<int64_t>(shared_cu_count()) * resident;
-  if (blocks > tiles) blocks = (tiles + 7) / 8 * 8;
-  shared_gemm_kernel<Cfg><<<static_cast<unsigned>(blocks), Cfg::THREADS, lds, stream>>>(a, n_ntiles, kplanes, ktp, tile_group_m());
-  return hipGetLastError();
-}
-
 constexpr int kBigBand = 4;   // row tiles per band, see launch_big_cfg
 
+// Tiles of the XCD that owns most of them (see the tile order), i.e. eight times that many workgroups take them in one round.
+static int64_t longest_list(int64_t mt, int64_t nk) { return nk >= 16 ? (nk + 7) / 8 * mt : (mt + 7) / 8 * nk; }
+static unsigned gemm_blocks(int64_t longest) { return static_cast<unsigned>(std::min<int64_t>(shared_cu_count() / 8 * 8, longest * 8)); }
+
+template <typename K>
+static hipError_t allow_lds(K* kernel, int bytes) {
+  return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+}
+
+// The plain kernels (rg == nullptr), or one plane per K range.
 template <typename Cfg>
 static hipError_t launch_big_cfg(const SharedGemmArgs& a, int kplanes, const RowGroups* rg, hipStream_t stream) {
   const int n_ntiles = (a.N + Cfg::BN - 1) / Cfg::BN, n_mtiles = (a.M + Cfg::BM - 1) / Cfg::BM;
@@ -1042,26 +872,83 @@ static hipError_t launch_big_cfg(const SharedGemmArgs& a, int kplanes, const Row
   const int ktp = (KT + kplanes - 1) / kplanes;   // chunks per plane
   static bool attr_set = false;
   if (!attr_set) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(big_gemm_kernel<Cfg>), hipFuncAttributeMaxDynamicSharedMemorySize, Cfg::LDS_BYTES);
-    if constexpr (Cfg::MODE == 1) if (e == hipSuccess)
-      e = hipFuncSetAttribute(reinterpret_cast<const void*>(big_kgrouped_gemm_kernel<Cfg>), hipFuncAttributeMaxDynamicSharedMemorySize, Cfg::LDS_BYTES);
+    hipError_t e = allow_lds(big_gemm_kernel<Cfg>, Cfg::LDS_BYTES);
+    if constexpr (Cfg::MODE == 1) if (e == hipSuccess) e = allow_lds(big_kgrouped_gemm_kernel<Cfg>, Cfg::LDS_BYTES);
     if (e != hipSuccess) return e;
     attr_set = true;
   }
-  const int64_t tiles = static_cast<int64_t>(n_mtiles) * n_ntiles * kplanes;
-  int64_t blocks = shared_cu_count();
-  if (blocks > tiles) blocks = (tiles + 7) / 8 * 8;
+  const unsigned blocks = gemm_blocks(longest_list(n_mtiles, static_cast<int64_t>(n_ntiles) * kplanes));
   // Band height: the 32 workgroups of an XCD share the least operand bytes as 4 x 8 tiles (16 groups of 1088 rows, K
   // ranges: 809 us with bands of two row tiles, 769 of four, 840 of eight).  Weights that the memory-side cache (256 MB)
   // does not keep are read once per band: bands of eight (16384 x 3584 x 18944 gate-up: 3235 us of two, 3210 of four, 3145 of
   // eight; with 90 MB of weights all the same).
   const int group_m = static_cast<int64_t>(Cfg::NMAT) * a.N * a.K * 2 > (int64_t{192} << 20) && rg == nullptr ? 8 : kBigBand;
   if constexpr (Cfg::MODE == 1) if (rg != nullptr) {
-    big_kgrouped_gemm_kernel<Cfg><<<static_cast<unsigned>(blocks), Cfg::THREADS, Cfg::LDS_BYTES, stream>>>(a, *rg, n_ntiles, group_m);
+    big_kgrouped_gemm_kernel<Cfg><<<blocks, Cfg::THREADS, Cfg::LDS_BYTES, stream>>>(a, *rg, n_ntiles, group_m);
     return hipGetLastError();
   }
-  big_gemm_kernel<Cfg><<<static_cast<unsigned>(blocks), Cfg::THREADS, Cfg::LDS_BYTES, stream>>>(a, n_ntiles, kplanes, ktp, group_m);
+  big_gemm_kernel<Cfg><<<blocks, Cfg::THREADS, Cfg::LDS_BYTES, stream>>>(a, n_ntiles, kplanes, ktp, group_m);
   return hipGetLastError();
+}
+
+template <typename Cfg>
+static hipError_t launch_mid_cfg(const SharedGemmArgs& a, int kplanes, const RowGroups* rg, hipStream_t stream) {
+  const int n_ntiles = (a.N + Cfg::BN - 1) / Cfg::BN, n_mtiles = (a.M + Cfg::BM - 1) / Cfg::BM;
+  const int KT = a.K >> 6;
+  const int ktp = (KT + kplanes - 1) / kplanes;   // chunks per plane
+  constexpr bool RANGES = Cfg::MODE == 1 && Cfg::BNT == 128;   // the tile that takes K ranges
+  static bool attr_set = false;
+  if (!attr_set) {
+    hipError_t e = allow_lds(mid_gemm_kernel<Cfg>, Cfg::LDS_BYTES);
+    if constexpr (RANGES) if (e == hipSuccess) e = allow_lds(mid_kgrouped_gemm_kernel<Cfg>, Cfg::LDS_BYTES);
+    if (e != hipSuccess) return e;
+    attr_set = true;
+  }
+  const unsigned blocks = gemm_blocks(longest_list(n_mtiles, static_cast<int64_t>(n_ntiles) * kplanes));
+  if constexpr (RANGES) if (rg != nullptr) {
+    mid_kgrouped_gemm_kernel<Cfg><<<blocks, Cfg::THREADS, Cfg::LDS_BYTES, stream>>>(a, *rg, n_ntiles, kBigBand);
+    return hipGetLastError();
+  }
+  mid_gemm_kernel<Cfg><<<blocks, Cfg::THREADS, Cfg::LDS_BYTES, stream>>>(a, n_ntiles, kplanes, ktp, kBigBand);
+  return hipGetLastError();
+}
+
+// Which tile takes a problem of M rows, N channels per matrix, K = 64 * KT, and in how many K planes (at most
+// max_planes): the cheapest by a model of what a CU does, rounds of tiles of the busiest XCD x (chunks x time of a chunk +
+// start and end of a tile) + reading a further plane back.  Measured per chunk at one workgroup per CU: 256 x 256
+// 1.28 us, 128 x 256 0.74 us, 128 x 128 0.50 us.  Times of the kernels alone, us (256 x 256 / 128 x 256 / 128 x 128;
+// before: 128-row tiles of four wavefronts on 64-byte rows):
+//   gate-up  2048 x 896 x 4864 39 / 38 / 40 (43);  500 x 2048 x 11008 41 / 48 / 50 (79);  1024 x 2048 x 11008 80 / 84 / 98 (97)
+//            300 x 1536 x 8960 29 / 21 / 25 (28);  130 x 3584 x 18944 75 / 84 / 78 (141);  600 x 896 x 4864 19 / - / 15 (23)
+//   down     2048 x 4864 x 896 in 2 planes 44 / 28 / 22 (30);  500 x 11008 x 2048 in 4: 49 / 32 / 26 (40 in 5)
+//            1024 x 11008 x 2048 in 4: 50 / 42 / 49 (57);  300 x 8960 x 1536 in 4: 40 / 25 / 17 (31 in 7)
+//            2048 x 8960 x 1536 in 2: 75 / 56 / 65 (74)
+// From four rounds of 256 x 256 tiles on those are taken in any case: the others move more operand bytes per flop.
+// A pure function of the number of 128-row tiles (the workspace layout depends on the planes).
+enum GemmTile { kTileMid128 = 1, kTileMid256, kTileBig };
+struct GemmChoice { GemmTile tile; int planes; };
+static GemmChoice gemm_choice(int M, int N, int K, int nmat, int max_planes) {
+  const int KT = K >> 6, cus8 = shared_cu_count() / 8;
+  const int m128 = (M + 127) / 128, m256 = (M + 255) / 256;
+  const struct { GemmTile tile; int mt, bn; double chunk, ends; } kinds[3] = {
+      {kTileBig, m256, 256 / nmat, 1.28, 3.0}, {kTileMid256, m128, 256 / nmat, 0.74, 1.5}, {kTileMid128, m128, 128 / nmat, 0.50, 1.0}};
+  const double plane_us = static_cast<double>(m128) * 128 * N * 4 / 5e6;
+  const int forced = shared_variant();   // experiments: one of the three tiles
+  GemmChoice best{kTileBig, 1};
+  double best_us = 1e30;
+  for (const auto& k : kinds) {
+    const int64_t nt = (N + k.bn - 1) / k.bn;
+    if (forced != 0 && forced != k.tile) continue;
+    for (int p = 1; p <= max_planes; ++p) {
+      const int ktp = (KT + p - 1) / p;
+      if ((KT + ktp - 1) / ktp != p) continue;   // an empty plane
+      const int64_t rounds = (longest_list(k.mt, nt * p) + cus8 - 1) / cus8;
+      const double us = static_cast<double>(rounds) * (ktp * k.chunk + k.ends) + (p - 1) * plane_us;
+      if (us < best_us) { best_us = us; best = {k.tile, p}; }
+    }
+    if (k.tile == kTileBig && k.mt * nt >= 4 * 8 * cus8) break;
+  }
+  return best;
 }
 
 hipError_t launch_shared_gate_up(const uint16_t* x, const uint16_t* w_gate, const uint16_t* w_up, int T, int d,
@@ -1073,71 +960,38 @@ hipError_t launch_shared_gate_up_scaled(const uint16_t* x, const uint16_t* w_gat
                                         const float* s_gate, const float* s_up, int T, int d, int F, uint16_t* h_s,
                                         hipStream_t stream) {
   if (T == 0) return hipSuccess;
-  SharedGemmArgs a{x, w_gate, w_up, T, F, d, h_s, nullptr, 0, s_gate, s_up};
-  // Operand traffic per flop halves with a 256 x 256 tile (one 8-wavefront workgroup per CU): the
-  // 128-row tile at two workgroups per CU saturates the L2 -> L1 path first.  Small problems keep
-  // the 128-row tile, which leaves fewer CUs idle in the last round.  Of its two forms, eight
-  // wavefronts of 64 x (32+32) are faster alone (C2: 47.8 vs 49.7 us) but fill every wavefront
-  // slot of a CU; four wavefronts of 64 x (64+64) leave room for the routed chain's kernels that
-  // run beside it, and the whole forward is faster (C2 steady state: 0.1563 vs 0.1643 ms).
-  int v = shared_variant();
-  if (v == 0) v = static_cast<int64_t>((T + 255) / 256) * ((F + 127) / 128) >= 384 ? 5 : 3;
-  // fewer 128 x (128+128) tiles than fill the workgroup slots: half-width tiles (d=896, T=512:
-  // 0.090 -> 0.083 ms per forward; d=1536, T=512: 0.143 -> 0.131 ms).  Not below four row tiles:
-  // at most one full-width tile per CU then, and a tile of either width takes about as long
-  // (this kernel alone, T=256: d=896 14.7 vs 18.7 us, d=1536 24 vs 38 us, d=2048 31 vs 49 us).
-  if (shared_variant() == 0 && (T + 127) / 128 >= 4 &&
-      static_cast<int64_t>((T + 127) / 128) * ((F + 127) / 128) < 300)
-    v = 1;
-  switch (v) {
-    case 1: return launch_shared_cfg<SharedCfg<0, 2, 1, 2, 2, 2>>(a, 1, stream);   // 128 x (64+64)
-    case 2: return launch_shared_cfg<SharedCfg<0, 2, 2, 4, 2, 1>>(a, 1, stream);   // 256 x (128+128), 8 wavefronts, 1 workgroup / CU
-    case 5: return launch_big_cfg<BigCfg<0>>(a, 1, nullptr, stream);   // the same with the ring of four stages (C5 4.08 -> 4.02 ms)
-    case 4: return launch_shared_cfg<SharedCfg<0, 2, 1, 2, 4, 4>>(a, 1, stream);   // 128 x (128+128), 8 wavefronts of 64 x (32+32), 2 workgroups / CU
-    default: return launch_shared_cfg<SharedCfg<0, 2, 2, 2, 2, 2>>(a, 1, stream);  // 128 x (128+128), 2 workgroups / CU
+  SharedGemmArgs a{x, w_gate, w_up, T, F, d, h_s, nullptr, 0, s_gate, s_up, nullptr};
+  switch (gemm_choice(T, F, d, 2, 1).tile) {
+    case kTileMid128: return launch_mid_cfg<MidCfg<0, 128>>(a, 1, nullptr, stream);
+    case kTileMid256: return launch_mid_cfg<MidCfg<0, 256>>(a, 1, nullptr, stream);
+    default: return launch_big_cfg<BigCfg<0>>(a, 1, nullptr, stream);
   }
 }
 
-// K planes of the large-batch down projection: enough (row tile, channel tile, plane) triples
-// for two workgroups per CU, but planes of at least 2048 channels: every further plane adds an
-// fp32 partial output that is written here and read by the combine (C2, F = 4864: four planes
-// 42 us, two planes 35 us and a faster combine; the 3B width with T = 2048, F = 11008: one plane
-// on 128 of 512 workgroup slots 220 us).  Pure function of the shape: the workspace layout
-// depends on it.
-// Mid-size batches at the 3B width: 48 to 64 output tiles of 256 x 256, so that four or five K planes
-// of them fill the chip once (one workgroup per CU); the big tile moves less operand data per flop
-// than two planes of 128 x 128 tiles.  Measured alone this kernel takes 111 -> 84 us at the 3B width with
-// T = 2048 (122 -> 87 us on the slower kind of box); the forward, where it shares the chip with the routed
-// chain, gains 1 to 3.5 % at T = 2048 and 0 to 2 % at T = 1536.
-// Not elsewhere: eight planes at T = 1024 make the combine and the kernels after it slower (371 -> 373 us),
-// the 1.5B width (six channel tiles) 293 -> 294 us, the 0.5B width 152 -> 160 us.
-static int shared_down_big_planes(int T, int d, int F) {
-  const int64_t tiles256 = static_cast<int64_t>((T + 255) / 256) * ((d + 255) / 256);
-  if (T < 1536 || d < 2048 || tiles256 > 64) return 0;
-  int planes = static_cast<int>(256 / tiles256);
-  if (planes > F / 1024) planes = F / 1024;
-  return planes >= 2 ? planes : 0;
-}
-
-int shared_down_planes(int T, int d, int F) {
-  if (const int big = shared_down_big_planes(T, d, F)) {
-    const int KT = F >> 6, ktp = (KT + big - 1) / big;
-    return (KT + ktp - 1) / ktp;
-  }
-  const int64_t tiles = static_cast<int64_t>((T + 127) / 128) * ((d + 127) / 128);
+// K planes that the down projection may have: every further plane adds an fp32 partial output that is written by the GEMM
+// and read back by the combine, and room for it in the scratch.  At most what two 128 x 128 tiles per CU or one
+// plane of 2048 channels ask for, few tiles (small T, whose partial outputs are small) up to one tile per CU and planes of
+// eight chunks; 48 to 64 tiles of 256 x 256 as many as fill the chip once.  Pure function of the shape.
+static int shared_down_max_planes(int T, int d, int F) {
   const int KT = F >> 6;
-  int planes = tiles > 0 ? static_cast<int>(512 / tiles) : 1;   // rounded down: a third plane at the 1.5B width (192 tiles) cost 5 %
-  if (planes > F / 2048) planes = F / 2048;
-  // few tiles (small T): the partial outputs are small then, and an empty CU costs more than a
-  // plane; up to one workgroup per CU, planes of at least 8 K steps of 64
-  int fill = tiles > 0 ? static_cast<int>(256 / tiles) : 1;
-  if (fill > KT / 8) fill = KT / 8;
-  if (planes < fill) planes = fill;
-  if (planes > 8) planes = 8;
+  const int64_t tiles256 = static_cast<int64_t>((T + 255) / 256) * ((d + 255) / 256);
+  int planes = 0;
+  if (T >= 1536 && d >= 2048 && tiles256 <= 64) planes = std::min(static_cast<int>(256 / tiles256), F / 1024);
+  if (planes < 2) {
+    const int64_t tiles = static_cast<int64_t>((T + 127) / 128) * ((d + 127) / 128);
+    planes = tiles > 0 ? static_cast<int>(512 / tiles) : 1;
+    if (planes > F / 2048) planes = F / 2048;
+    int fill = tiles > 0 ? static_cast<int>(256 / tiles) : 1;
+    if (fill > KT / 8) fill = KT / 8;
+    if (planes < fill) planes = fill;
+    if (planes > 8) planes = 8;
+  }
   if (planes < 1) planes = 1;
   const int ktp = (KT + planes - 1) / planes;
   return (KT + ktp - 1) / ktp;
 }
+
+int shared_down_planes(int T, int d, int F) { return gemm_choice(T, d, F, 1, shared_down_max_planes(T, d, F)).planes; }
 
 hipError_t launch_shared_down(const uint16_t* h_s, const uint16_t* w_down, int T, int d, int F, float* y_s,
                               hipStream_t stream) {
@@ -1147,24 +1001,18 @@ hipError_t launch_shared_down(const uint16_t* h_s, const uint16_t* w_down, int T
 hipError_t launch_shared_down_scaled(const uint16_t* h_s, const uint16_t* w_down, const float* s_down, int T, int d,
                                      int F, float* y_s, hipStream_t stream) {
   if (T == 0) return hipSuccess;
-  SharedGemmArgs a{h_s, w_down, nullptr, T, d, F, nullptr, y_s, static_cast<int64_t>(T) * d, s_down, nullptr};
-  const int planes = shared_down_planes(T, d, F);
-  if (shared_down_big_planes(T, d, F) != 0) return launch_big_cfg<BigCfg<1>>(a, planes, nullptr, stream);
-  if (planes > 1) return launch_shared_cfg<SharedCfg<1, 2, 2, 2, 2, 2>>(a, planes, stream);   // small problem: 128 x 128 tiles
-  int v = shared_variant();
-  if (v == 0) v = static_cast<int64_t>((T + 255) / 256) * ((d + 255) / 256) >= 256 ? 5 : 3;
-  switch (v) {
-    case 1: return launch_shared_cfg<SharedCfg<1, 2, 2, 2, 2, 2>>(a, 1, stream);    // 128 x 128
-    case 2: return launch_shared_cfg<SharedCfg<1, 2, 4, 4, 2, 1>>(a, 1, stream);    // 256 x 256, 8 wavefronts, 1 workgroup / CU
-    case 5: return launch_big_cfg<BigCfg<1>>(a, 1, nullptr, stream);    // the same with the ring of four stages (C5 2.15 -> 2.09 ms)
-    default: return launch_shared_cfg<SharedCfg<1, 2, 4, 2, 2, 2>>(a, 1, stream);   // 128 x 256
+  SharedGemmArgs a{h_s, w_down, nullptr, T, d, F, nullptr, y_s, static_cast<int64_t>(T) * d, s_down, nullptr, nullptr};
+  const GemmChoice c = gemm_choice(T, d, F, 1, shared_down_max_planes(T, d, F));
+  switch (c.tile) {
+    case kTileMid128: return launch_mid_cfg<MidCfg<1, 128>>(a, c.planes, nullptr, stream);
+    case kTileMid256: return launch_mid_cfg<MidCfg<1, 256>>(a, c.planes, nullptr, stream);
+    default: return launch_big_cfg<BigCfg<1>>(a, c.planes, nullptr, stream);
   }
 }
 
-template <typename Cfg>
-static hipError_t launch_grouped_cfg(const SharedGemmArgs& a, const int32_t* row0, int n_groups, int kplanes, int split_mt,
-                                     hipStream_t stream) {
-  constexpr bool BIG = Cfg::BM == 256;
+template <typename Cfg, typename Kernel>
+static hipError_t launch_grouped_cfg(Kernel* kernel, const SharedGemmArgs& a, const int32_t* row0, int n_groups, int kplanes,
+                                     int split_mt, hipStream_t stream) {
   RowGroups rg;
   rg.split_mt = split_mt;
   rg.n = n_groups;
@@ -1179,28 +1027,16 @@ static hipError_t launch_grouped_cfg(const SharedGemmArgs& a, const int32_t* row
   for (int e = n_groups + 1; e <= kMaxRowGroups; ++e) rg.row0[e] = rg.tile0[e] = 0;
   if (tiles_m == 0) return hipSuccess;
   const int n_ntiles = (a.N + Cfg::BN - 1) / Cfg::BN;
-  const int KT64 = a.K >> 6;
-  const int ktp64 = (KT64 + kplanes - 1) / kplanes;
-  const size_t lds = Cfg::LDS_BYTES;
+  const int KT = a.K >> 6;
+  const int ktp = (KT + kplanes - 1) / kplanes;
   static bool attr_set = false;
-  static int resident = 1;
   if (!attr_set) {
-    const void* kernel;
-    if constexpr (BIG) kernel = reinterpret_cast<const void*>(big_grouped_gemm_kernel);
-    else kernel = reinterpret_cast<const void*>(grouped_gemm_kernel<Cfg>);
-    hipError_t e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
+    hipError_t e = allow_lds(kernel, Cfg::LDS_BYTES);
     if (e != hipSuccess) return e;
-    int n = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, kernel, Cfg::THREADS, lds) == hipSuccess && n > 0) resident = n;
     attr_set = true;
   }
-  const int64_t tiles = (static_cast<int64_t>(split_mt) + static_cast<int64_t>(tiles_m - split_mt) * kplanes) * n_ntiles;
-  int64_t blocks = static_cast<int64_t>(shared_cu_count()) * resident;
-  if (blocks > tiles) blocks = (tiles + 7) / 8 * 8;
-  if constexpr (BIG)
-    big_grouped_gemm_kernel<<<static_cast<unsigned>(blocks), Cfg::THREADS, lds, stream>>>(a, rg, n_ntiles, kplanes, ktp64, kBigBand);
-  else
-    grouped_gemm_kernel<Cfg><<<static_cast<unsigned>(blocks), Cfg::THREADS, lds, stream>>>(a, rg, n_ntiles, kplanes, 2 * ktp64, tile_group_m());
+  const unsigned blocks = gemm_blocks(longest_list(split_mt, n_ntiles) + longest_list(tiles_m - split_mt, static_cast<int64_t>(n_ntiles) * kplanes));
+  kernel<<<blocks, Cfg::THREADS, Cfg::LDS_BYTES, stream>>>(a, rg, n_ntiles, kplanes, ktp, kBigBand);
   return hipGetLastError();
 }
 
@@ -1265,7 +1101,7 @@ GemmSplit grouped_gemm_split(const int32_t* row0_host, int n_groups, int N, int 
 
 // Grouped GEMM for other callers: rows row0_host[e] .. row0_host[e+1]-1 of act (row0_host: n_groups + 1
 // ascending HOST integers; act, out and the rows are counted from row0_host[0], which act and out point at)
-// are contracted with matrix e of w ([n_groups] matrices of [N, K] ternary blocks, SharedCfg) and scaled per
+// are contracted with matrix e of w ([n_groups] matrices of [N, K] ternary blocks) and scaled per
 // channel by row e of scale ([n_groups][N]): out[r, n] = scale[e][n] * sum_k act[r, k] * t[e][n, k].  sp as given by
 // grouped_gemm_split: the rows below sp.split_row go to out; with more than one plane, plane p of the others writes its
 // partial sums to planes_out + p * (rows - split_row) * N (row split_row first) and the caller adds them.
@@ -1278,33 +1114,9 @@ hipError_t launch_gemm_grouped_f32(const uint16_t* act, const uint32_t* w, const
   float* const y_split = sp.planes > 1 ? planes_out - static_cast<int64_t>(sp.split_row) * N : out;
   SharedGemmArgs a{act, reinterpret_cast<const uint16_t*>(w), nullptr, M, N, K, nullptr, out, static_cast<int64_t>(M - sp.split_row) * N, scale, nullptr, y_split};
   if (grouped_row_tiles(row0_host, n_groups, 256) * ((N + 255) / 256) >= (3 * shared_cu_count()) / 4)
-    return launch_grouped_cfg<BigCfg<1, true>>(a, row0_host, n_groups, sp.planes, sp.split_mt, stream);          // 256 x 256
+    return launch_grouped_cfg<BigCfg<1, true>>(big_grouped_gemm_kernel, a, row0_host, n_groups, sp.planes, sp.split_mt, stream);   // 256 x 256
   a.y_out = y_split;
-  return launch_grouped_cfg<SharedCfg<1, 2, 2, 2, 2, 2, 4, true>>(a, row0_host, n_groups, sp.planes, 0, stream);   // 128 x 128
-}
-
-template <typename Cfg>
-static hipError_t launch_kgrouped_cfg(const SharedGemmArgs& a, const RowGroups& rg, hipStream_t stream) {
-  const int n_groups = rg.n;
-  const int n_ntiles = (a.N + Cfg::BN - 1) / Cfg::BN;
-  const int n_mtiles = (a.M + Cfg::BM - 1) / Cfg::BM;
-  const size_t lds = Cfg::LDS_BYTES;
-  static bool attr_set = false;
-  static int resident = Cfg::MIN_BLOCKS;
-  if (!attr_set) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kgrouped_gemm_kernel<Cfg>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
-    if (e != hipSuccess) return e;
-    int n = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, kgrouped_gemm_kernel<Cfg>, Cfg::THREADS, lds) == hipSuccess && n > 0)
-      resident = n;
-    attr_set = true;
-  }
-  const int64_t tiles = static_cast<int64_t>(n_mtiles) * n_ntiles * n_groups;
-  int64_t blocks = static_cast<int64_t>(shared_cu_count()) * resident;
-  if (blocks > tiles) blocks = (tiles + 7) / 8 * 8;
-  kgrouped_gemm_kernel<Cfg><<<static_cast<unsigned>(blocks), Cfg::THREADS, lds, stream>>>(a, rg, n_ntiles, tile_group_m());
-  return hipGetLastError();
+  return launch_grouped_cfg<MidCfg<1, 128, true>>(mid_grouped_gemm_kernel, a, row0_host, n_groups, sp.planes, 0, stream);   // 128 x 128
 }
 
 // Several contractions over consecutive K ranges of the same two operands in one launch: plane p,
@@ -1319,13 +1131,14 @@ hipError_t launch_gemm_tn_f32_kgroups(const uint16_t* act, const uint16_t* w, in
   SharedGemmArgs a{act, w, nullptr, M, N, K, nullptr, out, static_cast<int64_t>(M) * N, nullptr, nullptr};
   RowGroups rg;
   rg.n = n_groups;
+  rg.split_mt = 0;
   for (int e = 0; e <= kMaxRowGroups; ++e) {
     rg.row0[e] = k0_host[std::min(e, n_groups)];
     rg.tile0[e] = 0;
   }
   if (static_cast<int64_t>((M + 255) / 256) * ((N + 255) / 256) * n_groups >= 256)
     return launch_big_cfg<BigCfg<1>>(a, n_groups, &rg, stream);              // 256 x 256
-  return launch_kgrouped_cfg<SharedCfg<1, 2, 2, 2, 2, 2>>(a, rg, stream);    // 128 x 128
+  return launch_mid_cfg<MidCfg<1, 128>>(a, n_groups, &rg, stream);           // 128 x 128
 }
 
 }  // namespace mote

@@ -28,7 +28,7 @@ namespace mote {
 constexpr int kSteThreads = 256;
 
 // One wavefront re-blocks one packed tile (32 output rows x 128 input channels): the operand of dX contracts over
-// the rows, so its blocks (SharedCfg in shared_ffn.hip) are [channel block 4][this row tile] of 32 x 32 codes.
+// the rows, so its blocks (described in shared_ffn.hip) are [channel block 4][this row tile] of 32 x 32 codes.
 // Lane (s, b, Q) takes the channels 32s + 4b .. +3 and 16 further on, byte-parallel, and the rows 8Q .. 8Q+7 of their words.  Memory-bound: 90 MB in and out for 16 experts of 11008 x 2048, where the bf16
 // matrices they replaced were 721 MB (136 us to write, and the GEMM read them back).
 __device__ __forceinline__ void reblock_ternary_t_tile(const uint32_t* __restrict__ tile, uint32_t* __restrict__ out, int64_t block_stride,
