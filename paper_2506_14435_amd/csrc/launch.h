@@ -12,9 +12,9 @@ enum Knob {
   kKnobForkMinLog2,          // log2 of T*d*F_s from which the forward forks
   kKnobEventFence,           // 1: fork / join events carry a system-scope fence
   kKnobQuantWide,            // 1: 256-thread row quantiser for every row length
-  kKnobRoutedVariant,        // tile configuration of the large-batch routed gate-up GEMM
-  kKnobRoutedDownVariant,    // ... of the routed down GEMM (-1: same as gate-up)
-  kKnobSharedVariant,        // ... of the shared GEMMs (0: by shape)
+  kKnobRoutedVariant,        // without effect (the large-batch routed GEMMs have one tile configuration each)
+  kKnobRoutedDownVariant,    // without effect
+  kKnobSharedVariant,        // tile of the large-batch shared GEMMs (0: by shape, 1: 128 x 128, 2: 128 x 256, 3: 256 x 256)
   kKnobGroupM,               // row tiles per band of the tile order
   kKnobDynamicRounds,        // tiles per workgroup from which tiles are drawn
   kKnobDecodeVariant,        // routed decode kernel: 0 K-split, 1 / 2 wave-streaming with 4 / 8 wavefronts per workgroup

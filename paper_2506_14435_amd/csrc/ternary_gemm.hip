@@ -25,7 +25,9 @@
 // Why 16x16 and not 32x32 tiles: the chip is power-limited inside these GEMMs.  Register-only loops over random operands
 // on all CUs sustain 3.99 POP/s with v_mfma_i32_16x16x64_i8 and 3.37 with v_mfma_i32_32x32x32_i8, fed from LDS 3.49 and
 // 2.97.  On the small tiles (the same loop otherwise; 16 experts, top-2): T = 8192 at the 3B width gate-up 664 -> 619 us,
-// down 329 -> 298; T = 16384 at the 7B width, loads of 10x spread, 3560 -> 3217 and 1710 -> 1555 (2.87 POP/s).
+// down 329 -> 298; T = 16384 at the 7B width, loads of 10x spread, 3560 -> 3217 and 1710 -> 1555 (2.87 POP/s).  With all 128
+// rows of a tile in every wavefront (see the kernel): 619 -> 588, 298 -> 285; 3225 -> 3070 and 1560 -> 1470 (3.02 POP/s); few rows
+// per expert (16 experts, 3B width) T = 500 71 -> 58 and 39.7 -> 34.2, T = 1024 106 -> 97 and 70 -> 57.
 //
 // Epilogue: every wavefront transposes its result fragments through a private LDS patch so
 // that a global store instruction covers whole rows of a 32-row block.
@@ -38,12 +40,13 @@
 
 namespace mote {
 
+// Tiles of 32 BM_W WAVES_M rows x 32 BN_W WAVES_N channels (per matrix); two workgroups share a CU.
 template <int MODE_, int BM_W_, int BN_W_, int WAVES_M_, int WAVES_N_, int MIN_BLOCKS_ = 1>
 struct RoutedCfg {
   static constexpr int MODE = MODE_;  // 0 gate-up (two matrices, SwiGLU epilogue), 1 down
   static constexpr int NMAT = MODE_ == 0 ? 2 : 1;
   static constexpr int BM_W = BM_W_, BN_W = BN_W_, WAVES_M = WAVES_M_, WAVES_N = WAVES_N_;
-  static constexpr int MIN_BLOCKS = MIN_BLOCKS_;  // wavefronts per SIMD the register budget must allow (2 workgroups per CU)
+  static constexpr int MIN_BLOCKS = MIN_BLOCKS_;  // wavefronts per SIMD the register budget must allow
   static constexpr int BM = 32 * BM_W_ * WAVES_M_;
   static constexpr int BN = 32 * BN_W_ * WAVES_N_;
   static constexpr int WAVES = WAVES_M_ * WAVES_N_;
@@ -63,6 +66,10 @@ struct RoutedCfg {
   static_assert(W_FRAGS % WAVES == 0, "every wavefront requests the same number of weight fragments");
   static_assert(64 % (PATCH_F * 32 * OUT_BYTES / 16) == 0, "an epilogue read covers whole rows");
 };
+
+using GateUpCfg = RoutedCfg<0, 4, 1, 1, 4, 2>;       // 128 x (128+128), four wavefronts of 128 x (32+32)
+using DownCfg = RoutedCfg<1, 4, 2, 1, 4, 2>;         // 128 x 256
+using DownPlanesCfg = RoutedCfg<1, 4, 1, 1, 4, 2>;   // 128 x 128: small problems, K planes
 
 #ifdef MOTE_TRACE
 __device__ unsigned long long g_trace[1024 * 32 * 8];
@@ -86,23 +93,21 @@ __device__ __forceinline__ int lds_a_offset(int row, int chunk) { return row * 1
 // about 800 cycles per K step) before it reaches its first MFMA.
 constexpr int kFixedShares = 1 << 20;   // n_static from which every tile of a workgroup is fixed
 
-// SKIP_: what a partly filled row tile (the last one of an expert, half empty on average) saves.
-//   2: every 32-row fragment that holds no rows is neither read nor contracted.  The conditions
-//      cost full tiles about 8 % (scalar branches between the MFMAs), so this variant is launched
-//      only when most row tiles are partly filled (few rows per expert).
-//   1: only a wavefront whose whole block of rows is empty idles through the K steps (it still
-//      issues its share of the loads and meets the barriers): one scalar branch per K step.
-template <typename Cfg, int SKIP_>
+// Every wavefront has all 128 rows of the tile and a quarter of its channels: a weight fragment is unpacked once
+// per eight MFMAs (with 64 rows per wavefront once per four; vector and matrix instructions then took about as many
+// cycles of a SIMD, 0.46 and 0.59 of them, and hardly overlapped).  A partly filled row tile (the last one of an
+// expert, half empty on average) runs a K loop of its own for 32, 64 or 96 rows: one test per tile, none between
+// the MFMAs.
+template <typename Cfg>
 __global__ __launch_bounds__(Cfg::THREADS, Cfg::MIN_BLOCKS) void routed_gemm_kernel(RoutedGemmArgs a, int n_ntiles, int kplanes, int ktp, int group_m, int n_static) {
   constexpr int NMAT = Cfg::NMAT, BM_W = Cfg::BM_W, BN_W = Cfg::BN_W;
   constexpr int BM = Cfg::BM, BN = Cfg::BN, THREADS = Cfg::THREADS;
   constexpr int A_BYTES = Cfg::A_BYTES, STAGE_BYTES = Cfg::STAGE_BYTES;
-  constexpr bool SKIP = SKIP_ == 2;                 // fragment-level tests inside the K loop
   constexpr int NB = BN / 32;                       // 32-channel blocks of the tile
   constexpr int W_PER_WAVE = Cfg::W_PER_WAVE;       // weight fragments a wavefront requests per K step
   constexpr int NLOAD = Cfg::A_PASSES + W_PER_WAVE; // vector-memory operations a wavefront issues per K step
   static_assert(BM <= THREADS, "one thread per tile row publishes the row metadata");
-  static_assert((Cfg::WAVES == 4 || Cfg::WAVES == 8) && Cfg::ROWS_PER_PASS == 8 * Cfg::WAVES, "a loader pass is 8 rows per wavefront");
+  static_assert(Cfg::WAVES_M == 1 && BM_W == 4 && Cfg::WAVES == 4, "what the row counts of the K loops and the row metadata are written for");
   static_assert(NLOAD < 16, "fits the low vmcnt field");
   __shared__ __attribute__((aligned(16))) unsigned char s_lds[3 * STAGE_BYTES];
   __shared__ float s_beta[2][BM];   // row metadata (absmax, integer row sum), double buffered by tile parity
@@ -112,13 +117,13 @@ __global__ __launch_bounds__(Cfg::THREADS, Cfg::MIN_BLOCKS) void routed_gemm_ker
   const int KT = K >> 7;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wave_u = __builtin_amdgcn_readfirstlane(wave);
-  const int wm = wave % Cfg::WAVES_M, wn = wave / Cfg::WAVES_M;
+  const int wn = wave;   // channel quarter of the tile
   const int r16 = lane & 15, quart = lane >> 4;
   constexpr int A16 = 2 * BM_W, B16 = 2 * BN_W, NF = NMAT * B16;   // 16-row / 16-channel fragments of a wavefront
   // This lane's operand bytes in a stage.  Quarter q of the wavefront takes, in MFMA j = 0, 1 of a K step, the channels
   // 32 (2 (q & 1) + j) + 16 (q / 2) .. +15 of its row: word 2 (q & 1) + j of 16-byte unit 32 (q / 2) + row of a packed tile,
   // so one 8-byte read brings both MFMAs' words (and the reads of 32 lanes cover the banks once)
-  const int a_rd = lds_a_offset(wm * BM_W * 32 + r16, 4 * (quart & 1) + (quart >> 1));   // j = 1: ^ 32
+  const int a_rd = lds_a_offset(r16, 4 * (quart & 1) + (quart >> 1));   // j = 1: ^ 32
   const int w_rd = (32 * (quart >> 1) + r16) * 16 + (quart & 1) * 8;
   const int64_t expert_words = static_cast<int64_t>(N) * K / 16;
   // LDS byte address of the stage area (what M0 takes for a direct-to-LDS load)
@@ -430,11 +435,6 @@ __global__ __launch_bounds__(Cfg::THREADS, Cfg::MIN_BLOCKS) void routed_gemm_ker
 
     // row gather of the next tile: the indices are in registers when the K loop ends
     if (has_next) MOTE_GATHER(row02, rows2);
-    // Rows of this wavefront's block that exist: the last row tile of an expert is half empty on
-    // average, and a pair of 16-row fragments without rows is neither read nor contracted (its MFMA slots go
-    // to the other wavefronts of the SIMD).  Wavefront-uniform, so these are scalar branches.
-    const int rows_w = SKIP_ != 0 ? __builtin_amdgcn_readfirstlane(rows - (wave_u % Cfg::WAVES_M) * BM_W * 32) : BM_W * 32;
-
     // (2) K loop.  K step kt contracts stage st_cur while the loads of kt+2 are issued, one
     // quarter of them per quarter of the MFMAs (a burst of loads right after the barrier fills
     // the CU's vector-memory queue and stalls every wavefront in issue), into the stage that the
@@ -442,65 +442,67 @@ __global__ __launch_bounds__(Cfg::THREADS, Cfg::MIN_BLOCKS) void routed_gemm_ker
     int ktl2 = ktl;
     // Accumulators start at -rowsum(q): the stored codes are t+1, so sum (t+1) q - sum q = sum t q.
     v4i acc[A16][NF];   // dispatch rows 16i .., channels of fragment n (gate first, then up)
-#pragma unroll
-    for (int i = 0; i < A16; ++i) {
-      const int nrs = kc == 0 ? -s_rs[par][wm * BM_W * 32 + i * 16 + r16] : 0;   // the correction enters plane 0 only
-#pragma unroll
-      for (int n = 0; n < NF; ++n) acc[i][n] = v4i{nrs, nrs, nrs, nrs};
-    }
-    for (int kt = 0; kt < ktl; ++kt) {
-      const bool pf = kt + 2 < ktl;
-      const unsigned char* const st = s_lds + st_cur;
-      // quarter s_ of the loads of K step kt+2
+    // quarter s_ of the loads of K step kt+2
 #define MOTE_LOAD_QUARTER(s_)                                                                      \
-      if (pf) {                                                                                    \
+      {                                                                                            \
         _Pragma("unroll") for (int p = 0; p < Cfg::A_PASSES; ++p)                                  \
           if ((p & 3) == (s_)) MOTE_DMA_A(st_nx2, kt + 2, p);                                      \
         _Pragma("unroll") for (int i = 0; i < W_PER_WAVE; ++i)                                     \
           if (((i + 1) & 3) == (s_)) MOTE_DMA_W(st_nx2, kt + 2, i);                                \
       }
-      // Where the wavefront's rows are tested: around the whole step, or, with 128 registers (the allocator then copies and
-      // spills accumulators behind the loop), around the MFMAs of every quarter.
-      constexpr bool PER_QUARTER = Cfg::MIN_BLOCKS >= 4;
-      if (PER_QUARTER || SKIP_ == 0 || rows_w > 0) {
-        // the packed words of both 64-channel halves of the step, and the activations of the first
-        uint2 wf[NF];
-#pragma unroll
-        for (int n = 0; n < NF; ++n)
-          wf[n] = *reinterpret_cast<const uint2*>(st + A_BYTES + ((n / B16) * NB + wn * BN_W + (n % B16) / 2) * 1024 + (n & 1) * 256 + w_rd);
-        v4i af[A16];
-#pragma unroll
-        for (int i = 0; i < A16; ++i)
-          if (!SKIP || (i & ~1) * 16 < rows_w) af[i] = *reinterpret_cast<const v4i*>(st + a_rd + i * 2048);
-#pragma unroll
-        for (int s = 0; s < 4; ++s) {   // quarter s: half s / 2 of the channels, half s % 2 of the weight fragments
-          MOTE_LOAD_QUARTER(s)
-          if (!PER_QUARTER || SKIP_ == 0 || rows_w > 0) {
-            v4i bf[NF / 2];
-#pragma unroll
-            for (int n = 0; n < NF / 2; ++n) bf[n] = unpack_codes(s < 2 ? wf[(s & 1) * (NF / 2) + n].x : wf[(s & 1) * (NF / 2) + n].y);
-#pragma unroll
-            for (int i = 0; i < A16; ++i)
-              if (!SKIP || (i & ~1) * 16 < rows_w) {
-#pragma unroll
-                for (int n = 0; n < NF / 2; ++n)
-                  acc[i][(s & 1) * (NF / 2) + n] = __builtin_amdgcn_mfma_i32_16x16x64_i8(bf[n], af[i], acc[i][(s & 1) * (NF / 2) + n], 0, 0, 0);
-                // the second half's activations, a fragment behind its last MFMA of the first half
-                if (s == 1) af[i] = *reinterpret_cast<const v4i*>(st + (a_rd ^ 32) + i * 2048);
-              }
-          }
-          __builtin_amdgcn_sched_barrier(0);  // keep each quarter's loads with its quarter
-        }
-      } else {   // a wavefront without rows contracts nothing: it issues its share of the loads and meets the barriers
-#pragma unroll
-        for (int s = 0; s < 4; ++s) MOTE_LOAD_QUARTER(s)
-      }
-#undef MOTE_LOAD_QUARTER
-      // K step kt+1 landed everywhere (kt+2 stays in flight); after the last step: every
-      // wavefront has read its last stage
-      MOTE_WAIT_BARRIER(pf);
+    // K step kt+1 landed everywhere (kt+2 stays in flight); after the last step: every
+    // wavefront has read its last stage
+#define MOTE_STEP_END(PF_)                                                                         \
+      MOTE_WAIT_BARRIER(PF_);                                                                      \
       const int t = st_cur; st_cur = st_nxt; st_nxt = st_nx2; st_nx2 = t;
+    // a step of the first NI_ row fragments with (PF_) or without the loads of K step kt+2
+#define MOTE_KSTEP(PF_, NI_)                                                                            \
+    {                                                                                              \
+      const unsigned char* const st = s_lds + st_cur;                                              \
+      /* the packed words of both 64-channel halves of the step, and the activations of the first */ \
+      uint2 wf[NF];                                                                                \
+      _Pragma("unroll") for (int n = 0; n < NF; ++n)                                               \
+        wf[n] = *reinterpret_cast<const uint2*>(st + A_BYTES + ((n / B16) * NB + wn * BN_W + (n % B16) / 2) * 1024 + (n & 1) * 256 + w_rd); \
+      v4i af[A16];                                                                                 \
+      _Pragma("unroll") for (int i = 0; i < (NI_); ++i)                                              \
+        af[i] = *reinterpret_cast<const v4i*>(st + a_rd + i * 2048);                               \
+      _Pragma("unroll") for (int s = 0; s < 4; ++s) { /* quarter s: half s / 2 of the channels, half s % 2 of the weight fragments */ \
+        if (PF_) MOTE_LOAD_QUARTER(s)                                                              \
+        v4i bf[NF / 2];                                                                            \
+        _Pragma("unroll") for (int n = 0; n < NF / 2; ++n)                                         \
+          bf[n] = unpack_codes(s < 2 ? wf[(s & 1) * (NF / 2) + n].x : wf[(s & 1) * (NF / 2) + n].y); \
+        _Pragma("unroll") for (int i = 0; i < (NI_); ++i) {                                        \
+          _Pragma("unroll") for (int n = 0; n < NF / 2; ++n)                                       \
+            acc[i][(s & 1) * (NF / 2) + n] =                                                       \
+                __builtin_amdgcn_mfma_i32_16x16x64_i8(bf[n], af[i], acc[i][(s & 1) * (NF / 2) + n], 0, 0, 0); \
+          /* the second half's activations, a fragment behind its last MFMA of the first half */   \
+          if (s == 1) af[i] = *reinterpret_cast<const v4i*>(st + (a_rd ^ 32) + i * 2048);          \
+        }                                                                                          \
+        __builtin_amdgcn_sched_barrier(0); /* keep each quarter's loads with its quarter */        \
+      }                                                                                            \
+      MOTE_STEP_END(PF_)                                                                           \
     }
+#pragma unroll
+    for (int i = 0; i < A16; ++i) {
+      const int nrs = kc == 0 ? -s_rs[par][i * 16 + r16] : 0;   // the correction enters plane 0 only
+#pragma unroll
+      for (int n = 0; n < NF; ++n) acc[i][n] = v4i{nrs, nrs, nrs, nrs};
+    }
+    // the steps with loads and those without in loops of their own: no test in front of every quarter's loads
+#define MOTE_KLOOP(NI_)                                                                            \
+    {                                                                                              \
+      int kt = 0;                                                                                  \
+      for (; kt + 2 < ktl; ++kt) MOTE_KSTEP(true, NI_)                                             \
+      for (; kt < ktl; ++kt) MOTE_KSTEP(false, NI_)                                                \
+    }
+    if (rows <= 32) MOTE_KLOOP(2)
+    else if (rows <= 64) MOTE_KLOOP(4)
+    else if (rows <= 96) MOTE_KLOOP(6)
+    else MOTE_KLOOP(8)
+#undef MOTE_KLOOP
+#undef MOTE_KSTEP
+#undef MOTE_STEP_END
+#undef MOTE_LOAD_QUARTER
 
     MOTE_TP(2)
     MOTE_START_NEXT
@@ -529,12 +531,12 @@ __global__ __launch_bounds__(Cfg::THREADS, Cfg::MIN_BLOCKS) void routed_gemm_ker
     const int rd_row = lane_e / LANES_PER_ROW, rd_chunk = lane_e % LANES_PER_ROW;
 #pragma unroll
     for (int i = 0; i < BM_W; ++i) {
-      if ((SKIP && i * 32 >= rows_w) || (SKIP_ == 1 && rows_w <= 0)) continue;   // nothing to store
+      if (i * 32 >= rows) continue;   // nothing to store
       float sg[2] = {0.0f, 0.0f}, su[2] = {0.0f, 0.0f};
       if constexpr (Cfg::MODE == 0) {
 #pragma unroll
         for (int r = 0; r < 2; ++r) {
-          const float sx = s_beta[par][wm * BM_W * 32 + i * 32 + r * 16 + r16e] / 127.0f;
+          const float sx = s_beta[par][i * 32 + r * 16 + r16e] / 127.0f;
           sg[r] = sx * al0;
           su[r] = sx * al1;
         }
@@ -559,7 +561,7 @@ __global__ __launch_bounds__(Cfg::THREADS, Cfg::MIN_BLOCKS) void routed_gemm_ker
               packed.x = cvt_pk_bf16(hv[0], hv[1]);
               packed.y = cvt_pk_bf16(hv[2], hv[3]);
               *reinterpret_cast<uint2*>(dst) = packed;
-              const int rl = wm * BM_W * 32 + i * 32 + r * 16 + r16e;
+              const int rl = i * 32 + r * 16 + r16e;
               if ((a.tap_gate != nullptr || a.tap_up != nullptr) && rl < rows && n_wave0 + col < N) {   // parity taps (tests only), each optional
                 const int64_t o = static_cast<int64_t>(row0 + rl) * N + n_wave0 + col;
                 if (a.tap_gate != nullptr) *reinterpret_cast<v4i*>(a.tap_gate + o) = d0;
@@ -578,7 +580,7 @@ __global__ __launch_bounds__(Cfg::THREADS, Cfg::MIN_BLOCKS) void routed_gemm_ker
         for (int p = 0; p < 32 / ROWS_PER_READ; ++p) {
           const int pr = p * ROWS_PER_READ + rd_row;
           const u4 v = *reinterpret_cast<const u4*>(patch + pr * PATCH_ROW + rd_chunk * 16);
-          const int orow = wm * BM_W * 32 + i * 32 + pr;
+          const int orow = i * 32 + pr;
           if (orow < rows && rd_n < N) {
             const int64_t o = static_cast<int64_t>(row0 + orow) * N + rd_n;
             if constexpr (Cfg::MODE == 0) *reinterpret_cast<u4*>(a.h + o) = v;
@@ -649,7 +651,7 @@ template <typename Cfg>
 static int resident_blocks() {
   static int n = 0;
   if (n == 0) {
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, routed_gemm_kernel<Cfg, 1>, Cfg::THREADS, 0) != hipSuccess || n <= 0)
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, routed_gemm_kernel<Cfg>, Cfg::THREADS, 0) != hipSuccess || n <= 0)
       n = Cfg::MIN_BLOCKS;
   }
   return n;
@@ -684,19 +686,9 @@ static hipError_t launch_cfg(const RoutedGemmArgs& a, int kplanes, hipStream_t s
   // (max_tiles bounds the row tiles for any routing; the expected number is rows / tile_m plus a few)
   const int64_t expected = std::min<int64_t>(a.max_tiles, a.out_rows / a.tile_m + 8) * n_ntiles * kplanes;
   const int n_static = expected >= routed_dynamic_rounds() * blocks ? 1 : kAllStatic;
-  // few rows per expert: most row tiles are partly filled (T = 512 at the 3B width with 16 experts:
-  // gate-up 88.8 -> 73.2 us, down 47.6 -> 40.1 us; T = 1024: 134 -> 116 us)
-  const int64_t n_experts = std::max<int64_t>(1, a.max_tiles - a.out_rows / a.tile_m);
-  if (a.out_rows <= 160 * n_experts)
-    routed_gemm_kernel<Cfg, 2><<<static_cast<unsigned>(blocks), Cfg::THREADS, 0, stream>>>(a, n_ntiles, kplanes, ktp, tile_group_m(), n_static);
-  else
-    routed_gemm_kernel<Cfg, 1><<<static_cast<unsigned>(blocks), Cfg::THREADS, 0, stream>>>(a, n_ntiles, kplanes, ktp, tile_group_m(), n_static);
+  routed_gemm_kernel<Cfg><<<static_cast<unsigned>(blocks), Cfg::THREADS, 0, stream>>>(a, n_ntiles, kplanes, ktp, tile_group_m(), n_static);
   return hipGetLastError();
 }
-
-// Knob routed_variant: selects the tile
-// configuration of the large-batch kernels.
-static int routed_variant() { return knob(kKnobRoutedVariant); }
 
 // Plan tile height by the average number of rows an expert sees: 32-row tiles for few rows
 // (decode kernels), 64-row tiles for some tens of rows where the wave-streaming kernel fits the
@@ -731,11 +723,7 @@ int routed_decode_rows(int T, int E, int d, int F, bool shared_quantised) {
 
 hipError_t launch_routed_gate_up(const RoutedGemmArgs& a, hipStream_t stream) {
   if (a.max_tiles == 0) return hipSuccess;
-  switch (routed_variant()) {
-    case 1: return launch_cfg<RoutedCfg<0, 4, 1, 1, 4, 2>>(a, 1, stream);   // 4 wavefronts of 128 x (32+32)
-    case 2: return launch_cfg<RoutedCfg<0, 2, 2, 2, 2, 2>>(a, 1, stream);   // 4 wavefronts of 64 x (64+64)
-    default: return launch_cfg<RoutedCfg<0, 2, 1, 2, 4, 4>>(a, 1, stream);  // 8 wavefronts of 64 x (32+32): four per SIMD (2-3 % faster)
-  }
+  return launch_cfg<GateUpCfg>(a, 1, stream);
 }
 
 // K planes of the large-batch down projection (see shared_down_planes): pure function of the
@@ -759,29 +747,13 @@ int routed_down_planes(int T, int k, int E, int d, int F) {
   return (KT + ktp - 1) / ktp;
 }
 
-static int routed_down_variant() {
-  const int v = knob(kKnobRoutedDownVariant);
-  return v < 0 ? routed_variant() : v;
-}
-
 // Channels per tile of the large-batch down projection (the unit of plan.row_planes).
-int routed_down_tile_n(int planes) {
-  if (planes > 1) return RoutedCfg<1, 2, 2, 2, 2, 2>::BN;
-  switch (routed_down_variant()) {
-    case 1: return RoutedCfg<1, 4, 2, 1, 4, 2>::BN;
-    case 2: return RoutedCfg<1, 2, 2, 2, 2, 2>::BN;
-    default: return RoutedCfg<1, 2, 4, 2, 2, 2>::BN;
-  }
-}
+int routed_down_tile_n(int planes) { return planes > 1 ? DownPlanesCfg::BN : DownCfg::BN; }
 
 hipError_t launch_routed_down(const RoutedGemmArgs& a, hipStream_t stream) {
   if (a.max_tiles == 0) return hipSuccess;
-  if (a.planes > 1) return launch_cfg<RoutedCfg<1, 2, 2, 2, 2, 2>>(a, a.planes, stream);   // small problem: 128 x 128 tiles
-  switch (routed_down_variant()) {
-    case 1: return launch_cfg<RoutedCfg<1, 4, 2, 1, 4, 2>>(a, 1, stream);
-    case 2: return launch_cfg<RoutedCfg<1, 2, 2, 2, 2, 2>>(a, 1, stream);
-    default: return launch_cfg<RoutedCfg<1, 2, 4, 2, 2, 2>>(a, 1, stream);
-  }
+  if (a.planes > 1) return launch_cfg<DownPlanesCfg>(a, a.planes, stream);   // small problem
+  return launch_cfg<DownCfg>(a, 1, stream);
 }
 
 }  // namespace mote
