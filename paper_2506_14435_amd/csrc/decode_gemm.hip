@@ -1350,7 +1350,7 @@ template <int NW, int RING>
 __device__ __forceinline__ void router_role(const RouterRoleArgs& r, int tok) {
   extern __shared__ __attribute__((aligned(16))) unsigned char s_ring[];
   static_assert(sizeof(RouterScratch<1, NW>) <= RING, "");
-  router_quant_group<16, 1, NW, 2>(*reinterpret_cast<RouterScratch<1, NW>*>(s_ring), tok, r.x, r.w_router, r.bias, r.T, r.d, r.E, r.k,
+  router_quant_group<16, 1, NW, 8>(*reinterpret_cast<RouterScratch<1, NW>*>(s_ring), tok, r.x, r.w_router, r.bias, r.T, r.d, r.E, r.k,
                                    r.topk_idx, r.topk_p, r.q_x, r.beta_x, r.rowsum_x, nullptr);
 }
 template <int NT, int RING>
@@ -1362,7 +1362,10 @@ __device__ __forceinline__ void quant_role(const QuantRoleArgs& r, int row) {
 
 // Workgroups of four wavefronts for the sake of the small kernels; a streaming unit is one wavefront, the
 // other three end at once.  (One wavefront per workgroup left the router a chain of memory round trips
-// behind the weight stream: the head kernel took 29 us at T = 1 and T = 64.)
+// behind the weight stream: the head kernel took 29 us at T = 1 and T = 64.)  A router requests all eight router rows of
+// its chunk before it uses one: two at a time they were four round trips that end after the stream does (us per forward,
+// two -> eight at a time: d = 2048, F = 11008, E = 16 T = 1 59.1 -> 57.4, T = 16 91.5 -> 88.3, T = 64 106.8 -> 106.1;
+// d = 256 T = 64 29.2 -> 27.1; d = 896, E = 8 T = 1 30.3 -> 29.6, T = 64 41.8 -> 42.2).
 template <int AL, int KIB>
 __global__ __launch_bounds__(256) void decode_head_kernel(RouterRoleArgs r, SharedDecodeArgs a) {
   constexpr int LDS = SharedWaveCfg<0, AL, KIB>::LDS;

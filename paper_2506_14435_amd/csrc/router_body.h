@@ -41,6 +41,33 @@ __device__ __forceinline__ void load_router_row(const uint16_t* __restrict__ row
   }
 }
 
+// The same in two steps, so that all rows of a chunk can be on their way together: the bf16 patterns of a row, two
+// per register, and their conversion.  vec: 8 for rows of whole 16-byte runs, 4 for 8-byte runs (of an aligned matrix).
+template <int EMAX>
+__device__ __forceinline__ void load_router_row_raw(const uint16_t* __restrict__ row, int E, int vec, uint32_t (&r)[EMAX / 2]) {
+#pragma unroll
+  for (int i = 0; i < EMAX / 2; ++i) r[i] = 0u;
+  if (vec == 8) {
+#pragma unroll
+    for (int v = 0; v < EMAX / 8; ++v)
+      if (v * 8 < E) {
+        const uint4 p = *reinterpret_cast<const uint4*>(row + v * 8);
+        r[v * 4] = p.x; r[v * 4 + 1] = p.y; r[v * 4 + 2] = p.z; r[v * 4 + 3] = p.w;
+      }
+  } else if (vec == 4) {
+#pragma unroll
+    for (int v = 0; v < EMAX / 4; ++v)
+      if (v * 4 < E) {
+        const uint2 p = *reinterpret_cast<const uint2*>(row + v * 4);
+        r[v * 2] = p.x; r[v * 2 + 1] = p.y;
+      }
+  } else {
+#pragma unroll
+    for (int e = 0; e < EMAX; ++e)
+      if (e < E) r[e / 2] |= static_cast<uint32_t>(row[e]) << (16 * (e & 1));
+  }
+}
+
 // Gate softmax (Eq.3) and top-k of one token on the EMAX consecutive lanes that hold its logits
 // (lane's expert e; logits beyond E are padding).  `store`: whether this lane group's token exists
 // and is this group's to write (the lanes still take part in the shuffles otherwise).
@@ -101,7 +128,8 @@ struct RouterScratch {   // LDS of a workgroup
 };
 
 // One token group = TPW tokens from t0 on; the NW wavefronts of the workgroup split its channels.
-// ROWS: router rows of a chunk requested together (registers against latency).
+// ROWS: router rows of a chunk requested together (registers against latency); 8: all of them, as raw patterns, in front
+// of the first multiplication - one memory round trip per chunk, for workgroups whose time is that chain.
 template <int EMAX, int TPW, int NW, int ROWS>
 __device__ __forceinline__ void router_quant_group(
     RouterScratch<TPW, NW>& lds, int t0, const uint16_t* __restrict__ x, const uint16_t* __restrict__ w_router, const float* __restrict__ bias, int T,
@@ -114,6 +142,7 @@ __device__ __forceinline__ void router_quant_group(
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int n_chunks = d >> 3;
   const bool vec_ok = (E & 7) == 0;
+  const int vec = vec_ok ? 8 : (E & 3) == 0 && (reinterpret_cast<uintptr_t>(w_router) & 7) == 0 ? 4 : 0;
 
   const uint16_t* xrow[TPW];
 #pragma unroll
@@ -143,6 +172,25 @@ __device__ __forceinline__ void router_quant_group(
 #pragma unroll
       for (int i = 0; i < 8; ++i) amax[t] = fmaxf(amax[t], fabsf(xf[t][i]));
     }
+    if constexpr (ROWS == 8) {
+      uint32_t raw[8][EMAX / 2];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) load_router_row_raw<EMAX>(w_router + static_cast<int64_t>(c0 + i) * E, E, vec, raw[i]);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+#pragma unroll
+        for (int t = 0; t < TPW; ++t) {
+          const double xv = static_cast<double>(xf[t][i]);
+#pragma unroll
+          for (int e = 0; e < EMAX; ++e) {
+            const uint32_t p = raw[i][e / 2];
+            acc[t * EMAX + e] = fma(xv, static_cast<double>(e & 1 ? bf16_hi(p) : bf16_lo(p)), acc[t * EMAX + e]);
+          }
+        }
+        __builtin_amdgcn_sched_barrier(0);   // a row at a time: all conversions at once would take 256 registers
+      }
+    } else
 #pragma unroll ROWS
     for (int i = 0; i < 8; ++i) {
       double w[EMAX];

@@ -966,3 +966,49 @@ def test_decode_step_with_the_plan_alone_inside_the_gate_up_kernel(T, k, shared_
     assert taps[0]["counts"].sum() == T * k
     for n in taps[0]:
         assert torch.equal(taps[0][n], taps[1][n]), n
+
+
+def _small_layer(M, d, F, E, k, w_router, shared_bits=0, seed=0):
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    rnd = lambda *s, std=1.0: torch.randn(*s, device="cuda", generator=g) * std
+    shared, scales = [rnd(*s, std=0.02).to(torch.bfloat16) for s in ((F, d), (F, d), (d, F))], None
+    dense = [w.double() for w in shared]
+    if shared_bits:
+        q = [O.rtn_quantize(W.bf16_bits(w.cpu()), shared_bits) for w in shared]
+        dense = [torch.from_numpy(c).cuda().double() * torch.from_numpy(s).cuda().double()[:, None] for c, s in q]
+        packed = [M.mote_pack_rtn(w, shared_bits) for w in shared]
+        shared, scales = [p for p, _ in packed], tuple(s for _, s in packed)
+    wt = [torch.empty(E, d * F // 16, dtype=torch.int32, device="cuda") for _ in range(3)]
+    alpha = torch.empty(3, E, 1, dtype=torch.float32, device="cuda")
+    for e in range(E):
+        for m in range(3):
+            M.mote_pack_ternary(rnd(*((F, d) if m < 2 else (d, F)), std=0.02), packed=wt[m][e], alpha=alpha[m, e])
+    layer = M.MoteLayer(w_router, *shared, *wt, alpha[:, :, 0].t().contiguous(), k, shared_bits=shared_bits, shared_scales=scales)
+    layer.shared_dense = dense
+    return layer
+
+
+# The router inside the decode kernel reads a chunk's router rows as whole 16-byte runs, 8-byte runs of an aligned matrix
+# or single elements: expert counts of each kind, and matrices that begin 2 and 4 bytes past an 8-byte boundary.  The same
+# experts, weights and codes as the router kernel of its own, to the bit (same sums in the same order).
+@pytest.mark.parametrize("E,k,offset", [(16, 2, 0), (8, 1, 0), (12, 2, 0), (4, 4, 0), (12, 2, 1), (4, 1, 2), (6, 2, 0), (13, 3, 0), (1, 1, 1)])
+@pytest.mark.parametrize("T,d,shared_bits", [(1, 128, 0), (5, 2176, 0), (64, 384, 8)])
+def test_router_rows_of_every_alignment_inside_the_decode_kernel(E, k, offset, T, d, shared_bits):
+    M = _m()
+    g = torch.Generator(device="cuda").manual_seed(E * 100 + T)
+    w = torch.empty(d * E + 8, dtype=torch.bfloat16, device="cuda")[offset:offset + d * E].view(d, E)
+    w.copy_(torch.randn(d, E, device="cuda", generator=g) * d ** -0.5)
+    layer = _small_layer(M, d, 256, E, k, w, shared_bits=shared_bits, seed=E)
+    x = torch.randn(T, d, device="cuda", generator=g).to(torch.bfloat16)
+    names = ("topk_idx", "topk_p", "q_x", "beta_x", "out_f32")
+    taps = {}
+    try:
+        for mode in (0, 2):
+            M.mote_tuning_set("decode_roles", mode)
+            taps[mode] = M.alloc_taps(layer, T, names)
+            M.mote_layer_forward(layer, x, taps=taps[mode])
+            torch.cuda.synchronize()
+    finally:
+        M.mote_tuning_set("decode_roles", 1)
+    for n in names:
+        assert torch.equal(taps[0][n], taps[2][n]), n
