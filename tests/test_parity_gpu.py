@@ -1012,3 +1012,23 @@ def test_router_rows_of_every_alignment_inside_the_decode_kernel(E, k, offset, T
         M.mote_tuning_set("decode_roles", 1)
     for n in names:
         assert torch.equal(taps[0][n], taps[2][n]), n
+
+
+# Batches of up to 64 tokens with at most two experts per token have a combine kernel of their own; with the fp32 output
+# tapped the general one runs.  Same sums in the same order: equal to the bit, with the residual of a block too.
+# One token and the most, one more, one channel group per row tile and a wide row, one and several planes of either kind.
+@pytest.mark.parametrize("T,d,F,E,k", [(1, 128, 256, 4, 1), (64, 256, 512, 4, 2), (65, 256, 512, 4, 2), (3, 2176, 640, 4, 2), (2, 128, 4096, 4, 2),
+                                       (63, 1536, 8960, 4, 1), (5, 256, 512, 4, 3)])
+@pytest.mark.parametrize("shared_bits", [0, 4])
+def test_combine_of_few_tokens_equals_the_general_one(T, d, F, E, k, shared_bits):
+    M = _m()
+    g = torch.Generator(device="cuda").manual_seed(T + d)
+    layer = _small_layer(M, d, F, E, k, (torch.randn(d, E, device="cuda", generator=g) * d ** -0.5).to(torch.bfloat16), shared_bits, T)
+    x = torch.randn(T, d, device="cuda", generator=g).to(torch.bfloat16)
+    gamma = torch.ones(d, dtype=torch.bfloat16, device="cuda")
+    for call in (lambda **kw: M.mote_layer_forward(layer, x, **kw), lambda **kw: M.mote_block_forward(layer, x, gamma, None, eps=1e-6, **kw)):
+        taps = M.alloc_taps(layer, T, ("out_f32",))
+        plain, general = call(), call(taps=taps)
+        torch.cuda.synchronize()
+        assert torch.equal(plain, general) and torch.equal(general, taps["out_f32"].to(torch.bfloat16))
+        assert general.float().abs().max() > 0
