@@ -1032,3 +1032,74 @@ def test_combine_of_few_tokens_equals_the_general_one(T, d, F, E, k, shared_bits
         torch.cuda.synchronize()
         assert torch.equal(plain, general) and torch.equal(general, taps["out_f32"].to(torch.bfloat16))
         assert general.float().abs().max() > 0
+
+
+def _unpacked(words, n_rows, n_cols):
+    """Ternary matrix of the packed words (layout of O.pack_int2), as float64 on the device."""
+    w = words.view(n_rows // 32, n_cols // 128, 2, 32, 4)                       # row tile, K tile, g, r, s
+    code = torch.stack([(w >> (8 * (i % 4) + 2 * (i // 4))) & 3 for i in range(16)], dim=-1)
+    return (code.permute(0, 3, 1, 4, 2, 5).reshape(n_rows, n_cols) - 1).double()
+
+
+# Routed tiles run K loops of 32, 64, 96 or 128 rows: tiles of every height at and beside those limits, alone and behind a
+# full tile, an expert without rows, one K plane and several.  Integer accumulators, exact.
+@pytest.mark.parametrize("counts", [(1, 32, 33, 64, 65, 96, 97, 128), (129, 160, 161, 225, 256, 300, 0, 31)])
+@pytest.mark.parametrize("d,F", [(128, 256), (384, 640), (256, 4096), (2176, 384)])
+def test_routed_tiles_of_every_height(d, F, counts):
+    M = _m()
+    E, T = len(counts), sum(counts)
+    g = torch.Generator(device="cuda").manual_seed(d + T)
+    w = torch.zeros(d, E, device="cuda")
+    w[torch.arange(E), torch.arange(E)] = 1.0                    # channel e alone decides for expert e
+    layer = _small_layer(M, d, F, E, 1, w.to(torch.bfloat16), seed=d)
+    expert = torch.repeat_interleave(torch.arange(E), torch.tensor(counts))[torch.randperm(T, generator=torch.Generator().manual_seed(T))]
+    x = torch.randn(T, d, device="cuda", generator=g)
+    x[:, :E] = 0
+    x[torch.arange(T), expert] = 6.0
+    taps = M.alloc_taps(layer, T, ("counts", "tok_of", "q_x", "acc_gate", "acc_up", "q_h", "acc_down"))
+    M.mote_layer_forward(layer, x.to(torch.bfloat16), taps=taps)
+    torch.cuda.synchronize()
+    assert tuple(taps["counts"].tolist()) == counts
+    q_x, tok_of, q_h = taps["q_x"].double(), taps["tok_of"].long(), taps["q_h"].double()
+    lo = 0
+    for e, n in enumerate(counts):
+        if n:
+            t = [_unpacked(layer.tensors[m][e], *((F, d) if m != "wt_down" else (d, F))) for m in ("wt_gate", "wt_up", "wt_down")]
+            rows = q_x[tok_of[lo:lo + n]]
+            assert torch.equal(taps["acc_gate"][lo:lo + n].double(), rows @ t[0].T), e
+            assert torch.equal(taps["acc_up"][lo:lo + n].double(), rows @ t[1].T), e
+            assert torch.equal(taps["acc_down"][lo:lo + n].double(), q_h[lo:lo + n] @ t[2].T), e
+        lo += n
+
+
+# The shared expert's GEMM tiles (128 x 128, 128 x 256 and 256 x 256, by the cost model and each of them forced): token and
+# channel remainders of every tile, one K chunk and a few, K planes of the down projection, and the scaled epilogue of
+# a quantised expert whose expanded codes take the same kernels.
+@pytest.mark.parametrize("variant", [0, 1, 2, 3])
+@pytest.mark.parametrize("T,d,F,shared_bits", [(65, 128, 256, 0), (129, 384, 640, 0), (300, 256, 4096, 0), (257, 896, 1152, 0),
+                                               (1025, 256, 384, 0), (513, 256, 640, 8), (520, 384, 512, 4)])
+def test_shared_gemm_tiles(variant, T, d, F, shared_bits):
+    M = _m()
+    g = torch.Generator(device="cuda").manual_seed(T + d)
+    layer = _small_layer(M, d, F, 4, 1, (torch.randn(d, 4, device="cuda", generator=g) * d ** -0.5).to(torch.bfloat16), shared_bits, T)
+    x = torch.randn(T, d, device="cuda", generator=g).to(torch.bfloat16)
+    w = layer.shared_dense
+    taps = M.alloc_taps(layer, T, ("h_s", "y_s"))
+    try:
+        M.mote_tuning_set("shared_variant", variant)
+        M.mote_layer_forward(layer, x, taps=taps)
+        torch.cuda.synchronize()
+    finally:
+        M.mote_tuning_set("shared_variant", 0)
+    xd = x.double()
+    gate = xd @ w[0].T
+    h_ref = (gate * torch.sigmoid(gate) * (xd @ w[1].T)).float().to(torch.bfloat16)
+    h = taps["h_s"]
+    neq = h != h_ref                     # fp32 sums against fp64: a rounding flips now and then, by one bf16 step
+    a, b = h[neq].double(), h_ref[neq].double()
+    assert neq.double().mean() <= 5e-3
+    assert ((a - b).abs() <= torch.maximum(a.abs(), b.abs()) * 2.0 ** -7 + 1e-5 * h_ref.abs().max().double()).all()
+    # F products summed in fp32 in any order: at most F roundings of 2^-24, each of no more than the sum of magnitudes
+    hd = h.double()
+    bound = F * 2.0 ** -24 * (hd.abs() @ w[2].abs().T) + 1e-30
+    assert ((taps["y_s"].double() - hd @ w[2].T).abs() <= bound).all()
