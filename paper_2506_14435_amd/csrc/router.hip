@@ -9,6 +9,8 @@
 // summation order).  A 6-step butterfly reduce-scatter leaves lane l with the finished
 // logit (token l / EMAX, expert l % EMAX).  The token rows are then read a second time
 // (L2 hits) to emit the int8 row, its absmax and its integer row sum.
+#include <type_traits>
+
 #include "common.h"
 #include "launch.h"
 #include "router_body.h"
@@ -33,29 +35,33 @@ __global__ __launch_bounds__(64 * NW) void router_quant_kernel(
 // (v_mfma_f64_16x16x4: the products of bf16 values are exact in fp64, the sums are fp64 as in the
 // kernel above, one instruction where that kernel issues sixteen vector FMAs).  A workgroup of four
 // wavefronts owns 16 tokens; wavefront w takes the channels 128 j + 32 w .. + 31 of every 128.  Lane
-// (t = lane % 16, g = lane / 16) loads the 8 channels 128 j + 32 w + 8 g .. + 7 of token t (16 bytes) for
-// every j up front and keeps them in registers for the quantisation pass: element i of that chunk is
-// this lane's A operand (row t, contraction slot g) of MFMA (j, i), whose B operand (slot g, expert
-// lane % 16) is router row 128 j + 32 w + 8 g + i.  The router matrix goes through LDS in blocks of 256
-// channels, converted to fp64 once per workgroup and stored in the order the B operands are read:
-// [group (j, w)][i][lane], rows of 64 doubles padded by 16 bytes so that the staging writes (one channel
-// row per thread, sixteen experts = 128 contiguous bytes) spread over the banks.
+// (t = lane % 16, g = lane / 16) loads the 8 channels 128 j + 32 w + 8 g .. + 7 of token t (16 bytes) and
+// keeps them in registers for the quantisation pass: element i of that chunk is this lane's A operand (row t,
+// contraction slot g) of MFMA (j, i), whose B operand (slot g, expert lane % 16) is router row
+// 128 j + 32 w + 8 g + i.  Every router row is used by one wavefront of the workgroup, so each wavefront
+// turns its 32 rows of a step, converted to fp64, through LDS of its own ([i][lane], rows of 64 doubles padded by
+// 16 bytes so that the writes of four rows at a time spread over the banks) and the steps need no barrier.  Tokens and
+// rows are requested eight steps ahead in step order, the next step's rows are turned in front of a step's MFMAs.
+// Bound by fp64 issue: an MFMA takes 29 - 33 ns per SIMD, a conversion to fp64 some 4 (T = 8192, d = 2048: 8.6 + 2 us
+// of the 19.6 the kernel takes; 23.6 with the router in LDS blocks of the workgroup, two barriers each, behind all tokens'
+// loads; with the counts, us, before -> after: T = 8192 at E = 16 31.0 -> 25.7, E = 12 33.5 -> 25.0, E = 6 32.0 -> 29.1,
+// d = 3584 43.3 -> 34.6, T = 16384 79 -> 64).  Eight wavefronts per workgroup: d = 2048 -1 us, d = 3584 +2.5 (T = 8192).
 typedef double v4d __attribute__((ext_vector_type(4)));
 constexpr int kRmTokens = 16;
-// From this many tokens on.  Measured (d = 2048, E = 16): T = 8192 40.9 -> 30.8 us, T = 16384 at d = 3584
-// 125 -> 97 us; at T <= 2048 the T / 16 workgroups are too few and the kernels above are as fast or faster
-// (T = 1024: 13 vs 19 us).  Both kernels are bound by fp64 issue: one matrix instruction takes 40-60 ns per
-// SIMD for its 1024 multiply-adds, about what sixteen vector FMAs take.
+// From this many tokens on.  Measured against the kernels above (d = 2048, E = 16): T = 4096 a fifth faster, more beyond;
+// at T <= 2048 the T / 16 workgroups are too few and the kernels above are as fast or faster
+// (T = 1024: 13 vs 19 us).
 constexpr int kRmMinTokens = 4096;
-constexpr int kRmBlockChannels = 256;
+constexpr int kRmAhead = 8;   // steps of 128 channels on their way to each wavefront
 constexpr int kRmRowBytes = 64 * 8 + 16;
 
-template <int NGW>   // upper bound of the 128-channel steps (d / 128) the registers are sized for
+// NGW: upper bound of the 128-channel steps (d / 128) the registers are sized for.  VEC: elements per load of a router row.
+template <int NGW, int VEC>
 __global__ __launch_bounds__(256) void router_mfma_kernel(
-    const uint16_t* __restrict__ x, const uint16_t* __restrict__ w_router, const float* __restrict__ bias, int T,
+    const uint16_t* x, const uint16_t* w_router, const float* __restrict__ bias, int T,
     int d, int E, int k, int32_t* __restrict__ topk_idx, float* __restrict__ topk_p, int8_t* __restrict__ q_x,
     float* __restrict__ beta_x, int32_t* __restrict__ rowsum_x, float* __restrict__ gate_p) {
-  __shared__ __attribute__((aligned(16))) unsigned char s_b[(kRmBlockChannels / 32) * 8 * kRmRowBytes];
+  __shared__ __attribute__((aligned(16))) unsigned char s_b[4][8 * kRmRowBytes];
   __shared__ double s_part[4][kRmTokens][16];
   __shared__ float s_amax[4][kRmTokens];
   __shared__ int s_rsum[4][kRmTokens];
@@ -64,69 +70,83 @@ __global__ __launch_bounds__(256) void router_mfma_kernel(
   const int t0 = blockIdx.x * kRmTokens;
   const int ngw = d >> 7;
   const uint16_t* const xrow = x + static_cast<int64_t>(min(t0 + t, T - 1)) * d + 32 * wave + 8 * g;
+  // staging: this lane's router row of the 32 of a step, and its half of the experts (zero beyond E)
+  const int sr = lane >> 1, se = 8 * (lane & 1);
+  const uint16_t* const wrow = w_router + static_cast<int64_t>(32 * wave + sr) * E;
+  const int64_t wstep = static_cast<int64_t>(128) * E;
+  // eight elements as they come, addresses clamped to the row: what lies beyond E is zeroed when it is staged
+  constexpr int kRaw = VEC == 1 ? 8 : 4;
+  struct Raw { uint32_t v[kRaw]; };
+  auto load_w = [&](int j) __attribute__((always_inline)) {
+    Raw r;
+    const uint16_t* const wr = wrow + j * wstep;
+    if constexpr (VEC == 8) {
+      const u4 p = *reinterpret_cast<const u4*>(wr + min(se, E - 8));
+      r.v[0] = p.x; r.v[1] = p.y; r.v[2] = p.z; r.v[3] = p.w;
+    } else if constexpr (VEC == 4) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const uint2 p = *reinterpret_cast<const uint2*>(wr + min(se + 4 * h, E - 4));
+        r.v[2 * h] = p.x; r.v[2 * h + 1] = p.y;
+      }
+    } else {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) r.v[e] = wr[min(se + e, E - 1)];
+    }
+    return r;
+  };
+  auto weight = [&](const Raw& r, int e) __attribute__((always_inline)) {
+    const uint32_t v = VEC == 1 ? r.v[e] << 16 : e & 1 ? r.v[e >> 1] & 0xFFFF0000u : r.v[e >> 1] << 16;
+    return static_cast<double>(__uint_as_float(se + e < E ? v : 0u));
+  };
+  unsigned char* const s_dst = s_b[wave] + (sr & 7) * kRmRowBytes + (sr >> 3) * 128 + se * 8;
+  const unsigned char* const s_src = s_b[wave] + lane * 8;
 
   u4 xk[NGW];
+  Raw wk[kRmAhead];
 #pragma unroll
-  for (int j = 0; j < NGW; ++j)
-    xk[j] = j < ngw ? *reinterpret_cast<const u4*>(xrow + 128 * j) : u4{0u, 0u, 0u, 0u};
-
+  for (int j = 0; j < kRmAhead && j < NGW; ++j) {
+    wk[j] = load_w(min(j, ngw - 1));
+    xk[j] = *reinterpret_cast<const u4*>(xrow + 128 * min(j, ngw - 1));
+    __builtin_amdgcn_sched_barrier(0);   // loads stay where they are issued: in step order, all in front of the work
+  }
+  // router rows of a step, as fp64, through this wavefront's own LDS (in order within a wavefront: no barrier)
+  auto turn = [&](const Raw& wq, double (&b)[8]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int e = 0; e < 8; e += 2) *reinterpret_cast<double2*>(s_dst + e * 8) = make_double2(weight(wq, e), weight(wq, e + 1));
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+    for (int i = 0; i < 8; ++i) b[i] = *reinterpret_cast<const double*>(s_src + i * kRmRowBytes);
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  };
   v4d acc = {0.0, 0.0, 0.0, 0.0};
   float amax = 0.0f;
-  // staging: thread sc owns channel row sc of the block; its router row (E bf16 values, zero beyond E) is
-  // fetched one block ahead, so that it travels while the previous block is contracted
-  const int sc = threadIdx.x;
-  unsigned char* const s_dst = s_b + (((sc >> 5) * 8 + (sc & 7)) * kRmRowBytes) + ((sc >> 3) & 3) * 128;
-  const bool vec_ok = (E & 7) == 0;
-  auto load_w = [&](int jb, uint32_t (&wq)[8]) {
-#pragma unroll
-    for (int i = 0; i < 8; ++i) wq[i] = 0u;
-    const int c = jb * 128 + sc;
-    if (jb < ngw && c < d) {
-      const uint16_t* const wr = w_router + static_cast<int64_t>(c) * E;
-      if (vec_ok) {
-        const u4 lo = *reinterpret_cast<const u4*>(wr);
-        wq[0] = lo.x; wq[1] = lo.y; wq[2] = lo.z; wq[3] = lo.w;
-        if (E > 8) {
-          const u4 hi = *reinterpret_cast<const u4*>(wr + 8);
-          wq[4] = hi.x; wq[5] = hi.y; wq[6] = hi.z; wq[7] = hi.w;
-        }
-      } else {
-#pragma unroll
-        for (int e = 0; e < 16; ++e)
-          if (e < E) wq[e >> 1] |= static_cast<uint32_t>(wr[e]) << (16 * (e & 1));
-      }
+  double b[2][8];
+  turn(wk[0], b[0]);
+  // the steps nest (step j + 1 inside the condition of step j): each has one way in, so its wait counts the loads behind it
+  auto step = [&](auto self, auto jc) __attribute__((always_inline)) {
+    constexpr int j = decltype(jc)::value;
+    if (j >= ngw) return;
+    if constexpr (j + kRmAhead < NGW) {   // the clamp keeps the loads of a step free of a branch of their own
+      wk[j % kRmAhead] = load_w(min(j + kRmAhead, ngw - 1));
+      xk[j + kRmAhead] = *reinterpret_cast<const u4*>(xrow + 128 * min(j + kRmAhead, ngw - 1));
     }
+    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (j + 1 < NGW) turn(wk[(j + 1) % kRmAhead], b[(j + 1) & 1]);   // travels under the matrix instructions
+    __builtin_amdgcn_sched_barrier(0);
+    const u4 p = xk[j];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const float xv = (i & 1) ? bf16_hi(p[i >> 1]) : bf16_lo(p[i >> 1]);
+      amax = fmaxf(amax, fabsf(xv));
+      acc = __builtin_amdgcn_mfma_f64_16x16x4f64(static_cast<double>(xv), b[j & 1][i], acc, 0, 0, 0);
+    }
+    if constexpr (j + 1 < NGW) self(self, std::integral_constant<int, j + 1>{});
   };
-  uint32_t wq[8];
-  load_w(0, wq);
-#pragma unroll
-  for (int jb = 0; jb < NGW; jb += 2) {   // blocks of 256 channels = two steps j
-    if (jb < ngw) {
-      __syncthreads();   // every wavefront is done with the previous block
-#pragma unroll
-      for (int e = 0; e < 16; e += 2)
-        *reinterpret_cast<double2*>(s_dst + e * 8) =
-            make_double2(static_cast<double>(bf16_lo(wq[e >> 1])), static_cast<double>(bf16_hi(wq[e >> 1])));
-      load_w(jb + 2, wq);
-      __syncthreads();
-#pragma unroll
-      for (int jj = 0; jj < 2; ++jj) {
-        const int j = jb + jj;
-        if (j < NGW && j < ngw) {
-          const u4 p = xk[j];
-          const uint32_t pw[4] = {p.x, p.y, p.z, p.w};
-          const unsigned char* const rows = s_b + (jj * 4 + wave) * 8 * kRmRowBytes + lane * 8;
-#pragma unroll
-          for (int i = 0; i < 8; ++i) {
-            const float xv = (i & 1) ? bf16_hi(pw[i >> 1]) : bf16_lo(pw[i >> 1]);
-            amax = fmaxf(amax, fabsf(xv));
-            const double b = *reinterpret_cast<const double*>(rows + i * kRmRowBytes);
-            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(static_cast<double>(xv), b, acc, 0, 0, 0);
-          }
-        }
-      }
-    }
-  }
+  step(step, std::integral_constant<int, 0>{});
 
   // accumulator element v of lane (t, g) is logit (token g + 4 v, expert t) over this wavefront's channels
 #pragma unroll
@@ -190,15 +210,15 @@ hipError_t launch_router_quant(const uint16_t* x, const uint16_t* w_router, cons
                                                            rowsum_x, gate_p);
     else if (T >= kRmMinTokens && d <= 4096) {   // 16 tokens per workgroup on the fp64 matrix instruction
       const int wgs = (T + kRmTokens - 1) / kRmTokens;
-      if (d <= 1024)
-        router_mfma_kernel<8><<<wgs, 256, 0, stream>>>(x, w_router, bias, T, d, E, k, topk_idx, topk_p, q_x, beta_x,
-                                                       rowsum_x, gate_p);
-      else if (d <= 2048)
-        router_mfma_kernel<16><<<wgs, 256, 0, stream>>>(x, w_router, bias, T, d, E, k, topk_idx, topk_p, q_x, beta_x,
-                                                        rowsum_x, gate_p);
-      else
-        router_mfma_kernel<32><<<wgs, 256, 0, stream>>>(x, w_router, bias, T, d, E, k, topk_idx, topk_p, q_x, beta_x,
-                                                        rowsum_x, gate_p);
+      const int vec = (E & 7) == 0 ? 8 : (E & 3) == 0 && (reinterpret_cast<uintptr_t>(w_router) & 7) == 0 ? 4 : 1;
+#define MOTE_RM(NGW_, VEC_) router_mfma_kernel<NGW_, VEC_><<<wgs, 256, 0, stream>>>(x, w_router, bias, T, d, E, k, topk_idx, topk_p, q_x, beta_x, rowsum_x, gate_p)
+#define MOTE_RM_VEC(NGW_) \
+  if (vec == 8) MOTE_RM(NGW_, 8); else if (vec == 4) MOTE_RM(NGW_, 4); else MOTE_RM(NGW_, 1)
+      if (d <= 1024) { MOTE_RM_VEC(8); }
+      else if (d <= 2048) { MOTE_RM_VEC(16); }
+      else { MOTE_RM_VEC(32); }
+#undef MOTE_RM_VEC
+#undef MOTE_RM
     }
     else if (coop)
       router_quant_kernel<16, kTpw, 4><<<blocks, 256, 0, stream>>>(x, w_router, bias, T, d, E, k, topk_idx, topk_p, q_x,

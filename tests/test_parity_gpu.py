@@ -1103,3 +1103,26 @@ def test_shared_gemm_tiles(variant, T, d, F, shared_bits):
     hd = h.double()
     bound = F * 2.0 ** -24 * (hd.abs() @ w[2].abs().T) + 1e-30
     assert ((taps["y_s"].double() - hd @ w[2].T).abs() <= bound).all()
+
+
+# Many tokens go through the fp64 matrix kernel, with router rows read by 16 or 8 bytes or by elements: every such kind and
+# register bound (d = 1024, 2048, 4096), a number of channel steps that is no multiple of those in flight, a last
+# workgroup of one token, and a matrix that begins 2 bytes past an 8-byte boundary.  Against the kernel of smaller batches.
+@pytest.mark.parametrize("d,E,k,offset", [(128, 16, 2, 0), (896, 8, 2, 0), (1024, 12, 2, 1), (1152, 4, 1, 0), (2048, 12, 3, 0), (2048, 13, 2, 0),
+                                          (2176, 16, 2, 0), (3584, 6, 2, 0), (4096, 1, 1, 0), (4096, 16, 8, 0)])
+def test_router_many_tokens_equals_smaller_batches(d, E, k, offset):
+    M = _m()
+    T = 4096 + 17
+    g = torch.Generator(device="cuda").manual_seed(d + E)
+    w = torch.empty(d * E + 8, dtype=torch.bfloat16, device="cuda")[offset:offset + d * E].view(d, E)
+    w.copy_(torch.randn(d, E, device="cuda", generator=g) * d ** -0.5)
+    x = torch.randn(T, d, device="cuda", generator=g).to(torch.bfloat16)
+    x[5, 3], x[4100, d - 1] = float("inf"), float("nan")
+    idx, p, counts = M.mote_router_topk(x, w, k)
+    parts = [M.mote_router_topk(x[i:i + 1024], w, k) for i in range(0, T, 1024)]
+    torch.cuda.synchronize()
+    keep = torch.ones(T, dtype=torch.bool, device="cuda")
+    keep[5] = keep[4100] = False                        # not finite: some valid expert
+    assert torch.equal(idx[keep], torch.cat([q[0] for q in parts])[keep])
+    assert torch.allclose(p[keep], torch.cat([q[1] for q in parts])[keep], rtol=2e-6, atol=1e-9)   # as against the oracle
+    assert (idx >= 0).all() and (idx < E).all() and counts.sum().item() == T * k
