@@ -48,10 +48,11 @@ __global__ __launch_bounds__(64 * NW) void router_quant_kernel(
 // d = 3584 43.3 -> 34.6, T = 16384 79 -> 64).  Eight wavefronts per workgroup: d = 2048 -1 us, d = 3584 +2.5 (T = 8192).
 typedef double v4d __attribute__((ext_vector_type(4)));
 constexpr int kRmTokens = 16;
-// From this many tokens on.  Measured against the kernels above (d = 2048, E = 16): T = 4096 a fifth faster, more beyond;
-// at T <= 2048 the T / 16 workgroups are too few and the kernels above are as fast or faster
-// (T = 1024: 13 vs 19 us).
-constexpr int kRmMinTokens = 4096;
+// Above this many tokens, and for rows of up to 1024 channels above the batches of a workgroup per token.  us of the
+// kernels above -> of this one: d = 2048, E = 16 T = 512 11.2 -> 11.4, T = 1024 11.7 -> 11.4, T = 2048 14.9 -> 11.6, T = 4000
+// 23.7 -> 12.7; d = 896, E = 8 T = 512 9.1 -> 7.4, T = 2048 11.8 -> 7.8; d = 3584 T = 512 15.1 -> 17.1, T = 1024 15.8 -> 17.0,
+// T = 1536 20.8 -> 17.0, T = 4000 37.9 -> 17.4.
+constexpr int kRmMinTokens = 1024, kRmNarrow = 1024;
 constexpr int kRmAhead = 8;   // steps of 128 channels on their way to each wavefront
 constexpr int kRmRowBytes = 64 * 8 + 16;
 
@@ -208,7 +209,7 @@ hipError_t launch_router_quant(const uint16_t* x, const uint16_t* w_router, cons
     if (T <= router_token_blocks())   // a few tokens: one token per workgroup, a quarter of the arithmetic and of the reduction per lane
       router_quant_kernel<16, 1, 4><<<T, 256, 0, stream>>>(x, w_router, bias, T, d, E, k, topk_idx, topk_p, q_x, beta_x,
                                                            rowsum_x, gate_p);
-    else if (T >= kRmMinTokens && d <= 4096) {   // 16 tokens per workgroup on the fp64 matrix instruction
+    else if ((T > kRmMinTokens || d <= kRmNarrow) && d <= 4096) {   // 16 tokens per workgroup on the fp64 matrix instruction
       const int wgs = (T + kRmTokens - 1) / kRmTokens;
       const int vec = (E & 7) == 0 ? 8 : (E & 3) == 0 && (reinterpret_cast<uintptr_t>(w_router) & 7) == 0 ? 4 : 1;
 #define MOTE_RM(NGW_, VEC_) router_mfma_kernel<NGW_, VEC_><<<wgs, 256, 0, stream>>>(x, w_router, bias, T, d, E, k, topk_idx, topk_p, q_x, beta_x, rowsum_x, gate_p)
