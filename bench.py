@@ -139,7 +139,7 @@ def measure_ste(workload: str, steps, warmup):
             "steps": steps, "warmup": warmup, "ms_per_step": round(ms, 5), "higher_is_better": True, "scaling": "weak",
             "vs_baseline": None, "dtype": "bf16", "data": "synthetic",
             "config": {"workload": f"ste_backward_{cfg.name}", "rows": R, "n_out": N, "n_in": K, "n_experts": E},
-            "roofline": {"kernel": "shared_gemm_kernel (dX and dW contractions)", "bound": "mfma", "achieved": round(ach, 2),
+            "roofline": {"kernel": "big_gemm kernels (dX and dW contractions)", "bound": "mfma", "achieved": round(ach, 2),
                          "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s", "frac": round(ach / PEAK_BF16_TFLOPS, 4), "traffic": None}}
 
 
