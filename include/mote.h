@@ -130,7 +130,7 @@ mote_status mote_pack_rtn(const void* w, int64_t n_out, int64_t n_in, int bits, 
  *                   (the re-blocked 2-bit codes of the experts that share a launch, the transposed gradient
  *                   rows and codes, partial sums of dx: about E N K / 4 + 2 R (N + K) + 32 R K bytes)
  * Limits: N % 128 == 0, K % 128 == 0, 1 <= E <= 64, R >= 0; every operand of one expert below
- * 2 GiB.  Enqueued on hip_stream; the host array is read before the call returns.
+ * 2 GiB (those of all experts together may be larger).  Enqueued on hip_stream; the host array is read before the call returns.
  * Returns MOTE_ERR_INVALID_ARG for NULL pointers or offsets that are not ascending from 0 to R,
  * MOTE_ERR_UNSUPPORTED_SHAPE, MOTE_ERR_WORKSPACE_TOO_SMALL, MOTE_ERR_HIP. */
 size_t mote_ste_backward_workspace_bytes(int R, int N, int K, int E);

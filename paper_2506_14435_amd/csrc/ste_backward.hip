@@ -191,9 +191,12 @@ __global__ __launch_bounds__(kSteThreads) void sum_planes_kernel(const float* __
 
 static inline size_t ste_align(size_t v) { return (v + 255) / 256 * 256; }
 
+// The GEMMs address each operand of a launch with 32-bit byte offsets: the experts of one launch have operands below this.
+constexpr int64_t kSteOperandBytes = int64_t{1} << 32;
+
 // K planes of the dX contraction at most; dX runs as one grouped GEMM over as many experts as have their
-// weights, counted as bf16, below 4 GiB together (the kernel addresses the blocks, an eighth of that, with 32-bit
-// byte offsets; the limit is a tuning knob so that tests reach the loop over batches with small matrices).
+// weights, counted as bf16, below 4 GiB together (the blocks are an eighth of that; the limit is a tuning knob so that
+// tests reach the loop over batches with small matrices) and their gradient rows below kSteOperandBytes.
 constexpr int kSteMaxPlanes = 8;
 static int ste_dx_batch(int N, int K, int E) {
   const int64_t per = static_cast<int64_t>(N) * K * 2;
@@ -232,8 +235,7 @@ hipError_t launch_ste_backward(const uint16_t* dy, const int32_t* offsets_host, 
 
   SteGroups grp;
   grp.n = E;
-  int32_t pad0[65];   // first padded row of every expert = K ranges of the dW contraction
-  int64_t sum_pad = 0, tight = 0;
+  int64_t tight = 0;
   int longest = 0;
   for (int e = 0; e < E; ++e) {
     const int rows_pad = (offsets_host[e + 1] - offsets_host[e] + 63) / 64 * 64;
@@ -244,17 +246,16 @@ hipError_t launch_ste_backward(const uint16_t* dy, const int32_t* offsets_host, 
   // equal length keep the workgroups of the dW GEMM in step (3B width, 16 groups of about 1024 rows:
   // 966 -> 921 us for the GEMM)
   const bool uniform = static_cast<int64_t>(E) * longest * 16 <= tight * 17;
-  for (int e = 0; e <= 64; ++e) {
-    grp.row0[e] = offsets_host[std::min(e, E)];
-    grp.col0[e] = pad0[e] = static_cast<int32_t>(sum_pad);
-    if (e < E) sum_pad += uniform ? longest : (offsets_host[e + 1] - offsets_host[e] + 63) / 64 * 64;
-  }
+  int block[64];   // columns of an expert's block in the transposed operands
+  for (int e = 0; e < E; ++e) block[e] = uniform ? longest : (offsets_host[e + 1] - offsets_host[e] + 63) / 64 * 64;
+  for (int e = 0; e <= 64; ++e) grp.row0[e] = offsets_host[std::min(e, E)], grp.col0[e] = 0;
 
   fill_alpha_kernel<<<(E * K + kSteThreads - 1) / kSteThreads, kSteThreads, 0, stream>>>(alpha, alpha_stride, E, K, alpha_vec);
   // dX: the codes of a batch of experts re-blocked along the contraction, then one grouped GEMM over their rows, scaled by alpha
-  for (int e0 = 0; e0 < E; e0 += batch) {
-    const int nb = std::min(batch, E - e0);
-    const int row0 = offsets_host[e0], rows = offsets_host[e0 + nb] - row0;
+  for (int e0 = 0, nb; e0 < E; e0 += nb) {
+    const int row0 = offsets_host[e0];
+    for (nb = 1; nb < std::min(batch, E - e0) && static_cast<int64_t>(offsets_host[e0 + nb + 1] - row0) * N * 2 < kSteOperandBytes;) ++nb;
+    const int rows = offsets_host[e0 + nb] - row0;
     if (rows == 0) continue;
     reblock_ternary_t_kernel<<<dim3((N / 128) * (K / 128), nb), kSteThreads, 0, stream>>>(packed, N, K, grp, e0, wt);
     const GemmSplit sp = grouped_gemm_split(offsets_host + e0, nb, K, N, kSteMaxPlanes);
@@ -269,18 +270,34 @@ hipError_t launch_ste_backward(const uint16_t* dy, const int32_t* offsets_host, 
                           0, stream>>>(dx_planes, sp.planes, n4, nullptr, dx_b + static_cast<int64_t>(sp.split_row) * K);
     }
   }
-  // dW: the scaled gradient rows and the codes of every expert transposed into [N, sum_pad] and [K, sum_pad]
-  // (expert e in the columns pad0[e] .., padded with zeros to a multiple of 64), then ONE GEMM whose K
-  // ranges are the experts: plane e = dW_e, zeros for an expert without rows.
-  if (sum_pad == 0) {
-    fill_zero_kernel<<<1024, kSteThreads, 0, stream>>>(dw, static_cast<int64_t>(E) * N * K / 4);
-    return hipGetLastError();
+  // dW: the scaled gradient rows and the codes of every expert transposed into [N, columns] and [K, columns]
+  // (an expert's block padded with zeros to a multiple of 64 columns), then ONE GEMM whose K ranges are the experts:
+  // plane e = dW_e, zeros for an expert without rows.  Experts whose blocks reach kSteOperandBytes together go in several
+  // such rounds, which use the same scratch one after the other.
+  for (int e0 = 0, nb; e0 < E; e0 += nb) {
+    int32_t col0[65] = {0};   // first column of every block = K ranges of the contraction
+    int rows_max = 0;
+    for (nb = 0; e0 + nb < E; ++nb) {
+      const int64_t cols = static_cast<int64_t>(col0[nb]) + block[e0 + nb];
+      if (nb > 0 && cols * std::max(N, K) * 2 >= kSteOperandBytes) break;
+      col0[nb + 1] = static_cast<int32_t>(cols);
+      rows_max = std::max(rows_max, block[e0 + nb]);
+    }
+    float* const dw_b = dw + static_cast<int64_t>(e0) * N * K;
+    const int64_t ld = col0[nb];
+    if (ld == 0) {
+      fill_zero_kernel<<<1024, kSteThreads, 0, stream>>>(dw_b, static_cast<int64_t>(nb) * N * K / 4);
+      continue;
+    }
+    SteGroups part;
+    part.n = nb;
+    for (int i = 0; i <= 64; ++i) part.row0[i] = offsets_host[std::min(e0 + i, E)], part.col0[i] = col0[std::min(i, nb)];
+    const unsigned tiles_r = static_cast<unsigned>(rows_max / 64);
+    transpose_groups_kernel<false><<<dim3(tiles_r * (N / 64), nb), kSteThreads, 0, stream>>>(dy, beta, part, N, ld, dyt);
+    transpose_groups_kernel<true><<<dim3(tiles_r * (K / 64), nb), kSteThreads, 0, stream>>>(q, nullptr, part, K, ld, qt);
+    hipError_t err = launch_gemm_tn_f32_kgroups(dyt, qt, N, K, col0, nb, dw_b, stream);
+    if (err != hipSuccess) return err;
   }
-  const unsigned tiles_r = static_cast<unsigned>(longest / 64);
-  transpose_groups_kernel<false><<<dim3(tiles_r * (N / 64), E), kSteThreads, 0, stream>>>(dy, beta, grp, N, sum_pad, dyt);
-  transpose_groups_kernel<true><<<dim3(tiles_r * (K / 64), E), kSteThreads, 0, stream>>>(q, nullptr, grp, K, sum_pad, qt);
-  hipError_t err = launch_gemm_tn_f32_kgroups(dyt, qt, N, K, pad0, E, dw, stream);
-  if (err != hipSuccess) return err;
   return hipGetLastError();
 }
 

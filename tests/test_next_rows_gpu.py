@@ -492,6 +492,33 @@ def test_ste_dx_with_the_last_row_tiles_in_planes_is_exact(R, N, K, E, cuts):
 # Sums near both ends of the fp32 range: the contraction and the scale keep the exponents of dy, t and alpha.  Every
 # row of dy follows the signs of one channel at 2^120, so its own sum is 2^120 times that channel's number of
 # non-zero codes (above 2^127 for more than 128 of 256); every product and partial sum is exact, as is alpha's value.
+def test_ste_gradients_of_rows_beyond_32_bit_offsets():
+    """Gradient rows of 4.33 GB (each expert's below 2 GiB): the experts of one launch of either GEMM stay below 4 GiB, which
+    is as far as its byte offsets reach.  An expert without rows, unequal ones; integer gradients and an activation scale of
+    one, so every sum is an integer below 2^24, and exact times a power of two (in K planes too)."""
+    M = _m()
+    R, N, K, E = 131200, 16512, 128, 9
+    cuts = [16400, 32800, 32800, 49200, 65600, 82000, 98400, 114801]
+    assert R * N * 2 > 1 << 32
+    _log(f"ste backward R={R} N={N} K={K} E={E}")
+    offsets = [0, *cuts, R]
+    g = torch.Generator(device="cuda").manual_seed(9)
+    latent = [torch.randn(N, K, device="cuda", generator=g) * 0.02 for _ in range(E)]
+    packed = torch.cat([M.mote_pack_ternary(w)[0] for w in latent])
+    alpha = torch.tensor([2.0 ** -(e % 3) for e in range(E)], device="cuda")
+    dy = torch.randint(-2, 3, (R, N), dtype=torch.int8, device="cuda", generator=g).to(torch.bfloat16)
+    q = torch.randint(-4, 5, (R, K), dtype=torch.int8, device="cuda", generator=g)
+    dx, dw = M.mote_ste_linear_backward(dy, offsets, packed, alpha, 1, q,
+                                        torch.full((R,), 127.0, device="cuda"), N, K)
+    torch.cuda.synchronize()
+    for e in range(E):
+        a, b = offsets[e], offsets[e + 1]
+        t = torch.from_numpy(O.ternarize(latent[e].cpu().numpy())[0].astype(np.float32)).cuda()
+        rows = dy[a:b].float()
+        assert torch.equal(dx[a:b], (rows @ t) * alpha[e]), e
+        assert torch.equal(dw[e], rows.t() @ q[a:b].float()), e
+
+
 @pytest.mark.parametrize("alpha", [0.0173, float(np.float32(2.0 ** -126) * np.float32(1 + 2.0 ** -23))])
 def test_ste_dx_keeps_the_fp32_range(alpha):
     M = _m()
