@@ -520,13 +520,15 @@ __global__ __launch_bounds__(512, 2) void big_grouped_gemm_kernel(SharedGemmArgs
 // half are read during the half before it, into the other one of two register sets.  The one barrier of a chunk stands
 // between its halves: it publishes the next chunk and frees this one's stage, both its halves' fragments having been read.
 // BNT: channels of a tile, both matrices together.  GROUPED: 0 plain, 1 row groups, 2 K ranges.  TERN: ternary weights, a
-// half's fragments unpacked in front of its MFMAs.
+// half's fragments unpacked in front of its MFMAs: a wavefront has 64 rows x 32 channels of them (with 32 x 64 it unpacks twice as
+// much: 16 groups of 6 rows, N = 2048, K = 10496: 101 -> 88 us).  Tiles of row groups with few rows: wavefronts without rows
+// only load, and rows past the group's end are loads of its last row (88 -> 62; four wavefronts and two workgroups per CU, before: 80).
 template <int MODE_, int BNT_, bool TERN_ = false>
 struct MidCfg {
   static constexpr int MODE = MODE_;
   static constexpr int NMAT = MODE_ == 0 ? 2 : 1;
   static constexpr int BM = 128, BNT = BNT_, BN = BNT_ / NMAT, WAVES = 8, THREADS = 512;
-  static constexpr int WAVES_M = BNT_ == 128 ? 4 : 2, WAVES_N = 8 / WAVES_M;
+  static constexpr int WAVES_M = BNT_ == 128 && !TERN_ ? 4 : 2, WAVES_N = 8 / WAVES_M;
   static constexpr int A16 = BM / WAVES_M / 16, NB = BNT_ / WAVES_N / 16, B16 = NB / NMAT;   // fragments of a wavefront
   static constexpr bool TERN = TERN_;
   static constexpr int A_BYTES = BM * 128, STAGE = A_BYTES + BNT_ * (TERN_ ? 16 : 128);
@@ -552,7 +554,8 @@ __device__ __forceinline__ void mid_gemm_body(const SharedGemmArgs& a, const Row
   const int KT = K >> 6;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wave_u = __builtin_amdgcn_readfirstlane(wave);
-  const int wm = wave % Cfg::WAVES_M, wn = wave / Cfg::WAVES_M;
+  // TERN: the four wavefronts of 64 rows on different SIMDs
+  const int wm = Cfg::TERN ? wave / Cfg::WAVES_N : wave % Cfg::WAVES_M, wn = Cfg::TERN ? wave % Cfg::WAVES_N : wave / Cfg::WAVES_M;
   const int r16 = lane & 15, quart = lane >> 4;
   const uint32_t lds0 = (uint32_t)(uintptr_t)((__attribute__((address_space(3))) unsigned char*)s_lds);
   const int frag = r16 * 128 + ((quart ^ (r16 >> 1)) << 4);   // as in big_gemm_body; K half 1 at ^ 64
@@ -625,11 +628,11 @@ __device__ __forceinline__ void mid_gemm_body(const SharedGemmArgs& a, const Row
       mrow_ = (mt_) * BM;                                                       \
     }                                                                           \
   }
-#define MOTE_POINTERS(mrow_, grp_, nt_, kb_)                                                       \
+#define MOTE_POINTERS(mrow_, mlast_, grp_, nt_, kb_)                                                     \
   {                                                                                                \
     const uint32_t k0_ = (kb_) + ld_chunk;                                                         \
     _Pragma("unroll") for (int p = 0; p < Cfg::A_LOADS; ++p)                                       \
-      a_off[p] = static_cast<uint32_t>(min((mrow_) + p * 64 + ld_row, M - 1)) * static_cast<uint32_t>(K) * 2u + k0_; \
+      a_off[p] = static_cast<uint32_t>(min((mrow_) + p * 64 + ld_row, (mlast_) - 1)) * static_cast<uint32_t>(K) * 2u + k0_; \
     if constexpr (Cfg::TERN) {                                                                     \
       const int blk_ = min((nt_) * (BN / 32) + (wave_u & 3), (N >> 5) - 1) + (grp_) * (N >> 5);    \
       b_off[0] = static_cast<uint32_t>(blk_) * static_cast<uint32_t>(K) * 8u + (kb_) * 4u + (wave_u >> 2) * 256u + lane * 4u; \
@@ -667,7 +670,7 @@ __device__ __forceinline__ void mid_gemm_body(const SharedGemmArgs& a, const Row
   uint32_t kb;
   MOTE_KRANGE(kc, kb, ktl);
   MOTE_ROWS(mt, mrow, mend, grp);
-  MOTE_POINTERS(mrow, grp, nt, kb);
+  MOTE_POINTERS(mrow, mend, grp, nt, kb);
 #pragma unroll
   for (int i = 0; i < Cfg::AHEAD; ++i)
     if (i < ktl) MOTE_ISSUE(MOTE_STAGE(i), i);
@@ -697,8 +700,6 @@ __device__ __forceinline__ void mid_gemm_body(const SharedGemmArgs& a, const Row
       for (int b = 0; b < NB; ++b) acc[i][b] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
     bf16x8 ax[A16], bx[NB], ay[A16], by[NB];
     uint32_t wx[NB / 2], wy[NB / 2];
-#pragma unroll
-    for (int r = 0; r < NB + A16; ++r) MOTE_READ(ax, bx, wx, st, 0, r)
     // a half: MFMAs of (af_, b_), behind MFMA j the statement side_(j)
 #define MOTE_HALF(af_, b_, w_, side_)                                                              \
     if constexpr (Cfg::TERN) { _Pragma("unroll") for (int b = 0; b < NB; ++b) b_[b] = ternary_operand(w_[b / 2], b & 1); } \
@@ -726,22 +727,37 @@ __device__ __forceinline__ void mid_gemm_body(const SharedGemmArgs& a, const Row
       })                                                                                           \
       st = nx;                                                                                     \
     }
+    // chunk c + 1 has landed: the `later` chunks behind it may be on their way
+#define MOTE_WAIT_LAST(later_)                                                                     \
+    {                                                                                              \
+      if (STAGES > 4 && (later_) >= 3) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"(3 * NLOAD) : "memory");  \
+      else if (STAGES > 3 && (later_) >= 2) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"(2 * NLOAD) : "memory"); \
+      else if ((later_) >= 1) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"(NLOAD) : "memory"); \
+      else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");                             \
+    }
     int c = 0;
-    for (; c + STAGES < ktl; ++c)
-      MOTE_CHUNK(true, asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"((STAGES - 2) * NLOAD) : "memory");)
-    for (; c < ktl; ++c)
-      MOTE_CHUNK(false, {
-        const int later = ktl - 2 - c;   // chunks behind the next one that are on their way
-        if (STAGES > 4 && later >= 3) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"(3 * NLOAD) : "memory");
-        else if (STAGES > 3 && later >= 2) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"(2 * NLOAD) : "memory");
-        else if (later >= 1) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"(NLOAD) : "memory");
-        else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
-      })
+    if (GROUPED == 1 && mrow + wave_u / Cfg::WAVES_N * A16 * 16 >= mend) {   // no rows for this wavefront: its share of the loads, and the barriers
+      for (; c < ktl; ++c) {
+        const int nx = MOTE_STAGE(1);
+        if (c + STAGES < ktl) asm volatile("s_waitcnt vmcnt(%0)" :: "n"((STAGES - 2) * NLOAD) : "memory");
+        else MOTE_WAIT_LAST(ktl - 2 - c)
+        asm volatile("s_barrier" ::: "memory");
+        if (c + STAGES < ktl) MOTE_ISSUE(st, c + STAGES);
+        st = nx;
+      }
+    } else {
+#pragma unroll
+      for (int r = 0; r < NB + A16; ++r) MOTE_READ(ax, bx, wx, st, 0, r)
+      for (; c + STAGES < ktl; ++c)
+        MOTE_CHUNK(true, asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"((STAGES - 2) * NLOAD) : "memory");)
+      for (; c < ktl; ++c) MOTE_CHUNK(false, MOTE_WAIT_LAST(ktl - 2 - c))
+    }
+#undef MOTE_WAIT_LAST
 #undef MOTE_CHUNK
 #undef MOTE_HALF
 
     if (has_next) {   // the next tile's first loads travel while this tile runs its epilogue in the stages behind them
-      MOTE_POINTERS(mrow2, grp2, nt2, kb2);
+      MOTE_POINTERS(mrow2, mend2, grp2, nt2, kb2);
 #pragma unroll
       for (int i = 0; i < Cfg::AHEAD; ++i)
         if (i < ktl2) MOTE_ISSUE(MOTE_STAGE(i), i);
@@ -1053,8 +1069,9 @@ static int64_t grouped_row_tiles(const int32_t* row0, int n_groups, int bm) {
 // 256 CUs are two rounds of 512 and 64 tiles in four planes: 669 + 70 us (two planes for all rows, and their sum) -> 624 + 10.
 // With fewer than 16 channel tiles the row tiles are dealt to the XCDs, so whole rounds are whole rounds of every XCD.
 // Where no such cut exists: two planes for all rows when one plane leaves more than 15 % of the last round empty and two
-// leave less.  Small problems (128 x 128 tiles): as many planes as give two workgroups per CU, planes of at least 16 K
-// steps of 64.
+// leave less.  Small problems (128 x 128 tiles, one workgroup per CU): by rounds of tiles, 0.36 - 0.44 us per chunk (tiles of up to
+// 64 rows, more), and the launch that adds the planes.  16 groups of 6 rows, N = 2048, K = 10496: 256 tiles are one round and one
+// plane (60 us; two planes 62 + 5); 16 of 125 rows, N = 1536, K = 8960: 300 tiles, two planes (98 + 3; one 122).
 GemmSplit grouped_gemm_split(const int32_t* row0_host, int n_groups, int N, int K, int max_planes) {
   GemmSplit sp{1, 0, 0};
   const int cus = shared_cu_count();
@@ -1090,12 +1107,17 @@ GemmSplit grouped_gemm_split(const int32_t* row0_host, int n_groups, int N, int 
     if (eff(2) > eff(1) + 0.05) sp.planes = 2;
     return sp;
   }
-  const int64_t t128 = grouped_row_tiles(row0_host, n_groups, 128) * ((N + 127) / 128);
-  if (t128 == 0) return sp;
-  int planes = static_cast<int>((2 * cus) / t128);
-  if (planes > KT / 16) planes = KT / 16;
-  if (planes > max_planes) planes = max_planes;
-  sp.planes = planes < 1 ? 1 : planes;
+  // 128 x 128 tiles: the cheapest number of planes, of at least 16 chunks each, as in gemm_choice
+  const int m128 = static_cast<int>(grouped_row_tiles(row0_host, n_groups, 128)), n128 = (N + 127) / 128, cus8 = cus / 8;
+  const double plane_us = static_cast<double>(row0_host[n_groups] - row0_host[0]) * N * 4 / 5e6;
+  double best_us = 1e30;
+  for (int p = 1; p <= std::max(1, std::min(max_planes, KT / 16)); ++p) {
+    const int ktp = (KT + p - 1) / p;
+    if ((KT + ktp - 1) / ktp != p) continue;   // an empty plane
+    const int64_t rounds = (longest_list(m128, static_cast<int64_t>(n128) * p) + cus8 - 1) / cus8;
+    const double us = static_cast<double>(rounds) * (ktp * 0.40 + 2.0) + (p > 1 ? 5.0 + p * plane_us : 0.0);
+    if (us < best_us) { best_us = us; sp.planes = p; }
+  }
   return sp;
 }
 

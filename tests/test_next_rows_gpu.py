@@ -454,9 +454,11 @@ def test_ste_linear_backward_arguments_are_validated():
 
 # The 2-bit operand of dX: exact sums (integer gradients, sums below 2^24) make every code's place visible.
 # 128 channels: half a 256-wide tile; 640: a last tile of half a width, on 256-row tiles; 128 output rows: one
-# workgroup of the re-blocking kernel; a group of one row and an empty one.
+# workgroup of the re-blocking kernel; a group of one row and an empty one; groups whose last 128-row tile has up to 64 rows
+# (half of its wavefronts without any) and one more, several such tiles in turn per workgroup.
 @pytest.mark.parametrize("R,N,K,E,cuts", [(70, 128, 128, 3, [1, 1]), (300, 384, 640, 2, [130]), (16700, 128, 640, 2, [16600]),
-                                          (129, 1408, 256, 4, [0, 64, 128])])
+                                          (129, 1408, 256, 4, [0, 64, 128]),
+                                          (642, 1024, 5120, 8, [64, 129, 257, 386, 387, 387, 450])])
 def test_ste_dx_of_integer_gradients_is_exact(R, N, K, E, cuts):
     M = _m()
     p = _ste_problem(R, N, K, E, seed=77 + R, cuts=cuts)
@@ -472,9 +474,11 @@ def test_ste_dx_of_integer_gradients_is_exact(R, N, K, E, cuts):
 
 
 # The last row tiles in K planes of their own: 36 row tiles of 256 x 8 channel tiles, the last four row tiles (from the
-# middle of a group on) in four planes; 33 row tiles, a group of 40 rows in two planes (K steps: 32).  Every plane is
-# multiplied by alpha before they are added, so alpha is a power of two here and everything stays exact.
-@pytest.mark.parametrize("R,N,K,E,cuts", [(8700, 4096, 2048, 3, [2900, 5800]), (8232, 2048, 2048, 3, [0, 8192])])
+# middle of a group on) in four planes; 33 row tiles, a group of 40 rows in two planes (K steps: 32).  128-row tiles of up to 64
+# rows and of 65 in four planes.  Every plane is multiplied by alpha before they are added, so alpha is a power of two here
+# and everything stays exact.
+@pytest.mark.parametrize("R,N,K,E,cuts", [(8700, 4096, 2048, 3, [2900, 5800]), (8232, 2048, 2048, 3, [0, 8192]),
+                                          (150, 4096, 640, 3, [64, 129])])
 def test_ste_dx_with_the_last_row_tiles_in_planes_is_exact(R, N, K, E, cuts):
     M = _m()
     p = _ste_problem(R, N, K, E, seed=5 + R, cuts=cuts)
@@ -489,9 +493,6 @@ def test_ste_dx_with_the_last_row_tiles_in_planes_is_exact(R, N, K, E, cuts):
         assert np.array_equal(dx[a:b].cpu().numpy(), ref * np.float32(2.0 ** -6))
 
 
-# Sums near both ends of the fp32 range: the contraction and the scale keep the exponents of dy, t and alpha.  Every
-# row of dy follows the signs of one channel at 2^120, so its own sum is 2^120 times that channel's number of
-# non-zero codes (above 2^127 for more than 128 of 256); every product and partial sum is exact, as is alpha's value.
 def test_ste_gradients_of_rows_beyond_32_bit_offsets():
     """Gradient rows of 4.33 GB (each expert's below 2 GiB): the experts of one launch of either GEMM stay below 4 GiB, which
     is as far as its byte offsets reach.  An expert without rows, unequal ones; integer gradients and an activation scale of
@@ -519,6 +520,9 @@ def test_ste_gradients_of_rows_beyond_32_bit_offsets():
         assert torch.equal(dw[e], rows.t() @ q[a:b].float()), e
 
 
+# Sums near both ends of the fp32 range: the contraction and the scale keep the exponents of dy, t and alpha.  Every
+# row of dy follows the signs of one channel at 2^120, so its own sum is 2^120 times that channel's number of
+# non-zero codes (above 2^127 for more than 128 of 256); every product and partial sum is exact, as is alpha's value.
 @pytest.mark.parametrize("alpha", [0.0173, float(np.float32(2.0 ** -126) * np.float32(1 + 2.0 ** -23))])
 def test_ste_dx_keeps_the_fp32_range(alpha):
     M = _m()
