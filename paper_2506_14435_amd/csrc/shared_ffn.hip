@@ -894,11 +894,14 @@ static hipError_t launch_big_cfg(const SharedGemmArgs& a, int kplanes, const Row
     attr_set = true;
   }
   const unsigned blocks = gemm_blocks(longest_list(n_mtiles, static_cast<int64_t>(n_ntiles) * kplanes));
-  // Band height: the 32 workgroups of an XCD share the least operand bytes as 4 x 8 tiles (16 groups of 1088 rows, K
-  // ranges: 809 us with bands of two row tiles, 769 of four, 840 of eight).  Weights that the memory-side cache (256 MB)
-  // does not keep are read once per band: bands of eight (16384 x 3584 x 18944 gate-up: 3235 us of two, 3210 of four, 3145 of
-  // eight; with 90 MB of weights all the same).
-  const int group_m = static_cast<int64_t>(Cfg::NMAT) * a.N * a.K * 2 > (int64_t{192} << 20) && rg == nullptr ? 8 : kBigBand;
+  // Band height: the 32 workgroups of an XCD share the least operand bytes as 4 x 8 tiles.  Weights that the memory-side cache
+  // (256 MB) does not keep are read once per band: bands of eight (16384 x 3584 x 18944 gate-up: 3235 us of two, 3210 of four, 3145 of
+  // eight; with 90 MB of weights all the same).  K ranges write more than they read; from eight ranges and eight channel
+  // tiles on bands of three (us of bands of two / three / four: 16 ranges, 18944 x 3584, 200 rows in all 792 / 794 / 846, 4000 rows 1151 /
+  // 1113 / 1337; 11008 x 2048, 4000 rows 452 / 364 / 387, 16384 rows 818 / 802 / 802; 3584 x 18944, 4000 rows 1272 / 1258 / 1329), but four below:
+  // four ranges, 18944 x 3584, 4000 rows 514 / 520 / 487; 16 ranges, 8960 x 1536, 4000 rows 235 / 258 / 233.
+  const int group_m = rg != nullptr ? (kplanes >= 8 && n_ntiles >= 8 ? 3 : kBigBand)
+                                    : static_cast<int64_t>(Cfg::NMAT) * a.N * a.K * 2 > (int64_t{192} << 20) ? 8 : kBigBand;
   if constexpr (Cfg::MODE == 1) if (rg != nullptr) {
     big_kgrouped_gemm_kernel<Cfg><<<blocks, Cfg::THREADS, Cfg::LDS_BYTES, stream>>>(a, *rg, n_ntiles, group_m);
     return hipGetLastError();
