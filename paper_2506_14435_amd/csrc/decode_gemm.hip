@@ -1362,12 +1362,10 @@ __device__ __forceinline__ void quant_role(const QuantRoleArgs& r, int row) {
 
 // Workgroups of four wavefronts for the sake of the small kernels; a streaming unit is one wavefront, the
 // other three end at once.  (One wavefront per workgroup left the router a chain of memory round trips
-// behind the weight stream: the head kernel took 29 us at T = 1 and T = 64.)  A router requests all eight router rows of
-// its chunk before it uses one: two at a time they were four round trips that end after the stream does (us per forward,
-// two -> eight at a time: d = 2048, F = 11008, E = 16 T = 1 59.1 -> 57.4, T = 16 91.5 -> 88.3, T = 64 106.8 -> 106.1;
-// d = 256 T = 64 29.2 -> 27.1; d = 896, E = 8 T = 1 30.3 -> 29.6, T = 64 41.8 -> 42.2).
+// behind the weight stream: the head kernel took 29 us at T = 1 and T = 64.)  How many router rows a router requests at a
+// time: router_all_rows.  With rings of 52 KiB the registers leave room for three workgroups per CU.
 template <int AL, int KIB>
-__global__ __launch_bounds__(256) void decode_head_kernel(RouterRoleArgs r, SharedDecodeArgs a) {
+__global__ __launch_bounds__(256, KIB == kRoleLdsKiB && AL < 8 ? 3 : 1) void decode_head_kernel(RouterRoleArgs r, SharedDecodeArgs a) {
   constexpr int LDS = SharedWaveCfg<0, AL, KIB>::LDS;
   static_assert(lds_fits(KIB == kRoleLdsKiB ? 3 : 2, LDS), "three workgroups per CU, or two with the longer ring");
   if (static_cast<int>(blockIdx.x) < r.T) router_role<4, LDS>(r, blockIdx.x);
