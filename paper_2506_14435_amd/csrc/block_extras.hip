@@ -6,6 +6,8 @@
 //                            (Section 4.3, Table 3) and its packed storage
 //   * rtn_dequant_kernel     packed codes -> integer-valued bf16 matrix (exact), the operand of the
 //                            large-batch shared GEMM whose epilogue applies the row scales
+#include <algorithm>
+
 #include "common.h"
 #include "launch.h"
 
@@ -95,13 +97,14 @@ hipError_t launch_norm_rows(const uint16_t* x, const uint16_t* gamma, const uint
 // the gate distribution in fp64 (fixed order: per-thread partial sums, lanes of a wavefront, butterfly) and
 // the loss, all in one workgroup (the interface has no room for partial results of several).
 // A thread owns one column group of VEC experts (16 bytes where E is a multiple of 4) and walks the rows, so
-// that a wavefront reads whole cache lines, kBalanceUnroll loads in flight per thread: what bounds it is
+// that a wavefront reads whole cache lines, U loads in flight per thread: what bounds it is
 // what one CU takes in, 8192 x 16: 512 KB.  One
 // 4-byte load at a time down a column took 56 us there, beside a histogram kernel of 5 us; this kernel does both in
-// 8.7 us (9.7 with eight loads in flight and the indices behind the probabilities).
-constexpr int kBalanceThreads = 1024, kBalanceWaves = kBalanceThreads / kWave, kBalanceUnroll = 16;
+// 8.7 us (9.7 with eight loads in flight and the indices behind the probabilities).  Sixteen loads of which most are past the end
+// cost a microsecond (E = 16, T = 600 4.0 -> 5.0 us): up to 24 per thread it is eight (17 per thread 7.4 against 7.5, 32 9.6 against 8.8).
+constexpr int kBalanceThreads = 1024, kBalanceWaves = kBalanceThreads / kWave;
 
-template <int VEC>
+template <int VEC, int U>
 __global__ __launch_bounds__(kBalanceThreads) void balance_kernel(const float* __restrict__ gate_p, const int32_t* topk_idx, int T, int R, int E,
                                                                   int32_t* __restrict__ counts,
                                                                   float* __restrict__ gate_p_sum, float* __restrict__ loss) {
@@ -111,9 +114,9 @@ __global__ __launch_bounds__(kBalanceThreads) void balance_kernel(const float* _
   __shared__ int s_cnt[kBalanceWaves][64];   // a histogram per wavefront
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   // the first pass over the indices travels beside the probabilities
-  int idx[kBalanceUnroll];
+  int idx[U];
 #pragma unroll
-  for (int u = 0; u < kBalanceUnroll; ++u) idx[u] = tid + u * kBalanceThreads < R ? topk_idx[tid + u * kBalanceThreads] : -1;
+  for (int u = 0; u < U; ++u) idx[u] = tid + u * kBalanceThreads < R ? topk_idx[tid + u * kBalanceThreads] : -1;
   __builtin_amdgcn_sched_barrier(0);
   s_cnt[wave][lane] = 0;
   const int groups = E / VEC;                        // column groups of a row
@@ -125,15 +128,15 @@ __global__ __launch_bounds__(kBalanceThreads) void balance_kernel(const float* _
   if (tid < active) {
     const vec_t* const p = reinterpret_cast<const vec_t*>(gate_p);
     const int64_t n = static_cast<int64_t>(T) * groups;
-    for (int64_t i = tid; i < n; i += static_cast<int64_t>(active) * kBalanceUnroll) {
-      vec_t x[kBalanceUnroll];
+    for (int64_t i = tid; i < n; i += static_cast<int64_t>(active) * U) {
+      vec_t x[U];
 #pragma unroll
-      for (int u = 0; u < kBalanceUnroll; ++u) {
+      for (int u = 0; u < U; ++u) {
         const int64_t j = i + static_cast<int64_t>(u) * active;
         x[u] = j < n ? p[j] : vec_t{};
       }
 #pragma unroll
-      for (int u = 0; u < kBalanceUnroll; ++u)
+      for (int u = 0; u < U; ++u)
 #pragma unroll
         for (int v = 0; v < VEC; ++v) acc[v] += static_cast<double>(x[u][v]);
     }
@@ -142,12 +145,12 @@ __global__ __launch_bounds__(kBalanceThreads) void balance_kernel(const float* _
   for (int v = 0; v < VEC; ++v) s_acc[v][tid] = acc[v];
   for (int i = tid;;) {
 #pragma unroll
-    for (int u = 0; u < kBalanceUnroll; ++u)
+    for (int u = 0; u < U; ++u)
       if (idx[u] >= 0) atomicAdd(&s_cnt[wave][idx[u]], 1);
-    i += kBalanceThreads * kBalanceUnroll;
+    i += kBalanceThreads * U;
     if (i >= R) break;
 #pragma unroll
-    for (int u = 0; u < kBalanceUnroll; ++u) idx[u] = i + u * kBalanceThreads < R ? topk_idx[i + u * kBalanceThreads] : -1;
+    for (int u = 0; u < U; ++u) idx[u] = i + u * kBalanceThreads < R ? topk_idx[i + u * kBalanceThreads] : -1;
   }
   __syncthreads();
   for (int e = wave; e < E; e += kBalanceWaves) {    // one wavefront per expert
@@ -173,10 +176,13 @@ __global__ __launch_bounds__(kBalanceThreads) void balance_kernel(const float* _
 
 hipError_t launch_balance(const float* gate_p, const int32_t* topk_idx, int T, int k, int E, int32_t* counts,
                           float* gate_p_sum, float* loss, hipStream_t stream) {
-  if (E % 4 == 0)
-    balance_kernel<4><<<1, kBalanceThreads, 0, stream>>>(gate_p, topk_idx, T, T * k, E, counts, gate_p_sum, loss);
-  else
-    balance_kernel<1><<<1, kBalanceThreads, 0, stream>>>(gate_p, topk_idx, T, T * k, E, counts, gate_p_sum, loss);
+  const int vec = E % 4 == 0 ? 4 : 1;
+  const int64_t loads = std::max<int64_t>(static_cast<int64_t>(T) * (E / vec), static_cast<int64_t>(T) * k);
+  const bool many = loads > 24 * kBalanceThreads;
+  if (vec == 4 && many) balance_kernel<4, 16><<<1, kBalanceThreads, 0, stream>>>(gate_p, topk_idx, T, T * k, E, counts, gate_p_sum, loss);
+  else if (vec == 4) balance_kernel<4, 8><<<1, kBalanceThreads, 0, stream>>>(gate_p, topk_idx, T, T * k, E, counts, gate_p_sum, loss);
+  else if (many) balance_kernel<1, 16><<<1, kBalanceThreads, 0, stream>>>(gate_p, topk_idx, T, T * k, E, counts, gate_p_sum, loss);
+  else balance_kernel<1, 8><<<1, kBalanceThreads, 0, stream>>>(gate_p, topk_idx, T, T * k, E, counts, gate_p_sum, loss);
   return hipGetLastError();
 }
 

@@ -106,9 +106,10 @@ def test_router_balance_matches_oracle(T, d, E, k, bias):
 
 
 # column groups of the balance kernel: 16-byte groups that do and do not divide the workgroup, single experts,
-# rows that end inside a pass of the workgroup, fewer rows than lanes
+# rows that end inside a pass of the workgroup, fewer rows than lanes; eight and sixteen loads in flight (up to 24576
+# probabilities or indices, and more)
 @pytest.mark.parametrize("T,d,E,k", [(1030, 128, 12, 2), (2050, 128, 64, 8), (3, 128, 64, 1), (1025, 128, 1, 1),
-                                     (7, 128, 5, 2), (9000, 128, 4, 2)])
+                                     (7, 128, 5, 2), (9000, 128, 4, 2), (4096, 128, 6, 2), (4097, 128, 6, 2), (3073, 128, 8, 8)])
 def test_router_balance_column_groups(T, d, E, k):
     M = _m()
     g = torch.Generator().manual_seed(T + E)
