@@ -313,10 +313,14 @@ enum {
   MOTE_KNOB_EVENT_FENCE = 2,         /* 1: fork/join events with a system-scope fence; before the first
                                         forked forward (0)                                             */
   MOTE_KNOB_QUANT_WIDE = 3,          /* 1: 256-thread row quantiser for every row length (0)           */
-  MOTE_KNOB_ROUTED_VARIANT = 4,      /* tile configuration of the large-batch routed gate-up GEMM (0)  */
-  MOTE_KNOB_ROUTED_DOWN_VARIANT = 5, /* ... of the routed down GEMM (-1: as gate-up)                   */
-  MOTE_KNOB_SHARED_VARIANT = 6,      /* ... of the shared GEMMs (0: chosen by shape)                   */
-  MOTE_KNOB_GROUP_M = 7,             /* row tiles per band of the tile order (2)                       */
+  MOTE_KNOB_ROUTED_VARIANT = 4,      /* without effect: the large-batch routed GEMMs have one tile each (0) */
+  MOTE_KNOB_ROUTED_DOWN_VARIANT = 5, /* without effect (-1)                                            */
+  MOTE_KNOB_SHARED_VARIANT = 6,      /* rows x channels per tile of the large-batch shared GEMMs: 1 128 x 128,
+                                        2 128 x 256, 3 256 x 256 (0: by shape).  Each tile has its own number
+                                        of K planes of the down projection, so the workspace depends on it;
+                                        other values mean 256 x 256 with one plane                     */
+  MOTE_KNOB_GROUP_M = 7,             /* row tiles per band of the tile order of the large-batch routed
+                                        GEMMs (2)                                                      */
   MOTE_KNOB_DYNAMIC_ROUNDS = 8,      /* tiles per workgroup from which tiles are drawn (4)             */
   MOTE_KNOB_DECODE_VARIANT = 9,      /* routed decode kernel: 0 K-split, 1 / 2 wave-streaming with two
                                         workgroups of four / one of eight wavefronts per CU (-1: by shape) */

@@ -15,7 +15,7 @@ enum Knob {
   kKnobRoutedVariant,        // without effect (the large-batch routed GEMMs have one tile configuration each)
   kKnobRoutedDownVariant,    // without effect
   kKnobSharedVariant,        // tile of the large-batch shared GEMMs (0: by shape, 1: 128 x 128, 2: 128 x 256, 3: 256 x 256)
-  kKnobGroupM,               // row tiles per band of the tile order
+  kKnobGroupM,               // row tiles per band of the tile order of the large-batch routed GEMMs
   kKnobDynamicRounds,        // tiles per workgroup from which tiles are drawn
   kKnobDecodeVariant,        // routed decode kernel: 0 K-split, 1 / 2 wave-streaming with 4 / 8 wavefronts per workgroup
   kKnobRouterTokenBlocks,    // largest T with one token per router workgroup

@@ -88,9 +88,9 @@ __device__ __forceinline__ int lds_a_offset(int row, int chunk) { return row * 1
 // One 128-channel K step of a wavefront is four quarters, half of its channels x half of its weight
 // fragments each; a quarter unpacks 16 codes per lane and fragment and feeds 2 BM_W MFMAs per
 // fragment.  The global loads of a later K step are spread over
-// the four quarters: issued in one burst right after the barrier, eight wavefronts x eight
-// 1-KiB loads fill the CU's vector-memory queue and every wavefront stalls in issue (measured:
-// about 800 cycles per K step) before it reaches its first MFMA.
+// the four quarters: issued in one burst right after the barrier, the loads of a K step (six 1-KiB loads
+// of each of the eight wavefronts of a CU) fill its vector-memory queue and every wavefront stalls in issue (about 800
+// cycles per K step, measured with eight loads each) before it reaches its first MFMA.
 constexpr int kFixedShares = 1 << 20;   // n_static from which every tile of a workgroup is fixed
 
 // Every wavefront has all 128 rows of the tile and a quarter of its channels: a weight fragment is unpacked once
@@ -509,8 +509,8 @@ __global__ __launch_bounds__(Cfg::THREADS, Cfg::MIN_BLOCKS) void routed_gemm_ker
 
     MOTE_TP(3)
     // ---- epilogue ----
-    // In registers lane l owns dispatch row r32 and runs of four consecutive output channels
-    // (8q + 4g .. +3).  Each wavefront writes one 32-row block of PATCH_F fragments into its
+    // In registers lane l owns row r16e of every 16-row fragment and four consecutive output channels of every
+    // 16-channel one (4 * qe .. +3).  Each wavefront writes one 32-row block of PATCH_F 32-channel fragments into its
     // private LDS patch and reads it back row-major, 16 bytes per lane, so that a global store
     // instruction covers whole rows of the block.
     constexpr int PATCH_F = Cfg::PATCH_F;
