@@ -404,8 +404,8 @@ def test_ste_linear_backward_3b_gate_matrix_sampled():
 @pytest.mark.parametrize("R,N,K,E,cuts,what", [
     # 32 row tiles of 256 x 8 channel tiles = one round of workgroups: one K plane
     (7816, 1024, 2048, 4, [1000, 2030, 5030], "one plane"),
-    # 34 row tiles x 8 channel tiles = a full round and a nearly empty one: two K planes, added afterwards
-    (8192, 2048, 2048, 8, [1000, 2100, 3100, 4200, 5200, 6150, 7170], "two planes")])
+    # 34 row tiles x 8 channel tiles = a full round and a nearly empty one: its two row tiles in two K planes, added afterwards
+    (8192, 2048, 2048, 8, [1000, 2100, 3100, 4200, 5200, 6150, 7170], "two planes of the last two row tiles")])
 def test_ste_linear_backward_grouped_dx_on_256_row_tiles(R, N, K, E, cuts, what):
     """dX of all experts in one grouped GEMM on 256 x 256 tiles: groups that end inside a tile, tiles
     that read the next group's rows, the last tile clamped at R."""
@@ -476,10 +476,13 @@ def test_ste_dx_of_integer_gradients_is_exact(R, N, K, E, cuts):
 
 # The last row tiles in K planes of their own: 36 row tiles of 256 x 8 channel tiles, the last four row tiles (from the
 # middle of a group on) in four planes; 33 row tiles, a group of 40 rows in two planes (K steps: 32).  128-row tiles of up to 64
-# rows and of 65 in four planes.  Every plane is multiplied by alpha before they are added, so alpha is a power of two here
+# rows and of 65 in four planes.  All rows of 256-row tiles in two planes, where no whole rounds can be cut off: 21 row tiles x 14
+# channel tiles (294 tiles fill two rounds of 256 workgroups to 57 %, twice as many half as long ones three to 77 %) with an empty
+# group, and 19 x 16 (59 and 79 %).  Every plane is multiplied by alpha before they are added, so alpha is a power of two here
 # and everything stays exact.
 @pytest.mark.parametrize("R,N,K,E,cuts", [(8700, 4096, 2048, 3, [2900, 5800]), (8232, 2048, 2048, 3, [0, 8192]),
-                                          (150, 4096, 640, 3, [64, 129])])
+                                          (150, 4096, 640, 3, [64, 129]),
+                                          (5000, 2048, 3584, 4, [700, 2500, 2500]), (4400, 2048, 4096, 2, [300])])
 def test_ste_dx_with_the_last_row_tiles_in_planes_is_exact(R, N, K, E, cuts):
     M = _m()
     p = _ste_problem(R, N, K, E, seed=5 + R, cuts=cuts)

@@ -100,11 +100,14 @@ def test_pack_ternary_at_the_rounding_threshold(shape, dtype):
                                           (515, 896, 8, 2, False), (130, 2048, 16, 2, True),
                                           (33, 256, 6, 3, False), (70, 512, 32, 4, True), (9, 128, 64, 8, False),
                                           (16, 128, 16, 16, False),
-                                          # from 4096 tokens on, E <= 16: 16 tokens per workgroup on the fp64 matrix
-                                          # instruction (ragged last workgroup; E not a multiple of 8; a last
-                                          # block of 128 channels; the widest register variant)
+                                          # above 1024 tokens (256 for d <= 1024), E <= 16: 16 tokens per workgroup on the
+                                          # fp64 matrix instruction (ragged last workgroup; E not a multiple of 8; a last
+                                          # block of 128 channels; the widest register variant), the kernels on
+                                          # either side of both limits, and wider rows of many tokens
                                           (4099, 384, 6, 3, True), (4112, 896, 8, 2, True), (4100, 3584, 16, 2, False),
-                                          (4096, 128, 16, 1, False), (4097, 4096, 2, 2, True), (4200, 256, 16, 8, False)])
+                                          (4096, 128, 16, 1, False), (4097, 4096, 2, 2, True), (4200, 256, 16, 8, False),
+                                          (256, 896, 8, 2, False), (257, 1024, 12, 2, True), (1024, 1152, 16, 2, False),
+                                          (1025, 1152, 16, 2, True), (2049, 4224, 13, 2, False)])
 def test_router_topk_matches_oracle(T, d, E, k, bias):
     M = _m()
     _log(f"router T={T} d={d} E={E} k={k} bias={bias}")
@@ -165,7 +168,7 @@ def test_router_non_finite_hidden_states_select_valid_experts():
 
 
 def test_router_non_finite_hidden_states_many_tokens():
-    """The same on the kernel that takes over from 4096 tokens: a non-finite token touches neither
+    """The same on the kernel of many tokens (above 256 at this width): a non-finite token touches neither
     its 15 neighbours in the accumulator tile nor the range of the indices."""
     M = _m()
     T, d, E, k = 4100, 256, 5, 3
@@ -990,11 +993,13 @@ def _small_layer(M, d, F, E, k, w_router, shared_bits=0, seed=0):
 
 # The router inside the decode kernel reads a chunk's router rows as whole 16-byte runs, 8-byte runs of an aligned matrix
 # or single elements: expert counts of each kind, and matrices that begin 2 and 4 bytes past an 8-byte boundary.  The same
-# experts, weights and codes as the router kernel of its own, to the bit (same sums in the same order).
+# experts, weights and codes as the router kernel of its own, to the bit (same sums in the same order).  At most 31 rows per
+# expert: with more the routed GEMMs may leave the decode kernels, and the router would have a kernel of its own in both modes.
 @pytest.mark.parametrize("E,k,offset", [(16, 2, 0), (8, 1, 0), (12, 2, 0), (4, 4, 0), (12, 2, 1), (4, 1, 2), (6, 2, 0), (13, 3, 0), (1, 1, 1)])
 @pytest.mark.parametrize("T,d,shared_bits", [(1, 128, 0), (5, 2176, 0), (64, 384, 8)])
 def test_router_rows_of_every_alignment_inside_the_decode_kernel(E, k, offset, T, d, shared_bits):
     M = _m()
+    T = min(T, 31 * E // k)
     g = torch.Generator(device="cuda").manual_seed(E * 100 + T)
     w = torch.empty(d * E + 8, dtype=torch.bfloat16, device="cuda")[offset:offset + d * E].view(d, E)
     w.copy_(torch.randn(d, E, device="cuda", generator=g) * d ** -0.5)
@@ -1073,7 +1078,7 @@ def test_routed_tiles_of_every_height(d, F, counts):
 
 
 # The shared expert's GEMM tiles (128 x 128, 128 x 256 and 256 x 256, by the cost model and each of them forced): token and
-# channel remainders of every tile, one K chunk and a few, K planes of the down projection, and the scaled epilogue of
+# channel remainders of every tile, two K chunks (the fewest a shape has) and more, K planes of the down projection, and the scaled epilogue of
 # a quantised expert whose expanded codes take the same kernels.
 @pytest.mark.parametrize("variant", [0, 1, 2, 3])
 @pytest.mark.parametrize("T,d,F,shared_bits", [(65, 128, 256, 0), (129, 384, 640, 0), (300, 256, 4096, 0), (257, 896, 1152, 0),
