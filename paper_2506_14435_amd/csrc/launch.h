@@ -96,6 +96,7 @@ hipError_t launch_routed_down(const RoutedGemmArgs& a, hipStream_t stream);
 int routed_down_tile_n(int planes);
 int routed_down_planes(int T, int k, int E, int d, int F);   // large-batch down: K planes for a shape
 int shared_down_planes(int T, int d, int F);
+constexpr int kSharedDownWideTokens = 1536;   // where the bound on those planes steps within a number of row tiles
 int tile_group_m();                      // row tiles per band of the large-batch tile order
 // plan tile size chosen for a workload (32, 64: decode kernels); decode_rows: largest average number of rows per
 // expert on 32-row tiles, by choice and where the scratch asks for it

@@ -319,7 +319,7 @@ size_t mote_layer_workspace_bytes(const mote_layer* layer, int T_max) {
   // must serve every T <= T_max, so the result is the largest layout over them.  Between two
   // batch sizes at which a plane count or the kernel family can change, the layout grows with
   // T; those sizes are: the family switches, every T at which floor(T*k/128) steps (routed row
-  // tiles) and every multiple of 128 (shared row tiles).  Only the last T before each is tried.
+  // tiles), every multiple of 128 (shared row tiles) and kSharedDownWideTokens.  Only the last T before each is tried.
   const int k = layer->top_k, E = layer->n_experts;
   size_t need = 0;
   auto consider = [&](int64_t t) {
@@ -329,6 +329,7 @@ size_t mote_layer_workspace_bytes(const mote_layer* layer, int T_max) {
   };
   need = carve(layer, T_max, nullptr).bytes;
   consider(kSharedDecodeMaxTokens);
+  consider(kSharedDownWideTokens - 1);
   if (layer->shared_bits != 0) consider(shared_q_tokens(layer));
   // the largest T on 32-row tiles, among the batches whose shared expert is streamed and among the others
   consider(std::min<int64_t>(kSharedDecodeMaxTokens, static_cast<int64_t>(decode_rows(layer, 1)) * E / k));

@@ -943,7 +943,9 @@ static hipError_t launch_mid_cfg(const SharedGemmArgs& a, int kplanes, const Row
 //            1024 x 11008 x 2048 in 4: 50 / 42 / 49 (57);  300 x 8960 x 1536 in 4: 40 / 25 / 17 (31 in 7)
 //            2048 x 8960 x 1536 in 2: 75 / 56 / 65 (74)
 // From four rounds of 256 x 256 tiles on those are taken in any case: the others move more operand bytes per flop.
-// A pure function of the number of 128-row tiles (the workspace layout depends on the planes).
+// M counts in 128-row tiles and by max_planes only: the workspace has room for the planes, and mote_layer_workspace_bytes tries the
+// last batch of every number of tiles (and the one in front of kSharedDownWideTokens).  Beside the shape the choice depends on
+// the number of CUs and on the shared_variant knob.
 enum GemmTile { kTileMid128 = 1, kTileMid256, kTileBig };
 struct GemmChoice { GemmTile tile; int planes; };
 static GemmChoice gemm_choice(int M, int N, int K, int nmat, int max_planes) {
@@ -990,12 +992,13 @@ hipError_t launch_shared_gate_up_scaled(const uint16_t* x, const uint16_t* w_gat
 // K planes that the down projection may have: every further plane adds an fp32 partial output that is written by the GEMM
 // and read back by the combine, and room for it in the scratch.  At most what two 128 x 128 tiles per CU or one
 // plane of 2048 channels ask for, few tiles (small T, whose partial outputs are small) up to one tile per CU and planes of
-// eight chunks; 48 to 64 tiles of 256 x 256 as many as fill the chip once.  Pure function of the shape.
+// eight chunks; 48 to 64 tiles of 256 x 256 as many as fill the chip once, from kSharedDownWideTokens on (from
+// 1409 = the first batch of as many row tiles 1 % slower: d = 2048, T = 1500, E = 16 430 -> 436 us per forward, T = 1472, E = 4, top-1 310 -> 314).
 static int shared_down_max_planes(int T, int d, int F) {
   const int KT = F >> 6;
   const int64_t tiles256 = static_cast<int64_t>((T + 255) / 256) * ((d + 255) / 256);
   int planes = 0;
-  if (T >= 1536 && d >= 2048 && tiles256 <= 64) planes = std::min(static_cast<int>(256 / tiles256), F / 1024);
+  if (T >= kSharedDownWideTokens && d >= 2048 && tiles256 <= 64) planes = std::min(static_cast<int>(256 / tiles256), F / 1024);
   if (planes < 2) {
     const int64_t tiles = static_cast<int64_t>((T + 127) / 128) * ((d + 127) / 128);
     planes = tiles > 0 ? static_cast<int>(512 / tiles) : 1;

@@ -106,7 +106,8 @@ def test_bench_refuses_more_than_one_gpu_and_names_every_workload():
 
 
 @pytest.mark.parametrize("d,F,E,k,T_max", [(896, 4864, 8, 2, 300), (2048, 11008, 16, 2, 520),
-                                            (1536, 8960, 4, 1, 2100), (256, 512, 4, 3, 700)])
+                                            (1536, 8960, 4, 1, 2100), (256, 512, 4, 3, 700),
+                                            (2048, 11008, 4, 1, 1700)])   # the bound on the shared planes steps at 1536
 def test_workspace_for_T_max_serves_every_smaller_batch(lib, d, F, E, k, T_max):
     """mote_layer_workspace_bytes(T) is what a forward of exactly T tokens needs at least, and the
     value for T_max must serve every T <= T_max although the number of K-split partial planes
