@@ -972,6 +972,13 @@ static GemmChoice gemm_choice(int M, int N, int K, int nmat, int max_planes) {
   return best;
 }
 
+int shared_gate_up_rows_on_every_cu(int T, int d, int F) {
+  const GemmTile tile = gemm_choice(T, F, d, 2, 1).tile;
+  if (tile == kTileMid128) return 0;
+  const int rows = tile == kTileBig ? 256 : 128;
+  return static_cast<int64_t>((T + rows - 1) / rows) * ((F + 127) / 128) >= shared_cu_count() ? rows : 0;
+}
+
 hipError_t launch_shared_gate_up(const uint16_t* x, const uint16_t* w_gate, const uint16_t* w_up, int T, int d,
                                  int F, uint16_t* h_s, hipStream_t stream) {
   return launch_shared_gate_up_scaled(x, w_gate, w_up, nullptr, nullptr, T, d, F, h_s, stream);

@@ -1110,6 +1110,37 @@ def test_shared_gemm_tiles(variant, T, d, F, shared_bits):
     assert ((taps["y_s"].double() - hd @ w[2].T).abs() <= bound).all()
 
 
+# Narrow layers whose shared gate-up GEMM has a 256 x 256 tile for every CU start the shared expert behind the router, those with a 128 x 256
+# one behind the plan (the last two): the fewest such tiles and a row of them less, a quantised expert (its expansion goes first), a block,
+# alternating inputs without a wait between them, and replays of a captured forward.  Equal to one stream, to the bit.
+@pytest.mark.parametrize("T,d,F,E,k,shared_bits", [(4096, 128, 2048, 8, 2, 0), (3840, 128, 2048, 8, 2, 0), (4090, 256, 2048, 4, 1, 8), (8192, 256, 1024, 16, 3, 0),
+                                                   (2048, 512, 2048, 8, 2, 0), (8192, 256, 512, 4, 2, 4)])
+def test_shared_expert_started_behind_the_router(T, d, F, E, k, shared_bits):
+    M = _m()
+    g = torch.Generator(device="cuda").manual_seed(T + d)
+    layer = _small_layer(M, d, F, E, k, (torch.randn(d, E, device="cuda", generator=g) * d ** -0.5).to(torch.bfloat16), shared_bits, T)
+    xs = [torch.randn(T, d, device="cuda", generator=g).to(torch.bfloat16) for _ in range(2)]
+    gamma = torch.ones(d, dtype=torch.bfloat16, device="cuda")
+    try:
+        M.mote_tuning_set("no_fork", 1)
+        want = [M.mote_layer_forward(layer, x) for x in xs] + [M.mote_block_forward(layer, xs[0], gamma, None, eps=1e-6)]
+        torch.cuda.synchronize()
+    finally:
+        M.mote_tuning_set("no_fork", 0)
+    outs = [M.mote_layer_forward(layer, xs[i % 2]) for i in range(12)]
+    block = M.mote_block_forward(layer, xs[0], gamma, None, eps=1e-6)
+    torch.cuda.synchronize()
+    assert all(torch.equal(o, want[i % 2]) for i, o in enumerate(outs)) and torch.equal(block, want[2])
+    x, out = xs[0].clone(), torch.empty_like(xs[0])
+    graph = M.ForwardGraph(layer, x, out, layer.workspace(T))
+    for i in (1, 0, 1):
+        x.copy_(xs[i])
+        out.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, want[i])
+
+
 # Many tokens go through the fp64 matrix kernel, with router rows read by 16 or 8 bytes or by elements: every such kind and
 # register bound (d = 1024, 2048, 4096), a number of channel steps that is no multiple of those in flight, a last
 # workgroup of one token, and a matrix that begins 2 bytes past an 8-byte boundary.  Against the kernel of smaller batches.
