@@ -1362,10 +1362,15 @@ __device__ __forceinline__ void quant_role(const QuantRoleArgs& r, int row) {
 
 // Workgroups of four wavefronts for the sake of the small kernels; a streaming unit is one wavefront, the
 // other three end at once.  (One wavefront per workgroup left the router a chain of memory round trips
-// behind the weight stream: the head kernel took 29 us at T = 1 and T = 64.)  How many router rows a router requests at a
-// time: router_all_rows.  With rings of 52 KiB the registers leave room for three workgroups per CU.
+// behind the weight stream: the head kernel took 29 us at T = 1 and T = 64.)  A router requests all eight router rows of
+// its chunk before it uses one: two at a time they were four round trips that end after the stream does (us per forward with
+// weights from HBM, two -> eight at a time: E = 16 d = 2048 T = 1 59.8 -> 56.8, T = 16 94.7 -> 90.4, T = 64 107.7 -> 106.3, d = 1536 T = 1
+// 47.4 -> 46.4, d = 896 T = 64 51.3 -> 50.0, d = 3584 T = 16 246.4 -> 242.4; E = 8 d = 896 T = 1 32.0 -> 30.9, T = 32 40.6 -> 39.2).  Of eight experts
+// a lane's rows are one cache line, requested eight times over, which costs a little where the stream is long for the chain
+// (d = 1536 T = 8 58.5 -> 57.9, but T = 24 / 32 62.2 / 64.1 -> 63.3 / 65.2; d = 896 T = 64 44.0 -> 44.4).  Both forms in one kernel cost
+// E = 16 its gain (d = 2048 T = 1 57.9 with eight rows taken, 59.1 with two).
 template <int AL, int KIB>
-__global__ __launch_bounds__(256, KIB == kRoleLdsKiB && AL < 8 ? 3 : 1) void decode_head_kernel(RouterRoleArgs r, SharedDecodeArgs a) {
+__global__ __launch_bounds__(256) void decode_head_kernel(RouterRoleArgs r, SharedDecodeArgs a) {
   constexpr int LDS = SharedWaveCfg<0, AL, KIB>::LDS;
   static_assert(lds_fits(KIB == kRoleLdsKiB ? 3 : 2, LDS), "three workgroups per CU, or two with the longer ring");
   if (static_cast<int>(blockIdx.x) < r.T) router_role<4, LDS>(r, blockIdx.x);

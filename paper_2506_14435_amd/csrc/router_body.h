@@ -120,14 +120,6 @@ __device__ __forceinline__ void gate_topk(double l, int e, bool store, int tok, 
   }
 }
 
-// Whether a router beside the weight stream requests all rows of a chunk at once where they are whole 16-byte runs.  Lanes
-// read 128 to 256 bytes each, 16 at a time, and requests for a line on its way are not merged: eight requests per line in
-// place of one and seven hits, which pays while memory has room for them (us per forward, two rows at a time -> all: d = 256, E = 16,
-// T = 64 27.1 -> 25.4; d = 896, E = 8 T = 1 30.1 -> 29.1, T = 32 37.8 -> 36.9, but T = 64 41.8 -> 42.2; d = 1536, E = 8, T = 16 55.7 -> 57.3;
-// d = 2048, F = 10112, E = 16, T = 2 55.9 -> 56.8).  Rows that would otherwise be read by elements: always (d = 896, T = 1, E = 12 38.2 ->
-// 29.9, E = 6 34.1 -> 32.5).
-__device__ __forceinline__ bool router_all_rows(int T, int d) { return d <= 1024 && T * d <= 32768; }
-
 template <int TPW, int NW>
 struct RouterScratch {   // LDS of a workgroup
   double logit[NW][64];
@@ -137,7 +129,7 @@ struct RouterScratch {   // LDS of a workgroup
 
 // One token group = TPW tokens from t0 on; the NW wavefronts of the workgroup split its channels.
 // ROWS: router rows of a chunk requested together (registers against latency); 8: all of them, as raw patterns, in front
-// of the first multiplication - one memory round trip per chunk, for workgroups whose time is that chain - or two (router_all_rows).
+// of the first multiplication - one memory round trip per chunk, for workgroups whose time is that chain.
 template <int EMAX, int TPW, int NW, int ROWS>
 __device__ __forceinline__ void router_quant_group(
     RouterScratch<TPW, NW>& lds, int t0, const uint16_t* __restrict__ x, const uint16_t* __restrict__ w_router, const float* __restrict__ bias, int T,
@@ -180,7 +172,7 @@ __device__ __forceinline__ void router_quant_group(
 #pragma unroll
       for (int i = 0; i < 8; ++i) amax[t] = fmaxf(amax[t], fabsf(xf[t][i]));
     }
-    if (ROWS == 8 && (vec != 8 || router_all_rows(T, d))) {
+    if constexpr (ROWS == 8) {
       uint32_t raw[8][EMAX / 2];
 #pragma unroll
       for (int i = 0; i < 8; ++i) load_router_row_raw<EMAX>(w_router + static_cast<int64_t>(c0 + i) * E, E, vec, raw[i]);
@@ -199,7 +191,7 @@ __device__ __forceinline__ void router_quant_group(
         __builtin_amdgcn_sched_barrier(0);   // a row at a time: all conversions at once would take 256 registers
       }
     } else
-#pragma unroll (ROWS == 8 ? 2 : ROWS)
+#pragma unroll ROWS
     for (int i = 0; i < 8; ++i) {
       double w[EMAX];
       load_router_row<EMAX>(w_router + static_cast<int64_t>(c0 + i) * E, E, vec_ok, w);
