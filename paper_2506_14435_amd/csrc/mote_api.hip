@@ -66,15 +66,17 @@ bool layer_shape_ok(const mote_layer* l) {
 // Largest batch at which the RTN codes of a quantised shared expert are streamed (decode kernels) instead of tiled, a
 // few times 64 tokens: the tiled GEMMs want them expanded to bf16 in every forward (39 us at d = 2048) and
 // have a tile or two per CU there.  Expanded and tiled -> streamed, us per forward (top-2, INT8 / INT4):
-//   below 2^20 weights  d = 256, F = 512 (E = 4) T=128 84 -> 49, T=512 73 -> 59;  d = 2048, F = 384 (E = 8) T=512 132 -> 93;
-//                       d = 896, F = 1024 T=384 125 -> 81, but T=512 86 -> 90;  d = 384, F = 2560 T=384 99 -> 84, T=512 84 -> 96
-//   2^20                d = 896, F = 4864 (E = 8) T=128 79 -> 66, T=192 81 -> 80, T=256 72 -> 89
-//   2^23                d = 2048, F = 4352 T=192 136 -> 114 / 138 -> 122, T=256 145 -> 142 / 148 -> 159;  d = 1536, F = 8960 T=192
-//                       133 -> 133, T=193 133 -> 148;  F = 11008, d = 2048 T=128 188 -> 142, T=192 194 -> 176, T=256 190 -> 215;
-//                       but d = 1024, F = 8192 T=128 92 -> 79 / 96 -> 80, T=192 96 -> 100 / 97 -> 104
-//   2^25                d = 3584, F = 18944 T=128 473 -> 352 / 478 -> 372, T=256 550 -> 528 / 566 -> 494, T=320 615 -> 606 /
-//                       616 -> 572, T=384 640 -> 664 / 643 -> 654;  E = 8 T=320 511 -> 487, T=384 543 -> 550;
-//                       d = 4096, F = 14336 (E = 8) T=320 448 -> 426, T=384 477 -> 487
+//   below 2^20 weights  d = 256, F = 512 (E = 4) T=128 57 -> 50 / 58 -> 50, T=512 59 -> 56 / 59 -> 56;  d = 896, F = 1024 (E = 8) T=256 66 -> 65 /
+//                       67 -> 67, but T=384 73 -> 81 / 73 -> 83;  d = 384, F = 2560 T=256 64 -> 68, T=384 68 -> 81;  d = 2048, F = 384 T=512 92 -> 97 / 92 -> 99
+//   2^20                d = 896, F = 4864 (E = 8) T=96 73 -> 69, T=128 83 -> 78 / 83 -> 77, T=192 83 -> 78 / 84 -> 83, T=256 85 -> 85 / 87 -> 89
+//   2^23                d = 2048, F = 11008 (E = 16) T=96 143 -> 136, T=128 148 -> 142 / 148 -> 141, but T=192 173 -> 182 / 170 -> 175, T=256 185 -> 215;
+//                       d = 1536, F = 8960 T=128 110 -> 111 / 107 -> 114, T=192 127 -> 132 / 122 -> 136;  d = 2048, F = 4352 T=128 90 -> 96 /
+//                       88 -> 98, T=192 96 -> 114 / 96 -> 123;  d = 1024, F = 8192 T=128 88 -> 81 / 87 -> 84, T=192 93 -> 104 / 94 -> 109
+//   2^25                d = 3584, F = 18944 (E = 16) T=128 460 -> 343 / 464 -> 367, T=256 464 -> 471 / 484 -> 456, T=320 515 -> 546 / 510 -> 521;
+//                       E = 8 T=256 398 -> 377 / 406 -> 391, T=320 430 -> 454 / 436 -> 457;  d = 4096, F = 14336 (E = 8) T=256 347 -> 332 / 350 -> 362,
+//                       T=320 376 -> 398 / 376 -> 413
+// The limits are those of the 128-row GEMMs before the present ones (d = 2048, F = 4352 T=192 136 -> 114; d = 3584 T=320 615 -> 606) and
+// lie up to 64 or 128 tokens late from 2^23 weights on, and between 2^19 and 2^20.
 int shared_q_tokens(const mote_layer* l) {
   if (knob(kKnobSharedQTokens) >= 0) return knob(kKnobSharedQTokens);
   const int64_t weights = static_cast<int64_t>(l->d_model) * l->d_ff_shared;

@@ -693,7 +693,9 @@ static hipError_t launch_cfg(const RoutedGemmArgs& a, int kplanes, hipStream_t s
 // Plan tile height by the average number of rows an expert sees: 32-row tiles for few rows
 // (decode kernels), 64-row tiles for some tens of rows where the wave-streaming kernel fits the
 // shape (the weights are then streamed once per 64 rows; the large-batch kernel would run half-empty
-// 128-row tiles and re-read the activations for every channel tile), else 128.
+// 128-row tiles and re-read the activations for every channel tile; us per forward, without 64-row tiles -> with them, 16 experts, r rows
+// each: 3B width r = 32 156 -> 145, r = 40 191 -> 163, r = 48 210 -> 171, r = 56 184 -> 184, r = 60 189 -> 196; 1.5B width r = 40 135 -> 120,
+// r = 48 136 -> 125, r = 56 143 -> 150), else 128.
 int routed_tile_m(int T, int k, int E, int d, int F, int decode_rows) {
   const int64_t avg = (static_cast<int64_t>(T) * k + E - 1) / E;
   if (avg > knob(kKnobMidRowsLo) && avg <= knob(kKnobMidRowsHi) && routed_mid_kernel_fits(d, F)) return 64;
@@ -702,17 +704,20 @@ int routed_tile_m(int T, int k, int E, int d, int F, int decode_rows) {
 int routed_decode_rows_max() { return knob(kKnobDecodeRows) >= 0 ? knob(kKnobDecodeRows) : 48; }
 int routed_decode_rows_min(int d) { return knob(kKnobDecodeRows) >= 0 ? knob(kKnobDecodeRows) : d > 2048 ? 16 : 48; }
 // Rows longer than one 16-step plane (d > 2048) have no wave-streaming gate-up kernel, and the register-ring kernel
-// streams the weights once per 32 rows behind a gather per unit: from some 20 to 30 rows per expert on the 128-row
+// streams the weights once per 32 rows behind a gather per unit: from some 16 to 30 rows per expert on the 128-row
 // kernel is faster.  us per forward on 32-row -> on 128-row tiles, r rows per expert (top-2 unless noted):
-//   few narrow experts (F = 640, E = 8, d = 2304)  r = 17 255 -> 271, r = 48 178 -> 195;  F = 2560 r = 17 103 -> 114, r = 48 121 -> 124
-//   F = 5120, d = 3072, E = 16  r = 24 143 -> 150, r = 28 150 -> 154, r = 32 168 -> 160, r = 40 210 -> 160;  F = 6912, d = 2560
-//     r = 24 143 -> 152, r = 30 166 -> 160;  INT8 shared expert r = 24 170 -> 178, r = 30 190 -> 189
-//   F = 18944, d = 3584, E = 16  r = 20 403 -> 408, r = 24 427 -> 412, r = 32 544 -> 445;  E = 4, top-1 r = 24 203 -> 192;  INT8
-//     r = 20 422 -> 430, r = 24 447 -> 442;  but up to 64 tokens (E = 4), where the shared expert is streamed, r = 20
-//     169 -> 189, r = 28 186 -> 193, r = 32 204 -> 190
-//   E = 64, top-4, d = 3072, F = 1920  r = 24 228 -> 267, r = 28 231 -> 225;  F = 4096 r = 24 295 -> 335, r = 28 352 -> 313;
-//     top-8, d = 2560, F = 6912 r = 17 364 -> 329, r = 24 433 -> 339, INT8 r = 20 396 -> 407, r = 24 420 -> 413
-// Up to d = 2048 the 32-row kernels win longer (E = 8, T=100 113.8 against 121; d = 896, T=190 69.8 against 72.2).
+//   few narrow experts (E = 8, d = 2304)  F = 640 r = 17 57 -> 67, r = 48 64 -> 73;  F = 2560 r = 17 68 -> 69, r = 48 73 -> 73
+//   F = 5120, d = 3072, E = 16  r = 24 127 -> 116, r = 28 137 -> 120, r = 32 151 -> 126, r = 40 177 -> 133;  F = 6912, d = 2560
+//     r = 24 134 -> 128, r = 30 156 -> 136;  INT8 shared expert r = 24 178 -> 165, r = 30 190 -> 166
+//   F = 18944, d = 3584, E = 16  r = 16 370 -> 370, r = 20 372 -> 342, r = 24 389 -> 346, r = 32 501 -> 368;  E = 4, top-1 r = 20 169 -> 167,
+//     r = 24 175 -> 166;  INT8 r = 20 203 -> 197, r = 24 209 -> 198;  up to 64 tokens (E = 4), where the shared expert is streamed, r = 20
+//     170 -> 173, r = 28 192 -> 178, r = 32 198 -> 176
+//   E = 64, top-4, d = 3072, F = 1920  r = 24 200 -> 180, r = 28 231 -> 208;  F = 4096 r = 24 309 -> 262, r = 28 356 -> 286;
+//     top-8, d = 2560, F = 6912 r = 17 342 -> 283, r = 24 422 -> 300, INT8 r = 20 382 -> 337, r = 24 450 -> 343
+// The limits are those of the 128-row kernel before its K loops by height (F = 5120 r = 28 150 -> 154; F = 18944 r = 20 403 -> 408;
+// E = 64, F = 4096 r = 24 295 -> 335) and lie up to ten rows late for F >= 4096 or E >= 32.
+// Up to d = 2048 the 32-row kernels win longer (E = 8 T=100 91 against 97, T=120 95 against 100; d = 1536, E = 16 T=160 96 against 98, T=240 114
+// against 109; d = 896, T=120 64 against 62, T=190 69 against 69).
 int routed_decode_rows(int T, int E, int d, int F, bool shared_quantised) {
   if (knob(kKnobDecodeRows) >= 0) return knob(kKnobDecodeRows);
   if (d <= 2048 || (F < 4096 && E < 32)) return 48;
@@ -734,8 +739,8 @@ int routed_down_planes(int T, int k, int E, int d, int F) {
   const int KT = F >> 7;
   int planes = tiles > 0 ? static_cast<int>((512 + tiles / 2) / tiles) : 1;
   // between one and two workgroups per CU's worth of 128 x 128 tiles, two planes of 128-wide tiles fill the
-  // chip better than one plane of 256-wide ones (3B width, 16 experts: T = 1024 398 -> 367 us per forward,
-  // T = 1536 520 -> 503 us; from T = 2048 on, 640 tiles, no gain, and a loss at T = 3072)
+  // chip better than one plane of 256-wide ones (16 experts, 3B width: T = 1024 339 -> 330 us per forward, but T = 1536 435 -> 442;
+  // 1.5B width T = 1536 305 -> 297, T = 2048 393 -> 379; from 640 tiles on, 3B width T = 2048, no gain, and at T = 3072 756 -> 794)
   if (planes == 1 && tiles < knob(kKnobDownSplitTiles)) planes = 2;
   if (planes > F / 2048) planes = F / 2048;   // every plane adds an int32 partial output (C2, F = 4864: 2 planes 30 us, 3 planes 41 us)
   int fill = tiles > 0 ? static_cast<int>(256 / tiles) : 1;   // few tiles: up to one workgroup per CU, planes of at least 4 K steps
