@@ -482,22 +482,20 @@ mote_status forward_impl(const mote_layer* layer, const mote_norm* norm, const v
     if (e == hipSuccess) e = shared_down(sstream);
     return e == hipSuccess ? hipEventRecord(side->join, side->stream) : e;
   };
-  // The fork is in front of the router, except for narrow layers whose shared gate-up GEMM takes the LDS of every CU: the
+  // The fork is in front of the router, except for narrow layers whose shared gate-up GEMM takes the LDS of every CU to its end: the
   // router then runs behind that GEMM instead of beside it, and the dispatch plan, as long as both shared GEMMs and a handful of
-  // workgroups, with nothing beside it.  us per forward, fork in front of the router / behind it / behind the plan's launch (E = 8, top-2):
-  //   256 x 256 tiles  d = 256, F = 512, T = 16384 147.8 / 140.9 / 143.0;  d = 384, F = 1024, T = 8192 126.6 / 118.3 / 126.8;  d = 512, F = 2048,
-  //                    T = 4096 128.3 / 123.2 / 128.7;  d = 256, F = 4096, T = 2048 100.4 / 96.9 / 91.1, T = 16384 467.9 / 445.6 / 463.1
-  //   128 x 256 tiles  d = 512, F = 2048, T = 2048 100.5 / 97.3 / 83.4;  d = 256, F = 512, T = 8192 89.7 / 88.7 / 87.9;  d = 896, F = 512, T = 8192
-  //                    138.0 / 131.5 / 135.1;  but d = 384, F = 1024, T = 4096 84.0 / 85.6 / 84.8
-  // (before GEMMs of one workgroup per CU, in front: d = 256, T = 16384 139, d = 512, T = 2048 / 4096 89 / 121.)  With fewer tiles the two chains
-  // overlap (d = 512, F = 2048, T = 3000 93.7 / 101.4), and wider layers have longer shared GEMMs than plans (d = 768, F = 3072, T = 2048
-  // 108.5 / 121.7; d = 896, F = 4864, T = 3000 202.8 / 214.5).
-  int fork_at = 0;   // 1: behind the router, 2: behind the plan kernel's launch
-  if (side && shared_weights <= (int64_t{1} << 20)) {
-    const int rows = shared_gate_up_rows_on_every_cu(T, d, Fs);
-    fork_at = rows == 256 ? 1 : rows == 128 ? 2 : 0;
-  }
-  if (side && fork_at == 0) MOTE_HIP(start_shared());
+  // workgroups, with nothing beside it.  us per forward, fork in front of the router / behind it / behind the plan's launch (E = 8, top-2; three
+  // layers in turn):
+  //   d = 256, F = 512, T = 16384 148.2 / 139.6 / 148.1 (E = 4, top-1 105.1 / 98.9 / 107.3);  d = 384, F = 1024, T = 8192 127.1 / 120.7 / 130.0 (but
+  //   94.1 / 96.0 / 94.4);  d = 512, F = 2048, T = 4096 131.7 / 126.0 / 130.3 (107.3 / 104.9 / 108.1);  d = 256, F = 2048, T = 4096 112.5 / 107.0 / 111.7;
+  //   F = 4096, T = 2048 103.4 / 100.2 / 96.2, T = 16384 464.6 / 447.7 / 454.7
+  // (before GEMMs of one workgroup per CU, in front: d = 256, T = 16384 137, d = 512, T = 4096 122.)  Elsewhere the two chains overlap by themselves:
+  //   a last round half full    d = 512, F = 2048, T = 6000 152.3 / 151.2 / 161.6 (114.9 / 123.5 / 125.3)
+  //   128-row tiles, fewer tiles  d = 256, F = 512, T = 10000 96.4 / 99.1 / 99.0, T = 12000 105.7 / 108.9 / 117.2;  d = 384, F = 2560, T = 1664 74.0 / 82.6 / 81.8;
+  //                               d = 512, F = 2048, T = 2500 88.1 / 92.7 / 94.7, but T = 2048 99.3 / 95.0 / 82.1 (70.7 / 75.6 / 75.5)
+  //   wider layers, whose shared GEMMs are longer than the plan  d = 768, F = 3072, T = 2048 in front / behind the plan 108.5 / 121.7
+  const bool fork_late = side && shared_weights <= (int64_t{1} << 20) && shared_gate_up_fills_every_cu(T, d, Fs);
+  if (side && !fork_late) MOTE_HIP(start_shared());
 
   const DecodeSharedArgs ds{xb, layer->ws_gate, layer->ws_up, layer->ws_down, layer->ss_gate, layer->ss_up, layer->ss_down, sbits, T, d, Fs};
   MOTE_HIP(mark(0));
@@ -508,11 +506,10 @@ mote_status forward_impl(const mote_layer* layer, const mote_norm* norm, const v
     MOTE_HIP(launch_router_quant(xb, static_cast<const uint16_t*>(layer->w_router), layer->router_bias, T, d, E, k,
                                  w.topk_idx, w.topk_p, w.q_x, w.beta_x, w.rs_x, nullptr, stream));
   MOTE_HIP(mark(1));
-  if (fork_at == 1) MOTE_HIP(start_shared());
+  if (fork_late) MOTE_HIP(start_shared());
   DispatchPlan plan{w.counts, w.offsets, w.row_of, w.tok_of, w.tile_expert, w.tile_row0, w.tile_rows, w.n_tiles, w.row_planes, w.sched};
   // local_plan: the gate-up kernel makes the plan itself (at most 64 * 8 dispatch rows)
   if (!local_plan) MOTE_HIP(launch_dispatch_plan(w.topk_idx, T, k, E, tile_m, plan, stream));
-  if (fork_at == 2) MOTE_HIP(start_shared());
   MOTE_HIP(mark(2));
 
   RoutedGemmArgs ga{};

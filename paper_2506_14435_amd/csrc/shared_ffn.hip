@@ -972,11 +972,10 @@ static GemmChoice gemm_choice(int M, int N, int K, int nmat, int max_planes) {
   return best;
 }
 
-int shared_gate_up_rows_on_every_cu(int T, int d, int F) {
-  const GemmTile tile = gemm_choice(T, F, d, 2, 1).tile;
-  if (tile == kTileMid128) return 0;
-  const int rows = tile == kTileBig ? 256 : 128;
-  return static_cast<int64_t>((T + rows - 1) / rows) * ((F + 127) / 128) >= shared_cu_count() ? rows : 0;
+bool shared_gate_up_fills_every_cu(int T, int d, int F) {
+  if (gemm_choice(T, F, d, 2, 1).tile != kTileBig) return false;
+  const int64_t tiles = static_cast<int64_t>((T + 255) / 256) * ((F + 127) / 128), cus = shared_cu_count();
+  return tiles >= cus && ((tiles - 1) % cus + 1) * 4 >= cus * 3;
 }
 
 hipError_t launch_shared_gate_up(const uint16_t* x, const uint16_t* w_gate, const uint16_t* w_up, int T, int d,
