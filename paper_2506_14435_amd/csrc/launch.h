@@ -96,8 +96,8 @@ hipError_t launch_routed_down(const RoutedGemmArgs& a, hipStream_t stream);
 int routed_down_tile_n(int planes);
 int routed_down_planes(int T, int k, int E, int d, int F);   // large-batch down: K planes for a shape
 int shared_down_planes(int T, int d, int F);
-// tiled: 256 x 256 tiles, all of a CU's LDS each, in rounds that take every CU (the last one three quarters of them)
-bool shared_gate_up_fills_every_cu(int T, int d, int F);
+// tiled: rounds of one tile per CU, of the tiles of 256 channels, all of a CU's LDS each (0 with smaller ones)
+double shared_gate_up_rounds(int T, int d, int F, int* tile_rows);
 constexpr int kSharedDownWideTokens = 1536;   // where the bound on those planes steps within a number of row tiles
 int tile_group_m();                      // row tiles per band of the large-batch tile order
 // plan tile size chosen for a workload (32, 64: decode kernels); decode_rows: largest average number of rows per

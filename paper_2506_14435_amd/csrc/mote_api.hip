@@ -6,6 +6,7 @@
 
 #include "launch.h"
 #include <algorithm>
+#include <cmath>
 
 namespace mote {
 // Tuning knobs: defaults are what the measurements chose; mote_tuning_set overwrites them.
@@ -494,7 +495,16 @@ mote_status forward_impl(const mote_layer* layer, const mote_norm* norm, const v
   //   128-row tiles, fewer tiles  d = 256, F = 512, T = 10000 96.4 / 99.1 / 99.0, T = 12000 105.7 / 108.9 / 117.2;  d = 384, F = 2560, T = 1664 74.0 / 82.6 / 81.8;
   //                               d = 512, F = 2048, T = 2500 88.1 / 92.7 / 94.7, but T = 2048 99.3 / 95.0 / 82.1 (70.7 / 75.6 / 75.5)
   //   wider layers, whose shared GEMMs are longer than the plan  d = 768, F = 3072, T = 2048 in front / behind the plan 108.5 / 121.7
-  const bool fork_late = side && shared_weights <= (int64_t{1} << 20) && shared_gate_up_fills_every_cu(T, d, Fs);
+  // More than 16 experts: a router several times as long, for which such a GEMM is in the way already when it takes most of the CUs, in
+  // 128-row tiles too (E = 64, top-2, in front / behind: d = 256, F = 512, T = 8100 222.9 / 212.5, T = 12000 305.8 / 295.4; d = 384, F = 1024, T = 4096 161.0 / 154.2;
+  // d = 512, F = 2048, T = 4096 201.0 / 189.8, but T = 2500, 160 tiles, top-1 130.5 / 134.0); not with the longest of these GEMMs (d = 256, F = 4096, E = 32, T = 2048
+  // 197.3 / 204.6, E = 64, top-1, T = 16384 553.8 / 567.7).
+  bool fork_late = false;
+  if (side && shared_weights <= (int64_t{1} << 20)) {
+    int rows;
+    const double rounds = shared_gate_up_rounds(T, d, Fs, &rows), last = rounds - (std::ceil(rounds) - 1.0);   // share of the CUs in the last round
+    fork_late = E > 16 ? Fs < 4096 && rounds > 0.0 && last >= 0.7 : rows == 256 && rounds >= 1.0 && last >= 0.75;
+  }
   if (side && !fork_late) MOTE_HIP(start_shared());
 
   const DecodeSharedArgs ds{xb, layer->ws_gate, layer->ws_up, layer->ws_down, layer->ss_gate, layer->ss_up, layer->ss_down, sbits, T, d, Fs};

@@ -972,10 +972,11 @@ static GemmChoice gemm_choice(int M, int N, int K, int nmat, int max_planes) {
   return best;
 }
 
-bool shared_gate_up_fills_every_cu(int T, int d, int F) {
-  if (gemm_choice(T, F, d, 2, 1).tile != kTileBig) return false;
-  const int64_t tiles = static_cast<int64_t>((T + 255) / 256) * ((F + 127) / 128), cus = shared_cu_count();
-  return tiles >= cus && ((tiles - 1) % cus + 1) * 4 >= cus * 3;
+double shared_gate_up_rounds(int T, int d, int F, int* tile_rows) {
+  const GemmTile tile = gemm_choice(T, F, d, 2, 1).tile;
+  *tile_rows = tile == kTileBig ? 256 : 128;
+  if (tile == kTileMid128) return 0.0;
+  return static_cast<double>((T + *tile_rows - 1) / *tile_rows) * ((F + 127) / 128) / shared_cu_count();
 }
 
 hipError_t launch_shared_gate_up(const uint16_t* x, const uint16_t* w_gate, const uint16_t* w_up, int T, int d,

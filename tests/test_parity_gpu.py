@@ -1110,11 +1110,12 @@ def test_shared_gemm_tiles(variant, T, d, F, shared_bits):
     assert ((taps["y_s"].double() - hd @ w[2].T).abs() <= bound).all()
 
 
-# Narrow layers whose shared gate-up GEMM has a 256 x 256 tile for every CU start the shared expert behind the router, others (the last
-# two: 128 x 256 tiles) in front of it: the fewest such tiles and a row of them less, a quantised expert (its expansion goes first), a block,
+# Narrow layers whose shared gate-up GEMM has a 256 x 256 tile for every CU start the shared expert behind the router, others (128 x 256
+# tiles, fifth and sixth) in front of it, those of more than 16 experts (the last two) already with either tile for most CUs: the fewest such tiles and a row of them less, a quantised expert (its expansion goes first), a block,
 # alternating inputs without a wait between them, and replays of a captured forward.  Equal to one stream, to the bit.
 @pytest.mark.parametrize("T,d,F,E,k,shared_bits", [(4096, 128, 2048, 8, 2, 0), (3840, 128, 2048, 8, 2, 0), (4090, 256, 2048, 4, 1, 8), (8192, 256, 1024, 16, 3, 0),
-                                                   (2048, 512, 2048, 8, 2, 0), (8192, 256, 512, 4, 2, 4)])
+                                                   (2048, 512, 2048, 8, 2, 0), (8192, 256, 512, 4, 2, 4),
+                                                   (2000, 512, 2048, 32, 2, 0), (6144, 256, 1024, 17, 1, 8)])
 def test_shared_expert_started_behind_the_router(T, d, F, E, k, shared_bits):
     M = _m()
     g = torch.Generator(device="cuda").manual_seed(T + d)
